@@ -11,32 +11,29 @@
 namespace gosh {
 
 // ---------------------------------------------------------------------------------
-// Philox4x32-10 (Salmon et al., SC'11).  Returns the first two output words as one
-// 64-bit draw; w2/w3 optionally receive the other two.  Usable on host and device.
+// Philox4x32-10 (Salmon et al., SC'11).  philox_draw returns the first two output words as
+// one 64-bit draw.  Usable on host and device.
 // ---------------------------------------------------------------------------------
 __host__ __device__ __forceinline__ uint32_t mul_hi32(uint32_t a, uint32_t b) {
   return static_cast<uint32_t>((static_cast<uint64_t>(a) * b) >> 32);
 }
 
+constexpr uint32_t kPhiloxMulA = 0xD2511F53u, kPhiloxMulB = 0xCD9E8D57u;
+constexpr uint32_t kPhiloxWeylA = 0x9E3779B9u, kPhiloxWeylB = 0xBB67AE85u;
+
 __host__ __device__ __forceinline__ uint64_t philox_draw(uint32_t c0, uint32_t c1, uint32_t c2,
-                                                         uint32_t c3, uint32_t k0, uint32_t k1,
-                                                         uint32_t *w2 = nullptr,
-                                                         uint32_t *w3 = nullptr) {
-  constexpr uint32_t kMulA = 0xD2511F53u, kMulB = 0xCD9E8D57u;
-  constexpr uint32_t kWeylA = 0x9E3779B9u, kWeylB = 0xBB67AE85u;
+                                                         uint32_t c3, uint32_t k0, uint32_t k1) {
 #pragma unroll
   for (int r = 0; r < 10; ++r) {
-    const uint32_t hiA = mul_hi32(kMulA, c0), loA = kMulA * c0;
-    const uint32_t hiB = mul_hi32(kMulB, c2), loB = kMulB * c2;
+    const uint32_t hiA = mul_hi32(kPhiloxMulA, c0), loA = kPhiloxMulA * c0;
+    const uint32_t hiB = mul_hi32(kPhiloxMulB, c2), loB = kPhiloxMulB * c2;
     c0 = hiB ^ c1 ^ k0;
     c1 = loB;
     c2 = hiA ^ c3 ^ k1;
     c3 = loA;
-    k0 += kWeylA;
-    k1 += kWeylB;
+    k0 += kPhiloxWeylA;
+    k1 += kPhiloxWeylB;
   }
-  if (w2) *w2 = c2;
-  if (w3) *w3 = c3;
   return static_cast<uint64_t>(c0) | (static_cast<uint64_t>(c1) << 32);
 }
 

@@ -1,11 +1,40 @@
-"""The divergence check at the edges of its tiles of 2,048 units of 128 bits."""
+"""The tile-walking kernels (initial matrix, projection, divergence check) at the edges of their
+tiles: 2,048 units of 128 bits or 256 rows per tile, 2,048 units per turn of the check."""
+import numpy as np
 import pytest
 import torch
 
 import paper_2008_12336_amd as G
+from oracle import gosh_oracle as O
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
+# a row of one unit, rows that do not divide a tile, the largest row; 1 row, a tile less one row,
+# a whole tile, one row more, several tiles
+SHAPES = [(d, n) for d in (4, 36, 100, 128, 260, 508, 512)
+          for t in [min(256, 2048 // (d // 4))] for n in (1, t - 1, t, t + 1, 5 * t + 3)]
+
+
+@pytest.mark.parametrize("d,n", SHAPES)
+def test_initial_rows_and_projection_bit_for_bit(d, n):
+    seed, level = 0x1234567890ABCDEF, 3
+    M = torch.full((n, d), 7.0, device=DEV)
+    G.gosh_init_embedding(M, seed, level)
+    assert np.array_equal(M.cpu().numpy(), O.init_embedding(n, d, seed, level))
+    coarse_n = max(1, n // 3)
+    rng = np.random.default_rng(n * 1000 + d)
+    coarse = rng.standard_normal((coarse_n, d)).astype(np.float32)
+    cmap = rng.integers(0, coarse_n, n).astype(np.int32)
+    cmap[rng.integers(0, n)] = -1        # names no coarse vertex: a row of zeros
+    cmap[rng.integers(0, n)] = coarse_n  # the same
+    fine = torch.full((n + 1, d), 7.0, device=DEV)
+    G.gosh_project(torch.from_numpy(coarse).to(DEV), torch.from_numpy(cmap).to(DEV), fine[:n])
+    ok = (cmap >= 0) & (cmap < coarse_n)
+    want = np.where(ok[:, None], coarse[np.where(ok, cmap, 0)], np.float32(0))
+    got = fine.cpu().numpy()
+    assert np.array_equal(got[:n], want)
+    assert (got[n] == 7.0).all()  # nothing past the last row
+
 
 @pytest.mark.parametrize("n", [1, 255, 256, 257, 2047, 2048, 2049, 4096, 5 * 2048 + 1, 2048 * 2048 + 17])
 def test_check_counts_every_entry_once(n):
