@@ -177,8 +177,8 @@ int gosh_coarsen(const gosh_csr *g0_host, int64_t threshold, double min_shrink,
 
 /* MultiEdgeCollapse on the current HIP device: the same hierarchy, bit for bit (Alg. 4 has
  * one result), with the degree order a device radix sort, the marking sweep resolved in
- * parallel rounds, and "Coarsen" (the rebuild of the CSR of G_{i+1}, Sec. 3.2.1) a sort
- * and a reduction of (cluster, cluster) keys.  g0 may be a host graph, which is uploaded
+ * parallel rounds, and "Coarsen" (the rebuild of the CSR of G_{i+1}, Sec. 3.2.1) a move of
+ * the fine rows together by cluster and a merge of each coarse row.  g0 may be a host graph, which is uploaded
  * once, or a graph already in the current device's memory (detected from the pointers),
  * which is used where it is: in both cases it is borrowed for the lifetime of the
  * hierarchy, and its offsets and neighbour ids are range-checked on the device
@@ -186,9 +186,9 @@ int gosh_coarsen(const gosh_csr *g0_host, int64_t threshold, double min_shrink,
  * that device, where gosh_embed / gosh_embed_host read it without another upload, and the
  * host arrays behind gosh_hierarchy_graph / _map / _mult are downloaded on first request.
  * A graph whose marking does not resolve in a bounded number of rounds (long chains of
- * equal degrees) is marked on the host instead.  Device memory: about 36 bytes per entry
+ * equal degrees) is marked on the host instead.  Device memory: about 24 bytes per entry
  * of G_0 while running; afterwards 12 bytes per entry of all levels, and the run's scratch
- * blocks (about 32 bytes per entry of G_0), which stay allocated until
+ * blocks (about 8 bytes per entry of G_0), which stay allocated until
  * gosh_hierarchy_trim_scratch, gosh_hierarchy_release_device or gosh_hierarchy_free
  * (called with the same device current) because freeing them at once would slow the host
  * link down for whatever follows (the driver clears freed memory in the background).

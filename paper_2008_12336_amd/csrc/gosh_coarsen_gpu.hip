@@ -1,5 +1,5 @@
-// MultiEdgeCollapse (Alg. 4 of the paper) on the device: the degree order, the marking
-// sweep and the rebuild of the coarse CSR, with the results of the sequential algorithm.
+// MultiEdgeCollapse (Alg. 4 of the paper) on the device: the degree order and the marking
+// sweep, with the results of the sequential algorithm.
 //
 // Order: a stable radix sort of the vertex ids by descending degree.
 //
@@ -12,16 +12,8 @@
 // and equals the sequential one, so stale reads can only delay it.  Hubs are numbered by
 // a scan over the order; every other vertex joins its first hub in the order.
 //
-// Rebuild: every fine entry (x, y) becomes the 64-bit key map[x] * n' + map[y] (entries
-// inside one cluster get a sentinel key above all others); a radix sort of the keys with
-// their multiplicities followed by a reduction of equal keys leaves exactly the distinct
-// coarse entries, in row-major ascending order, with the merged multiplicities -- the
-// same arrays the host implementation produces, since sorted distinct keys are unique.
-// The keys are made one thread per entry (the row of an entry is found by a search that a
-// block narrows to the few rows it spans), so hub rows are no long tail.
-//
-// Sort, scan and reduce-by-key are rocPRIM device primitives; the kernels around them
-// are here.  Everything runs on the null stream and the calls block.
+// Sort and scan are rocPRIM device primitives; the kernels around them are here.  The rebuild
+// is in gosh_quotient.hip.  Everything runs on the null stream and the calls block.
 #include <hip/hip_runtime.h>
 #include <omp.h>
 
@@ -33,8 +25,12 @@
 
 #include "gosh_coarsen_internal.h"
 #include "gosh_common.h"
+#include "gosh_device_pool.h"
 
 namespace {
+
+using gosh::blocks_for;
+using gosh::persistent;
 
 constexpr uint32_t kHighBit = 0x80000000u;   // set in rk[v] when deg(v) is above the mean
 constexpr uint32_t kRankMask = 0x7FFFFFFFu;  // rk[v] & kRankMask = position of v in the order
@@ -196,161 +192,6 @@ __global__ __launch_bounds__(256) void check_neighbours_kernel(const int32_t *__
     if (adj[e] < 0 || adj[e] >= n) *bad = 1;
 }
 
-// Largest row r in [lo, hi] with xadj[r] <= e, i.e. the row that holds entry e (empty rows
-// share their offset with the next row and are skipped).
-template <typename OffT>
-__device__ inline int64_t row_of_entry(const OffT *__restrict__ xadj, int64_t lo, int64_t hi, int64_t e) {
-  while (lo < hi) {
-    const int64_t mid = lo + (hi - lo + 1) / 2;
-    if (static_cast<int64_t>(xadj[mid]) <= e) lo = mid;
-    else hi = mid - 1;
-  }
-  return lo;
-}
-
-// One thread per fine entry, kKeysPerBlock consecutive entries per block: the block first
-// finds the rows of its first and last entry, then every thread searches only between
-// them (a handful of rows; none at all inside a hub's row), so hubs and short rows cost
-// the same per entry and all accesses to adj, keys and vals are coalesced.
-constexpr int kKeysPerBlock = 4096;
-template <typename OffT>
-__global__ __launch_bounds__(256) void make_keys_kernel(const OffT *__restrict__ xadj,
-                                                        const int32_t *__restrict__ adj,
-                                                        const int64_t *__restrict__ mult_in,
-                                                        const int32_t *__restrict__ map, int64_t n,
-                                                        int64_t nnz, uint64_t n_coarse, uint64_t sentinel,
-                                                        uint64_t *__restrict__ keys,
-                                                        int64_t *__restrict__ vals) {
-  __shared__ int64_t span[2];
-  for (int64_t e0 = static_cast<int64_t>(blockIdx.x) * kKeysPerBlock; e0 < nnz;
-       e0 += static_cast<int64_t>(gridDim.x) * kKeysPerBlock) {
-    const int64_t e_last = min(e0 + kKeysPerBlock, nnz) - 1;
-    if (threadIdx.x < 2) span[threadIdx.x] = row_of_entry(xadj, 0, n - 1, threadIdx.x == 0 ? e0 : e_last);
-    __syncthreads();
-    const int64_t row_lo = span[0], row_hi = span[1];
-    for (int64_t e = e0 + threadIdx.x; e <= e_last; e += 256) {
-      const int64_t x = row_of_entry(xadj, row_lo, row_hi, e);
-      const uint64_t a = static_cast<uint64_t>(map[x]);
-      const uint64_t b = static_cast<uint64_t>(map[adj[e]]);
-      keys[e] = a != b ? a * n_coarse + b : sentinel;
-      if (mult_in) vals[e] = mult_in[e];  // without multiplicities every entry counts once
-    }
-    __syncthreads();  // span is rewritten in the next round
-  }
-}
-
-// xadj_out[a] = number of distinct keys below a * n_coarse (binary search per coarse row).
-__global__ __launch_bounds__(256) void offsets_kernel(const uint64_t *__restrict__ unique_keys,
-                                                      int64_t n_unique, uint64_t n_coarse,
-                                                      int64_t *__restrict__ xadj_out) {
-  for (uint64_t a = blockIdx.x * 256ull + threadIdx.x; a <= n_coarse; a += gridDim.x * 256ull) {
-    const uint64_t target = a * n_coarse;
-    int64_t lo = 0, hi = n_unique;
-    while (lo < hi) {
-      const int64_t mid = lo + (hi - lo) / 2;
-      if (unique_keys[mid] < target) lo = mid + 1;
-      else hi = mid;
-    }
-    xadj_out[a] = lo;
-  }
-}
-
-// adj_out[i] = column of distinct key i; mult_out[i] = its merged multiplicity.
-__global__ __launch_bounds__(256) void columns_kernel(const uint64_t *__restrict__ unique_keys,
-                                                      const int64_t *__restrict__ sums, int64_t n_unique,
-                                                      uint64_t n_coarse, int32_t *__restrict__ adj_out,
-                                                      int64_t *__restrict__ mult_out) {
-  for (int64_t i = blockIdx.x * 256LL + threadIdx.x; i < n_unique; i += gridDim.x * 256LL) {
-    adj_out[i] = static_cast<int32_t>(unique_keys[i] % n_coarse);
-    mult_out[i] = sums[i];
-  }
-}
-
-// Device blocks recycled over the levels of one run: hipMalloc and hipFree of gigabyte
-// blocks cost more than the kernels of a small level.  Levels only shrink, so the blocks
-// of the first level serve all later ones (best fit).
-struct Pool {
-  struct Block {
-    void *p;
-    size_t bytes;
-    bool busy;
-  };
-  std::vector<Block> blocks;
-  ~Pool() { trim(); }
-  void trim() {
-    for (Block &b : blocks) (void)hipFree(b.p);
-    blocks.clear();
-  }
-  void *take(size_t bytes) {
-    // best fit, but a small request never occupies a block that a large one will want
-    const size_t too_big = std::max<size_t>(bytes * 8, size_t(64) << 20);
-    Block *best = nullptr;
-    for (Block &b : blocks)
-      if (!b.busy && b.bytes >= bytes && b.bytes <= too_big && (best == nullptr || b.bytes < best->bytes))
-        best = &b;
-    if (best != nullptr) {
-      best->busy = true;
-      return best->p;
-    }
-    void *p = nullptr;
-    if (hipMalloc(&p, bytes) != hipSuccess) {
-      (void)hipGetLastError();
-      return nullptr;
-    }
-    blocks.push_back(Block{p, bytes, true});
-    return p;
-  }
-  void give(void *p) {
-    for (Block &b : blocks)
-      if (b.p == p) b.busy = false;
-  }
-};
-
-// The blocks one call holds; they go back to the pool on return.
-struct Buffers {
-  Pool &pool;
-  std::vector<void *> ptrs;
-  explicit Buffers(Pool &pl) : pool(pl) {}
-  ~Buffers() {
-    for (void *p : ptrs)
-      if (p) pool.give(p);
-  }
-  template <typename T>
-  int alloc(T **out, size_t count, const char *what) {
-    const size_t bytes = std::max<size_t>(count, 1) * sizeof(T);
-    void *p = pool.take(bytes);
-    if (p == nullptr) return gosh::fail(GOSH_ENOMEM, "cannot allocate %zu device bytes for %s", bytes, what);
-    ptrs.push_back(p);
-    *out = static_cast<T *>(p);
-    return GOSH_OK;
-  }
-  void release(void *p) {
-    for (void *&q : ptrs)
-      if (q == p) {
-        pool.give(q);
-        q = nullptr;
-      }
-  }
-};
-
-int blocks_for(int64_t items, int per_block) {
-  int64_t b = (items + per_block - 1) / per_block;
-  return static_cast<int>(std::min<int64_t>(std::max<int64_t>(b, 1), 1 << 16));
-}
-
-// Exact-sized block that outlives the run (a level's array).
-template <typename T>
-int persistent(T **out, size_t count, const char *what) {
-  void *p = nullptr;
-  const size_t bytes = std::max<size_t>(count, 1) * sizeof(T);
-  if (hipMalloc(&p, bytes) != hipSuccess) {
-    (void)hipGetLastError();
-    return gosh::fail(GOSH_ENOMEM, "cannot allocate %zu device bytes for %s", bytes, what);
-  }
-  *out = static_cast<T *>(p);
-  return GOSH_OK;
-}
-
 double ms_since(std::chrono::steady_clock::time_point t0) {
   return std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - t0).count();
 }
@@ -358,20 +199,6 @@ double ms_since(std::chrono::steady_clock::time_point t0) {
 }  // namespace
 
 namespace gosh {
-
-struct DeviceCoarsener {
-  Pool pool;
-  int threads = 1;
-  // Two pinned staging slots for large downloads, made on first use and kept.  The copy
-  // stream is NOT kept: a process has few hardware queues, and an idle stream of ours
-  // would make the streams of a later training call share one.
-  static constexpr size_t kSlotBytes = size_t(64) << 20;
-  char *slot[2] = {nullptr, nullptr};
-  ~DeviceCoarsener() {
-    for (int i = 0; i < 2; ++i)
-      if (slot[i]) (void)hipHostFree(slot[i]);
-  }
-};
 
 DeviceCoarsener *device_coarsener_new(int threads) {
   DeviceCoarsener *dc = new DeviceCoarsener();
@@ -402,7 +229,7 @@ int device_level_upload(DeviceCoarsener *dc, const gosh_csr &host, DeviceLevel &
   device_level_free(out);
   GOSH_TRY_HIP(hipGetDevice(&out.device), "hipGetDevice");
   out.n = host.n;
-  out.nnz = host.nnz;
+  out.nnz = out.weight = host.nnz;
   out.xadj_is64 = host.xadj_is64 ? 1 : 0;
   const size_t off_bytes = static_cast<size_t>(host.n + 1) * (host.xadj_is64 ? 8 : 4);
   char *offsets = nullptr;
@@ -418,7 +245,7 @@ int device_level_borrow(const gosh_csr &on_device, DeviceLevel &out) {
   device_level_free(out);
   GOSH_TRY_HIP(hipGetDevice(&out.device), "hipGetDevice");
   out.n = on_device.n;
-  out.nnz = on_device.nnz;
+  out.nnz = out.weight = on_device.nnz;
   out.xadj_is64 = on_device.xadj_is64 ? 1 : 0;
   out.xadj = const_cast<void *>(on_device.xadj);
   out.adj = const_cast<int32_t *>(on_device.adj);
@@ -690,129 +517,6 @@ int device_mark(DeviceCoarsener *dc, DeviceLevel &fine, int64_t *n_coarse, bool 
   if (dc == nullptr || !fine.present() || fine.n < 1) return gosh::fail(GOSH_EINVAL, "device level is missing");
   return fine.xadj_is64 ? mark_impl<int64_t>(dc, fine, n_coarse, done, order_ms)
                         : mark_impl<int32_t>(dc, fine, n_coarse, done, order_ms);
-}
-
-int device_rebuild(DeviceCoarsener *dc, const DeviceLevel &fine, int64_t n_coarse, DeviceLevel &coarse) {
-  if (dc == nullptr || !fine.present() || fine.map == nullptr)
-    return gosh::fail(GOSH_EINVAL, "device level or its map is missing");
-  device_level_free(coarse);
-  const int64_t n = fine.n, nnz = fine.nnz;
-  const uint64_t nc = static_cast<uint64_t>(n_coarse);
-  const uint64_t sentinel = nc * nc;  // above every real key
-  unsigned end_bit = 1;
-  while (end_bit < 64 && (sentinel >> end_bit) != 0) ++end_bit;
-  coarse.device = fine.device;
-  coarse.n = n_coarse;
-  coarse.xadj_is64 = 1;
-  int64_t *xadj_out = nullptr;
-  if (int rc = persistent(&xadj_out, static_cast<size_t>(n_coarse) + 1, "coarse offsets")) return rc;
-  coarse.xadj = xadj_out;
-  if (nnz == 0) {
-    coarse.nnz = 0;
-    GOSH_TRY_HIP(hipMemset(xadj_out, 0, (static_cast<size_t>(n_coarse) + 1) * 8), "clear coarse offsets");
-    if (int rc = persistent(&coarse.adj, 0, "coarse adjacency")) return rc;
-    if (int rc = persistent(&coarse.mult, 0, "coarse multiplicities")) return rc;
-    return GOSH_OK;
-  }
-
-  Buffers buf(dc->pool);
-  // G_0 carries no multiplicities (every entry counts once): its keys are sorted alone and
-  // the reduction adds a constant 1 per key, which halves the bytes the sort moves.
-  const bool weighted = fine.mult != nullptr;
-  uint64_t *keys = nullptr, *keys_sorted = nullptr;
-  int64_t *vals = nullptr, *vals_sorted = nullptr;
-  if (int rc = buf.alloc(&keys, static_cast<size_t>(nnz), "keys")) return rc;
-  if (weighted)
-    if (int rc = buf.alloc(&vals, static_cast<size_t>(nnz), "values")) return rc;
-  const int key_blocks = blocks_for(nnz, kKeysPerBlock);
-  if (fine.xadj_is64)
-    hipLaunchKernelGGL(make_keys_kernel<int64_t>, dim3(key_blocks), dim3(256), 0, nullptr,
-                       static_cast<const int64_t *>(fine.xadj), fine.adj, fine.mult, fine.map, n, nnz, nc,
-                       sentinel, keys, vals);
-  else
-    hipLaunchKernelGGL(make_keys_kernel<int32_t>, dim3(key_blocks), dim3(256), 0, nullptr,
-                       static_cast<const int32_t *>(fine.xadj), fine.adj, fine.mult, fine.map, n, nnz, nc,
-                       sentinel, keys, vals);
-  if (int rc = gosh::check_launch("make_keys_kernel")) return rc;
-
-  if (int rc = buf.alloc(&keys_sorted, static_cast<size_t>(nnz), "sorted keys")) return rc;
-  if (weighted)
-    if (int rc = buf.alloc(&vals_sorted, static_cast<size_t>(nnz), "sorted values")) return rc;
-  size_t temp_bytes = 0;
-  if (weighted)
-    GOSH_TRY_HIP(rocprim::radix_sort_pairs(nullptr, temp_bytes, keys, keys_sorted, vals, vals_sorted,
-                                         static_cast<size_t>(nnz), 0u, end_bit, nullptr),
-               "radix sort (size query)");
-  else
-    GOSH_TRY_HIP(rocprim::radix_sort_keys(nullptr, temp_bytes, keys, keys_sorted, static_cast<size_t>(nnz), 0u,
-                                        end_bit, nullptr),
-               "radix sort (size query)");
-  {
-    char *temp = nullptr;
-    if (int rc = buf.alloc(&temp, temp_bytes, "sort workspace")) return rc;
-    if (weighted)
-      GOSH_TRY_HIP(rocprim::radix_sort_pairs(temp, temp_bytes, keys, keys_sorted, vals, vals_sorted,
-                                           static_cast<size_t>(nnz), 0u, end_bit, nullptr),
-                 "radix sort");
-    else
-      GOSH_TRY_HIP(rocprim::radix_sort_keys(temp, temp_bytes, keys, keys_sorted, static_cast<size_t>(nnz), 0u,
-                                          end_bit, nullptr),
-                 "radix sort");
-    GOSH_TRY_HIP(hipDeviceSynchronize(), "radix sort");
-    buf.release(temp);
-  }
-  // distinct keys go where the unsorted ones were (at most one distinct key per fine entry;
-  // the count is only known afterwards), their summed multiplicities beside them
-  uint64_t *unique_keys = keys;
-  int64_t *sums = vals;
-  if (!weighted)
-    if (int rc = buf.alloc(&sums, static_cast<size_t>(nnz), "merged multiplicities")) return rc;
-  unsigned long long *count_dev = nullptr;
-  if (int rc = buf.alloc(&count_dev, 1, "distinct count")) return rc;
-  unsigned long long n_unique = 0;
-  auto reduce = [&](auto values_in) -> int {
-    size_t bytes = 0;
-    GOSH_TRY_HIP(rocprim::reduce_by_key(nullptr, bytes, keys_sorted, values_in, static_cast<size_t>(nnz),
-                                      unique_keys, sums, count_dev, rocprim::plus<int64_t>(),
-                                      rocprim::equal_to<uint64_t>(), nullptr),
-               "reduce by key (size query)");
-    char *temp = nullptr;
-    if (int rc = buf.alloc(&temp, bytes, "reduce workspace")) return rc;
-    GOSH_TRY_HIP(rocprim::reduce_by_key(temp, bytes, keys_sorted, values_in, static_cast<size_t>(nnz),
-                                      unique_keys, sums, count_dev, rocprim::plus<int64_t>(),
-                                      rocprim::equal_to<uint64_t>(), nullptr),
-               "reduce by key");
-    GOSH_TRY_HIP(hipMemcpy(&n_unique, count_dev, sizeof(n_unique), hipMemcpyDeviceToHost), "copy distinct count");
-    buf.release(temp);
-    return GOSH_OK;
-  };
-  if (weighted) {
-    if (int rc = reduce(static_cast<const int64_t *>(vals_sorted))) return rc;
-  } else {
-    if (int rc = reduce(rocprim::constant_iterator<int64_t>(1))) return rc;
-  }
-  buf.release(keys_sorted);
-  if (vals_sorted) buf.release(vals_sorted);
-  // entries inside clusters collapse into one sentinel key, the largest: drop it
-  if (n_unique > 0) {
-    uint64_t last = 0;
-    GOSH_TRY_HIP(hipMemcpy(&last, unique_keys + (n_unique - 1), 8, hipMemcpyDeviceToHost), "copy last key");
-    if (last == sentinel) --n_unique;
-  }
-  const int64_t nnz_coarse = static_cast<int64_t>(n_unique);
-  coarse.nnz = nnz_coarse;
-  if (int rc = persistent(&coarse.adj, static_cast<size_t>(nnz_coarse), "coarse adjacency")) return rc;
-  if (int rc = persistent(&coarse.mult, static_cast<size_t>(nnz_coarse), "coarse multiplicities")) return rc;
-  hipLaunchKernelGGL(offsets_kernel, dim3(blocks_for(n_coarse + 1, 256)), dim3(256), 0, nullptr, unique_keys,
-                     nnz_coarse, nc, xadj_out);
-  if (int rc = gosh::check_launch("offsets_kernel")) return rc;
-  if (nnz_coarse > 0) {
-    hipLaunchKernelGGL(columns_kernel, dim3(blocks_for(nnz_coarse, 256)), dim3(256), 0, nullptr, unique_keys, sums,
-                       nnz_coarse, nc, coarse.adj, coarse.mult);
-    if (int rc = gosh::check_launch("columns_kernel")) return rc;
-  }
-  GOSH_TRY_HIP(hipDeviceSynchronize(), "coarse CSR");
-  return GOSH_OK;
 }
 
 }  // namespace gosh

@@ -64,6 +64,7 @@ using RawVector = std::vector<T, NoInitAlloc<T>>;
 struct DeviceLevel {
   int device = -1;
   int64_t n = 0, nnz = 0;
+  int64_t weight = 0;  // entries of G_0, which no sum of multiplicities exceeds
   int32_t xadj_is64 = 1;
   void *xadj = nullptr;     // n + 1 offsets
   int32_t *adj = nullptr;   // nnz neighbours

@@ -1,0 +1,813 @@
+// "Coarsen(G_i, map_i)" on the device: the quotient graph of a level under its map.
+//
+// Every coarse row is the union of the fine rows of its members, so the entries of a coarse
+// row are brought together by moving whole fine rows, not by sorting entries: the vertices are
+// sorted by cluster, a scan of their degrees in that order gives every fine row its place, and
+// one pass over the entries writes the cluster of each neighbour there.  What is left is to
+// sort each coarse row ("segment") by itself and to merge equal entries.  Three ways, by the
+// length S of the segment:
+//   S <= 512            one wavefront, bitonic in registers
+//   S <= bitmap_from()  one workgroup, the same
+//   longer              no comparisons: a bitmap in LDS with a bit per possible neighbour, 2^18
+//                       ("piece") at a time, whose set bits are the merged row in order
+// The first two merge in place and are copied out once the length of every coarse row is
+// known.  The bitmap is made to count a row and made again to write it where it belongs; the
+// number of bits below an entry is the place of its sum.  Rows longer than dense_from(), whose
+// sums would fill the LDS many times over, are written by direct counting instead: a counter
+// per possible neighbour, 2^14 ("strip") at a time, each strip by a workgroup of its own.
+//
+// Sorted distinct entries with summed multiplicities are unique, so the arrays are those of
+// the sequential algorithm.  Against a radix sort of 64-bit (row, column) keys of all entries
+// and a reduction of equal keys, which this replaced: 128 M entries of a 4 M-vertex R-MAT graph
+// took 8.9 ms and take 4.4, 117 M weighted entries of its second level 10.5 and 4.5; 8 (wide
+// sums: 12) bytes of scratch per entry instead of 32.  A third of it is the gather.
+#include <hip/hip_runtime.h>
+
+#include <algorithm>
+#include <cstring>
+#include <type_traits>
+
+#include <rocprim/rocprim.hpp>
+
+#include "gosh_coarsen_internal.h"
+#include "gosh_common.h"
+#include "gosh_device_pool.h"
+
+namespace {
+
+using gosh::blocks_for;
+using gosh::persistent;
+
+constexpr uint32_t kInside = 0xFFFFFFFFu;  // an entry inside its cluster: above every cluster id
+constexpr int kGatherTile = 4096;          // entries per workgroup of the gather
+constexpr int kGatherRows = 1024;          // rows of a tile that are looked up in LDS
+// Longest segments that are sorted in the registers of a wavefront, 1, 2, 4 or 8 per lane, and
+// in those of a workgroup.
+constexpr int kSortClasses = 5;
+constexpr int kSortMax[kSortClasses] = {64, 128, 256, 512, 2048};
+enum : int { kBitmap = kSortClasses, kDense, kWays };
+constexpr int kPieceBits = 18, kPieceWords = 1 << (kPieceBits - 5);
+constexpr int kStripBits = 14, kStripsPerPiece = 1 << (kPieceBits - kStripBits);
+constexpr int kSumBytes = 30 << 10;  // LDS for the columns and sums of a piece, as many at a time as fit
+
+// Number of segments per way of merging, and 1 + the largest column met.
+struct Classes {
+  unsigned int count[kWays], columns;
+};
+
+// Raises *word to the largest `mine` of the workgroup: one atomic, and only if that is above
+// what is read there (the word only grows, so a stale value costs an atomic at most).
+__device__ inline void raise_by_block(unsigned int *word, unsigned int mine, unsigned int *block_top) {
+  if (mine) atomicMax(block_top, mine);
+  __syncthreads();
+  if (threadIdx.x == 0 && *block_top > __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+    atomicMax(word, *block_top);
+}
+
+__host__ __device__ inline int64_t pieces_of(int64_t columns) {
+  return std::max<int64_t>((columns + (int64_t{1} << kPieceBits) - 1) >> kPieceBits, 1);
+}
+
+// Longest segment that is sorted: the bitmap costs a fixed time per 2^14 columns, as much as
+// sorting about 160 entries, and longer ones have no network.
+__host__ __device__ inline int64_t bitmap_from(int64_t columns) {
+  return std::min<int64_t>(kSortMax[kSortClasses - 1], std::max<int64_t>(512, ((columns >> kStripBits) + 1) * 160));
+}
+
+// Longest segment whose sums are placed by rank.  Every kSumBytes of sums read the segment
+// again, in one workgroup; every strip of a counted segment does too, but side by side.
+__host__ __device__ inline int64_t dense_from(int64_t columns) { return std::max<int64_t>(1 << 15, columns / 8); }
+
+// len[t] = degree of the t-th vertex in cluster order, len[n] = 0.
+template <typename OffT>
+__global__ __launch_bounds__(256) void row_lengths_kernel(const OffT *__restrict__ xadj,
+                                                          const int32_t *__restrict__ order, int64_t n,
+                                                          int64_t *__restrict__ len) {
+  for (int64_t t = blockIdx.x * 256LL + threadIdx.x; t <= n; t += gridDim.x * 256LL) {
+    const int64_t v = t < n ? order[t] : 0;
+    len[t] = t < n ? static_cast<int64_t>(xadj[v + 1] - xadj[v]) : 0;
+  }
+}
+
+__global__ __launch_bounds__(256) void iota_kernel(int32_t *__restrict__ ids, int64_t n) {
+  for (int64_t v = blockIdx.x * 256LL + threadIdx.x; v < n; v += gridDim.x * 256LL) ids[v] = static_cast<int32_t>(v);
+}
+
+// segment[a] = place of the first entry of cluster a (segment[n_coarse] = nnz); tile_row[k] =
+// row that holds entry k * kGatherTile.  pos is the scan of the row lengths.
+__global__ __launch_bounds__(256) void segments_kernel(const int32_t *__restrict__ cluster,
+                                                       const int64_t *__restrict__ pos, int64_t n, int64_t nnz,
+                                                       int64_t n_coarse, int64_t *__restrict__ segment,
+                                                       int32_t *__restrict__ tile_row) {
+  for (int64_t t = blockIdx.x * 256LL + threadIdx.x; t < n; t += gridDim.x * 256LL) {
+    const int64_t a = cluster[t], lo = pos[t], hi = pos[t + 1];
+    // every cluster has a member, so each of these loops writes one entry or none
+    for (int64_t c = t == 0 ? 0 : cluster[t - 1] + 1LL; c <= a; ++c) segment[c] = lo;
+    if (t == n - 1)
+      for (int64_t c = a + 1; c <= n_coarse; ++c) segment[c] = nnz;
+    for (int64_t k = (lo + kGatherTile - 1) / kGatherTile; k * kGatherTile < hi; ++k) tile_row[k] = static_cast<int32_t>(t);
+  }
+}
+
+// Largest row r in [lo, hi] with pos[r] <= e, i.e. the row that holds entry e (empty rows
+// share their place with the next row and are skipped).
+template <typename PosT>
+__device__ inline int32_t row_of_entry(const PosT *pos, int32_t lo, int32_t hi, PosT e) {
+  while (lo < hi) {
+    const int32_t mid = lo + (hi - lo + 1) / 2;
+    if (pos[mid] <= e) lo = mid;
+    else hi = mid - 1;
+  }
+  return lo;
+}
+
+// Entry e in cluster order: the cluster of its neighbour (kInside if that is its own) and its
+// multiplicity.  A workgroup takes kGatherTile consecutive entries, so hub rows are no long
+// tail and the writes are coalesced; the rows it spans are looked up in LDS.  Bound by the
+// 4-byte gathers from the map.
+template <typename OffT, typename WT, bool WEIGHTED>
+__global__ __launch_bounds__(256) void gather_kernel(const OffT *__restrict__ xadj, const int32_t *__restrict__ adj,
+                                                     const int64_t *__restrict__ mult,
+                                                     const int32_t *__restrict__ map,
+                                                     const int32_t *__restrict__ order,
+                                                     const int32_t *__restrict__ cluster,
+                                                     const int64_t *__restrict__ pos,
+                                                     const int32_t *__restrict__ tile_row, int64_t n, int64_t nnz,
+                                                     uint32_t *__restrict__ column, WT *__restrict__ weight,
+                                                     Classes *__restrict__ classes) {
+  constexpr int kUnits = 4;
+  __shared__ unsigned int block_top;
+  if (threadIdx.x == 0) block_top = 0;
+  unsigned int top = 0;
+  __shared__ int32_t place[kGatherRows];  // relative to the tile; rows that began before it count as 0
+  __shared__ int64_t from[kGatherRows];   // fine entry of place 0 of the row, were it that long
+  __shared__ int32_t owner[kGatherRows];
+  const int64_t tiles = (nnz + kGatherTile - 1) / kGatherTile;
+  for (int64_t tile = blockIdx.x; tile < tiles; tile += gridDim.x) {
+    const int64_t e0 = tile * kGatherTile, e1 = std::min(e0 + kGatherTile, nnz);
+    const int32_t row0 = tile_row[tile];
+    const int32_t row1 = tile + 1 < tiles ? tile_row[tile + 1] : static_cast<int32_t>(n - 1);
+    const bool in_lds = row1 - row0 < kGatherRows;
+    __syncthreads();  // the tables of the previous tile have been used
+    if (in_lds)
+      for (int32_t r = threadIdx.x; r <= row1 - row0; r += 256) {
+        const int64_t p = pos[row0 + r];
+        place[r] = static_cast<int32_t>(std::min<int64_t>(std::max<int64_t>(p - e0, 0), kGatherTile));
+        from[r] = static_cast<int64_t>(xadj[order[row0 + r]]) - p;
+        owner[r] = cluster[row0 + r];
+      }
+    __syncthreads();
+    for (int64_t first = e0 + threadIdx.x; first < e1; first += 256 * kUnits) {
+      int64_t at[kUnits];
+      int32_t own[kUnits], y[kUnits];
+#pragma unroll
+      for (int q = 0; q < kUnits; ++q) {
+        const int64_t e = std::min(first + q * 256, e1 - 1);
+        if (in_lds) {
+          const int32_t r = row_of_entry<int32_t>(place, 0, row1 - row0, static_cast<int32_t>(e - e0));
+          at[q] = from[r] + e;
+          own[q] = owner[r];
+        } else {
+          const int32_t r = row_of_entry<int64_t>(pos, row0, row1, e);
+          at[q] = static_cast<int64_t>(xadj[order[r]]) - pos[r] + e;
+          own[q] = cluster[r];
+        }
+      }
+#pragma unroll
+      for (int q = 0; q < kUnits; ++q) y[q] = adj[at[q]];
+#pragma unroll
+      for (int q = 0; q < kUnits; ++q) {
+        const int64_t e = first + q * 256;
+        const int32_t b = map[y[q]];
+        if (e < e1) {
+          column[e] = b == own[q] ? kInside : static_cast<uint32_t>(b);
+          top = max(top, static_cast<unsigned int>(b) + 1);
+          if constexpr (WEIGHTED) weight[e] = static_cast<WT>(mult[at[q]]);
+        }
+      }
+    }
+  }
+  raise_by_block(&classes->columns, top, &block_top);
+}
+
+// Sorts the segments into kWays lists (list + 0, + n_coarse, ...) and clears the
+// lengths that are not set by assignment.  One atomic per workgroup and list.
+__global__ __launch_bounds__(1024) void classify_segments_kernel(const int64_t *__restrict__ segment, int64_t n_coarse,
+                                                                 int32_t *__restrict__ list,
+                                                                 int64_t *__restrict__ length,
+                                                                 Classes *__restrict__ classes) {
+  __shared__ unsigned int count[kWays], base[kWays];
+  const int64_t longest_sorted = bitmap_from(classes->columns), longest_ranked = dense_from(classes->columns);
+  for (int64_t first = blockIdx.x * 1024LL; first < n_coarse; first += gridDim.x * 1024LL) {
+    if (threadIdx.x < kWays) count[threadIdx.x] = 0;
+    __syncthreads();
+    const int64_t a = first + threadIdx.x;
+    int cls = -1;
+    unsigned int mine = 0;
+    if (a < n_coarse) {
+      const int64_t s = segment[a + 1] - segment[a];
+      if (s > longest_sorted) cls = s <= longest_ranked ? kBitmap : kDense;
+      else if (s > 0)
+        for (cls = 0; s > kSortMax[cls];) ++cls;
+      if (cls < 0 || cls >= kBitmap) length[a] = 0;
+    }
+    if (cls >= 0) mine = atomicAdd(&count[cls], 1u);
+    __syncthreads();
+    if (threadIdx.x < kWays && count[threadIdx.x]) 
+      base[threadIdx.x] = atomicAdd(&classes->count[threadIdx.x], count[threadIdx.x]);
+    __syncthreads();
+    if (cls >= 0) list[cls * n_coarse + base[cls] + mine] = static_cast<int32_t>(a);
+    __syncthreads();
+  }
+}
+
+// The value of lane ^ MASK.
+template <int MASK>
+__device__ __forceinline__ uint32_t lane_xor(uint32_t x) {
+  const int v = static_cast<int>(x);
+  if constexpr (MASK == 1) return __builtin_amdgcn_update_dpp(0, v, 0xB1, 0xF, 0xF, false);       // quad_perm [1,0,3,2]
+  else if constexpr (MASK == 2) return __builtin_amdgcn_update_dpp(0, v, 0x4E, 0xF, 0xF, false);  // quad_perm [2,3,0,1]
+  else if constexpr (MASK == 4) return __builtin_amdgcn_ds_swizzle(v, 0x101F);
+  else if constexpr (MASK == 8) return __builtin_amdgcn_update_dpp(0, v, 0x128, 0xF, 0xF, false);  // row_ror 8
+  else if constexpr (MASK == 16) return __builtin_amdgcn_ds_swizzle(v, 0x401F);
+  else return __shfl_xor(v, 32, 64);
+}
+template <int MASK>
+__device__ __forceinline__ unsigned long long lane_xor(unsigned long long x) {
+  return static_cast<unsigned long long>(lane_xor<MASK>(static_cast<uint32_t>(x >> 32))) << 32 |
+         lane_xor<MASK>(static_cast<uint32_t>(x));
+}
+
+// One stage (distance J, in blocks of K) of a bitonic network over the elements first + r,
+// r < R, of consecutive lanes; distances below 64 R.  Equal keys stay where they are on both sides.
+template <int K, int J, int R, bool WEIGHTED, typename WT>
+__device__ __forceinline__ void bitonic_stage(uint32_t (&key)[R], WT (&w)[R], uint32_t first) {
+  if constexpr (J < R) {
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+      if ((r & J) == 0) {
+        const bool up = ((first + r) & K) == 0;
+        if ((key[r] > key[r | J]) == up && key[r] != key[r | J]) {
+          const uint32_t k = key[r];
+          key[r] = key[r | J];
+          key[r | J] = k;
+          if constexpr (WEIGHTED) {
+            const WT x = w[r];
+            w[r] = w[r | J];
+            w[r | J] = x;
+          }
+        }
+      }
+  } else {
+    const bool keep_small = ((first & J) == 0) == ((first & K) == 0);
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      const uint32_t other = lane_xor<J / R>(key[r]);
+      if constexpr (WEIGHTED) {
+        const WT other_w = lane_xor<J / R>(w[r]);
+        const bool take = keep_small ? other < key[r] : other > key[r];
+        key[r] = take ? other : key[r];
+        w[r] = take ? other_w : w[r];
+      } else {
+        key[r] = keep_small ? min(key[r], other) : max(key[r], other);
+      }
+    }
+  }
+}
+template <int K, int J, int R, bool WEIGHTED, typename WT>
+__device__ __forceinline__ void bitonic_merge(uint32_t (&key)[R], WT (&w)[R], uint32_t first) {
+  bitonic_stage<K, J, R, WEIGHTED>(key, w, first);
+  if constexpr (J > 1) bitonic_merge<K, J / 2, R, WEIGHTED>(key, w, first);
+}
+template <int K, int TOP, int R, bool WEIGHTED, typename WT>
+__device__ __forceinline__ void bitonic_blocks(uint32_t (&key)[R], WT (&w)[R], uint32_t first) {
+  bitonic_merge<K, K / 2, R, WEIGHTED>(key, w, first);
+  if constexpr (K < TOP) bitonic_blocks<K * 2, TOP, R, WEIGHTED>(key, w, first);
+}
+
+// Segments of at most WAVES * 64 * R entries, WAVES wavefronts each: a bitonic network over the
+// registers of the lanes (R consecutive elements per lane; between wavefronts through LDS),
+// then equal columns are merged in place.  The sum of a run is the difference of the running
+// sums at its end and at the end of the run before.  Bound by the network's instructions: 67 M
+// entries in segments of 65 to 2,048 take 0.70 ms, weighted 1.18 ms (with the keys in LDS and a
+// barrier per stage, bound by latency, those up to 1,024 alone took 1.46 and 1.86 ms).
+template <int R, int WAVES, typename WT, bool WEIGHTED>
+__global__ __launch_bounds__(256) void merge_sorted_kernel(const int64_t *__restrict__ segment,
+                                                           const int32_t *__restrict__ list, int64_t count,
+                                                           uint32_t *__restrict__ column, WT *__restrict__ weight,
+                                                           int64_t *__restrict__ length) {
+  static_assert(WAVES == 1 || WAVES == 4, "a wavefront or a workgroup");
+  constexpr int kWave = 64 * R, kAll = kWave * WAVES;
+  constexpr int kTeams = 4 / WAVES;  // segments a workgroup works at
+  __shared__ uint32_t swap_key[WAVES > 1 ? kAll : 1];
+  __shared__ WT swap_w[WAVES > 1 && WEIGHTED ? kAll : 1];
+  __shared__ WT run_end[kTeams][kAll];  // running sum at the end of each run
+  __shared__ int wave_heads[4];
+  __shared__ WT wave_sum[4];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, team = wave / WAVES;
+  const int member = wave % WAVES;  // wavefront within the team
+  const uint32_t first = (member * 64 + lane) * R;
+  // a team takes the segments team, team + teams, ...; with several teams there are no barriers
+  auto team_sync = [] {
+    if constexpr (WAVES > 1) {
+      __syncthreads();
+    } else {  // LDS accesses of a wavefront take effect in their order; the compiler must keep it
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+    }
+  };
+  for (int64_t i = static_cast<int64_t>(blockIdx.x) * kTeams + team; i < count; i += static_cast<int64_t>(gridDim.x) * kTeams) {
+    const int32_t a = list[i];
+    const int64_t lo = segment[a];
+    const uint32_t size = static_cast<uint32_t>(segment[a + 1] - lo);
+    uint32_t key[R];
+    WT w[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      // lane-consecutive loads; where an element starts does not matter to a sort
+      const uint32_t e = member * kWave + r * 64 + lane;
+      key[r] = e < size ? column[lo + e] : kInside;
+      w[r] = WT(1);
+      if constexpr (WEIGHTED) w[r] = e < size ? weight[lo + e] : WT(0);
+    }
+    bitonic_blocks<2, kWave, R, WEIGHTED>(key, w, first);
+    if constexpr (WAVES == 4) {
+#pragma unroll
+      for (int k = 2 * kWave; k <= kAll; k *= 2) {
+#pragma unroll
+        for (int j = k / 2; j >= kWave; j /= 2) {
+          __syncthreads();
+#pragma unroll
+          for (int r = 0; r < R; ++r) {
+            swap_key[r * 256 + threadIdx.x] = key[r];
+            if constexpr (WEIGHTED) swap_w[r * 256 + threadIdx.x] = w[r];
+          }
+          __syncthreads();
+          const bool keep_small = ((first & j) == 0) == ((first & k) == 0);
+          const int partner = threadIdx.x ^ (j / R);
+#pragma unroll
+          for (int r = 0; r < R; ++r) {
+            const uint32_t other = swap_key[r * 256 + partner];
+            const bool take = keep_small ? other < key[r] : other > key[r];
+            key[r] = take ? other : key[r];
+            if constexpr (WEIGHTED) w[r] = take ? swap_w[r * 256 + partner] : w[r];
+          }
+        }
+        if (k == 2 * kWave) bitonic_merge<2 * kWave, kWave / 2, R, WEIGHTED>(key, w, first);
+        else bitonic_merge<4 * kWave, kWave / 2, R, WEIGHTED>(key, w, first);
+      }
+      __syncthreads();
+      if (lane == 63) swap_key[wave] = key[R - 1];  // the element before the next wavefront's first
+      __syncthreads();
+    }
+    uint32_t before = __shfl_up(key[R - 1], 1, 64);
+    if (lane == 0) before = kInside;  // nothing equals it that counts
+    if constexpr (WAVES == 4)
+      if (lane == 0 && wave > 0) before = swap_key[wave - 1];
+    // heads and running sums: over the lane's elements, the lanes, the team's wavefronts
+    bool head[R];
+    int heads = 0;
+    WT sum = 0;
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      head[r] = key[r] != kInside && key[r] != (r == 0 ? before : key[r - 1]);
+      heads += head[r];
+      sum += key[r] != kInside ? w[r] : WT(0);
+    }
+    int upto = heads;
+    WT sum_upto = sum;
+#pragma unroll
+    for (int step = 1; step < 64; step <<= 1) {
+      const int h = __shfl_up(upto, step, 64);
+      const WT s = __shfl_up(sum_upto, step, 64);
+      if (lane >= step) {
+        upto += h;
+        sum_upto += s;
+      }
+    }
+    int rank = upto - heads - 1;  // of the run that the element before belongs to
+    WT running = sum_upto - sum;
+    int distinct = __shfl(upto, 63, 64);
+    if constexpr (WAVES == 4) {
+      if (lane == 63) {
+        wave_heads[wave] = upto;
+        wave_sum[wave] = sum_upto;
+      }
+      __syncthreads();
+      distinct = 0;
+      for (int q = 0; q < 4; ++q) {
+        if (q < wave) {
+          rank += wave_heads[q];
+          running += wave_sum[q];
+        }
+        distinct += wave_heads[q];
+      }
+    }
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      if (head[r]) {
+        if (rank >= 0) run_end[team][rank] = running;  // the run before ends here
+        ++rank;
+        column[lo + rank] = key[r];  // every column of the segment is in registers
+      }
+      running += key[r] != kInside ? w[r] : WT(0);
+    }
+    const uint32_t last = first + R - 1;  // the team's last lane knows the end of the last run
+    if (last == kAll - 1 && rank >= 0) run_end[team][rank] = running;
+    team_sync();
+    for (int c = member * 64 + lane; c < distinct; c += 64 * WAVES)
+      weight[lo + c] = run_end[team][c] - (c > 0 ? run_end[team][c - 1] : WT(0));
+    if (first == 0) length[a] = distinct;
+    team_sync();
+  }
+}
+
+// Calls body(entry, column) for the entries [lo, hi) with the workgroup's threads side by side,
+// eight requested before the first is used: a workgroup has its compute unit nearly to itself
+// and would otherwise wait for memory once per entry and thread (counting 55 M entries in 9,000
+// segments: 110 us, 690 us one by one).
+template <class Body>
+__device__ __forceinline__ void for_entries(const uint32_t *__restrict__ column, int64_t lo, int64_t hi, Body body) {
+  constexpr int kAhead = 8;
+  const int64_t step = blockDim.x;
+  for (int64_t first = lo + threadIdx.x; first < hi; first += kAhead * step) {
+    uint32_t b[kAhead];
+#pragma unroll
+    for (int q = 0; q < kAhead; ++q) b[q] = column[std::min(first + q * step, hi - 1)];
+#pragma unroll
+    for (int q = 0; q < kAhead; ++q)
+      if (first + q * step < hi) body(first + q * step, b[q]);
+  }
+}
+
+// Marks the columns of a piece of a segment in the bitmap.  Returns the number of its words.
+__device__ inline int mark_piece(const uint32_t *__restrict__ column, int64_t lo, int64_t hi, int64_t piece,
+                                 int64_t columns, uint32_t *bits) {
+  const uint32_t base = static_cast<uint32_t>(piece << kPieceBits);
+  const int words = static_cast<int>(std::min<int64_t>(kPieceWords, (columns - base + 31) / 32));
+  const uint32_t width = static_cast<uint32_t>(words) * 32u;
+  for (int w = threadIdx.x; w < kPieceWords; w += blockDim.x) bits[w] = 0;
+  __syncthreads();
+  for_entries(column, lo, hi, [&](int64_t, uint32_t b) {
+    b -= base;  // columns of other pieces, and kInside, are past the bitmap
+    if (b < width) atomicOr(&bits[b >> 5], 1u << (b & 31));
+  });
+  __syncthreads();
+  return words;
+}
+
+// Distinct columns of every strip of the segments of a list, and of the segments.
+__global__ __launch_bounds__(512) void count_pieces_kernel(const int64_t *__restrict__ segment,
+                                                           const int32_t *__restrict__ list, int64_t count,
+                                                           int64_t pieces, int64_t columns,
+                                                           const uint32_t *__restrict__ column,
+                                                           uint32_t *__restrict__ in_strip,
+                                                           int64_t *__restrict__ length) {
+  constexpr int kStripWords = kPieceWords / kStripsPerPiece;
+  __shared__ uint32_t bits[kPieceWords];
+  __shared__ uint32_t total;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  for (int64_t job = blockIdx.x; job < count * pieces; job += gridDim.x) {
+    const int32_t a = list[job / pieces];
+    if (threadIdx.x == 0) total = 0;
+    mark_piece(column, segment[a], segment[a + 1], job % pieces, columns, bits);
+    for (int strip = wave; strip < kStripsPerPiece; strip += 8) {
+      uint32_t mine = 0;
+      for (int w = lane; w < kStripWords; w += 64) mine += __popc(bits[strip * kStripWords + w]);
+      for (int off = 32; off >= 1; off >>= 1) mine += __shfl_xor(mine, off, 64);
+      if (lane == 0) {
+        in_strip[job * kStripsPerPiece + strip] = mine;
+        if (mine) atomicAdd(&total, mine);
+      }
+    }
+    __syncthreads();
+    if (threadIdx.x == 0 && total)
+      atomicAdd(reinterpret_cast<unsigned long long *>(length + a), static_cast<unsigned long long>(total));
+    __syncthreads();  // bits and total are rewritten in the next round
+  }
+}
+
+// Distinct columns in the strips [0, upto) of a segment, added to *sum (which is clear).
+__device__ inline void add_strips(const uint32_t *__restrict__ in_strip, int64_t upto, unsigned long long *sum) {
+  unsigned long long mine = 0;
+  for (int64_t p = threadIdx.x; p < upto; p += blockDim.x) mine += in_strip[p];
+  if (mine) atomicAdd(sum, mine);
+}
+
+// Writes the pieces of the segments of a list where they belong: the number of set bits below
+// an entry's column is the place of that column and of its sum (40 M entries of 8,900 segments:
+// 0.68 ms; walking the set bits instead, where the rows are dense in small ids, 1.21 ms).
+template <typename WT, bool WEIGHTED>
+__global__ __launch_bounds__(1024) void write_pieces_kernel(const int64_t *__restrict__ segment,
+                                                            const int32_t *__restrict__ list, int64_t count,
+                                                            int64_t pieces, int64_t columns,
+                                                            const uint32_t *__restrict__ column,
+                                                            const WT *__restrict__ weight,
+                                                            const uint32_t *__restrict__ in_strip,
+                                                            const int64_t *__restrict__ xadj_out,
+                                                            int32_t *__restrict__ adj_out,
+                                                            int64_t *__restrict__ mult_out) {
+  constexpr uint32_t kSums = kSumBytes / (sizeof(WT) + 4);
+  constexpr int kPairs = kPieceWords / 2, kPerThread = kPairs / 1024;
+  __shared__ unsigned long long bits[kPairs];
+  __shared__ uint32_t below[kPairs];  // set bits in the pairs of words before
+  __shared__ WT sums[kSums];
+  __shared__ uint32_t found[kSums];
+  __shared__ uint32_t wave_total[16];
+  __shared__ unsigned long long earlier;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  for (int64_t job = blockIdx.x; job < count * pieces; job += gridDim.x) {
+    const int64_t which = job / pieces, piece = job % pieces;
+    const int32_t a = list[which];
+    const int64_t lo = segment[a], hi = segment[a + 1];
+    __syncthreads();  // the previous piece is done with the LDS
+    if (threadIdx.x == 0) earlier = 0;
+    const uint32_t width = 32u * mark_piece(column, lo, hi, piece, columns, reinterpret_cast<uint32_t *>(bits));
+    add_strips(in_strip + which * pieces * kStripsPerPiece, piece * kStripsPerPiece, &earlier);
+    // exclusive scan of the set bits: kPerThread pairs per thread, then over the workgroup
+    const int p0 = threadIdx.x * kPerThread;
+    uint32_t mine = 0;
+#pragma unroll
+    for (int q = 0; q < kPerThread; ++q) mine += __popcll(bits[p0 + q]);
+    uint32_t upto = mine;
+    for (int step = 1; step < 64; step <<= 1) {
+      const uint32_t x = __shfl_up(upto, step, 64);
+      if (lane >= step) upto += x;
+    }
+    if (lane == 63) wave_total[wave] = upto;
+    __syncthreads();
+    uint32_t rank = upto - mine, distinct = 0;
+    for (int q = 0; q < 16; ++q) {
+      if (q < wave) rank += wave_total[q];
+      distinct += wave_total[q];
+    }
+    const int64_t out = xadj_out[a] + static_cast<int64_t>(earlier);
+    const uint32_t base = static_cast<uint32_t>(piece << kPieceBits);
+    for (int q = 0; q < kPerThread; ++q) {
+      below[p0 + q] = rank;
+      rank += __popcll(bits[p0 + q]);
+    }
+    for (uint32_t first = 0; first < distinct; first += kSums) {
+      const uint32_t here = std::min(kSums, distinct - first);
+      for (uint32_t c = threadIdx.x; c < here; c += 1024) sums[c] = 0;
+      __syncthreads();
+      for_entries(column, lo, hi, [&](int64_t e, uint32_t b) {
+        b -= base;
+        if (b < width) {
+          const uint32_t c = below[b >> 6] + __popcll(bits[b >> 6] & ((1ull << (b & 63)) - 1)) - first;
+          if (c < here) {
+            found[c] = base + b;  // by every entry of that column alike
+            atomicAdd(&sums[c], WEIGHTED ? weight[e] : WT(1));
+          }
+        }
+      });
+      __syncthreads();
+      for (uint32_t c = threadIdx.x; c < here; c += 1024) {
+        adj_out[out + first + c] = static_cast<int32_t>(found[c]);
+        mult_out[out + first + c] = static_cast<int64_t>(sums[c]);
+      }
+      __syncthreads();
+    }
+  }
+}
+
+// Writes the strips of the segments of a list where they belong, by counting (14 M entries of 46
+// segments: 84 us; ranked like the others, where the longest was read again 25 times by one
+// workgroup, they took 4 to 20 ms).
+template <typename WT, bool WEIGHTED>
+__global__ __launch_bounds__(1024) void write_strips_kernel(const int64_t *__restrict__ segment,
+                                                            const int32_t *__restrict__ list, int64_t count,
+                                                            int64_t strips, const uint32_t *__restrict__ column,
+                                                            const WT *__restrict__ weight,
+                                                            const uint32_t *__restrict__ in_strip,
+                                                            const int64_t *__restrict__ xadj_out,
+                                                            int32_t *__restrict__ adj_out,
+                                                            int64_t *__restrict__ mult_out) {
+  constexpr int kWidth = 1 << kStripBits, kPerWave = kWidth / 16;
+  __shared__ WT sums[kWidth];
+  __shared__ uint32_t wave_total[16];
+  __shared__ unsigned long long earlier;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  for (int64_t job = blockIdx.x; job < count * strips; job += gridDim.x) {
+    if (in_strip[job] == 0) continue;  // the same for the whole workgroup
+    const int64_t which = job / strips, strip = job % strips;
+    const int32_t a = list[which];
+    const uint32_t base = static_cast<uint32_t>(strip << kStripBits);
+    __syncthreads();  // the previous strip is done with the LDS
+    if (threadIdx.x == 0) earlier = 0;
+    for (int c = threadIdx.x; c < kWidth; c += 1024) sums[c] = 0;
+    __syncthreads();
+    add_strips(in_strip + which * strips, strip, &earlier);
+    for_entries(column, segment[a], segment[a + 1], [&](int64_t e, uint32_t b) {
+      b -= base;  // columns of other strips, and kInside, are past the counters
+      if (b < static_cast<uint32_t>(kWidth)) atomicAdd(&sums[b], WEIGHTED ? weight[e] : WT(1));
+    });
+    __syncthreads();
+    uint32_t mine = 0;
+    for (int c = lane; c < kPerWave; c += 64) mine += __popcll(__ballot(sums[wave * kPerWave + c] != 0));
+    if (lane == 0) wave_total[wave] = mine;
+    __syncthreads();
+    int64_t out = xadj_out[a] + static_cast<int64_t>(earlier);
+    for (int q = 0; q < wave; ++q) out += wave_total[q];
+    for (int c = lane; c < kPerWave; c += 64) {
+      const WT sum = sums[wave * kPerWave + c];
+      const unsigned long long set = __ballot(sum != 0);
+      if (sum != 0) {
+        const int64_t at = out + __popcll(set & ((1ull << lane) - 1));
+        adj_out[at] = static_cast<int32_t>(base + wave * kPerWave + c);
+        mult_out[at] = static_cast<int64_t>(sum);
+      }
+      out += __popcll(set);
+    }
+  }
+}
+
+// Copies the segments that were merged in place, one wavefront each.
+template <typename WT>
+__global__ __launch_bounds__(256) void copy_merged_kernel(const int64_t *__restrict__ segment,
+                                                          const int32_t *__restrict__ list, int64_t count,
+                                                          const uint32_t *__restrict__ column,
+                                                          const WT *__restrict__ weight,
+                                                          const int64_t *__restrict__ xadj_out,
+                                                          int32_t *__restrict__ adj_out,
+                                                          int64_t *__restrict__ mult_out) {
+  const int lane = threadIdx.x & 63;
+  const int64_t waves = (gridDim.x * 256LL) >> 6;
+  for (int64_t i = (blockIdx.x * 256LL + threadIdx.x) >> 6; i < count; i += waves) {
+    const int32_t a = list[i];
+    const int64_t lo = segment[a], out = xadj_out[a];
+    const int64_t size = xadj_out[a + 1] - out;
+    for (int64_t e = lane; e < size; e += 64) {
+      adj_out[out + e] = static_cast<int32_t>(column[lo + e]);
+      mult_out[out + e] = static_cast<int64_t>(weight[lo + e]);
+    }
+  }
+}
+
+__global__ void clear_classes_kernel(Classes *classes) { *classes = Classes{}; }
+
+template <typename OffT, typename WT, bool WEIGHTED>
+int quotient(gosh::DeviceCoarsener *dc, const gosh::DeviceLevel &fine, int64_t n_coarse, gosh::DeviceLevel &coarse,
+             int64_t *xadj_out) {
+  const int64_t n = fine.n, nnz = fine.nnz;
+  const OffT *xadj = static_cast<const OffT *>(fine.xadj);
+  gosh::Buffers buf(dc->pool);
+  uint32_t *column = nullptr;
+  WT *weight = nullptr;
+  int64_t *segment = nullptr, *length = nullptr;
+  int32_t *list = nullptr;
+  Classes *classes = nullptr;
+  if (int rc = buf.alloc(&column, static_cast<size_t>(nnz), "columns")) return rc;
+  if (int rc = buf.alloc(&weight, static_cast<size_t>(nnz), "multiplicities")) return rc;
+  if (int rc = buf.alloc(&segment, static_cast<size_t>(n_coarse) + 1, "coarse rows")) return rc;
+  if (int rc = buf.alloc(&length, static_cast<size_t>(n_coarse) + 1, "coarse row lengths")) return rc;
+  if (int rc = buf.alloc(&list, static_cast<size_t>(n_coarse) * kWays, "lists of coarse rows")) return rc;
+  if (int rc = buf.alloc(&classes, 1, "counters")) return rc;
+  hipLaunchKernelGGL(clear_classes_kernel, dim3(1), dim3(1), 0, nullptr, classes);
+  const int flat_blocks = blocks_for(n + 1, 256);
+
+  {  // the fine rows in cluster order
+    int32_t *ids = nullptr, *order = nullptr, *cluster = nullptr, *tile_row = nullptr;
+    int64_t *lengths = nullptr, *pos = nullptr;
+    const int64_t tiles = (nnz + kGatherTile - 1) / kGatherTile;
+    if (int rc = buf.alloc(&ids, static_cast<size_t>(n), "vertex ids")) return rc;
+    if (int rc = buf.alloc(&order, static_cast<size_t>(n), "cluster order")) return rc;
+    if (int rc = buf.alloc(&cluster, static_cast<size_t>(n), "sorted clusters")) return rc;
+    if (int rc = buf.alloc(&lengths, static_cast<size_t>(n) + 1, "row lengths")) return rc;
+    if (int rc = buf.alloc(&pos, static_cast<size_t>(n) + 1, "row places")) return rc;
+    if (int rc = buf.alloc(&tile_row, static_cast<size_t>(tiles), "tile rows")) return rc;
+    unsigned bits = 1;
+    while (bits < 31 && (n_coarse >> bits) != 0) ++bits;
+    size_t sort_bytes = 0, scan_bytes = 0;
+    GOSH_TRY_HIP(rocprim::radix_sort_pairs(nullptr, sort_bytes, fine.map, cluster, ids, order, static_cast<size_t>(n),
+                                           0u, bits, nullptr),
+                 "cluster sort (size query)");
+    GOSH_TRY_HIP(rocprim::exclusive_scan(nullptr, scan_bytes, lengths, pos, int64_t(0), static_cast<size_t>(n) + 1,
+                                         rocprim::plus<int64_t>(), nullptr),
+                 "row scan (size query)");
+    char *temp = nullptr;
+    if (int rc = buf.alloc(&temp, std::max(sort_bytes, scan_bytes), "sort workspace")) return rc;
+    hipLaunchKernelGGL(iota_kernel, dim3(flat_blocks), dim3(256), 0, nullptr, ids, n);
+    GOSH_TRY_HIP(rocprim::radix_sort_pairs(temp, sort_bytes, fine.map, cluster, ids, order, static_cast<size_t>(n), 0u,
+                                           bits, nullptr),
+                 "cluster sort");
+    hipLaunchKernelGGL(row_lengths_kernel<OffT>, dim3(flat_blocks), dim3(256), 0, nullptr, xadj, order, n, lengths);
+    GOSH_TRY_HIP(rocprim::exclusive_scan(temp, scan_bytes, lengths, pos, int64_t(0), static_cast<size_t>(n) + 1,
+                                         rocprim::plus<int64_t>(), nullptr),
+                 "row scan");
+    hipLaunchKernelGGL(segments_kernel, dim3(flat_blocks), dim3(256), 0, nullptr, cluster, pos, n, nnz, n_coarse,
+                       segment, tile_row);
+    hipLaunchKernelGGL((gather_kernel<OffT, WT, WEIGHTED>), dim3(blocks_for(nnz, kGatherTile)), dim3(256), 0, nullptr,
+                       xadj, fine.adj, fine.mult, fine.map, order, cluster, pos, tile_row, n, nnz, column, weight,
+                       classes);
+    if (int rc = gosh::check_launch("gather_kernel")) return rc;
+    for (void *p : {static_cast<void *>(ids), static_cast<void *>(order), static_cast<void *>(cluster),
+                    static_cast<void *>(lengths), static_cast<void *>(pos), static_cast<void *>(tile_row), static_cast<void *>(temp)})
+      buf.release(p);  // what takes them up again is on the same stream
+  }
+  hipLaunchKernelGGL(classify_segments_kernel, dim3(blocks_for(n_coarse, 1024)), dim3(1024), 0, nullptr, segment,
+                     n_coarse, list, length, classes);
+  if (int rc = gosh::check_launch("classify_segments_kernel")) return rc;
+  Classes c{};
+  GOSH_TRY_HIP(hipMemcpy(&c, classes, sizeof(c), hipMemcpyDeviceToHost), "read segment classes");
+
+  // merge: in place, or counted
+  const int32_t *bitmap_list = list + kBitmap * n_coarse, *dense_list = list + kDense * n_coarse;
+  const int64_t bitmaps = c.count[kBitmap], denses = c.count[kDense];
+  const int64_t pieces = pieces_of(c.columns), strips = pieces * kStripsPerPiece;
+  uint32_t *in_strip[2] = {nullptr, nullptr};
+  auto count_pieces = [&](const int32_t *which, int64_t count, uint32_t **strips_of) -> int {
+    if (count == 0) return GOSH_OK;
+    if (int rc = buf.alloc(strips_of, static_cast<size_t>(count * strips), "strips of coarse rows")) return rc;
+    hipLaunchKernelGGL(count_pieces_kernel, dim3(blocks_for(count * pieces, 1)), dim3(512), 0, nullptr, segment, which,
+                       count, pieces, static_cast<int64_t>(c.columns), column, *strips_of, length);
+    return GOSH_OK;
+  };
+  if (int rc = count_pieces(dense_list, denses, &in_strip[1])) return rc;
+  if (int rc = count_pieces(bitmap_list, bitmaps, &in_strip[0])) return rc;
+  auto merge_sorted = [&](auto kernel, int cls, int teams) {
+    if (c.count[cls] > 0)
+      hipLaunchKernelGGL(kernel, dim3(blocks_for(c.count[cls], teams)), dim3(256), 0, nullptr, segment,
+                         list + cls * n_coarse, static_cast<int64_t>(c.count[cls]), column, weight, length);
+  };
+  merge_sorted(merge_sorted_kernel<8, 4, WT, WEIGHTED>, 4, 1);
+  merge_sorted(merge_sorted_kernel<8, 1, WT, WEIGHTED>, 3, 4);
+  merge_sorted(merge_sorted_kernel<4, 1, WT, WEIGHTED>, 2, 4);
+  merge_sorted(merge_sorted_kernel<2, 1, WT, WEIGHTED>, 1, 4);
+  merge_sorted(merge_sorted_kernel<1, 1, WT, WEIGHTED>, 0, 4);
+  if (int rc = gosh::check_launch("merge of the coarse rows")) return rc;
+
+  // offsets; the last length is never read
+  {
+    size_t bytes = 0;
+    GOSH_TRY_HIP(rocprim::exclusive_scan(nullptr, bytes, length, xadj_out, int64_t(0), static_cast<size_t>(n_coarse) + 1,
+                                         rocprim::plus<int64_t>(), nullptr),
+                 "offset scan (size query)");
+    char *temp = nullptr;
+    if (int rc = buf.alloc(&temp, bytes, "scan workspace")) return rc;
+    GOSH_TRY_HIP(rocprim::exclusive_scan(temp, bytes, length, xadj_out, int64_t(0), static_cast<size_t>(n_coarse) + 1,
+                                         rocprim::plus<int64_t>(), nullptr),
+                 "offset scan");
+  }
+  GOSH_TRY_HIP(hipMemcpy(&coarse.nnz, xadj_out + n_coarse, 8, hipMemcpyDeviceToHost), "read coarse size");
+  if (int rc = persistent(&coarse.adj, static_cast<size_t>(coarse.nnz), "coarse adjacency")) return rc;
+  if (int rc = persistent(&coarse.mult, static_cast<size_t>(coarse.nnz), "coarse multiplicities")) return rc;
+  if (denses > 0)
+    hipLaunchKernelGGL((write_strips_kernel<WT, WEIGHTED>), dim3(blocks_for(denses * strips, 1)), dim3(1024), 0, nullptr,
+                       segment, dense_list, denses, strips, column, weight, in_strip[1], xadj_out,
+                       coarse.adj, coarse.mult);
+  if (bitmaps > 0)
+    hipLaunchKernelGGL((write_pieces_kernel<WT, WEIGHTED>), dim3(blocks_for(bitmaps * pieces, 1)), dim3(1024), 0,
+                       nullptr, segment, bitmap_list, bitmaps, pieces,
+                       static_cast<int64_t>(c.columns), column, weight, in_strip[0], xadj_out, coarse.adj, coarse.mult);
+  for (int cls = kSortClasses - 1; cls >= 0; --cls)
+    if (c.count[cls] > 0)
+      hipLaunchKernelGGL(copy_merged_kernel<WT>, dim3(blocks_for(c.count[cls], 4)), dim3(256), 0, nullptr, segment,
+                         list + cls * n_coarse, static_cast<int64_t>(c.count[cls]), column, weight, xadj_out, coarse.adj,
+                         coarse.mult);
+  if (int rc = gosh::check_launch("coarse rows")) return rc;
+  GOSH_TRY_HIP(hipDeviceSynchronize(), "coarse CSR");
+  return GOSH_OK;
+}
+
+template <typename WT, bool WEIGHTED>
+int quotient_by_offsets(gosh::DeviceCoarsener *dc, const gosh::DeviceLevel &fine, int64_t n_coarse,
+                        gosh::DeviceLevel &coarse, int64_t *xadj_out) {
+  return fine.xadj_is64 ? quotient<int64_t, WT, WEIGHTED>(dc, fine, n_coarse, coarse, xadj_out)
+                        : quotient<int32_t, WT, WEIGHTED>(dc, fine, n_coarse, coarse, xadj_out);
+}
+
+// Sums of multiplicities are kept in 32 bits unless a graph has more entries than those hold.
+constexpr int64_t kWideSumsFrom = int64_t{1} << 32;
+
+}  // namespace
+
+namespace gosh {
+
+int device_rebuild(DeviceCoarsener *dc, const DeviceLevel &fine, int64_t n_coarse, DeviceLevel &coarse) {
+  if (dc == nullptr || !fine.present() || fine.map == nullptr)
+    return fail(GOSH_EINVAL, "device level or its map is missing");
+  device_level_free(coarse);
+  coarse.device = fine.device;
+  coarse.n = n_coarse;
+  coarse.weight = fine.weight;
+  coarse.xadj_is64 = 1;
+  int64_t *xadj_out = nullptr;
+  if (int rc = persistent(&xadj_out, static_cast<size_t>(n_coarse) + 1, "coarse offsets")) return rc;
+  coarse.xadj = xadj_out;
+  if (fine.nnz == 0) {
+    coarse.nnz = 0;
+    GOSH_TRY_HIP(hipMemset(xadj_out, 0, (static_cast<size_t>(n_coarse) + 1) * 8), "clear coarse offsets");
+    if (int rc = persistent(&coarse.adj, 0, "coarse adjacency")) return rc;
+    if (int rc = persistent(&coarse.mult, 0, "coarse multiplicities")) return rc;
+    return GOSH_OK;
+  }
+  const bool weighted = fine.mult != nullptr;
+  if (fine.weight < kWideSumsFrom)
+    return weighted ? quotient_by_offsets<uint32_t, true>(dc, fine, n_coarse, coarse, xadj_out)
+                    : quotient_by_offsets<uint32_t, false>(dc, fine, n_coarse, coarse, xadj_out);
+  return weighted ? quotient_by_offsets<unsigned long long, true>(dc, fine, n_coarse, coarse, xadj_out)
+                  : quotient_by_offsets<unsigned long long, false>(dc, fine, n_coarse, coarse, xadj_out);
+}
+
+}  // namespace gosh

@@ -214,3 +214,40 @@ def test_device_random_tiny_graphs_match_oracle(g, offsets64):
     h = device_hierarchy(n, xadj, adj, offsets64, threshold=1, min_shrink=1.0)
     assert_same_hierarchy(h, graphs, maps, mults)
     h.free()
+
+
+def hub_graph(hubs, edges_of, seed):
+    """Hubs with leaves of degree one and two: a leaf joins its hub, and a leaf of two hubs
+    leaves an entry between them, so coarse row a merges about edges_of[a] + leaves entries."""
+    rng = np.random.default_rng(seed)
+    pairs, nxt = set(), hubs
+    for a, e in enumerate(edges_of):
+        pairs |= {(min(a, int(b)), max(a, int(b))) for b in rng.integers(0, hubs, e) if b != a}
+        for _ in range(12):
+            pairs.add((a, nxt))
+            if rng.random() < 0.7:
+                pairs.add((int(rng.integers(0, hubs)), nxt))
+            nxt += 1
+    return graphgen.to_csr(nxt, torch.tensor(sorted(pairs), dtype=torch.int64))
+
+
+@pytest.mark.parametrize("lengths", [range(20, 44), [*range(140, 250, 2), 1024], [2000, 2040, 2100, 9000, 17000, 40000]])
+def test_coarse_rows_of_every_way_of_merging(lengths):
+    """Rows around the lengths at which the rebuild changes its way (64, 128, 256, 512 entries: one
+    to eight per lane of a wavefront; 2,048: a workgroup; then a bitmap; from 32,768 counters),
+    level by level with growing multiplicities, against gosh_coarsen."""
+    lengths = list(lengths)
+    hubs = max(64, 3 * max(lengths))
+    edges = [lengths[a] if a < len(lengths) else 3 for a in range(hubs)]
+    csr = hub_graph(hubs, edges, 5)
+    n = csr.xadj.numel() - 1
+    h = G.gosh_coarsen_device(n, csr.xadj, csr.adj, threshold=4, min_shrink=1.0)
+    ref = G.gosh_coarsen(n, csr.xadj, csr.adj, threshold=4, min_shrink=1.0)
+    assert h.levels == ref.levels >= 3
+    for i in range(h.levels):
+        if i + 1 < h.levels:
+            assert np.array_equal(h.map(i), ref.map(i))
+        for got, want in zip(h.graph(i), ref.graph(i)):
+            assert np.array_equal(got, want)
+        if i:
+            assert np.array_equal(h.mult(i), ref.mult(i))
