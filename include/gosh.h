@@ -187,17 +187,21 @@ int gosh_coarsen(const gosh_csr *g0_host, int64_t threshold, double min_shrink,
  * host arrays behind gosh_hierarchy_graph / _map / _mult are downloaded on first request.
  * A graph whose marking does not resolve in a bounded number of rounds (long chains of
  * equal degrees) is marked on the host instead.  Device memory: about 24 bytes per entry
- * of G_0 while running; afterwards 12 bytes per entry of all levels, and the run's scratch
- * blocks (about 8 bytes per entry of G_0), which stay allocated until
- * gosh_hierarchy_trim_scratch, gosh_hierarchy_release_device or gosh_hierarchy_free
- * (called with the same device current) because freeing them at once would slow the host
- * link down for whatever follows (the driver clears freed memory in the background).
+ * of G_0 while running; afterwards 12 bytes per entry
+ * of all levels, and the run's scratch blocks (about 8 bytes per entry of G_0), which stay
+ * with the hierarchy until gosh_hierarchy_trim_scratch, gosh_hierarchy_release_device or
+ * gosh_hierarchy_free, because freeing them at once would slow the host link down for whatever
+ * follows (the driver clears freed memory in the background).  For the same reason
+ * gosh_hierarchy_free keeps device blocks for the next hierarchy, at most a 64th of the
+ * device's memory per process; they are given back when an allocation of this library needs
+ * them, and by either of the other two calls.
  * GOSH_ENOMEM / GOSH_EHIP if the device cannot.  Blocking; null stream. */
 int gosh_coarsen_device(const gosh_csr *g0, int64_t threshold, double min_shrink,
                         int32_t max_levels, int32_t n_threads, gosh_hierarchy **out);
 
-/* Returns the scratch blocks a device-built hierarchy still holds from its construction
- * (no-op otherwise).  The levels stay where they are. */
+/* Returns to the driver the scratch blocks a device-built hierarchy still holds from its
+ * construction and, whatever h is (NULL allowed), the blocks kept from freed hierarchies on the
+ * current device.  The levels stay where they are. */
 int gosh_hierarchy_trim_scratch(gosh_hierarchy *h);
 
 /* Brings every array of a device-built hierarchy to the host and frees its device copies

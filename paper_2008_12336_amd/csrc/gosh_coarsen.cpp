@@ -615,6 +615,7 @@ int gosh_hierarchy_mult(const gosh_hierarchy *h, int32_t i, const int64_t **mult
 
 int gosh_hierarchy_trim_scratch(gosh_hierarchy *h) {
   if (h != nullptr) gosh::device_coarsener_trim(h->dc);
+  gosh::device_blocks_trim();
   return GOSH_OK;
 }
 
@@ -627,6 +628,7 @@ int gosh_hierarchy_release_device(gosh_hierarchy *h) {
     if (int rc = ensure_host_mult(*h, l)) return rc;
     gosh::device_level_free(l.dev);
   }
+  gosh::device_blocks_trim();
   return GOSH_OK;
 }
 

@@ -212,16 +212,18 @@ void device_coarsener_trim(DeviceCoarsener *dc) {
   if (dc) dc->pool.trim();
 }
 
+void device_blocks_trim() { block_trim(); }
+
 void device_level_free(DeviceLevel &level) {
-  if (level.xadj && !level.borrowed_graph) (void)hipFree(level.xadj);
-  if (level.adj && !level.borrowed_graph) (void)hipFree(level.adj);
-  if (level.mult) (void)hipFree(level.mult);
-  if (level.map) (void)hipFree(level.map);
+  void *const blocks[4] = {level.borrowed_graph ? nullptr : level.xadj, level.borrowed_graph ? nullptr : level.adj,
+                           level.mult, level.map};
+  block_give(blocks, 4);
   level = DeviceLevel();
 }
 
 void device_level_drop_map(DeviceLevel &level) {
-  if (level.map) (void)hipFree(level.map);
+  void *const map = level.map;
+  block_give(&map, 1);
   level.map = nullptr;
 }
 
@@ -269,7 +271,10 @@ int device_level_check(const DeviceLevel &out) {
   if (int rc = persistent(&bad_dev, 1, "check flag")) return rc;
   struct FlagGuard {
     int32_t *p;
-    ~FlagGuard() { (void)hipFree(p); }
+    ~FlagGuard() {
+      void *const block = p;
+      block_give(&block, 1);
+    }
   } guard{bad_dev};
   int32_t bad = 0;
   GOSH_TRY_HIP(hipMemset(bad_dev, 0, 4), "clear check flag");
@@ -305,38 +310,41 @@ namespace {
 // Copies between pageable host memory and the device through two pinned slots, so that the
 // DMA of one piece overlaps the host-side copy of the next, which all threads share (on a
 // download that also spreads the page faults of a fresh destination over the threads).
-// The copy stream lives only for the call.
+// The runtime's own copy of pageable memory moves 12 GB/s and shares nothing.
 struct StagedCopy {
-  DeviceCoarsener *dc;
-  hipStream_t stream = nullptr;
+  const int threads;
+  char *slots;
   hipEvent_t done[2] = {nullptr, nullptr};  // the DMA that last used slot i
-  explicit StagedCopy(DeviceCoarsener *d) : dc(d) {}
+  explicit StagedCopy(const DeviceCoarsener *dc) : threads(dc->threads), slots(staging_take()) {}
   ~StagedCopy() {
+    (void)hipStreamSynchronize(nullptr);  // after a failed call a copy may still be using a slot
     for (int i = 0; i < 2; ++i)
       if (done[i]) (void)hipEventDestroy(done[i]);
-    if (stream) (void)hipStreamDestroy(stream);
+    staging_give(slots);
   }
   int open() {
-    for (int i = 0; i < 2; ++i)
-      if (dc->slot[i] == nullptr) {
-        void *p = nullptr;
-        GOSH_TRY_HIP(hipHostMalloc(&p, DeviceCoarsener::kSlotBytes, hipHostMallocDefault), "allocate pinned staging");
-        dc->slot[i] = static_cast<char *>(p);
-      }
-    GOSH_TRY_HIP(hipStreamCreate(&stream), "create copy stream");
+    if (slots == nullptr) return gosh::fail(GOSH_ENOMEM, "cannot allocate pinned staging");
     for (int i = 0; i < 2; ++i)
       GOSH_TRY_HIP(hipEventCreateWithFlags(&done[i], hipEventDisableTiming), "create copy event");
     return GOSH_OK;
   }
+  char *slot(size_t c) const { return slots + (c & 1) * kStagingBytes; }
   void host_copy(char *to, const char *from, size_t bytes) const {
     const int64_t len = static_cast<int64_t>(bytes);
-    const int64_t grain = int64_t(1) << 20;
+    const int64_t grain = int64_t(1) << 18;
     const int64_t grains = (len + grain - 1) / grain;
-#pragma omp parallel for num_threads(dc->threads) schedule(static)
+#pragma omp parallel for num_threads(threads) schedule(static)
     for (int64_t g = 0; g < grains; ++g)
       memcpy(to + g * grain, from + g * grain, static_cast<size_t>(std::min(grain, len - g * grain)));
   }
 };
+
+// Pieces of a copy: eight, but none shorter than a megabyte or longer than a slot.
+constexpr size_t kStagedFrom = size_t(4) << 20;  // below, one call of the runtime is as fast
+size_t piece_bytes_of(size_t bytes) {
+  const size_t eighth = ((bytes + 7) / 8 + 4095) / 4096 * 4096;
+  return std::min(std::max(eighth, size_t(1) << 20), kStagingBytes);
+}
 
 bool is_pinned_host(const void *p) {
   hipPointerAttribute_t attr;
@@ -351,50 +359,48 @@ bool is_pinned_host(const void *p) {
 
 int device_download(DeviceCoarsener *dc, void *dst, const void *src_dev, size_t bytes) {
   if (bytes == 0) return GOSH_OK;
-  if (dc == nullptr || bytes < 4 * DeviceCoarsener::kSlotBytes) {
+  if (dc == nullptr || bytes < kStagedFrom) {
     GOSH_TRY_HIP(hipMemcpy(dst, src_dev, bytes, hipMemcpyDeviceToHost), "download");
     return GOSH_OK;
   }
   StagedCopy q(dc);
   if (int rc = q.open()) return rc;
-  const size_t slot_bytes = DeviceCoarsener::kSlotBytes;
-  const size_t pieces = (bytes + slot_bytes - 1) / slot_bytes;
-  auto piece_bytes = [&](size_t c) { return std::min(slot_bytes, bytes - c * slot_bytes); };
+  const size_t piece = piece_bytes_of(bytes), pieces = (bytes + piece - 1) / piece;
+  auto len = [&](size_t c) { return std::min(piece, bytes - c * piece); };
   auto start = [&](size_t c) -> hipError_t {
-    hipError_t e = hipMemcpyAsync(dc->slot[c & 1], static_cast<const char *>(src_dev) + c * slot_bytes,
-                                  piece_bytes(c), hipMemcpyDeviceToHost, q.stream);
-    return e != hipSuccess ? e : hipEventRecord(q.done[c & 1], q.stream);
+    hipError_t e = hipMemcpyAsync(q.slot(c), static_cast<const char *>(src_dev) + c * piece, len(c),
+                                  hipMemcpyDeviceToHost, nullptr);
+    return e != hipSuccess ? e : hipEventRecord(q.done[c & 1], nullptr);
   };
   GOSH_TRY_HIP(start(0), "start download");
   for (size_t c = 0; c < pieces; ++c) {
     // slot (c + 1) & 1 was emptied in the previous iteration
     if (c + 1 < pieces) GOSH_TRY_HIP(start(c + 1), "start download");
     GOSH_TRY_HIP(hipEventSynchronize(q.done[c & 1]), "wait for download");
-    q.host_copy(static_cast<char *>(dst) + c * slot_bytes, dc->slot[c & 1], piece_bytes(c));
+    q.host_copy(static_cast<char *>(dst) + c * piece, q.slot(c), len(c));
   }
   return GOSH_OK;
 }
 
 int device_upload(DeviceCoarsener *dc, void *dst_dev, const void *src, size_t bytes) {
   if (bytes == 0) return GOSH_OK;
-  if (dc == nullptr || bytes < 4 * DeviceCoarsener::kSlotBytes || is_pinned_host(src)) {
+  if (dc == nullptr || bytes < kStagedFrom || is_pinned_host(src)) {
     GOSH_TRY_HIP(hipMemcpy(dst_dev, src, bytes, hipMemcpyHostToDevice), "upload");
     return GOSH_OK;
   }
   StagedCopy q(dc);
   if (int rc = q.open()) return rc;
-  const size_t slot_bytes = DeviceCoarsener::kSlotBytes;
-  const size_t pieces = (bytes + slot_bytes - 1) / slot_bytes;
+  const size_t piece = piece_bytes_of(bytes), pieces = (bytes + piece - 1) / piece;
   for (size_t c = 0; c < pieces; ++c) {
-    const size_t len = std::min(slot_bytes, bytes - c * slot_bytes);
+    const size_t len = std::min(piece, bytes - c * piece);
     // the DMA of piece c - 2 must have drained this slot
     if (c >= 2) GOSH_TRY_HIP(hipEventSynchronize(q.done[c & 1]), "wait for upload");
-    q.host_copy(dc->slot[c & 1], static_cast<const char *>(src) + c * slot_bytes, len);
-    GOSH_TRY_HIP(hipMemcpyAsync(static_cast<char *>(dst_dev) + c * slot_bytes, dc->slot[c & 1], len,
-                              hipMemcpyHostToDevice, q.stream), "upload piece");
-    GOSH_TRY_HIP(hipEventRecord(q.done[c & 1], q.stream), "record upload");
+    q.host_copy(q.slot(c), static_cast<const char *>(src) + c * piece, len);
+    GOSH_TRY_HIP(hipMemcpyAsync(static_cast<char *>(dst_dev) + c * piece, q.slot(c), len, hipMemcpyHostToDevice, nullptr),
+                 "upload piece");
+    GOSH_TRY_HIP(hipEventRecord(q.done[c & 1], nullptr), "record upload");
   }
-  GOSH_TRY_HIP(hipStreamSynchronize(q.stream), "finish upload");
+  GOSH_TRY_HIP(hipStreamSynchronize(nullptr), "finish upload");
   return GOSH_OK;
 }
 

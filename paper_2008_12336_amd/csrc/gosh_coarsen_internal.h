@@ -59,7 +59,7 @@ struct NoInitAlloc {
 template <typename T>
 using RawVector = std::vector<T, NoInitAlloc<T>>;
 
-// One graph of the hierarchy in device memory (all arrays exact-sized hipMalloc blocks on
+// One graph of the hierarchy in device memory (all arrays blocks of gosh_device_pool.cpp on
 // `device`; null when absent).
 struct DeviceLevel {
   int device = -1;
@@ -75,13 +75,14 @@ struct DeviceLevel {
 };
 void device_level_free(DeviceLevel &level);
 
-// State of one coarsening run: device blocks recycled over the levels and pinned staging
-// for downloads.
+// State of one coarsening run: device blocks recycled over the levels.
 struct DeviceCoarsener;
 DeviceCoarsener *device_coarsener_new(int threads);
 void device_coarsener_free(DeviceCoarsener *);
-// Returns the recycled device blocks; the staging stays (later downloads use it).
+// Gives up the recycled device blocks.
 void device_coarsener_trim(DeviceCoarsener *);
+// Returns to the driver what the current device has of the blocks of freed levels and runs.
+void device_blocks_trim();
 
 // Copies a host graph to the current device and range-checks it there.
 int device_level_upload(DeviceCoarsener *dc, const gosh_csr &host, DeviceLevel &out);

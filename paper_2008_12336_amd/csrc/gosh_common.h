@@ -40,6 +40,15 @@ int hip_fail(hipError_t e, const char *what);
     if (e_ != hipSuccess) return gosh::hip_fail(e_, what);       \
   } while (0)
 
+// hipMalloc, tried again without the device blocks kept from freed hierarchies if it fails, and
+// the number of bytes of those on the current device.
+hipError_t device_malloc_bytes(void **p, size_t bytes);
+template <typename T>
+hipError_t device_malloc(T **p, size_t bytes) {
+  return device_malloc_bytes(reinterpret_cast<void **>(p), bytes);
+}
+size_t block_kept();
+
 // The process-wide tuning record behind gosh_set_tuning / gosh_get_tuning (fields documented
 // in gosh.h).  Read at the start of every call that launches a training kernel.
 gosh_tuning tuning();

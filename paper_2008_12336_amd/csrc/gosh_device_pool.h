@@ -11,6 +11,19 @@
 
 namespace gosh {
 
+// Device blocks that outlive a hierarchy (gosh_device_pool.cpp): at least `bytes` on the
+// current device, or null; given back on any thread, whatever device is current; what is kept
+// of them on the current device, freed.
+void *block_take(size_t bytes);
+void block_give(void *const *blocks, size_t count);
+void block_trim();
+
+// Pinned staging for copies between pageable memory and the device: two slots of
+// kStagingBytes, null if there is no memory for them.  A pair or two are kept.
+constexpr size_t kStagingBytes = size_t(8) << 20;
+char *staging_take();
+void staging_give(char *both);
+
 // Device blocks recycled over the levels of one run: hipMalloc and hipFree of gigabyte
 // blocks cost more than the kernels of a small level.  Levels only shrink, so the blocks
 // of the first level serve all later ones (best fit).
@@ -23,7 +36,9 @@ struct Pool {
   std::vector<Block> blocks;
   ~Pool() { trim(); }
   void trim() {
-    for (Block &b : blocks) (void)hipFree(b.p);
+    std::vector<void *> all;
+    for (const Block &b : blocks) all.push_back(b.p);
+    block_give(all.data(), all.size());
     blocks.clear();
   }
   void *take(size_t bytes) {
@@ -37,11 +52,8 @@ struct Pool {
       best->busy = true;
       return best->p;
     }
-    void *p = nullptr;
-    if (hipMalloc(&p, bytes) != hipSuccess) {
-      (void)hipGetLastError();
-      return nullptr;
-    }
+    void *const p = block_take(bytes);
+    if (p == nullptr) return nullptr;
     blocks.push_back(Block{p, bytes, true});
     return p;
   }
@@ -83,15 +95,12 @@ inline int blocks_for(int64_t items, int per_block) {
   return static_cast<int>(std::min<int64_t>(std::max<int64_t>(b, 1), 1 << 16));
 }
 
-// Exact-sized block that outlives the run (a level's array).
+// Block that outlives the run (a level's array).
 template <typename T>
 int persistent(T **out, size_t count, const char *what) {
-  void *p = nullptr;
   const size_t bytes = std::max<size_t>(count, 1) * sizeof(T);
-  if (hipMalloc(&p, bytes) != hipSuccess) {
-    (void)hipGetLastError();
-    return fail(GOSH_ENOMEM, "cannot allocate %zu device bytes for %s", bytes, what);
-  }
+  void *const p = block_take(bytes);
+  if (p == nullptr) return fail(GOSH_ENOMEM, "cannot allocate %zu device bytes for %s", bytes, what);
   *out = static_cast<T *>(p);
   return GOSH_OK;
 }
@@ -99,15 +108,6 @@ int persistent(T **out, size_t count, const char *what) {
 struct DeviceCoarsener {
   Pool pool;
   int threads = 1;
-  // Two pinned staging slots for large downloads, made on first use and kept.  The copy
-  // stream is NOT kept: a process has few hardware queues, and an idle stream of ours
-  // would make the streams of a later training call share one.
-  static constexpr size_t kSlotBytes = size_t(64) << 20;
-  char *slot[2] = {nullptr, nullptr};
-  ~DeviceCoarsener() {
-    for (int i = 0; i < 2; ++i)
-      if (slot[i]) (void)hipHostFree(slot[i]);
-  }
 };
 
 }  // namespace gosh

@@ -28,7 +28,7 @@ struct DeviceBuffer {
   int alloc(size_t bytes, const char *what) {
     reset();
     if (bytes == 0) bytes = 16;
-    if (hipMalloc(&ptr, bytes) != hipSuccess) {
+    if (gosh::device_malloc(&ptr, bytes) != hipSuccess) {
       (void)hipGetLastError();
       ptr = nullptr;
       return gosh::fail(GOSH_ENOMEM, "cannot allocate %zu device bytes for %s", bytes, what);
@@ -484,6 +484,7 @@ int gosh_embed_host(const gosh_hierarchy *h, int32_t d, int32_t k_neg, int64_t e
   if (measure) {
     size_t free_bytes = 0, total_bytes = 0;
     GOSH_TRY_HIP(hipMemGetInfo(&free_bytes, &total_bytes), "hipMemGetInfo");
+    free_bytes += gosh::block_kept();  // given back when an allocation needs it
     device_budget_bytes = free_bytes - free_bytes / 16;
     if (device_budget_bytes == 0) return gosh::fail(GOSH_ENOMEM, "the device has no free memory");
   }

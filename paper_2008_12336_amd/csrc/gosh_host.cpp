@@ -133,7 +133,7 @@ int hot_scratch(size_t bytes, void **out) {
     h.ptr = nullptr;
     h.bytes = 0;
     const size_t want = bytes + bytes / 4 + 4096;
-    if (hipMalloc(&h.ptr, want) != hipSuccess) {
+    if (device_malloc(&h.ptr, want) != hipSuccess) {
       (void)hipGetLastError();
       return fail(GOSH_ENOMEM, "cannot allocate %zu bytes for the hot-row bitmap", want);
     }
@@ -151,7 +151,7 @@ int check_scratch(CheckResult **out) {
   std::lock_guard<std::mutex> lock(g_hot_scratch_mutex);
   if (table[dev] == nullptr) {
     void *p = nullptr;
-    if (hipMalloc(&p, sizeof(CheckResult)) != hipSuccess) {
+    if (device_malloc(&p, sizeof(CheckResult)) != hipSuccess) {
       (void)hipGetLastError();
       return fail(GOSH_ENOMEM, "cannot allocate the result of the divergence check");
     }

@@ -345,10 +345,10 @@ class Rotation {
         slot[s] = pl.M_host + static_cast<int64_t>(L.lo(s)) * pl.d;
         slot_part[s] = s;
       } else {
-        GOSH_TRY_HIP(hipMalloc(&slot[s], static_cast<size_t>(L.part_rows) * pl.d * 4), "hipMalloc part slot");
+        GOSH_TRY_HIP(gosh::device_malloc(&slot[s], static_cast<size_t>(L.part_rows) * pl.d * 4), "hipMalloc part slot");
       }
     }
-    for (int s = 0; s < S; ++s) GOSH_TRY_HIP(hipMalloc(&dpool[s], pool_ints * 4), "hipMalloc pool");
+    for (int s = 0; s < S; ++s) GOSH_TRY_HIP(gosh::device_malloc(&dpool[s], pool_ints * 4), "hipMalloc pool");
     for (int s = 0; s < NS && !graph_on_device; ++s)
       GOSH_TRY_HIP(hipHostMalloc(reinterpret_cast<void **>(&staging[s]), pool_ints * 4, hipHostMallocDefault),
               "hipHostMalloc staging");
@@ -359,7 +359,7 @@ class Rotation {
       GOSH_TRY_HIP(hipEventCreate(&k_begin[t]), "hipEventCreate");
       GOSH_TRY_HIP(hipEventCreate(&k_end[t]), "hipEventCreate");
     }
-    GOSH_TRY_HIP(hipMalloc(reinterpret_cast<void **>(&check), sizeof(gosh::CheckResult)), "hipMalloc check result");
+    GOSH_TRY_HIP(gosh::device_malloc(&check, sizeof(gosh::CheckResult)), "hipMalloc check result");
     if (int rc = gosh::matrix_check_clear(check, copy_out)) return rc;
     if (int rc = build_hot_set()) return rc;
     if (!graph_on_device) sampler = std::thread([this] { sampler_loop(); });
@@ -489,7 +489,7 @@ class Rotation {
                                        ? tune.hot_min_degree
                                        : pl.g->nnz / (tune.hot_inv_eps * in_flight * pl.B) + 1;
         const int64_t words = (n + 63) / 64;
-        GOSH_TRY_HIP(hipMalloc(&hot_bits_dev, static_cast<size_t>(words) * 8), "hipMalloc hot bitmap");
+        GOSH_TRY_HIP(gosh::device_malloc(&hot_bits_dev, static_cast<size_t>(words) * 8), "hipMalloc hot bitmap");
         if (graph_on_device) {
           const int blocks = static_cast<int>(std::min<int64_t>((words + 255) / 256, 65536));
           if (pl.g->xadj_is64)
@@ -522,7 +522,7 @@ class Rotation {
     }
     if (hot.bits == nullptr) {
       // the kernel reads word 0 of the bitmap unconditionally
-      GOSH_TRY_HIP(hipMalloc(&hot_bits_dev, 64), "hipMalloc hot bitmap");
+      GOSH_TRY_HIP(gosh::device_malloc(&hot_bits_dev, 64), "hipMalloc hot bitmap");
       GOSH_TRY_HIP(hipMemset(hot_bits_dev, 0, 64), "hipMemset hot bitmap");
       hot.bits = hot_bits_dev;
     }
@@ -861,9 +861,9 @@ int gosh_parts_sample_pair(const gosh_csr *g_host, int32_t K, int32_t pa, int32_
   const int64_t total = w.count() * samples;
   int rc = GOSH_OK;
   int32_t *d_pa = nullptr, *d_pb = nullptr, *d_out = nullptr;
-  PARTS_HIP(hipMalloc(&d_pa, pool_a.size() * 4), "hipMalloc");
-  PARTS_HIP(hipMalloc(&d_pb, pool_b.size() * 4), "hipMalloc");
-  PARTS_HIP(hipMalloc(&d_out, static_cast<size_t>(std::max<int64_t>(total, 1)) * 4), "hipMalloc");
+  PARTS_HIP(gosh::device_malloc(&d_pa, pool_a.size() * 4), "hipMalloc");
+  PARTS_HIP(gosh::device_malloc(&d_pb, pool_b.size() * 4), "hipMalloc");
+  PARTS_HIP(gosh::device_malloc(&d_out, static_cast<size_t>(std::max<int64_t>(total, 1)) * 4), "hipMalloc");
   PARTS_HIP(hipMemcpy(d_pa, pool_a.data(), pool_a.size() * 4, hipMemcpyHostToDevice), "copy pool");
   PARTS_HIP(hipMemcpy(d_pb, pool_b.data(), pool_b.size() * 4, hipMemcpyHostToDevice), "copy pool");
   w.pool_a = d_pa;

@@ -251,3 +251,52 @@ def test_coarse_rows_of_every_way_of_merging(lengths):
             assert np.array_equal(got, want)
         if i:
             assert np.array_equal(h.mult(i), ref.mult(i))
+
+
+def test_blocks_of_freed_hierarchies_are_reused_bounded_and_given_back():
+    n = 1 << 18
+    csr = graphgen.to_csr(n, graphgen.rmat(18, 1 << 22, 7)).to("cuda:0")
+    run = lambda: G.gosh_coarsen_device(n, csr.xadj, csr.adj, threshold=500, min_shrink=0.9)
+    free_bytes = lambda: torch.cuda.mem_get_info()[0]
+    h = run()
+    h.trim_scratch()
+    h.free()
+    trim = lambda: G.lib().gosh_hierarchy_trim_scratch(None)
+    assert trim() == 0
+    slack = 16 << 20
+    start, total = torch.cuda.mem_get_info()
+    run().free()
+    kept = start - free_bytes()
+    assert 0 < kept <= total // 64 + slack
+    for _ in range(3):
+        run().free()
+    assert abs(start - free_bytes() - kept) <= slack  # the same blocks again
+    assert trim() == 0
+    assert start - free_bytes() <= slack
+
+
+def test_hierarchies_built_and_freed_by_two_threads():
+    import threading
+
+    graphs = [graphgen.to_csr(1 << 15, graphgen.rmat(15, 1 << 18, s)) for s in (1, 2)]
+    refs = [G.gosh_coarsen(1 << 15, c.xadj, c.adj, threshold=50, min_shrink=0.9) for c in graphs]
+    failures = []
+
+    def work(c, ref):
+        try:
+            for _ in range(6):
+                h = G.gosh_coarsen_device(1 << 15, c.xadj, c.adj, threshold=50, min_shrink=0.9)
+                assert h.levels == ref.levels
+                for i in range(h.levels - 1):
+                    assert np.array_equal(h.map(i), ref.map(i))
+                    assert np.array_equal(h.mult(i + 1), ref.mult(i + 1))
+                h.free()
+        except BaseException as e:
+            failures.append(e)
+
+    threads = [threading.Thread(target=work, args=a) for a in zip(graphs, refs)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert not failures, failures
