@@ -105,6 +105,7 @@ __device__ __forceinline__ void atomic_step(float *p, float x) {
 // Policies whose loads the compiler issues itself need no explicit wait.
 struct TrackedLoads {
   static constexpr bool kWaveAtomics = false;  // a hot row is added to by the lanes that own it
+  static constexpr bool kAligned = false;      // lane g's first column is g, wherever the row starts
   static __device__ __forceinline__ void wait_all() {}
   template <int F>
   static __device__ __forceinline__ void settle(Unit<F> &) {}
@@ -131,6 +132,7 @@ struct RowPlain128 : TrackedLoads {
 struct RowAgent128 {
   static constexpr int F = 4;
   static constexpr bool kWaveAtomics = true;  // a hot row is added to by the whole wavefront, see add_rows_as_a_wave
+  static constexpr bool kAligned = false;
   static __device__ __forceinline__ Unit<4> load(const float *p) {
     Unit<4> u;
     asm volatile("global_load_dwordx4 %0, %1, off sc1" : "=v"(u.v) : "v"(p) : "memory");
@@ -153,6 +155,18 @@ struct RowAgent32 : TrackedLoads {
   static __device__ __forceinline__ void store(float *p, const Unit<1> &u) {
     __hip_atomic_store(p, u.v[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
+};
+
+// RowAgentLine: RowAgent32 for rows that do not start at line borders (d no multiple of 32, or
+// such a matrix).  With lane g at column g every access instruction of such a row straddles one
+// line more than it covers, and the memory system charges per instruction and 64-byte block
+// touched, for atomic adds above all (20.5 G blocks/s).  Here a lane's columns follow from the
+// address of the row: slot g + i * LPG lies that far behind the line border below the row's
+// start, and the slots before the start take the columns that are left over at the end.  An
+// element of the matrix keeps its lane, but two rows have theirs at different ones, so the source row
+// is held in LDS by column while its samples are worked at.
+struct RowAgentLine : RowAgent32 {
+  static constexpr bool kAligned = true;
 };
 
 // ---------------------------------------------------------------------------------
@@ -256,6 +270,7 @@ struct ChunkPos {
 //                                             vertex id of sample t from its draw r (-1 = none,
 //                                             or !want)
 //     float  *sample_row(int64_t i, int32_t v)
+//     bool    rows_at_lines()                 (host) every row starts at a line border, or near enough
 //     Both stages must be free of branches around their memory reads (read a safe address
 //     when !want).
 //   Sample t of a source is a positive iff t % (k_neg + 1) == 0.
@@ -315,14 +330,24 @@ __global__ __launch_bounds__(256) void sgd_kernel(W w, SgdArgs a) {
   // Lane gl owns floats [(gl + i*LPG)*F, +F) of a row, i < UPL: consecutive lanes touch
   // consecutive addresses, so each access instruction covers whole cache lines.  Columns
   // beyond d are read from the last unit of the row instead and masked.
-  int32_t col[UPL], col_read[UPL];
-  bool col_ok[UPL];
-#pragma unroll
-  for (int i = 0; i < UPL; ++i) {
-    col[i] = (gl + i * LPG) * F;
-    col_ok[i] = col[i] < d;
-    col_read[i] = col_ok[i] ? col[i] : d - F;
-  }
+  // With P::kAligned the lane's columns depend on the address of the row (see RowAgentLine).
+  constexpr int kSlots = LPG * UPL;
+  static_assert(!P::kAligned || (F == 1 && (kSlots & (kSlots - 1)) == 0), "slots wrap around by masking");
+  auto column = [&](const float *row, int i) -> int32_t {
+    if constexpr (P::kAligned) {
+      const int32_t behind_line = static_cast<int32_t>(reinterpret_cast<uintptr_t>(row) >> 2) & 31;
+      return (gl + i * LPG - behind_line) & (kSlots - 1);
+    } else {
+      return (gl + i * LPG) * F;
+    }
+  };
+  auto readable = [&](int32_t c) { return c < d ? c : d - F; };
+  // the source row by column; the entries past d stay zero
+  __shared__ float held_rows[P::kAligned ? 256 / LPG * kSlots : 1];
+  float *const held = held_rows + (P::kAligned ? threadIdx.x / LPG * kSlots : 0);
+  auto held_in_order = [] {  // the wavefront's LDS accesses take effect in program order; keep that order
+    if constexpr (P::kAligned) __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  };
 
   // Stage 2 for the chunk at `pos`: lane q of the group evaluates sample pos.t0 + q (in
   // several passes if the group has fewer than kChunk lanes).
@@ -374,7 +399,7 @@ __global__ __launch_bounds__(256) void sgd_kernel(W w, SgdArgs a) {
     // have been requested too (`fresh`): nothing may read a unit before P::settle.
     U s[UPL], s_before[UPL];
 #pragma unroll
-    for (int i = 0; i < UPL; ++i) s[i] = P::load(src_row + col_read[i]);
+    for (int i = 0; i < UPL; ++i) s[i] = P::load(src_row + readable(column(src_row, i)));
     const uint32_t src_word = bits[use_bitmap ? (src >> 5) : 0];
     bool fresh = true;
 
@@ -398,7 +423,7 @@ __global__ __launch_bounds__(256) void sgd_kernel(W w, SgdArgs a) {
         valid[q] = live && v[q] >= 0 && v[q] != src;  // a sample that hits the source applies no update
         const float *row = valid[q] ? w.sample_row(idx, v[q]) : src_row;
 #pragma unroll
-        for (int i = 0; i < UPL; ++i) r[q][i] = P::load(row + col_read[i]);
+        for (int i = 0; i < UPL; ++i) r[q][i] = P::load(row + readable(column(row, i)));
         word[q] = bits[(use_bitmap && valid[q]) ? (v[q] >> 5) : 0];
       }
       // While they are in flight: the ids of the next chunk (its offsets arrived a chunk
@@ -415,22 +440,32 @@ __global__ __launch_bounds__(256) void sgd_kernel(W w, SgdArgs a) {
         P::settle(s[i]);
 #pragma unroll
         for (int c = 0; c < F; ++c) {
-          s[i].v[c] = col_ok[i] ? s[i].v[c] : 0.f;
+          s[i].v[c] = column(src_row, i) < d ? s[i].v[c] : 0.f;
           s_before[i].v[c] = fresh ? s[i].v[c] : s_before[i].v[c];
         }
+        if constexpr (P::kAligned)
+          if (fresh) held[column(src_row, i)] = s[i].v[0];
       }
+      held_in_order();
       fresh = false;
 #pragma unroll
-      for (int q = 0; q < kChunk; ++q)
+      for (int q = 0; q < kChunk; ++q) {
+        const float *const row = valid[q] ? w.sample_row(idx, v[q]) : src_row;
 #pragma unroll
         for (int i = 0; i < UPL; ++i) {
           P::settle(r[q][i]);
 #pragma unroll
-          for (int c = 0; c < F; ++c) r[q][i].v[c] = col_ok[i] ? r[q][i].v[c] : 0.f;
+          for (int c = 0; c < F; ++c) r[q][i].v[c] = column(row, i) < d ? r[q][i].v[c] : 0.f;
         }
+      }
 
 #pragma unroll
       for (int q = 0; q < kChunk; ++q) {
+        float *const row = valid[q] ? w.sample_row(idx, v[q]) : src_row;
+        if constexpr (P::kAligned) {
+#pragma unroll
+          for (int i = 0; i < UPL; ++i) s[i].v[0] = held[column(row, i)];
+        }
         float partial = 0.f;
 #pragma unroll
         for (int i = 0; i < UPL; ++i)
@@ -447,13 +482,17 @@ __global__ __launch_bounds__(256) void sgd_kernel(W w, SgdArgs a) {
             s[i].v[c] = fmaf(g, r[q][i].v[c], s[i].v[c]);
             r[q][i].v[c] = fmaf(g, s[i].v[c], r[q][i].v[c]);
           }
+        if constexpr (P::kAligned) {
+#pragma unroll
+          for (int i = 0; i < UPL; ++i) held[column(row, i)] = s[i].v[0];
+          held_in_order();
+        }
         {
-          float *const row = valid[q] ? w.sample_row(idx, v[q]) : src_row;
           const bool hot = valid[q] && (all_hot || ((word[q] >> (v[q] & 31)) & 1u));
           if (valid[q] && !hot) {  // uniform over the group; only writes inside
 #pragma unroll
             for (int i = 0; i < UPL; ++i)
-              if (col_ok[i]) P::store(row + col[i], r[q][i]);
+              if (column(row, i) < d) P::store(row + column(row, i), r[q][i]);
           }
           if constexpr (P::kWaveAtomics) {
             static_assert(!P::kWaveAtomics || (UPL == 1 && F == 4), "one 128-bit unit per lane");
@@ -466,7 +505,7 @@ __global__ __launch_bounds__(256) void sgd_kernel(W w, SgdArgs a) {
             for (int i = 0; i < UPL; ++i)
 #pragma unroll
               for (int c = 0; c < F; ++c)
-                if (col_ok[i]) atomic_step(row + col[i] + c, g * s[i].v[c]);
+                if (column(row, i) < d) atomic_step(row + column(row, i) + c, g * s[i].v[c]);
           }
         }
         // A later sample of the same chunk that names the same vertex must see this
@@ -481,11 +520,16 @@ __global__ __launch_bounds__(256) void sgd_kernel(W w, SgdArgs a) {
         }
       }
     }
+    if constexpr (P::kAligned) {
+#pragma unroll
+      for (int i = 0; i < UPL; ++i) s[i].v[0] = held[column(src_row, i)];
+      held_in_order();
+    }
     const bool src_hot = live && (all_hot || ((src_word >> (src & 31)) & 1u));
     if (live && !src_hot) {
 #pragma unroll
       for (int i = 0; i < UPL; ++i)
-        if (col_ok[i]) P::store(src_row + col[i], s[i]);
+        if (column(src_row, i) < d) P::store(src_row + column(src_row, i), s[i]);
     }
     if constexpr (P::kWaveAtomics) {
       U step;
@@ -497,10 +541,14 @@ __global__ __launch_bounds__(256) void sgd_kernel(W w, SgdArgs a) {
       for (int i = 0; i < UPL; ++i)
 #pragma unroll
         for (int c = 0; c < F; ++c)
-          if (col_ok[i]) atomic_step(src_row + col[i] + c, s[i].v[c] - s_before[i].v[c]);
+          if (column(src_row, i) < d) atomic_step(src_row + column(src_row, i) + c, s[i].v[c] - s_before[i].v[c]);
     }
   }
 }
+
+// Whether the access instructions of lanes at columns 0, 1, 2, ... touch no more 64-byte blocks
+// than they cover in every row of a matrix.
+inline bool rows_at_lines(const float *M, int32_t d) { return reinterpret_cast<uintptr_t>(M) % 64 == 0 && d % 16 == 0; }
 
 // Launches sgd_kernel for a given dimension.  Geometry:
 //   plain_rows             plain 128-bit units, LPG = pow2ceil(d/4) lanes (<= 64): the layout
@@ -509,7 +557,8 @@ __global__ __launch_bounds__(256) void sgd_kernel(W w, SgdArgs a) {
 //                          lane (4..64 sources per wavefront); hot rows are added to by the
 //                          whole wavefront, one row at a time
 //   otherwise, d  > 64     32-bit agent-scope units interleaved over LPG = pow2ceil(d/4)
-//                          lanes (<= 64), four or eight units per lane
+//                          lanes (<= 64), four or eight units per lane; their columns from the
+//                          address of the row where rows do not start at line borders
 // Each of them runs concurrently (seq = false) or as one lane group (seq = true).
 // `a.sources_per_block` is filled in here from `count`.
 template <class W>
@@ -564,6 +613,17 @@ struct SgdLauncher {
         case 2: return run<RowAgent128, 2, 1>(w, a, count, seq, max_waves, st);
         default: return run<RowAgent128, 1, 1>(w, a, count, seq, max_waves, st);
       }
+    }
+    // Rows that straddle lines.  Measured before and after on 2^20 vertices (a mix of stores and
+    // atomic adds) and 2^17 (all atomic adds), k = 3, us: d = 68 1,076 / 215 -> 967 / 170; d = 100
+    // 1,456 / 304 -> 1,179 / 231; 124 1,620 / 356 -> 1,282 / 278; 132 1,417 / 348 -> 1,497 / 317;
+    // 200 1,742 / 473 -> 1,710 / 429; 300 2,792 / 733 -> 2,718 / 644; 444 4,132 / 1,066 ->
+    // 4,018 / 923.  At 132 half the lanes idle and the longer code costs more than the blocks
+    // saved, unless every write is an atomic add.
+    if (!w.rows_at_lines() && (d <= 128 || d > 192 || a.hot.mode == kHotAll)) {
+      if (d > 256) return run<RowAgentLine, 64, 8>(w, a, count, seq, max_waves, st);
+      if (d > 128) return run<RowAgentLine, 64, 4>(w, a, count, seq, max_waves, st);
+      return run<RowAgentLine, 32, 4>(w, a, count, seq, max_waves, st);
     }
     if (d > 256) return run<RowAgent32, 64, 8>(w, a, count, seq, max_waves, st);
     if (d > 128) return run<RowAgent32, 64, 4>(w, a, count, seq, max_waves, st);

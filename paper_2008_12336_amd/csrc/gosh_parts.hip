@@ -48,6 +48,7 @@ struct PairWork {
   int32_t B, per_round, d, diagonal;
   uint32_t key0, key1, rotation, word3;
 
+  bool rows_at_lines() const { return gosh::rows_at_lines(a_rows, d) && gosh::rows_at_lines(b_rows, d); }
   __host__ __device__ __forceinline__ int64_t count() const {
     return diagonal ? a_n : static_cast<int64_t>(a_n) + b_n;
   }

@@ -73,6 +73,7 @@ struct EpochWork {
   SamplerArgs s;
   float *M;
   int32_t d;
+  bool rows_at_lines() const { return gosh::rows_at_lines(M, d); }
   __device__ __forceinline__ int64_t count() const { return s.n; }
   __device__ __forceinline__ int32_t source_id(int64_t i) const { return static_cast<int32_t>(i); }
   __device__ __forceinline__ float *source_row(int64_t i) const { return M + i * d; }

@@ -181,3 +181,30 @@ def test_shipped_pair_kernel_in_sequential_order(d, K, B, k, stores_only, hot_de
         say(f"              {where}: err={err:.2e}")
         assert st["K"] == K and st["nonfinite"] == 0
         assert err <= TOL
+
+
+@pytest.mark.parametrize("paths", [MIX, ALL_ATOMIC])
+@pytest.mark.parametrize("d,offset", [(68, 0), (76, 4), (124, 0), (128, 8), (132, 0), (196, 12), (244, 0), (252, 4),
+                                      (256, 4), (260, 0), (384, 8), (444, 0), (508, 12), (512, 4)])
+def test_rows_that_straddle_lines_in_sequential_order(d, offset, paths, hot_degree):
+    """Rows that start anywhere between two line borders, because of d or of the matrix (which
+    starts `offset` floats past one), with columns left over at the end of the slots or not;
+    k = 6: chunks of 4 and 3 samples, the source row worked at twice.  Same bar as above."""
+    n, k = 1501, 6
+    xadj, adj = hub_graph(n, 9000, 4)
+    hot_degree(12)
+    g, keep = upload(n, xadj, adj, False)
+    M0 = start_matrix(n, d, 5, 0.4)
+    want = M0.copy()
+    room = torch.full((n * d + 64,), 7.0, device=DEV)
+    assert room.data_ptr() % 128 == 0
+    M = room[offset:offset + n * d].view(n, d)
+    M.copy_(torch.from_numpy(M0))
+    flags = SEQ_LAYOUT | (G.GOSH_FLAG_ATOMIC_ADDS if paths == ALL_ATOMIC else 0)
+    for epoch in range(2):
+        lr = G.gosh_lr(0.2, epoch, 3)
+        O.train_epoch(xadj, adj, want, k, lr, 77, epoch, 1)
+        G.gosh_train_epoch(g, M, k, lr, 77, epoch, 1, flags)
+    torch.cuda.synchronize()
+    assert rel_err(M.cpu().numpy(), want) <= TOL
+    assert (room[:offset] == 7.0).all() and (room[offset + n * d:] == 7.0).all()
