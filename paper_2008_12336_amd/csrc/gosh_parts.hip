@@ -100,32 +100,41 @@ __global__ __launch_bounds__(256) void pair_stream_kernel(PairWork w, int32_t sa
   }
 }
 
-// The positives of one side of a pair, drawn on the device from a graph that lives there:
-// the same runs (two binary searches in the ascending row) and the same draws as the host
-// sampler, one thread per source.
+// The positives of a pair, drawn on the device from a graph that lives there: the same runs (two
+// binary searches in the ascending row) and the same draws as the host sampler, one thread per
+// source, those of part a before those of part b.  Bound by the chain of reads of a search, so
+// both sides are one launch: a second one used to run into the write-back of a swap that starts
+// when the kernel before it ends, and took 155 us beside it instead of 9 (58,000 sources).
+struct PoolSide {
+  int32_t lo, cnt;   // the sources
+  int32_t olo, ohi;  // the partner part
+  int32_t *pool;
+};
 template <typename OffT>
 __global__ __launch_bounds__(256) void fill_pool_kernel(const OffT *__restrict__ xadj,
                                                         const int32_t *__restrict__ adj, int64_t nnz,
-                                                        int32_t lo, int32_t cnt, int32_t olo, int32_t ohi,
-                                                        int32_t side, int32_t B,
+                                                        PoolSide a, PoolSide b, int32_t B,
                                                         int32_t per_round, uint32_t key0, uint32_t key1,
-                                                        uint32_t rotation, uint32_t word3,
-                                                        int32_t *__restrict__ pool) {
-  for (int64_t local = blockIdx.x * 256LL + threadIdx.x; local < cnt; local += gridDim.x * 256LL) {
-    const int64_t src = static_cast<int64_t>(lo) + local;
+                                                        uint32_t rotation, uint32_t word3) {
+  const int64_t sources = static_cast<int64_t>(a.cnt) + b.cnt;
+  for (int64_t i = blockIdx.x * 256LL + threadIdx.x; i < sources; i += gridDim.x * 256LL) {
+    const int32_t side = i >= a.cnt;
+    const PoolSide &s = side ? b : a;
+    const int64_t local = side ? i - a.cnt : i;
+    const int64_t src = static_cast<int64_t>(s.lo) + local;
     int64_t first = static_cast<int64_t>(xadj[src]), end = static_cast<int64_t>(xadj[src + 1]);
     if (first < 0 || first > end || end > nnz) first = end = 0;  // offsets that leave adj: an empty row
     int64_t hi = end;
     while (first < hi) {  // first entry >= olo
       const int64_t mid = first + (hi - first) / 2;
-      if (adj[mid] < olo) first = mid + 1;
+      if (adj[mid] < s.olo) first = mid + 1;
       else hi = mid;
     }
     int64_t last = first;
     hi = end;
     while (last < hi) {  // first entry >= ohi
       const int64_t mid = last + (hi - last) / 2;
-      if (adj[mid] < ohi) last = mid + 1;
+      if (adj[mid] < s.ohi) last = mid + 1;
       else hi = mid;
     }
     const uint32_t candidates = static_cast<uint32_t>(last - first);
@@ -137,7 +146,7 @@ __global__ __launch_bounds__(256) void fill_pool_kernel(const OffT *__restrict__
                                           word3, key0, key1);
         pick = adj[first + scale_draw(draw, candidates)];
       }
-      pool[local * B + r] = pick;
+      s.pool[local * B + r] = pick;
     }
   }
 }
@@ -665,22 +674,21 @@ class Rotation {
   int pool_from_device(int64_t vi, const Visit &v) {
     const int ps = static_cast<int>(vi % S);
     const uint32_t w3 = level_word(pl.level, v.q);
-    auto fill = [&](int32_t lo, int32_t cnt, int32_t olo, int32_t ohi, int32_t side, int32_t *pool) {
-      if (cnt <= 0) return;
-      const int blocks = static_cast<int>(std::min<int64_t>((static_cast<int64_t>(cnt) + 255) / 256, 65536));
-      if (pl.g->xadj_is64)
-        hipLaunchKernelGGL(fill_pool_kernel<int64_t>, dim3(blocks), dim3(256), 0, compute,
-                           static_cast<const int64_t *>(pl.g->xadj), pl.g->adj, pl.g->nnz, lo, cnt, olo, ohi, side,
-                           pl.B, per_round, key0, key1, v.rot, w3, pool);
-      else
-        hipLaunchKernelGGL(fill_pool_kernel<int32_t>, dim3(blocks), dim3(256), 0, compute,
-                           static_cast<const int32_t *>(pl.g->xadj), pl.g->adj, pl.g->nnz, lo, cnt, olo, ohi, side,
-                           pl.B, per_round, key0, key1, v.rot, w3, pool);
-    };
-    fill(L.lo(v.a), L.size(v.a), L.lo(v.b), L.lo(v.b) + L.size(v.b), 0, dpool[ps]);
-    if (v.a != v.b)
-      fill(L.lo(v.b), L.size(v.b), L.lo(v.a), L.lo(v.a) + L.size(v.a), 1,
-           dpool[ps] + static_cast<size_t>(L.part_rows) * pl.B);
+    const PoolSide a{L.lo(v.a), L.size(v.a), L.lo(v.b), L.lo(v.b) + L.size(v.b), dpool[ps]};
+    const PoolSide b{L.lo(v.b), v.a != v.b ? L.size(v.b) : 0, L.lo(v.a), L.lo(v.a) + L.size(v.a),
+                     dpool[ps] + static_cast<size_t>(L.part_rows) * pl.B};
+    const int64_t sources = static_cast<int64_t>(a.cnt) + b.cnt;
+    const int blocks = static_cast<int>(std::min<int64_t>((sources + 255) / 256, 65536));
+    if (sources == 0) {  // an empty last part
+    } else if (pl.g->xadj_is64) {
+      hipLaunchKernelGGL(fill_pool_kernel<int64_t>, dim3(blocks), dim3(256), 0, compute,
+                         static_cast<const int64_t *>(pl.g->xadj), pl.g->adj, pl.g->nnz, a, b, pl.B, per_round, key0,
+                         key1, v.rot, w3);
+    } else {
+      hipLaunchKernelGGL(fill_pool_kernel<int32_t>, dim3(blocks), dim3(256), 0, compute,
+                         static_cast<const int32_t *>(pl.g->xadj), pl.g->adj, pl.g->nnz, a, b, pl.B, per_round, key0,
+                         key1, v.rot, w3);
+    }
     if (int rc = gosh::check_launch("fill_pool_kernel")) return rc;
     GOSH_TRY_HIP(hipEventRecord(pool_ready[ps], compute), "hipEventRecord");
     // marks, on the inbound stream, the point up to which this visit's parts are in
