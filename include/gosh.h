@@ -416,7 +416,7 @@ typedef struct {
   int64_t rotations;     /* ceil(epochs / (B*K)), at least 1 */
   int64_t pair_visits;   /* rotations * K(K+1)/2 pair kernels */
   int64_t updates;       /* updates of Alg. 1 attempted (sources * B * (k_neg+1) per visit) */
-  uint64_t device_bytes; /* part slots + sample pools + hot-row bitmap */
+  uint64_t device_bytes; /* part slots + sample pools + hot-row bitmap (+ row locks, if used) */
   uint64_t bytes_h2d;    /* parts and pools copied to the device */
   uint64_t bytes_d2h;    /* parts copied back */
   double kernel_ms;      /* sum of the pair kernels' durations (HIP events) */

@@ -7,6 +7,7 @@
 
 #include <algorithm>
 #include <cstdint>
+#include <type_traits>
 
 namespace gosh {
 
@@ -181,13 +182,37 @@ struct RowAgentLine : RowAgent32 {
 // which cannot be lost.  Cold rows are written back with plain stores, which cost
 // half as much on this memory system.
 // ---------------------------------------------------------------------------------
-enum HotMode : int32_t { kHotNone = 0, kHotBitmap = 1, kHotAll = 2 };
+//
+// Locked rows.  fp32 atomic adds run at 20.5 G 64-byte blocks per second on the whole chip, and
+// a launch in which every row is hot is bound by that.  A row can also be written without losing
+// an update by taking a lock first: one 32-bit exchange instead of an atomic add per block, then
+// the row is read, changed and written back like a cold one (5.3 G rows of 512 bytes per second,
+// read included, against 2.55 G as adds alone).  In kHotLocked mode every row is written that
+// way, except hubs, whose holders would queue up: their rows take atomic adds, always, so that a
+// row is only ever written one way in a launch.
+enum HotMode : int32_t { kHotNone = 0, kHotBitmap = 1, kHotAll = 2, kHotLocked = 3 };
 
 struct HotSet {
-  const uint32_t *bits;  // one bit per vertex when mode == kHotBitmap; in the other modes
-                         // still a readable device word (the kernel reads word 0 blindly)
+  const uint32_t *bits;  // one bit per vertex when mode is kHotBitmap (hot) or kHotLocked (hub); in
+                         // the other modes still a readable device word (the kernel reads word 0 blindly)
   int32_t mode;
+  uint32_t *locks;  // one word per vertex when mode == kHotLocked: 0 before and after a launch
 };
+
+// Whether a launch in which every row is hot takes locks.  An update of a row that spans three
+// or more blocks is cheaper locked (k = 3, us per epoch, adds against locks: 131,072 vertices at
+// d = 32 93 / 97; 262,144 at d = 64 272 / 156; 67,000 at d = 128 137 / 92; 60,000 at d = 512 285 /
+// 143; 130,000 at d = 36, k = 9 223 / 192), unless there are so few that the launch is bound by one
+// source's chain of round trips, which locks make longer (d = 128: 8,192 vertices 21 / 34, 32,768
+// 70 / 57).
+inline bool worth_locking(int64_t updates, int32_t d) {
+  const int64_t blocks = (d + 15) / 16;
+  return blocks >= 3 && updates * blocks >= 1000000;
+}
+// A vertex is a hub if more than 1 / kHubShare of a source in flight is expected to hold it as its
+// positive sample.  1, 2 and 4 are within 4 % of each other on power-law graphs; at 16 every row of
+// a graph of mean degree 200 is one (67,000 vertices: 140 us instead of 92).
+constexpr int64_t kHubShare = 2;
 
 struct SgdArgs {
   HotSet hot;
@@ -200,6 +225,10 @@ struct SgdArgs {
 };
 
 constexpr int kChunk = 4;  // sample rows in flight per source
+// Tries of a lock before an update is added without it.  Every holder lets go after its own
+// memory accesses and waits for no other lock meanwhile, so this is never reached in practice; it
+// bounds the kernel's time whatever the lock words hold.
+constexpr int32_t kMaxTries = 1 << 14;
 
 // Atomic adds of whole rows with 128-bit units, one row at a time by the whole wavefront.
 // A memory-side fp32 atomic costs one operation per instruction and line it touches, full or
@@ -295,7 +324,12 @@ struct ChunkPos {
 // (its step is forced to zero, its store is skipped).  All reads of a chunk are therefore
 // issued back to back and waited for once, which is what keeps their latencies overlapped;
 // with predicated reads the compiler splits the code into blocks and waits in each.
-template <class P, int LPG, int UPL, class W, bool SEQ>
+// LOCKED: the rows are locked (see kHotLocked).  A chunk's samples are then taken one after
+// another, each group at its own pace: try the lock of the next one (one exchange, never waited
+// for), read the row if it was free, update, write back.  The previous row's lock is released
+// behind the wait for that exchange, which is also the wait for the row's stores.  A group holds one
+// lock while it tries another but never waits for one, so no two can wait for each other.
+template <class P, int LPG, int UPL, class W, bool SEQ, bool LOCKED>
 __global__ __launch_bounds__(256) void sgd_kernel(W w, SgdArgs a) {
   constexpr int kGroupsPerWave = 64 / LPG;
   constexpr int kPasses = (kChunk + LPG - 1) / LPG;  // sampler passes per chunk (lane q takes sample q)
@@ -323,7 +357,7 @@ __global__ __launch_bounds__(256) void sgd_kernel(W w, SgdArgs a) {
   const int64_t first = first_of_wave + (SEQ ? 0 : lane / LPG);
   const int32_t d = a.d;
   const int32_t per_round = a.k_neg + 1;
-  const bool use_bitmap = a.hot.mode == kHotBitmap;
+  const bool use_bitmap = LOCKED || a.hot.mode == kHotBitmap;
   const bool all_hot = a.hot.mode == kHotAll;
   const uint32_t *const bits = a.hot.bits;  // always a readable word, also without a bitmap
 
@@ -377,6 +411,23 @@ __global__ __launch_bounds__(256) void sgd_kernel(W w, SgdArgs a) {
     return w.stage1(live ? pos.idx : 0, live);
   };
 
+  // The lock this group holds (vertex id, -1 none); its release, behind everything issued so far.
+  int32_t held_lock = -1;
+  auto release = [&]() {
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    if (held_lock >= 0 && gl == 0)
+      __hip_atomic_store(a.hot.locks + held_lock, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    held_lock = -1;
+  };
+  // One try at the lock of vertex id; true in the whole group if it was free.
+  auto try_lock = [&](bool want, int32_t id) -> bool {
+    bool mine = false;
+    if (want && gl == 0)
+      mine = __hip_atomic_exchange(a.hot.locks + id, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0u;
+    release();
+    return ((__ballot(mine) >> (lane & ~(LPG - 1))) & 1u) != 0;
+  };
+
   // Pipeline prologue: the ids of the group's first chunk and the offsets of its second.
   int32_t mine[kPasses];
   Pre pre_next;
@@ -415,15 +466,17 @@ __global__ __launch_bounds__(256) void sgd_kernel(W w, SgdArgs a) {
         for (int q = 0; q < LPG && p * LPG + q < kChunk; ++q) v[p * LPG + q] = __shfl(mine[p], q, LPG);
 
       // Request every row of the chunk (a missing sample reads the source row instead).
-      U r[kChunk][UPL];
+      U r[LOCKED ? 1 : kChunk][UPL];
       uint32_t word[kChunk];
       bool valid[kChunk];
 #pragma unroll
       for (int q = 0; q < kChunk; ++q) {
         valid[q] = live && v[q] >= 0 && v[q] != src;  // a sample that hits the source applies no update
-        const float *row = valid[q] ? w.sample_row(idx, v[q]) : src_row;
+        if constexpr (!LOCKED) {
+          const float *row = valid[q] ? w.sample_row(idx, v[q]) : src_row;
 #pragma unroll
-        for (int i = 0; i < UPL; ++i) r[q][i] = P::load(row + readable(column(row, i)));
+          for (int i = 0; i < UPL; ++i) r[q][i] = P::load(row + readable(column(row, i)));
+        }
         word[q] = bits[(use_bitmap && valid[q]) ? (v[q] >> 5) : 0];
       }
       // While they are in flight: the ids of the next chunk (its offsets arrived a chunk
@@ -448,6 +501,77 @@ __global__ __launch_bounds__(256) void sgd_kernel(W w, SgdArgs a) {
       }
       held_in_order();
       fresh = false;
+      if constexpr (LOCKED) {
+        release();
+        int next = 0;  // first sample of the chunk that this group has not applied yet
+        for (int32_t tries = 0;; ++tries) {
+          int32_t id = -1;
+          int at = kChunk;
+          bool positive = false, hub = false;
+#pragma unroll
+          for (int q = kChunk - 1; q >= 0; --q)
+            if (q >= next && valid[q]) {
+              at = q;
+              id = v[q];
+              positive = is_pos[q];
+              hub = (word[q] >> (v[q] & 31)) & 1u;
+            }
+          const bool want = id >= 0;
+          if (__ballot(want) == 0) break;  // the same for the whole wavefront
+          const bool locked = try_lock(want && !hub, id);
+          const bool add = want && (hub || (!locked && tries >= kMaxTries));
+          const bool apply = locked || add;
+          float *const row = apply ? w.sample_row(idx, id) : src_row;
+#pragma unroll
+          for (int i = 0; i < UPL; ++i) r[0][i] = P::load(row + readable(column(row, i)));
+          P::wait_all();
+          float partial = 0.f;
+#pragma unroll
+          for (int i = 0; i < UPL; ++i) {
+            P::settle(r[0][i]);
+            if constexpr (P::kAligned) s[i].v[0] = held[column(row, i)];
+#pragma unroll
+            for (int c = 0; c < F; ++c) {
+              r[0][i].v[c] = column(row, i) < d ? r[0][i].v[c] : 0.f;
+              partial = fmaf(s[i].v[c], r[0][i].v[c], partial);
+            }
+          }
+          const float x = group_sum<LPG>(partial);
+          const float g = apply ? a.lr * ((positive ? 1.f : 0.f) - 1.f / (1.f + expf(-x))) : 0.f;
+#pragma unroll
+          for (int i = 0; i < UPL; ++i)
+#pragma unroll
+            for (int c = 0; c < F; ++c) {
+              s[i].v[c] = fmaf(g, r[0][i].v[c], s[i].v[c]);
+              r[0][i].v[c] = fmaf(g, s[i].v[c], r[0][i].v[c]);
+            }
+          if constexpr (P::kAligned) {
+#pragma unroll
+            for (int i = 0; i < UPL; ++i) held[column(row, i)] = s[i].v[0];
+            held_in_order();
+          }
+          if (locked) {  // uniform over the group; only writes inside
+#pragma unroll
+            for (int i = 0; i < UPL; ++i)
+              if (column(row, i) < d) P::store(row + column(row, i), r[0][i]);
+          }
+          if constexpr (P::kWaveAtomics) {
+            U step;
+#pragma unroll
+            for (int c = 0; c < F; ++c) step.v[c] = g * s[0].v[c];
+            add_rows_as_a_wave<LPG>(add, row, step, d, lane);
+          } else if (add) {
+#pragma unroll
+            for (int i = 0; i < UPL; ++i)
+#pragma unroll
+              for (int c = 0; c < F; ++c)
+                if (column(row, i) < d) atomic_step(row + column(row, i) + c, g * s[i].v[c]);
+          }
+          held_lock = locked ? id : -1;
+          next = apply ? at + 1 : next;
+        }
+        continue;
+      }
 #pragma unroll
       for (int q = 0; q < kChunk; ++q) {
         const float *const row = valid[q] ? w.sample_row(idx, v[q]) : src_row;
@@ -525,6 +649,43 @@ __global__ __launch_bounds__(256) void sgd_kernel(W w, SgdArgs a) {
       for (int i = 0; i < UPL; ++i) s[i].v[0] = held[column(src_row, i)];
       held_in_order();
     }
+    if constexpr (LOCKED) {
+      // the source's change, added to its row as it is now
+      const bool hub = live && ((src_word >> (src & 31)) & 1u);
+      bool locked = false;
+      for (int32_t tries = 0; tries < kMaxTries; ++tries) {
+        if (__ballot(live && !hub && !locked) == 0) break;  // the same for the whole wavefront
+        if (try_lock(live && !hub && !locked, src)) {
+          locked = true;
+          U now[UPL];
+#pragma unroll
+          for (int i = 0; i < UPL; ++i) now[i] = P::load(src_row + readable(column(src_row, i)));
+          P::wait_all();
+#pragma unroll
+          for (int i = 0; i < UPL; ++i) {
+            P::settle(now[i]);
+#pragma unroll
+            for (int c = 0; c < F; ++c) now[i].v[c] += s[i].v[c] - s_before[i].v[c];
+            if (column(src_row, i) < d) P::store(src_row + column(src_row, i), now[i]);
+          }
+          held_lock = src;
+        }
+      }
+      const bool add = live && !locked;
+      if constexpr (P::kWaveAtomics) {
+        U step;
+#pragma unroll
+        for (int c = 0; c < F; ++c) step.v[c] = s[0].v[c] - s_before[0].v[c];
+        add_rows_as_a_wave<LPG>(add, src_row, step, d, lane);
+      } else if (add) {
+#pragma unroll
+        for (int i = 0; i < UPL; ++i)
+#pragma unroll
+          for (int c = 0; c < F; ++c)
+            if (column(src_row, i) < d) atomic_step(src_row + column(src_row, i) + c, s[i].v[c] - s_before[i].v[c]);
+      }
+      continue;
+    }
     const bool src_hot = live && (all_hot || ((src_word >> (src & 31)) & 1u));
     if (live && !src_hot) {
 #pragma unroll
@@ -544,6 +705,7 @@ __global__ __launch_bounds__(256) void sgd_kernel(W w, SgdArgs a) {
           if (column(src_row, i) < d) atomic_step(src_row + column(src_row, i) + c, s[i].v[c] - s_before[i].v[c]);
     }
   }
+  if constexpr (LOCKED) release();
 }
 
 // Whether the access instructions of lanes at columns 0, 1, 2, ... touch no more 64-byte blocks
@@ -573,12 +735,15 @@ struct SgdLauncher {
     const int64_t per_block = (turns + max_blocks - 1) / max_blocks;  // turns of one workgroup
     const int64_t blocks64 = (turns + per_block - 1) / per_block;
     a.sources_per_block = per_block * kPerTurn;
-    if (seq) {
-      hipLaunchKernelGGL((sgd_kernel<P, LPG, UPL, W, true>), dim3(1), dim3(64), 0, st, w, a);
-    } else {
-      const int blocks = static_cast<int>(blocks64);
-      hipLaunchKernelGGL((sgd_kernel<P, LPG, UPL, W, false>), dim3(blocks), dim3(256), 0, st, w, a);
+    const int blocks = static_cast<int>(blocks64);
+    const bool locked = a.hot.mode == kHotLocked;
+    if constexpr (!std::is_same_v<P, RowPlain128>) {
+      if (locked && seq) hipLaunchKernelGGL((sgd_kernel<P, LPG, UPL, W, true, true>), dim3(1), dim3(64), 0, st, w, a);
+      else if (locked) hipLaunchKernelGGL((sgd_kernel<P, LPG, UPL, W, false, true>), dim3(blocks), dim3(256), 0, st, w, a);
+      if (locked) return;
     }
+    if (seq) hipLaunchKernelGGL((sgd_kernel<P, LPG, UPL, W, true, false>), dim3(1), dim3(64), 0, st, w, a);
+    else hipLaunchKernelGGL((sgd_kernel<P, LPG, UPL, W, false, false>), dim3(blocks), dim3(256), 0, st, w, a);
   }
 
   static int pow2_lanes(int units) {
@@ -620,7 +785,7 @@ struct SgdLauncher {
     // 200 1,742 / 473 -> 1,710 / 429; 300 2,792 / 733 -> 2,718 / 644; 444 4,132 / 1,066 ->
     // 4,018 / 923.  At 132 half the lanes idle and the longer code costs more than the blocks
     // saved, unless every write is an atomic add.
-    if (!w.rows_at_lines() && (d <= 128 || d > 192 || a.hot.mode == kHotAll)) {
+    if (!w.rows_at_lines() && (d <= 128 || d > 192 || a.hot.mode >= kHotAll)) {
       if (d > 256) return run<RowAgentLine, 64, 8>(w, a, count, seq, max_waves, st);
       if (d > 128) return run<RowAgentLine, 64, 4>(w, a, count, seq, max_waves, st);
       return run<RowAgentLine, 32, 4>(w, a, count, seq, max_waves, st);

@@ -143,6 +143,33 @@ int hot_scratch(size_t bytes, void **out) {
   return GOSH_OK;
 }
 
+int lock_scratch(int64_t rows, uint32_t **out) {
+  static HotScratch table[kMaxDevices];
+  int dev = 0;
+  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices)
+    return fail(GOSH_EHIP, "cannot identify the current device");
+  std::lock_guard<std::mutex> lock(g_hot_scratch_mutex);
+  HotScratch &h = table[dev];
+  const size_t bytes = static_cast<size_t>(rows) * 4;
+  if (h.bytes < bytes) {
+    if (h.ptr) (void)hipFree(h.ptr);  // waits for the launches that use it
+    h.ptr = nullptr;
+    h.bytes = 0;
+    const size_t want = bytes + bytes / 4 + 4096;
+    if (device_malloc(&h.ptr, want) != hipSuccess) return fail(GOSH_ENOMEM, "cannot allocate %zu bytes for the row locks", want);
+    // ordered before any launch on any stream
+    if (hipMemset(h.ptr, 0, want) != hipSuccess || hipDeviceSynchronize() != hipSuccess) {
+      (void)hipGetLastError();
+      (void)hipFree(h.ptr);
+      h.ptr = nullptr;
+      return fail(GOSH_EHIP, "cannot clear the row locks");
+    }
+    h.bytes = want;
+  }
+  *out = static_cast<uint32_t *>(h.ptr);
+  return GOSH_OK;
+}
+
 int check_scratch(CheckResult **out) {
   static CheckResult *table[kMaxDevices] = {};
   int dev = 0;

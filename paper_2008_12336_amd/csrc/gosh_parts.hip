@@ -268,6 +268,7 @@ struct RotationPlan {
   int32_t K, P, S;    // parts, slots (K when the matrix is on the device), pools
   int32_t order_P;    // the slot count the blocked pair order is laid out for
   int64_t rotations;
+  bool room_for_locks;  // lock words for every vertex fit the budget beside the rest
 };
 
 // One call of gosh_train_parts: owns the device slots and pools, the three streams, the
@@ -324,6 +325,7 @@ class Rotation {
     for (auto p : dpool) if (p) (void)hipFree(p);
     for (auto p : staging) if (p) (void)hipHostFree(p);
     if (hot_bits_dev) (void)hipFree(hot_bits_dev);
+    if (locks) (void)hipFree(locks);
     if (check) (void)hipFree(check);
     for (hipStream_t s : {compute, copy, copy_out})
       if (s) (void)hipStreamDestroy(s);
@@ -422,6 +424,8 @@ class Rotation {
     return write_back_all();
   }
 
+  bool locked_rows() const { return locks != nullptr; }
+
   gosh_parts_stats st{};
 
  private:
@@ -457,7 +461,8 @@ class Rotation {
   std::vector<int32_t *> dpool, staging;
   std::vector<int32_t> slot_part;
   uint32_t *hot_bits_dev = nullptr;
-  gosh::HotSet hot{nullptr, gosh::kHotNone};
+  uint32_t *locks = nullptr;
+  gosh::HotSet hot{nullptr, gosh::kHotNone, nullptr};
   gosh::CheckResult *check = nullptr;  // divergence check, accumulated on the outbound stream
   hipStream_t compute = nullptr, copy = nullptr, copy_out = nullptr;
   std::vector<hipEvent_t> chunk_flushed, slot_ready, slot_used, pool_ready, pool_used, staging_done, k_begin, k_end;
@@ -492,12 +497,20 @@ class Rotation {
                   (static_cast<int64_t>(pl.B) * pl.k_neg + 1) * in_flight * tune.hot_all_inv_eps > pair_sources)
                      ? gosh::kHotAll
                      : gosh::kHotBitmap;
+      if (mode == gosh::kHotAll && pl.room_for_locks && tune.plain_rows == 0 &&
+          gosh::worth_locking(pair_sources * (samples + 1), pl.d))
+        mode = gosh::kHotLocked;
       if (pl.flags & GOSH_FLAG_PLAIN_STORES) mode = gosh::kHotNone;
       if (pl.flags & GOSH_FLAG_ATOMIC_ADDS) mode = gosh::kHotAll;
-      if (mode == gosh::kHotBitmap) {
-        const int64_t min_degree = tune.hot_min_degree > 0
-                                       ? tune.hot_min_degree
-                                       : pl.g->nnz / (tune.hot_inv_eps * in_flight * pl.B) + 1;
+      if (mode == gosh::kHotLocked) {
+        GOSH_TRY_HIP(gosh::device_malloc(&locks, static_cast<size_t>(n) * 4), "hipMalloc row locks");
+        GOSH_TRY_HIP(hipMemsetAsync(locks, 0, static_cast<size_t>(n) * 4, compute), "clear row locks");
+        hot.locks = locks;
+      }
+      if (mode == gosh::kHotBitmap || mode == gosh::kHotLocked) {
+        const int64_t share = mode == gosh::kHotLocked ? gosh::kHubShare : tune.hot_inv_eps * pl.B;
+        const int64_t min_degree =
+            tune.hot_min_degree > 0 ? tune.hot_min_degree : pl.g->nnz / (share * in_flight) + 1;
         const int64_t words = (n + 63) / 64;
         GOSH_TRY_HIP(gosh::device_malloc(&hot_bits_dev, static_cast<size_t>(words) * 8), "hipMalloc hot bitmap");
         if (graph_on_device) {
@@ -924,7 +937,8 @@ int gosh_train_parts(const gosh_csr *g_host, float *M_host, int32_t d, int32_t k
   rotations = std::max<int64_t>(1, (epochs + static_cast<int64_t>(B) * K - 1) / (static_cast<int64_t>(B) * K));
   const auto wall0 = std::chrono::steady_clock::now();
   const RotationPlan plan{g_host, M_host, matrix_on_device, d,     k_neg, B, lr0, seed, level, flags, K,
-                          matrix_on_device ? K : std::min(P_gpu, K), S_gpu, std::min(P_gpu, K), rotations};
+                          matrix_on_device ? K : std::min(P_gpu, K), S_gpu, std::min(P_gpu, K), rotations,
+                          device_budget_bytes == 0 || planned_bytes + static_cast<uint64_t>(n) * 4 <= device_budget_bytes};
   gosh_parts_stats st{};
   int rc = GOSH_OK;
   {
@@ -933,6 +947,7 @@ int gosh_train_parts(const gosh_csr *g_host, float *M_host, int32_t d, int32_t k
     if (rc == GOSH_OK) rc = rotation.run();
     rotation.finish();
     st = rotation.st;
+    if (rotation.locked_rows()) planned_bytes += static_cast<uint64_t>(n) * 4;
   }
   st.device_bytes = planned_bytes;
   st.wall_ms = std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - wall0).count();

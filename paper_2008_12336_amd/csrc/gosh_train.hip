@@ -403,6 +403,15 @@ SamplerArgs sampler_args(const gosh_csr *g, uint64_t seed, uint32_t epoch, uint3
   return s;
 }
 
+// Whether a call on this stream is being recorded.  Such calls, and gosh_train_epoch_static, take
+// no locks: the words may be replaced by larger ones later, which a recorded launch would not see.
+bool capturing(hipStream_t st) {
+  hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(st, &status) == hipSuccess) return status != hipStreamCaptureStatusNone;
+  (void)hipGetLastError();
+  return true;
+}
+
 // bits_override: the hot-row bitmap to use instead of the library's grown-on-demand scratch
 // (at least (n + 63) / 64 * 8 bytes), or null.
 template <typename OffT>
@@ -423,7 +432,7 @@ int launch_epoch(const gosh_csr *g, float *M, int32_t d, int32_t k_neg, float lr
   a.k_neg = k_neg;
   a.samples = k_neg + 1;
   a.lr = lr;
-  a.hot = gosh::HotSet{nullptr, gosh::kHotNone};
+  a.hot = gosh::HotSet{nullptr, gosh::kHotNone, nullptr};
   const int64_t max_waves = tune.max_waves;
   if (concurrent_paths) {
     // Sources in flight C, and the hot-row rule.  A vertex is hot if its expected
@@ -437,12 +446,17 @@ int launch_epoch(const gosh_csr *g, float *M, int32_t d, int32_t k_neg, float lr
     int64_t waves = std::min<int64_t>((n + gpw - 1) / gpw, max_waves);
     const int64_t in_flight = std::min<int64_t>(waves, gosh::resident_waves()) * gpw;
     int mode = gosh::kHotBitmap;
-    if (tune.hot_min_degree == 0 && (k_neg + 1) * in_flight * tune.hot_all_inv_eps > n) mode = gosh::kHotAll;
+    if (tune.hot_min_degree == 0 && (k_neg + 1) * in_flight * tune.hot_all_inv_eps > n)
+      mode = bits_override == nullptr && tune.plain_rows == 0 && gosh::worth_locking(n * (k_neg + 2), d) && !capturing(st)
+                 ? gosh::kHotLocked
+                 : gosh::kHotAll;
     if (flags & GOSH_FLAG_PLAIN_STORES) mode = gosh::kHotNone;
     if (flags & GOSH_FLAG_ATOMIC_ADDS) mode = gosh::kHotAll;
-    if (mode == gosh::kHotBitmap) {
-      const int64_t min_degree =
-          tune.hot_min_degree > 0 ? tune.hot_min_degree : g->nnz / (tune.hot_inv_eps * in_flight) + 1;
+    if (mode == gosh::kHotLocked)
+      if (int rc = gosh::lock_scratch(n, &a.hot.locks)) return rc;
+    if (mode == gosh::kHotBitmap || mode == gosh::kHotLocked) {
+      const int64_t share = mode == gosh::kHotLocked ? gosh::kHubShare : tune.hot_inv_eps;
+      const int64_t min_degree = tune.hot_min_degree > 0 ? tune.hot_min_degree : g->nnz / (share * in_flight) + 1;
       void *bits = bits_override;
       if (bits == nullptr)
         if (int rc = gosh::hot_scratch(static_cast<size_t>((n + 63) / 64) * 8, &bits)) return rc;

@@ -208,3 +208,65 @@ def test_rows_that_straddle_lines_in_sequential_order(d, offset, paths, hot_degr
     torch.cuda.synchronize()
     assert rel_err(M.cpu().numpy(), want) <= TOL
     assert (room[:offset] == 7.0).all() and (room[offset + n * d:] == 7.0).all()
+
+
+# n (k + 2) updates of rows of ceil(d / 16) blocks: at least a million, so that an epoch on a graph
+# small enough for every row to be written without losses takes row locks
+LOCKED = [(36, 30000, 10), (64, 20000, 11), (100, 12000, 11), (128, 40000, 3), (132, 9000, 11), (260, 8000, 6),
+          (512, 4500, 5)]
+
+
+@pytest.mark.parametrize("d,n,k", LOCKED)
+def test_locked_rows(d, n, k):
+    """Every row under its lock, hubs by atomic adds.  In sequential order: the sequential result.
+    Concurrent: no update is lost, so at a small learning rate every row ends within 2 % of its
+    own movement of the sequential result (the bar of the all-atomic epoch); twice in a row, so
+    that the locks of the first launch must have been given back."""
+    assert n * (k + 2) * -(-d // 16) >= 1_000_000
+    xadj, adj = hub_graph(n, 6 * n, 3)
+    g, keep = upload(n, xadj, adj, True)
+    M0 = start_matrix(n, d, 5, 0.5)
+    want = M0.copy()
+    O.train_epoch(xadj, adj, want, k, 0.1, 77, 0, 1)
+    M = torch.from_numpy(M0).to(DEV)
+    G.gosh_train_epoch(g, M, k, 0.1, 77, 0, 1, SEQ_LAYOUT)
+    torch.cuda.synchronize()
+    assert rel_err(M.cpu().numpy(), want) <= TOL
+    M = torch.from_numpy(M0).to(DEV)
+    for epoch in range(2):
+        before = M.cpu().numpy()
+        want = before.copy()
+        O.train_epoch(xadj, adj, want, k, 1e-3, 77, epoch, 1)
+        G.gosh_train_epoch(g, M, k, 1e-3, 77, epoch, 1)
+        torch.cuda.synchronize()
+        step = np.abs(want.astype(np.float64) - before).max(axis=1)
+        err = np.abs(M.cpu().numpy().astype(np.float64) - want).max(axis=1)
+        ok = err <= 0.02 * step + 2e-7 * np.abs(before).max()
+        say(f"[locked] d={d} n={n}: worst err/step {np.max(err / np.maximum(step, 1e-30)):.3e}")
+        assert ok.all()
+
+
+@pytest.mark.parametrize("where", ["device", "host"])
+def test_locked_rows_of_a_rotation(where):
+    """The pair kernel with locks (512 columns, 3 parts of 1,200 rows, 21 updates per source and
+    visit), sequential order against the oracle and concurrent to first order."""
+    n, d, k, K, B = 3600, 512, 3, 3, 5
+    xadj, adj = hub_graph(n, 9 * n, 8)
+    xt, at = torch.from_numpy(xadj), torch.from_numpy(adj)
+    if where == "device":
+        xt, at = xt.to(DEV), at.to(DEV)
+    M0 = start_matrix(n, d, 3, 0.5)
+    for flags, lr, tol in ((SEQ_LAYOUT, 0.1, None), (0, 1e-4, 0.02)):
+        want = M0.copy()
+        O.train_parts(xadj, adj, want, k, B * K, lr, 7, 2, K, B)
+        M = torch.from_numpy(M0.copy()).to(DEV) if where == "device" else torch.from_numpy(M0.copy()).pin_memory()
+        st = G.gosh_train_parts(n, xt, at, M, k, B * K, lr, 7, level=2, force_K=K, B=B, flags=flags)
+        torch.cuda.synchronize()
+        assert st["device_bytes"] >= 4 * n
+        got = M.cpu().numpy()
+        if tol is None:
+            assert rel_err(got, want) <= TOL
+        else:
+            step = np.abs(want.astype(np.float64) - M0).max(axis=1)
+            err = np.abs(got.astype(np.float64) - want).max(axis=1)
+            assert (err <= tol * step + 2e-7 * np.abs(M0).max()).all()
