@@ -328,9 +328,12 @@ struct ChunkPos {
 // another, each group at its own pace: try the lock of the next one (one exchange, never waited
 // for), read the row if it was free, update, write back.  The previous row's lock is released
 // behind the wait for that exchange, which is also the wait for the row's stores.  A group holds one
-// lock while it tries another but never waits for one, so no two can wait for each other.
+// lock while it tries another but never waits for one, so no two can wait for each other.  (Trying
+// the lock of the row after the next together with each row saves a round trip per row and loses
+// more to locks that are held longer: 67,000 vertices at d = 128 89 -> 101 us, 262,144 at d = 64
+// 154 -> 186; only the longest rows gain, 60,000 at d = 512 141 -> 130.)
 template <class P, int LPG, int UPL, class W, bool SEQ, bool LOCKED>
-__global__ __launch_bounds__(256) void sgd_kernel(W w, SgdArgs a) {
+__device__ __forceinline__ void sgd_walk(const W &w, const SgdArgs &a) {
   constexpr int kGroupsPerWave = 64 / LPG;
   constexpr int kPasses = (kChunk + LPG - 1) / LPG;  // sampler passes per chunk (lane q takes sample q)
   constexpr int F = P::F;
@@ -708,6 +711,15 @@ __global__ __launch_bounds__(256) void sgd_kernel(W w, SgdArgs a) {
   if constexpr (LOCKED) release();
 }
 
+template <class P, int LPG, int UPL, class W, bool SEQ>
+__global__ __launch_bounds__(256) void sgd_kernel(W w, SgdArgs a) {
+  sgd_walk<P, LPG, UPL, W, SEQ, false>(w, a);
+}
+template <class P, int LPG, int UPL, class W, bool SEQ>
+__global__ __launch_bounds__(256) void sgd_locked_kernel(W w, SgdArgs a) {
+  sgd_walk<P, LPG, UPL, W, SEQ, true>(w, a);
+}
+
 // Whether the access instructions of lanes at columns 0, 1, 2, ... touch no more 64-byte blocks
 // than they cover in every row of a matrix.
 inline bool rows_at_lines(const float *M, int32_t d) { return reinterpret_cast<uintptr_t>(M) % 64 == 0 && d % 16 == 0; }
@@ -738,12 +750,12 @@ struct SgdLauncher {
     const int blocks = static_cast<int>(blocks64);
     const bool locked = a.hot.mode == kHotLocked;
     if constexpr (!std::is_same_v<P, RowPlain128>) {
-      if (locked && seq) hipLaunchKernelGGL((sgd_kernel<P, LPG, UPL, W, true, true>), dim3(1), dim3(64), 0, st, w, a);
-      else if (locked) hipLaunchKernelGGL((sgd_kernel<P, LPG, UPL, W, false, true>), dim3(blocks), dim3(256), 0, st, w, a);
+      if (locked && seq) hipLaunchKernelGGL((sgd_locked_kernel<P, LPG, UPL, W, true>), dim3(1), dim3(64), 0, st, w, a);
+      else if (locked) hipLaunchKernelGGL((sgd_locked_kernel<P, LPG, UPL, W, false>), dim3(blocks), dim3(256), 0, st, w, a);
       if (locked) return;
     }
-    if (seq) hipLaunchKernelGGL((sgd_kernel<P, LPG, UPL, W, true, false>), dim3(1), dim3(64), 0, st, w, a);
-    else hipLaunchKernelGGL((sgd_kernel<P, LPG, UPL, W, false, false>), dim3(blocks), dim3(256), 0, st, w, a);
+    if (seq) hipLaunchKernelGGL((sgd_kernel<P, LPG, UPL, W, true>), dim3(1), dim3(64), 0, st, w, a);
+    else hipLaunchKernelGGL((sgd_kernel<P, LPG, UPL, W, false>), dim3(blocks), dim3(256), 0, st, w, a);
   }
 
   static int pow2_lanes(int units) {

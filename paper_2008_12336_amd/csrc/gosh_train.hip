@@ -446,10 +446,18 @@ int launch_epoch(const gosh_csr *g, float *M, int32_t d, int32_t k_neg, float lr
     int64_t waves = std::min<int64_t>((n + gpw - 1) / gpw, max_waves);
     const int64_t in_flight = std::min<int64_t>(waves, gosh::resident_waves()) * gpw;
     int mode = gosh::kHotBitmap;
-    if (tune.hot_min_degree == 0 && (k_neg + 1) * in_flight * tune.hot_all_inv_eps > n)
-      mode = bits_override == nullptr && tune.plain_rows == 0 && gosh::worth_locking(n * (k_neg + 2), d) && !capturing(st)
-                 ? gosh::kHotLocked
-                 : gosh::kHotAll;
+    if (tune.hot_min_degree == 0) {
+      const int64_t all_hot_below = (k_neg + 1) * in_flight * tune.hot_all_inv_eps;
+      // Rows of seven blocks or more are worth their locks for twice as many vertices: the degree
+      // rule would call a third of the writes or more hot there, and those are bound by the rate of
+      // atomic adds (k = 3, us: uniform 300,000 x 128 597 -> 363, power law 400,000 x 128 483 -> 441,
+      // 200,000 x 256 493 -> 401; at d = 64 a power law of 800,000 488 -> 526; at four times as many
+      // vertices an R-MAT graph of 2^19 x 128 466 -> 672).
+      const bool lock = bits_override == nullptr && tune.plain_rows == 0 && gosh::worth_locking(n * (k_neg + 2), d) &&
+                        n < all_hot_below * (d > 96 ? 2 : 1) && !capturing(st);
+      if (lock) mode = gosh::kHotLocked;
+      else if (n < all_hot_below) mode = gosh::kHotAll;
+    }
     if (flags & GOSH_FLAG_PLAIN_STORES) mode = gosh::kHotNone;
     if (flags & GOSH_FLAG_ATOMIC_ADDS) mode = gosh::kHotAll;
     if (mode == gosh::kHotLocked)
