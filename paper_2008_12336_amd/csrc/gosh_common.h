@@ -87,7 +87,7 @@ int check_scratch(CheckResult **out);
 // streams.
 int hot_scratch(size_t bytes, void **out);
 // Per-device lock words of the training kernels, one per vertex, zero between launches; grown on
-// demand and kept until the process ends.  Launches on different streams may share them.
+// demand and kept until the process ends.
 int lock_scratch(int64_t rows, uint32_t **out);
 
 }  // namespace gosh

@@ -20,7 +20,7 @@ void block_trim();
 
 // Pinned staging for copies between pageable memory and the device: two slots of
 // kStagingBytes, null if there is no memory for them.  A pair or two are kept.
-constexpr size_t kStagingBytes = size_t(8) << 20;
+constexpr size_t kStagingBytes = size_t(32) << 20;
 char *staging_take();
 void staging_give(char *both);
 

@@ -1,4 +1,5 @@
 // Host-side pieces of libgosh that need no device code: error state, schedule helpers.
+#include <algorithm>
 #include <cmath>
 #include <cstdio>
 #include <cstdlib>
@@ -152,18 +153,18 @@ int lock_scratch(int64_t rows, uint32_t **out) {
   HotScratch &h = table[dev];
   const size_t bytes = static_cast<size_t>(rows) * 4;
   if (h.bytes < bytes) {
-    if (h.ptr) (void)hipFree(h.ptr);  // waits for the launches that use it
-    h.ptr = nullptr;
-    h.bytes = 0;
-    const size_t want = bytes + bytes / 4 + 4096;
-    if (device_malloc(&h.ptr, want) != hipSuccess) return fail(GOSH_ENOMEM, "cannot allocate %zu bytes for the row locks", want);
+    // a smaller block is left alone, since another thread may be about to launch with it: every
+    // block is at least twice the one before, so all of them together are no more than the last
+    const size_t want = std::max(bytes + bytes / 4 + 4096, 2 * h.bytes);
+    void *p = nullptr;
+    if (device_malloc(&p, want) != hipSuccess) return fail(GOSH_ENOMEM, "cannot allocate %zu bytes for the row locks", want);
     // ordered before any launch on any stream
-    if (hipMemset(h.ptr, 0, want) != hipSuccess || hipDeviceSynchronize() != hipSuccess) {
+    if (hipMemset(p, 0, want) != hipSuccess || hipDeviceSynchronize() != hipSuccess) {
       (void)hipGetLastError();
-      (void)hipFree(h.ptr);
-      h.ptr = nullptr;
+      (void)hipFree(p);
       return fail(GOSH_EHIP, "cannot clear the row locks");
     }
+    h.ptr = p;
     h.bytes = want;
   }
   *out = static_cast<uint32_t *>(h.ptr);

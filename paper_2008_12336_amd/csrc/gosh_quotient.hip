@@ -13,14 +13,14 @@
 // The first two merge in place and are copied out once the length of every coarse row is
 // known.  The bitmap is made to count a row and made again to write it where it belongs; the
 // number of bits below an entry is the place of its sum.  Rows longer than dense_from(), whose
-// sums would fill the LDS many times over, are written by direct counting instead: a counter
-// per possible neighbour, 2^14 ("strip") at a time, each strip by a workgroup of its own.
+// sums would fill the LDS many times over, are counted instead: a word of a table per possible
+// neighbour, added up by workgroups that each take a slice of the row and 2^14 columns ("strip").
 //
 // Sorted distinct entries with summed multiplicities are unique, so the arrays are those of
 // the sequential algorithm.  Against a radix sort of 64-bit (row, column) keys of all entries
 // and a reduction of equal keys, which this replaced: 128 M entries of a 4 M-vertex R-MAT graph
-// took 8.9 ms and take 4.4, 117 M weighted entries of its second level 10.5 and 4.5; 8 (wide
-// sums: 12) bytes of scratch per entry instead of 32.  A third of it is the gather.
+// took 8.9 ms and take 4.4, 117 M weighted entries of its second level 10.5 and 4.2; 8 (wide
+// sums: 12) bytes of scratch per entry, and the table, instead of 32.  A third of it is the gather.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -48,11 +48,12 @@ constexpr int kSortMax[kSortClasses] = {64, 128, 256, 512, 2048};
 enum : int { kBitmap = kSortClasses, kDense, kWays };
 constexpr int kPieceBits = 18, kPieceWords = 1 << (kPieceBits - 5);
 constexpr int kStripBits = 14, kStripsPerPiece = 1 << (kPieceBits - kStripBits);
+constexpr int64_t kSlice = 1 << 16;  // entries of a counted segment that one workgroup takes
 constexpr int kSumBytes = 30 << 10;  // LDS for the columns and sums of a piece, as many at a time as fit
 
-// Number of segments per way of merging, and 1 + the largest column met.
+// Number of segments per way of merging, 1 + the largest column met, slices of the counted ones.
 struct Classes {
-  unsigned int count[kWays], columns;
+  unsigned int count[kWays], columns, slices;
 };
 
 // Raises *word to the largest `mine` of the workgroup: one atomic, and only if that is above
@@ -74,9 +75,14 @@ __host__ __device__ inline int64_t bitmap_from(int64_t columns) {
   return std::min<int64_t>(kSortMax[kSortClasses - 1], std::max<int64_t>(512, ((columns >> kStripBits) + 1) * 160));
 }
 
-// Longest segment whose sums are placed by rank.  Every kSumBytes of sums read the segment
-// again, in one workgroup; every strip of a counted segment does too, but side by side.
+// Longest segment whose sums are placed by rank.  Every kSumBytes of sums read the segment again,
+// in one workgroup; the counters of a longer one take up to eight words per entry.
 __host__ __device__ inline int64_t dense_from(int64_t columns) { return std::max<int64_t>(1 << 15, columns / 8); }
+
+// A slice of a counted segment: its place in the list, and which of its slices.
+struct Slice {
+  int32_t row, part;
+};
 
 // len[t] = degree of the t-th vertex in cluster order, len[n] = 0.
 template <typename OffT>
@@ -195,6 +201,7 @@ __global__ __launch_bounds__(256) void gather_kernel(const OffT *__restrict__ xa
 __global__ __launch_bounds__(1024) void classify_segments_kernel(const int64_t *__restrict__ segment, int64_t n_coarse,
                                                                  int32_t *__restrict__ list,
                                                                  int64_t *__restrict__ length,
+                                                                 Slice *__restrict__ slices,
                                                                  Classes *__restrict__ classes) {
   __shared__ unsigned int count[kWays], base[kWays];
   const int64_t longest_sorted = bitmap_from(classes->columns), longest_ranked = dense_from(classes->columns);
@@ -217,6 +224,11 @@ __global__ __launch_bounds__(1024) void classify_segments_kernel(const int64_t *
       base[threadIdx.x] = atomicAdd(&classes->count[threadIdx.x], count[threadIdx.x]);
     __syncthreads();
     if (cls >= 0) list[cls * n_coarse + base[cls] + mine] = static_cast<int32_t>(a);
+    if (cls == kDense) {
+      const int32_t parts = static_cast<int32_t>((segment[a + 1] - segment[a] + kSlice - 1) / kSlice);
+      const unsigned int at = atomicAdd(&classes->slices, static_cast<unsigned int>(parts));
+      for (int32_t q = 0; q < parts; ++q) slices[at + q] = Slice{static_cast<int32_t>(base[cls] + mine), q};
+    }
     __syncthreads();
   }
 }
@@ -571,50 +583,80 @@ __global__ __launch_bounds__(1024) void write_pieces_kernel(const int64_t *__res
   }
 }
 
-// Writes the strips of the segments of a list where they belong, by counting (14 M entries of 46
-// segments: 84 us; ranked like the others, where the longest was read again 25 times by one
-// workgroup, they took 4 to 20 ms).
+__global__ __launch_bounds__(256) void clear_table_kernel(uint4 *__restrict__ table, int64_t units) {
+  for (int64_t i = blockIdx.x * 256LL + threadIdx.x; i < units; i += gridDim.x * 256LL) table[i] = uint4{0, 0, 0, 0};
+}
+
+// Counts the entries of the longest segments by column: a workgroup takes a slice of a segment and
+// a strip of columns, counts in LDS and adds what it has to the segment's row of the table.  (With
+// one workgroup per strip of a segment, which read all of it, the second and third level of a
+// graph of 535 M entries, a few segments of tens of millions over two strips, took 60 and 28 ms.)
 template <typename WT, bool WEIGHTED>
-__global__ __launch_bounds__(1024) void write_strips_kernel(const int64_t *__restrict__ segment,
-                                                            const int32_t *__restrict__ list, int64_t count,
-                                                            int64_t strips, const uint32_t *__restrict__ column,
-                                                            const WT *__restrict__ weight,
-                                                            const uint32_t *__restrict__ in_strip,
+__global__ __launch_bounds__(1024) void count_dense_kernel(const int64_t *__restrict__ segment,
+                                                           const int32_t *__restrict__ list,
+                                                           const Slice *__restrict__ slices, int64_t first_strip,
+                                                           int64_t strips,
+                                                           const uint32_t *__restrict__ column,
+                                                           const WT *__restrict__ weight, WT *__restrict__ table) {
+  constexpr int kWidth = 1 << kStripBits;
+  __shared__ WT sums[kWidth];
+  const Slice slice = slices[blockIdx.x];
+  const int64_t strip = first_strip + blockIdx.y;
+  const int32_t a = list[slice.row];
+  const int64_t lo = segment[a] + slice.part * kSlice, hi = std::min(lo + kSlice, segment[a + 1]);
+  const uint32_t base = static_cast<uint32_t>(strip << kStripBits);
+  for (int c = threadIdx.x; c < kWidth; c += 1024) sums[c] = 0;
+  __syncthreads();
+  for_entries(column, lo, hi, [&](int64_t e, uint32_t b) {
+    b -= base;  // columns of other strips, and kInside, are past the counters
+    if (b < static_cast<uint32_t>(kWidth)) atomicAdd(&sums[b], WEIGHTED ? weight[e] : WT(1));
+  });
+  __syncthreads();
+  WT *const row = table + (slice.row * strips + strip) * kWidth;
+  for (int c = threadIdx.x; c < kWidth; c += 1024)
+    if (sums[c] != 0) atomicAdd(row + c, sums[c]);
+}
+
+// The number of columns met in every strip of the counted segments (WRITE = false), or those
+// columns and their sums where they belong.  One workgroup per segment and strip.
+template <typename WT, bool WRITE>
+__global__ __launch_bounds__(1024) void dense_strips_kernel(const int32_t *__restrict__ list, int64_t strips,
+                                                            const WT *__restrict__ table,
+                                                            uint32_t *__restrict__ in_strip,
+                                                            int64_t *__restrict__ length,
                                                             const int64_t *__restrict__ xadj_out,
                                                             int32_t *__restrict__ adj_out,
                                                             int64_t *__restrict__ mult_out) {
   constexpr int kWidth = 1 << kStripBits, kPerWave = kWidth / 16;
-  __shared__ WT sums[kWidth];
   __shared__ uint32_t wave_total[16];
   __shared__ unsigned long long earlier;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  for (int64_t job = blockIdx.x; job < count * strips; job += gridDim.x) {
-    if (in_strip[job] == 0) continue;  // the same for the whole workgroup
-    const int64_t which = job / strips, strip = job % strips;
-    const int32_t a = list[which];
-    const uint32_t base = static_cast<uint32_t>(strip << kStripBits);
-    __syncthreads();  // the previous strip is done with the LDS
-    if (threadIdx.x == 0) earlier = 0;
-    for (int c = threadIdx.x; c < kWidth; c += 1024) sums[c] = 0;
-    __syncthreads();
+  const int64_t job = blockIdx.x, which = job / strips, strip = job % strips;
+  const int32_t a = list[which];
+  const WT *const mine = table + job * kWidth + wave * kPerWave;
+  uint32_t met = 0;
+  for (int c = lane; c < kPerWave; c += 64) met += __popcll(__ballot(mine[c] != 0));
+  if (lane == 0) wave_total[wave] = met;
+  if (threadIdx.x == 0) earlier = 0;
+  __syncthreads();
+  if constexpr (!WRITE) {
+    if (threadIdx.x == 0) {
+      uint32_t total = 0;
+      for (int q = 0; q < 16; ++q) total += wave_total[q];
+      in_strip[job] = total;
+      if (total) atomicAdd(reinterpret_cast<unsigned long long *>(length + a), static_cast<unsigned long long>(total));
+    }
+  } else {
     add_strips(in_strip + which * strips, strip, &earlier);
-    for_entries(column, segment[a], segment[a + 1], [&](int64_t e, uint32_t b) {
-      b -= base;  // columns of other strips, and kInside, are past the counters
-      if (b < static_cast<uint32_t>(kWidth)) atomicAdd(&sums[b], WEIGHTED ? weight[e] : WT(1));
-    });
-    __syncthreads();
-    uint32_t mine = 0;
-    for (int c = lane; c < kPerWave; c += 64) mine += __popcll(__ballot(sums[wave * kPerWave + c] != 0));
-    if (lane == 0) wave_total[wave] = mine;
     __syncthreads();
     int64_t out = xadj_out[a] + static_cast<int64_t>(earlier);
     for (int q = 0; q < wave; ++q) out += wave_total[q];
     for (int c = lane; c < kPerWave; c += 64) {
-      const WT sum = sums[wave * kPerWave + c];
+      const WT sum = mine[c];
       const unsigned long long set = __ballot(sum != 0);
       if (sum != 0) {
         const int64_t at = out + __popcll(set & ((1ull << lane) - 1));
-        adj_out[at] = static_cast<int32_t>(base + wave * kPerWave + c);
+        adj_out[at] = static_cast<int32_t>((strip << kStripBits) + wave * kPerWave + c);
         mult_out[at] = static_cast<int64_t>(sum);
       }
       out += __popcll(set);
@@ -663,6 +705,8 @@ int quotient(gosh::DeviceCoarsener *dc, const gosh::DeviceLevel &fine, int64_t n
   if (int rc = buf.alloc(&length, static_cast<size_t>(n_coarse) + 1, "coarse row lengths")) return rc;
   if (int rc = buf.alloc(&list, static_cast<size_t>(n_coarse) * kWays, "lists of coarse rows")) return rc;
   if (int rc = buf.alloc(&classes, 1, "counters")) return rc;
+  Slice *slices = nullptr;  // of segments longer than 2^15 entries, at most 1 + S / kSlice each
+  if (int rc = buf.alloc(&slices, static_cast<size_t>(nnz / (1 << 14)) + 1, "slices")) return rc;
   hipLaunchKernelGGL(clear_classes_kernel, dim3(1), dim3(1), 0, nullptr, classes);
   const int flat_blocks = blocks_for(n + 1, 256);
 
@@ -706,7 +750,7 @@ int quotient(gosh::DeviceCoarsener *dc, const gosh::DeviceLevel &fine, int64_t n
       buf.release(p);  // what takes them up again is on the same stream
   }
   hipLaunchKernelGGL(classify_segments_kernel, dim3(blocks_for(n_coarse, 1024)), dim3(1024), 0, nullptr, segment,
-                     n_coarse, list, length, classes);
+                     n_coarse, list, length, slices, classes);
   if (int rc = gosh::check_launch("classify_segments_kernel")) return rc;
   Classes c{};
   GOSH_TRY_HIP(hipMemcpy(&c, classes, sizeof(c), hipMemcpyDeviceToHost), "read segment classes");
@@ -715,16 +759,30 @@ int quotient(gosh::DeviceCoarsener *dc, const gosh::DeviceLevel &fine, int64_t n
   const int32_t *bitmap_list = list + kBitmap * n_coarse, *dense_list = list + kDense * n_coarse;
   const int64_t bitmaps = c.count[kBitmap], denses = c.count[kDense];
   const int64_t pieces = pieces_of(c.columns), strips = pieces * kStripsPerPiece;
-  uint32_t *in_strip[2] = {nullptr, nullptr};
-  auto count_pieces = [&](const int32_t *which, int64_t count, uint32_t **strips_of) -> int {
-    if (count == 0) return GOSH_OK;
-    if (int rc = buf.alloc(strips_of, static_cast<size_t>(count * strips), "strips of coarse rows")) return rc;
-    hipLaunchKernelGGL(count_pieces_kernel, dim3(blocks_for(count * pieces, 1)), dim3(512), 0, nullptr, segment, which,
-                       count, pieces, static_cast<int64_t>(c.columns), column, *strips_of, length);
-    return GOSH_OK;
-  };
-  if (int rc = count_pieces(dense_list, denses, &in_strip[1])) return rc;
-  if (int rc = count_pieces(bitmap_list, bitmaps, &in_strip[0])) return rc;
+  uint32_t *in_strip = nullptr, *in_dense_strip = nullptr;
+  WT *table = nullptr;
+  const int64_t dense_strips = (static_cast<int64_t>(c.columns) + (1 << kStripBits) - 1) >> kStripBits;
+  const int64_t dense_jobs = denses * dense_strips;
+  if (denses > 0) {
+    const int64_t counters = dense_jobs << kStripBits;
+    if (int rc = buf.alloc(&table, static_cast<size_t>(counters), "counters of coarse rows")) return rc;
+    if (int rc = buf.alloc(&in_dense_strip, static_cast<size_t>(dense_jobs), "strips of coarse rows")) return rc;
+    const int64_t units = counters * static_cast<int64_t>(sizeof(WT)) / 16;
+    hipLaunchKernelGGL(clear_table_kernel, dim3(blocks_for(units, 256)), dim3(256), 0, nullptr,
+                       reinterpret_cast<uint4 *>(table), units);
+    // at most 2^17 strips: columns are below 2^31
+    for (int64_t first = 0; first < dense_strips; first += 65535)
+      hipLaunchKernelGGL((count_dense_kernel<WT, WEIGHTED>),
+                         dim3(c.slices, static_cast<unsigned>(std::min<int64_t>(dense_strips - first, 65535))), dim3(1024), 0,
+                         nullptr, segment, dense_list, slices, first, dense_strips, column, weight, table);
+    hipLaunchKernelGGL((dense_strips_kernel<WT, false>), dim3(static_cast<unsigned>(dense_jobs)), dim3(1024), 0, nullptr,
+                       dense_list, dense_strips, table, in_dense_strip, length, xadj_out, nullptr, nullptr);
+  }
+  if (bitmaps > 0) {
+    if (int rc = buf.alloc(&in_strip, static_cast<size_t>(bitmaps * strips), "strips of coarse rows")) return rc;
+    hipLaunchKernelGGL(count_pieces_kernel, dim3(blocks_for(bitmaps * pieces, 1)), dim3(512), 0, nullptr, segment,
+                       bitmap_list, bitmaps, pieces, static_cast<int64_t>(c.columns), column, in_strip, length);
+  }
   auto merge_sorted = [&](auto kernel, int cls, int teams) {
     if (c.count[cls] > 0)
       hipLaunchKernelGGL(kernel, dim3(blocks_for(c.count[cls], teams)), dim3(256), 0, nullptr, segment,
@@ -753,13 +811,12 @@ int quotient(gosh::DeviceCoarsener *dc, const gosh::DeviceLevel &fine, int64_t n
   if (int rc = persistent(&coarse.adj, static_cast<size_t>(coarse.nnz), "coarse adjacency")) return rc;
   if (int rc = persistent(&coarse.mult, static_cast<size_t>(coarse.nnz), "coarse multiplicities")) return rc;
   if (denses > 0)
-    hipLaunchKernelGGL((write_strips_kernel<WT, WEIGHTED>), dim3(blocks_for(denses * strips, 1)), dim3(1024), 0, nullptr,
-                       segment, dense_list, denses, strips, column, weight, in_strip[1], xadj_out,
-                       coarse.adj, coarse.mult);
+    hipLaunchKernelGGL((dense_strips_kernel<WT, true>), dim3(static_cast<unsigned>(dense_jobs)), dim3(1024), 0, nullptr,
+                       dense_list, dense_strips, table, in_dense_strip, length, xadj_out, coarse.adj, coarse.mult);
   if (bitmaps > 0)
     hipLaunchKernelGGL((write_pieces_kernel<WT, WEIGHTED>), dim3(blocks_for(bitmaps * pieces, 1)), dim3(1024), 0,
                        nullptr, segment, bitmap_list, bitmaps, pieces,
-                       static_cast<int64_t>(c.columns), column, weight, in_strip[0], xadj_out, coarse.adj, coarse.mult);
+                       static_cast<int64_t>(c.columns), column, weight, in_strip, xadj_out, coarse.adj, coarse.mult);
   for (int cls = kSortClasses - 1; cls >= 0; --cls)
     if (c.count[cls] > 0)
       hipLaunchKernelGGL(copy_merged_kernel<WT>, dim3(blocks_for(c.count[cls], 4)), dim3(256), 0, nullptr, segment,
