@@ -86,8 +86,14 @@ int check_scratch(CheckResult **out);
 // kept until the process ends.  Calls on one device must not overlap on different
 // streams.
 int hot_scratch(size_t bytes, void **out);
-// Per-device lock words of the training kernels, one per vertex, zero between launches; grown on
-// demand and kept until the process ends.
-int lock_scratch(int64_t rows, uint32_t **out);
+// Per-device words of the training kernels, per row: a lock, zero between launches, and two counts
+// of draws that launches use in turns.  The launch counts in `draws`, which are zero, and clears
+// the first `stale_rows` of `stale`, which the launch before may still be reading until then.
+// Grown on demand and kept until the process ends.
+struct LockWords {
+  uint32_t *locks, *draws, *stale;
+  int64_t stale_rows;
+};
+int lock_scratch(int64_t rows, LockWords *out);
 
 }  // namespace gosh

@@ -189,14 +189,18 @@ struct RowAgentLine : RowAgent32 {
 // the row is read, changed and written back like a cold one (5.3 G rows of 512 bytes per second,
 // read included, against 2.55 G as adds alone).  In kHotLocked mode every row is written that
 // way, except hubs, whose holders would queue up: their rows take atomic adds, always, so that a
-// row is only ever written one way in a launch.
+// row is only ever written one way in a launch (but see kMaxTries).
 enum HotMode : int32_t { kHotNone = 0, kHotBitmap = 1, kHotAll = 2, kHotLocked = 3 };
 
 struct HotSet {
-  const uint32_t *bits;  // one bit per vertex when mode is kHotBitmap (hot) or kHotLocked (hub); in
-                         // the other modes still a readable device word (the kernel reads word 0 blindly)
+  const uint32_t *bits;  // one bit per vertex when mode is kHotBitmap (hot); in the other modes still
+                         // a readable device word (the kernel reads word 0 blindly)
   int32_t mode;
-  uint32_t *locks;  // one word per vertex when mode == kHotLocked: 0 before and after a launch
+  // in kHotLocked mode, a word each per row: a lock, 0 before and after a launch, and how often the
+  // row is drawn (see most_draws); a hub is a row of which that is above `most`
+  uint32_t *locks;
+  const uint32_t *draws;
+  uint32_t most;
 };
 
 // Whether a launch in which every row is hot takes locks.  An update of a row that spans three
@@ -209,10 +213,47 @@ inline bool worth_locking(int64_t updates, int32_t d) {
   const int64_t blocks = (d + 15) / 16;
   return blocks >= 3 && updates * blocks >= 1000000;
 }
-// A vertex is a hub if more than 1 / kHubShare of a source in flight is expected to hold it as its
-// positive sample.  1, 2 and 4 are within 4 % of each other on power-law graphs; at 16 every row of
-// a graph of mean degree 200 is one (67,000 vertices: 140 us instead of 92).
-constexpr int64_t kHubShare = 2;
+// Hubs.  Whoever holds a row keeps the others waiting for about as long as a source takes for one
+// sample, so rows that are drawn too often as positive samples hold up the whole launch.  How
+// often a row is drawn is counted, draw by draw, before the launch: a degree does not tell (many
+// edges may lead to a vertex that has few of its own, and a vertex whose neighbours have no others
+// is drawn by each of them; with a degree rule a graph of 67,000 vertices, a fifth of whose edges
+// lead to twenty without out-edges, took 29 ms per epoch, 0.15 as adds and 0.15 like this).  A row
+// is a hub if its draws would keep it locked for more than 1 / kHubShare of the launch, C sources
+// at a time, each with `per_source` row updates in a row:
+//   draws > max(2, sources * per_source / (kHubShare * C))
+// or if more than kMostAtOnce of 64 consecutive sources draw it, which start at the same time.
+// Shares of 2 / 8 / 16 on 200,000 x 128, us: stars of ten leaves in a row 504 / 374 / 375, R-MAT
+// 231 / 228 / 226, power law 230 / 226 / 226; at 67,000 with a bound of 1 instead of 2 every fourth
+// row is a hub.  Counting takes 6 us of 95 at 67,000 x 128.
+constexpr int64_t kHubShare = 8;
+constexpr uint32_t kMostAtOnce = 2;
+constexpr uint32_t kDrawnAtOnce = 0x80000000u;  // flag in a word of draws
+
+inline uint32_t most_draws(int64_t sources, int64_t per_source, int64_t in_flight) {
+  const int64_t most = sources * per_source / (kHubShare * std::max<int64_t>(in_flight, 1));
+  return static_cast<uint32_t>(std::min<int64_t>(std::max<int64_t>(most, 2), 0x7FFFFFFF));
+}
+
+// One draw per lane (at = -1: none) added to the words of `draws`; all lanes of the wavefront are
+// present.  Equal draws of a wavefront are one atomic, since thousands of atomics on one word take
+// some 6 ns each one after another; only the first few rows met are gathered like that, which
+// is enough to meet one that many lanes draw.
+__device__ __forceinline__ void count_draws(int32_t at, uint32_t *draws) {
+  constexpr int kGathered = 8;
+  const int lane = threadIdx.x & 63;
+  unsigned long long todo = __ballot(at >= 0);
+  uint32_t mine = at >= 0 ? 1 : 0;  // draws that this lane adds
+#pragma unroll 1
+  for (int i = 0; i < kGathered && todo != 0; ++i) {
+    const int leader = __builtin_amdgcn_readfirstlane(__builtin_ctzll(todo));
+    const unsigned long long same = __ballot(at == __builtin_amdgcn_readlane(at, leader));
+    if ((same >> lane) & 1) mine = lane == leader ? static_cast<uint32_t>(__popcll(same)) : 0;
+    todo &= ~same;
+  }
+  if (mine > kMostAtOnce) atomicOr(draws + at, kDrawnAtOnce);
+  else if (mine != 0) atomicAdd(draws + at, mine);
+}
 
 struct SgdArgs {
   HotSet hot;
@@ -299,6 +340,8 @@ struct ChunkPos {
 //                                             vertex id of sample t from its draw r (-1 = none,
 //                                             or !want)
 //     float  *sample_row(int64_t i, int32_t v)
+//     int32_t source_slot(int64_t i), sample_slot(int64_t i, int32_t v)
+//                                             place of a row among the words of HotSet
 //     bool    rows_at_lines()                 (host) every row starts at a line border, or near enough
 //     Both stages must be free of branches around their memory reads (read a safe address
 //     when !want).
@@ -360,7 +403,7 @@ __device__ __forceinline__ void sgd_walk(const W &w, const SgdArgs &a) {
   const int64_t first = first_of_wave + (SEQ ? 0 : lane / LPG);
   const int32_t d = a.d;
   const int32_t per_round = a.k_neg + 1;
-  const bool use_bitmap = LOCKED || a.hot.mode == kHotBitmap;
+  const bool use_bitmap = !LOCKED && a.hot.mode == kHotBitmap;
   const bool all_hot = a.hot.mode == kHotAll;
   const uint32_t *const bits = a.hot.bits;  // always a readable word, also without a bitmap
 
@@ -414,7 +457,7 @@ __device__ __forceinline__ void sgd_walk(const W &w, const SgdArgs &a) {
     return w.stage1(live ? pos.idx : 0, live);
   };
 
-  // The lock this group holds (vertex id, -1 none); its release, behind everything issued so far.
+  // The lock this group holds (slot, -1 none); its release, behind everything issued so far.
   int32_t held_lock = -1;
   auto release = [&]() {
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
@@ -422,11 +465,11 @@ __device__ __forceinline__ void sgd_walk(const W &w, const SgdArgs &a) {
       __hip_atomic_store(a.hot.locks + held_lock, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     held_lock = -1;
   };
-  // One try at the lock of vertex id; true in the whole group if it was free.
-  auto try_lock = [&](bool want, int32_t id) -> bool {
+  // One try at a lock; true in the whole group if it was free.
+  auto try_lock = [&](bool want, int32_t slot) -> bool {
     bool mine = false;
     if (want && gl == 0)
-      mine = __hip_atomic_exchange(a.hot.locks + id, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0u;
+      mine = __hip_atomic_exchange(a.hot.locks + slot, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0u;
     release();
     return ((__ballot(mine) >> (lane & ~(LPG - 1))) & 1u) != 0;
   };
@@ -454,7 +497,8 @@ __device__ __forceinline__ void sgd_walk(const W &w, const SgdArgs &a) {
     U s[UPL], s_before[UPL];
 #pragma unroll
     for (int i = 0; i < UPL; ++i) s[i] = P::load(src_row + readable(column(src_row, i)));
-    const uint32_t src_word = bits[use_bitmap ? (src >> 5) : 0];
+    const int32_t src_slot = LOCKED ? w.source_slot(idx) : 0;
+    const uint32_t src_word = LOCKED ? a.hot.draws[src_slot] : bits[use_bitmap ? (src >> 5) : 0];
     bool fresh = true;
 
     ChunkPos cur{idx_raw, 0, 0};
@@ -470,7 +514,7 @@ __device__ __forceinline__ void sgd_walk(const W &w, const SgdArgs &a) {
 
       // Request every row of the chunk (a missing sample reads the source row instead).
       U r[LOCKED ? 1 : kChunk][UPL];
-      uint32_t word[kChunk];
+      uint32_t word[kChunk];  // of the bitmap, or of the draws
       bool valid[kChunk];
 #pragma unroll
       for (int q = 0; q < kChunk; ++q) {
@@ -480,7 +524,8 @@ __device__ __forceinline__ void sgd_walk(const W &w, const SgdArgs &a) {
 #pragma unroll
           for (int i = 0; i < UPL; ++i) r[q][i] = P::load(row + readable(column(row, i)));
         }
-        word[q] = bits[(use_bitmap && valid[q]) ? (v[q] >> 5) : 0];
+        if constexpr (LOCKED) word[q] = a.hot.draws[valid[q] ? w.sample_slot(idx, v[q]) : 0];
+        else word[q] = bits[(use_bitmap && valid[q]) ? (v[q] >> 5) : 0];
       }
       // While they are in flight: the ids of the next chunk (its offsets arrived a chunk
       // ago) and the offsets of the chunk after it.
@@ -517,11 +562,12 @@ __device__ __forceinline__ void sgd_walk(const W &w, const SgdArgs &a) {
               at = q;
               id = v[q];
               positive = is_pos[q];
-              hub = (word[q] >> (v[q] & 31)) & 1u;
+              hub = word[q] > a.hot.most;
             }
           const bool want = id >= 0;
+          const int32_t slot = want ? w.sample_slot(idx, id) : 0;
           if (__ballot(want) == 0) break;  // the same for the whole wavefront
-          const bool locked = try_lock(want && !hub, id);
+          const bool locked = try_lock(want && !hub, slot);
           const bool add = want && (hub || (!locked && tries >= kMaxTries));
           const bool apply = locked || add;
           float *const row = apply ? w.sample_row(idx, id) : src_row;
@@ -570,7 +616,7 @@ __device__ __forceinline__ void sgd_walk(const W &w, const SgdArgs &a) {
               for (int c = 0; c < F; ++c)
                 if (column(row, i) < d) atomic_step(row + column(row, i) + c, g * s[i].v[c]);
           }
-          held_lock = locked ? id : -1;
+          held_lock = locked ? slot : -1;
           next = apply ? at + 1 : next;
         }
         continue;
@@ -654,11 +700,11 @@ __device__ __forceinline__ void sgd_walk(const W &w, const SgdArgs &a) {
     }
     if constexpr (LOCKED) {
       // the source's change, added to its row as it is now
-      const bool hub = live && ((src_word >> (src & 31)) & 1u);
+      const bool hub = live && src_word > a.hot.most;
       bool locked = false;
       for (int32_t tries = 0; tries < kMaxTries; ++tries) {
         if (__ballot(live && !hub && !locked) == 0) break;  // the same for the whole wavefront
-        if (try_lock(live && !hub && !locked, src)) {
+        if (try_lock(live && !hub && !locked, src_slot)) {
           locked = true;
           U now[UPL];
 #pragma unroll
@@ -671,7 +717,7 @@ __device__ __forceinline__ void sgd_walk(const W &w, const SgdArgs &a) {
             for (int c = 0; c < F; ++c) now[i].v[c] += s[i].v[c] - s_before[i].v[c];
             if (column(src_row, i) < d) P::store(src_row + column(src_row, i), now[i]);
           }
-          held_lock = src;
+          held_lock = src_slot;
         }
       }
       const bool add = live && !locked;

@@ -1,6 +1,7 @@
 // Host-side pieces of libgosh that need no device code: error state, schedule helpers.
 #include <algorithm>
 #include <cmath>
+#include <cstdint>
 #include <cstdio>
 #include <cstdlib>
 #include <mutex>
@@ -144,30 +145,38 @@ int hot_scratch(size_t bytes, void **out) {
   return GOSH_OK;
 }
 
-int lock_scratch(int64_t rows, uint32_t **out) {
-  static HotScratch table[kMaxDevices];
+int lock_scratch(int64_t rows, LockWords *out) {
+  struct Words {
+    uint32_t *base = nullptr;
+    int64_t rows = 0;         // locks, then two times draws, that many each
+    int64_t counted[2] = {};  // rows whose draws were counted since they were cleared
+    int turn = 0;
+  };
+  static Words table[kMaxDevices];
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices)
     return fail(GOSH_EHIP, "cannot identify the current device");
   std::lock_guard<std::mutex> lock(g_hot_scratch_mutex);
-  HotScratch &h = table[dev];
-  const size_t bytes = static_cast<size_t>(rows) * 4;
-  if (h.bytes < bytes) {
+  Words &w = table[dev];
+  if (w.rows < rows) {
     // a smaller block is left alone, since another thread may be about to launch with it: every
     // block is at least twice the one before, so all of them together are no more than the last
-    const size_t want = std::max(bytes + bytes / 4 + 4096, 2 * h.bytes);
+    const int64_t want = std::max(rows + rows / 4 + 1024, 2 * w.rows);
+    const size_t bytes = static_cast<size_t>(want) * 12;
     void *p = nullptr;
-    if (device_malloc(&p, want) != hipSuccess) return fail(GOSH_ENOMEM, "cannot allocate %zu bytes for the row locks", want);
+    if (device_malloc(&p, bytes) != hipSuccess) return fail(GOSH_ENOMEM, "cannot allocate %zu bytes for the row locks", bytes);
     // ordered before any launch on any stream
-    if (hipMemset(p, 0, want) != hipSuccess || hipDeviceSynchronize() != hipSuccess) {
+    if (hipMemset(p, 0, bytes) != hipSuccess || hipDeviceSynchronize() != hipSuccess) {
       (void)hipGetLastError();
       (void)hipFree(p);
       return fail(GOSH_EHIP, "cannot clear the row locks");
     }
-    h.ptr = p;
-    h.bytes = want;
+    w = Words{static_cast<uint32_t *>(p), want, {0, 0}, 0};
   }
-  *out = static_cast<uint32_t *>(h.ptr);
+  w.turn ^= 1;
+  *out = LockWords{w.base, w.base + w.rows * (1 + w.turn), w.base + w.rows * (2 - w.turn), w.counted[w.turn ^ 1]};
+  w.counted[w.turn] = rows;
+  w.counted[w.turn ^ 1] = 0;
   return GOSH_OK;
 }
 

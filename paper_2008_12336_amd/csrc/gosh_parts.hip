@@ -46,6 +46,7 @@ struct PairWork {
   const int32_t *pool_a;         // a_n * B positives for the sources of a
   const int32_t *pool_b;         // b_n * B positives for the sources of b (unused if a == b)
   int32_t B, per_round, d, diagonal;
+  int32_t b_slot;  // the slots of part b begin here, those of part a at 0 (one part: both)
   uint32_t key0, key1, rotation, word3;
 
   bool rows_at_lines() const { return gosh::rows_at_lines(a_rows, d) && gosh::rows_at_lines(b_rows, d); }
@@ -85,6 +86,12 @@ struct PairWork {
   __device__ __forceinline__ float *sample_row(int64_t i, int32_t v) const {
     return i >= a_n ? a_rows + static_cast<int64_t>(v - a_lo) * d
                     : b_rows + static_cast<int64_t>(v - b_lo) * d;
+  }
+  __device__ __forceinline__ int32_t source_slot(int64_t i) const {
+    return static_cast<int32_t>(i < a_n ? i : b_slot + (i - a_n));
+  }
+  __device__ __forceinline__ int32_t sample_slot(int64_t i, int32_t v) const {
+    return i >= a_n ? v - a_lo : b_slot + (v - b_lo);
   }
 };
 
@@ -167,6 +174,25 @@ __global__ __launch_bounds__(256) void degree_bitmap_kernel(const OffT *__restri
   }
 }
 
+// Counts the positives that the sources of a visit draw in their first round by the row they name
+// (see gosh::most_draws; the other rounds draw from the same distribution), and clears the counts
+// of the visit before.
+__global__ __launch_bounds__(256) void count_pool_kernel(PairWork w, uint32_t *__restrict__ draws,
+                                                         uint32_t *__restrict__ stale, int64_t stale_rows) {
+  const int64_t count = w.count();
+  for (int64_t i = blockIdx.x * 256LL + threadIdx.x; i < stale_rows; i += gridDim.x * 256LL) stale[i] = 0;
+  for (int64_t first = blockIdx.x * 256LL; first < count; first += gridDim.x * 256LL) {
+    const int64_t i = first + threadIdx.x;
+    int32_t at = -1;
+    if (i < count) {
+      const int32_t src = w.source_id(i);
+      const int32_t v = w.stage2(i, src, 0, true, true, w.stage1(i, true), 0);
+      if (v >= 0 && v != src) at = w.sample_slot(i, v);
+    }
+    gosh::count_draws(at, draws);
+  }
+}
+
 struct HostCsr {
   const gosh_csr *g;
   int64_t begin(int64_t v) const {
@@ -232,6 +258,11 @@ uint64_t device_bytes_for(int64_t n, int32_t K, int32_t d, int32_t P, int32_t S,
   return static_cast<uint64_t>(P) * ps * d * 4 + static_cast<uint64_t>(S) * 2 * ps * B * 4 +
          static_cast<uint64_t>((n + 63) / 64) * 8;
 }
+
+// Row locks and counts of draws of a rotation, on top of device_bytes_for: a lock and two counts for
+// every row of a visit.
+int64_t visit_rows(int64_t n, int32_t K) { return (n + K - 1) / K * std::min(K, 2); }
+uint64_t lock_bytes(int64_t n, int32_t K) { return static_cast<uint64_t>(visit_rows(n, K)) * 12; }
 
 int check_parts_args(const gosh_csr *g, const float *M, int32_t d, int32_t k_neg, int32_t P,
                      int32_t S, int32_t B, uint32_t flags) {
@@ -461,7 +492,8 @@ class Rotation {
   std::vector<int32_t *> dpool, staging;
   std::vector<int32_t> slot_part;
   uint32_t *hot_bits_dev = nullptr;
-  uint32_t *locks = nullptr;
+  uint32_t *locks = nullptr;     // a lock per row of a visit, then two times its draws, in turns
+  int64_t lock_in_flight = 0;    // sources in flight that the hub rule counts with
   gosh::HotSet hot{nullptr, gosh::kHotNone, nullptr};
   gosh::CheckResult *check = nullptr;  // divergence check, accumulated on the outbound stream
   hipStream_t compute = nullptr, copy = nullptr, copy_out = nullptr;
@@ -503,16 +535,16 @@ class Rotation {
       if (pl.flags & GOSH_FLAG_PLAIN_STORES) mode = gosh::kHotNone;
       if (pl.flags & GOSH_FLAG_ATOMIC_ADDS) mode = gosh::kHotAll;
       if (mode == gosh::kHotLocked) {
-        GOSH_TRY_HIP(gosh::device_malloc(&locks, static_cast<size_t>(n) * 4), "hipMalloc row locks");
-        GOSH_TRY_HIP(hipMemsetAsync(locks, 0, static_cast<size_t>(n) * 4, compute), "clear row locks");
+        GOSH_TRY_HIP(gosh::device_malloc(&locks, lock_bytes(n, pl.K)), "hipMalloc row locks");
+        GOSH_TRY_HIP(hipMemsetAsync(locks, 0, lock_bytes(n, pl.K), compute), "clear row locks");
         hot.locks = locks;
+        lock_in_flight = in_flight;
       }
-      if (mode == gosh::kHotBitmap || mode == gosh::kHotLocked) {
-        const int64_t share = mode == gosh::kHotLocked ? gosh::kHubShare : tune.hot_inv_eps * pl.B;
-        const int64_t min_degree =
-            tune.hot_min_degree > 0 ? tune.hot_min_degree : pl.g->nnz / (share * in_flight) + 1;
+      if (mode == gosh::kHotBitmap) {
         const int64_t words = (n + 63) / 64;
         GOSH_TRY_HIP(gosh::device_malloc(&hot_bits_dev, static_cast<size_t>(words) * 8), "hipMalloc hot bitmap");
+        const int64_t min_degree =
+            tune.hot_min_degree > 0 ? tune.hot_min_degree : pl.g->nnz / (tune.hot_inv_eps * pl.B * in_flight) + 1;
         if (graph_on_device) {
           const int blocks = static_cast<int>(std::min<int64_t>((words + 255) / 256, 65536));
           if (pl.g->xadj_is64)
@@ -749,6 +781,7 @@ class Rotation {
     w.pool_a = dpool[ps];
     w.pool_b = dpool[ps] + static_cast<size_t>(L.part_rows) * pl.B;
     w.B = pl.B; w.per_round = per_round; w.d = pl.d; w.diagonal = v.a == v.b;
+    w.b_slot = w.diagonal ? 0 : static_cast<int32_t>(L.part_rows);
     w.key0 = key0; w.key1 = key1; w.rotation = v.rot; w.word3 = level_word(pl.level, v.q);
     gosh::SgdArgs args{};
     args.hot = hot;
@@ -763,6 +796,15 @@ class Rotation {
       GOSH_TRY_HIP(hipEventElapsedTime(&ms, k_begin[timer], k_end[timer]), "hipEventElapsedTime");
       st.kernel_ms += ms;
       k_pending[timer] = 0;
+    }
+    if (hot.mode == gosh::kHotLocked) {
+      const int64_t rows = visit_rows(pl.g->n, pl.K);
+      uint32_t *const draws = locks + rows * (1 + vi % 2);
+      const int blocks = static_cast<int>(std::min<int64_t>((rows + 255) / 256, 65536));
+      hipLaunchKernelGGL(count_pool_kernel, dim3(blocks), dim3(256), 0, compute, w, draws, locks + rows * (2 - vi % 2), rows);
+      if (int rc = gosh::check_launch("count_pool_kernel")) return rc;
+      args.hot.draws = draws;
+      args.hot.most = gosh::most_draws(w.count(), per_round, lock_in_flight);
     }
     GOSH_TRY_HIP(hipEventRecord(k_begin[timer], compute), "hipEventRecord");
     gosh::SgdLauncher<PairWork>::launch(w, args, w.count(), seq, tune.plain_rows != 0 || !concurrent_paths,
@@ -938,7 +980,7 @@ int gosh_train_parts(const gosh_csr *g_host, float *M_host, int32_t d, int32_t k
   const auto wall0 = std::chrono::steady_clock::now();
   const RotationPlan plan{g_host, M_host, matrix_on_device, d,     k_neg, B, lr0, seed, level, flags, K,
                           matrix_on_device ? K : std::min(P_gpu, K), S_gpu, std::min(P_gpu, K), rotations,
-                          device_budget_bytes == 0 || planned_bytes + static_cast<uint64_t>(n) * 4 <= device_budget_bytes};
+                          device_budget_bytes == 0 || planned_bytes + lock_bytes(n, K) <= device_budget_bytes};
   gosh_parts_stats st{};
   int rc = GOSH_OK;
   {
@@ -947,7 +989,7 @@ int gosh_train_parts(const gosh_csr *g_host, float *M_host, int32_t d, int32_t k
     if (rc == GOSH_OK) rc = rotation.run();
     rotation.finish();
     st = rotation.st;
-    if (rotation.locked_rows()) planned_bytes += static_cast<uint64_t>(n) * 4;
+    if (rotation.locked_rows()) planned_bytes += lock_bytes(n, K);
   }
   st.device_bytes = planned_bytes;
   st.wall_ms = std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - wall0).count();

@@ -108,6 +108,8 @@ struct EpochWork {
   __device__ __forceinline__ float *sample_row(int64_t, int32_t v) const {
     return M + static_cast<int64_t>(v) * d;
   }
+  __device__ __forceinline__ int32_t source_slot(int64_t i) const { return static_cast<int32_t>(i); }
+  __device__ __forceinline__ int32_t sample_slot(int64_t, int32_t v) const { return v; }
 };
 
 template <typename OffT>
@@ -125,6 +127,19 @@ __global__ __launch_bounds__(256) void mark_hot_kernel(const OffT *__restrict__ 
     if (v < n) hot = static_cast<int64_t>(xadj[v + 1]) - static_cast<int64_t>(xadj[v]) >= min_degree;
     const unsigned long long mask = __ballot(hot);
     if (lane == 0) bits[w] = mask;
+  }
+}
+
+// Counts the positive samples of an epoch by the row they name (see most_draws), and clears the
+// counts of the launch before.  Bound by the chain of reads of a draw: 6 us for 67,000 vertices.
+template <typename OffT>
+__global__ __launch_bounds__(256) void count_positives_kernel(SamplerArgs a, uint32_t *__restrict__ draws,
+                                                              uint32_t *__restrict__ stale, int64_t stale_rows) {
+  for (int64_t i = blockIdx.x * 256LL + threadIdx.x; i < stale_rows; i += gridDim.x * 256LL) stale[i] = 0;
+  for (int64_t first = blockIdx.x * 256LL; first < a.n; first += gridDim.x * 256LL) {
+    const int64_t src = first + threadIdx.x;
+    const int32_t v = src < a.n ? draw_sample<OffT>(a, static_cast<uint32_t>(src), 0) : -1;
+    gosh::count_draws(v == src ? -1 : v, draws);
   }
 }
 
@@ -460,11 +475,19 @@ int launch_epoch(const gosh_csr *g, float *M, int32_t d, int32_t k_neg, float lr
     }
     if (flags & GOSH_FLAG_PLAIN_STORES) mode = gosh::kHotNone;
     if (flags & GOSH_FLAG_ATOMIC_ADDS) mode = gosh::kHotAll;
-    if (mode == gosh::kHotLocked)
-      if (int rc = gosh::lock_scratch(n, &a.hot.locks)) return rc;
-    if (mode == gosh::kHotBitmap || mode == gosh::kHotLocked) {
-      const int64_t share = mode == gosh::kHotLocked ? gosh::kHubShare : tune.hot_inv_eps;
-      const int64_t min_degree = tune.hot_min_degree > 0 ? tune.hot_min_degree : g->nnz / (share * in_flight) + 1;
+    if (mode == gosh::kHotLocked) {
+      gosh::LockWords words{};
+      if (int rc = gosh::lock_scratch(n, &words)) return rc;
+      hipLaunchKernelGGL(count_positives_kernel<OffT>, dim3(grid_for(n, 256, 1 << 16)), dim3(256), 0, st, w.s,
+                         words.draws, words.stale, words.stale_rows);
+      if (int rc = gosh::check_launch("count_positives_kernel")) return rc;
+      a.hot.locks = words.locks;
+      a.hot.draws = words.draws;
+      a.hot.most = gosh::most_draws(n, k_neg + 2, in_flight);
+    }
+    if (mode == gosh::kHotBitmap) {
+      const int64_t min_degree =
+          tune.hot_min_degree > 0 ? tune.hot_min_degree : g->nnz / (tune.hot_inv_eps * in_flight) + 1;
       void *bits = bits_override;
       if (bits == nullptr)
         if (int rc = gosh::hot_scratch(static_cast<size_t>((n + 63) / 64) * 8, &bits)) return rc;
@@ -478,7 +501,8 @@ int launch_epoch(const gosh_csr *g, float *M, int32_t d, int32_t k_neg, float lr
     a.hot.mode = mode;
   }
   if (a.hot.bits == nullptr) {
-    // the kernel reads word 0 of the bitmap unconditionally
+    // the kernel reads word 0 of the bitmap unconditionally (one with locks does not, but a call under
+    // capture after it will, and cannot allocate)
     void *bits = bits_override;
     if (bits == nullptr)
       if (int rc = gosh::hot_scratch(8, &bits)) return rc;

@@ -1,0 +1,99 @@
+"""Row locks where many sources want one row: vertices that are drawn far more often than their
+own degree says, because edges lead to them and none (or few) lead away.  Such rows take atomic
+adds; under a lock their holders would queue up."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2008_12336_amd as G
+from oracle import gosh_oracle as O
+from tests.test_gpu_layout import DEV, SEQ_LAYOUT, TOL, say, start_matrix, upload
+from tests.util import rel_err
+
+pytestmark = pytest.mark.gpu
+
+
+def sink_graph(n, sinks, per_vertex, seed):
+    """Directed: every vertex but the `sinks` first ones has one edge to a sink and per_vertex - 1
+    to anywhere; the sinks have none."""
+    rng = np.random.default_rng(seed)
+    rows = np.sort(np.concatenate((rng.integers(0, sinks, (n - sinks, 1)),
+                                   rng.integers(sinks, n, (n - sinks, per_vertex - 1))), 1), 1)
+    xadj = np.concatenate((np.zeros(sinks, dtype=np.int64), np.arange(n - sinks + 1, dtype=np.int64) * per_vertex))
+    return xadj, rows.ravel().astype(np.int32)
+
+
+def milliseconds(run):
+    times = []
+    for _ in range(3):
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        a.record()
+        run()
+        b.record()
+        torch.cuda.synchronize()
+        times.append(a.elapsed_time(b))
+    return min(times)
+
+
+@pytest.mark.parametrize("sinks", [1, 40])
+@pytest.mark.parametrize("d,k", [(128, 3), (64, 9)])
+def test_epoch_does_not_queue_up_at_a_sink(d, k, sinks):
+    """As atomic adds a fifth of all positive samples on one row cost a few times an ordinary epoch;
+    one holder after another they cost a thousand times one.  The bar lies between: four times
+    the all-atomic epoch."""
+    n = 80_000
+    xadj, adj = sink_graph(n, sinks, 5, 3)
+    g, keep = upload(n, xadj, adj, True)
+    M0 = torch.from_numpy(start_matrix(n, d, 5, 0.5)).to(DEV)
+    ms = {}
+    for flags in (G.GOSH_FLAG_ATOMIC_ADDS, 0):
+        M = M0.clone()
+        ms[flags] = milliseconds(lambda: G.gosh_train_epoch(g, M, k, 1e-4, 7, 0, 0, flags))
+    say(f"[contended] d={d} k={k} sinks={sinks}: default {ms[0]:.3f} ms, adds {ms[G.GOSH_FLAG_ATOMIC_ADDS]:.3f} ms")
+    assert ms[0] <= 4 * ms[G.GOSH_FLAG_ATOMIC_ADDS]
+
+
+def test_rotation_does_not_queue_up_at_a_sink():
+    n, d, k, K = 400_000, 128, 3, 4
+    xadj, adj = sink_graph(n, 10, 5, 4)
+    xt, at = torch.from_numpy(xadj).to(DEV), torch.from_numpy(adj).to(DEV)
+    M0 = torch.from_numpy(start_matrix(n, d, 5, 0.5)).to(DEV)
+    ms = {}
+    for flags in (G.GOSH_FLAG_ATOMIC_ADDS, 0):
+        M = M0.clone()
+        ms[flags] = min(G.gosh_train_parts(n, xt, at, M, k, 1, 1e-5, 7, force_K=K, B=5, flags=flags)["kernel_ms"]
+                        for _ in range(2))
+    say(f"[contended] rotation: default {ms[0]:.2f} ms, adds {ms[G.GOSH_FLAG_ATOMIC_ADDS]:.2f} ms")
+    assert ms[0] <= 4 * ms[G.GOSH_FLAG_ATOMIC_ADDS]
+
+
+@pytest.mark.parametrize("d,n,k", [(36, 40_000, 10), (128, 40_000, 3)])
+def test_rows_drawn_often_lose_no_update(d, n, k):
+    """Sinks that thousands of sources draw, beside rows under locks: in sequential order the
+    sequential result; concurrent, to first order (the bar of the all-atomic epoch, see
+    test_locked_rows), twice, so that the counts of the first launch must have been cleared."""
+    xadj, adj = sink_graph(n, 30, 4, 9)
+    g, keep = upload(n, xadj, adj, False)
+    M0 = start_matrix(n, d, 5, 0.5)
+    want = M0.copy()
+    O.train_epoch(xadj, adj, want, k, 0.02, 77, 0, 1)
+    M = torch.from_numpy(M0).to(DEV)
+    G.gosh_train_epoch(g, M, k, 0.02, 77, 0, 1, SEQ_LAYOUT)
+    torch.cuda.synchronize()
+    assert rel_err(M.cpu().numpy(), want) <= TOL
+    M = torch.from_numpy(M0).to(DEV)
+    for epoch in range(2):
+        before = M.cpu().numpy()
+        want = before.copy()
+        O.train_epoch(xadj, adj, want, k, 1e-5, 77, epoch, 1)
+        G.gosh_train_epoch(g, M, k, 1e-5, 77, epoch, 1)
+        torch.cuda.synchronize()
+        step = np.abs(want.astype(np.float64) - before).max(axis=1)
+        err = np.abs(M.cpu().numpy().astype(np.float64) - want).max(axis=1)
+        say(f"[contended] d={d}: worst err/step {np.max(err / np.maximum(step, 1e-30)):.3e}")
+        # first order, and what the roundings of that many updates of a row can add up to
+        ids = torch.empty(n * (k + 1), dtype=torch.int32, device=DEV)
+        G.gosh_sample_epoch(g, k, 77, epoch, 1, ids)
+        ids = ids.cpu().numpy()
+        updates = np.bincount(ids[ids >= 0], minlength=n) + k + 2
+        assert (err <= 0.02 * step + updates * 2.0 ** -23 * np.abs(before).max()).all()
