@@ -33,6 +33,14 @@ int check_launch(const char *kernel);
 // GOSH_ENOMEM when device or pinned memory ran out, GOSH_EHIP otherwise.
 int hip_fail(hipError_t e, const char *what);
 
+// Seams for the library's own tests, one set per thread and not part of gosh.h:
+// gosh_testing(which, value) sets one and returns what it was.
+enum Seam : int32_t {
+  kSeamHotMode,  // written by every launch of the training kernels: its HotMode
+  kSeams
+};
+int64_t &seam(Seam which);
+
 // Returns from the enclosing function with that status if the call fails.
 #define GOSH_TRY_HIP(call, what)                                 \
   do {                                                           \

@@ -12,6 +12,11 @@ namespace gosh {
 
 static thread_local char g_error[512] = "";
 
+int64_t &seam(Seam which) {
+  static thread_local int64_t values[kSeams] = {-1};
+  return values[which];
+}
+
 int fail(int code, const char *fmt, ...) {
   va_list ap;
   va_start(ap, fmt);
@@ -203,6 +208,14 @@ int check_scratch(CheckResult **out) {
 extern "C" {
 
 const char *gosh_last_error(void) { return gosh::g_error; }
+
+int64_t gosh_testing(int32_t which, int64_t value) {
+  if (which < 0 || which >= gosh::kSeams) return INT64_MIN;
+  int64_t &held = gosh::seam(static_cast<gosh::Seam>(which));
+  const int64_t was = held;
+  held = value;
+  return was;
+}
 
 void gosh_tuning_defaults(gosh_tuning *t) {
   if (t) *t = gosh::kDefaultTuning;

@@ -575,6 +575,7 @@ class Rotation {
       }
       hot.mode = mode;
     }
+    gosh::seam(gosh::kSeamHotMode) = hot.mode;
     if (hot.bits == nullptr) {
       // the kernel reads word 0 of the bitmap unconditionally
       GOSH_TRY_HIP(gosh::device_malloc(&hot_bits_dev, 64), "hipMalloc hot bitmap");

@@ -461,18 +461,14 @@ int launch_epoch(const gosh_csr *g, float *M, int32_t d, int32_t k_neg, float lr
     int64_t waves = std::min<int64_t>((n + gpw - 1) / gpw, max_waves);
     const int64_t in_flight = std::min<int64_t>(waves, gosh::resident_waves()) * gpw;
     int mode = gosh::kHotBitmap;
-    if (tune.hot_min_degree == 0) {
-      const int64_t all_hot_below = (k_neg + 1) * in_flight * tune.hot_all_inv_eps;
-      // Rows of seven blocks or more are worth their locks for twice as many vertices: the degree
-      // rule would call a third of the writes or more hot there, and those are bound by the rate of
-      // atomic adds (k = 3, us: uniform 300,000 x 128 597 -> 363, power law 400,000 x 128 483 -> 441,
-      // 200,000 x 256 493 -> 401; at d = 64 a power law of 800,000 488 -> 526; at four times as many
-      // vertices an R-MAT graph of 2^19 x 128 466 -> 672).
-      const bool lock = bits_override == nullptr && tune.plain_rows == 0 && gosh::worth_locking(n * (k_neg + 2), d) &&
-                        n < all_hot_below * (d > 96 ? 2 : 1) && !capturing(st);
-      if (lock) mode = gosh::kHotLocked;
-      else if (n < all_hot_below) mode = gosh::kHotAll;
-    }
+    // Locks stand in for the adds of an all-hot launch and for nothing else: with more vertices the
+    // degree rule leaves most writes of a skewed graph to plain stores, which are cheaper (k = 3,
+    // d = 128, us, stores and adds by degree against locks: R-MAT of 300,000 vertices 246 / 307, of
+    // 500,000 445 / 626; power law 437 / 309 and 507 / 655; only uniform graphs gain throughout).
+    if (tune.hot_min_degree == 0 && (k_neg + 1) * in_flight * tune.hot_all_inv_eps > n)
+      mode = bits_override == nullptr && tune.plain_rows == 0 && gosh::worth_locking(n * (k_neg + 2), d) && !capturing(st)
+                 ? gosh::kHotLocked
+                 : gosh::kHotAll;
     if (flags & GOSH_FLAG_PLAIN_STORES) mode = gosh::kHotNone;
     if (flags & GOSH_FLAG_ATOMIC_ADDS) mode = gosh::kHotAll;
     if (mode == gosh::kHotLocked) {
@@ -500,6 +496,7 @@ int launch_epoch(const gosh_csr *g, float *M, int32_t d, int32_t k_neg, float lr
     }
     a.hot.mode = mode;
   }
+  gosh::seam(gosh::kSeamHotMode) = a.hot.mode;
   if (a.hot.bits == nullptr) {
     // the kernel reads word 0 of the bitmap unconditionally (one with locks does not, but a call under
     // capture after it will, and cannot allocate)

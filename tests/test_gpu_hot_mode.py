@@ -1,0 +1,36 @@
+"""Which way the rows of a launch are written: the rule that chooses between stores and adds by
+degree, adds everywhere, and row locks."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2008_12336_amd as G
+from tests.test_gpu_layout import DEV, upload
+from tests.util import HOT_ALL, HOT_BITMAP, HOT_LOCKED, HOT_NONE, last_hot_mode
+
+pytestmark = pytest.mark.gpu
+
+
+def ring(n):
+    """Every vertex beside its two neighbours: the rule asks for sizes only."""
+    rows = np.sort(np.stack(((np.arange(n) - 1) % n, (np.arange(n) + 1) % n), 1), 1)
+    return np.arange(n + 1, dtype=np.int64) * 2, rows.ravel().astype(np.int32)
+
+
+def mode_of(n, d, k, flags=0, call=None):
+    xadj, adj = ring(n)
+    g, keep = upload(n, xadj, adj, False)
+    M = torch.zeros(n, d, device=DEV)
+    (call or G.gosh_train_epoch)(g, M, k, 1e-3, 1, 0, 0, flags)
+    torch.cuda.synchronize()
+    return last_hot_mode()
+
+
+# every row is hot below 4 (k + 1) C vertices, C = 8,192 wavefronts of 64, 32, 16 or fewer lanes
+@pytest.mark.parametrize("n,d,k", [(262_143, 128, 3), (131_071, 256, 3), (524_287, 64, 3)])
+def test_locks_stand_in_for_adds_and_for_nothing_else(n, d, k):
+    assert mode_of(n, d, k) == HOT_LOCKED
+    assert mode_of(n + 1, d, k) == HOT_BITMAP
+    assert mode_of(n, d, k, G.GOSH_FLAG_ATOMIC_ADDS) == HOT_ALL
+    assert mode_of(n, d, k, G.GOSH_FLAG_PLAIN_STORES) == HOT_NONE
+    assert mode_of(n, d, k, call=G.gosh_train_epoch_static) == HOT_ALL

@@ -100,3 +100,23 @@ def conditioned_bar(sensitivity):
     one ulp, eight times that sensitivity -- the kernel's differences enter at every update,
     not once at the start."""
     return max(1e-5, 8.0 * float(sensitivity))
+
+
+# Seams of the library for its own tests (gosh_common.h), of the calling thread.
+SEAM_HOT_MODE = 0
+HOT_NONE, HOT_BITMAP, HOT_ALL, HOT_LOCKED = range(4)
+
+
+def set_seam(which, value):
+    """Sets a seam and returns what it held."""
+    import ctypes
+
+    import paper_2008_12336_amd as G
+    fn = G.lib().gosh_testing
+    fn.restype, fn.argtypes = ctypes.c_int64, [ctypes.c_int32, ctypes.c_int64]
+    return fn(which, value)
+
+
+def last_hot_mode():
+    """How the last training launch of this thread wrote its rows."""
+    return set_seam(SEAM_HOT_MODE, -1)
