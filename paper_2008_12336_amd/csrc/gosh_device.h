@@ -203,16 +203,28 @@ struct HotSet {
   uint32_t most;
 };
 
-// Whether a launch in which every row is hot takes locks.  An update of a row that spans three
-// or more blocks is cheaper locked (k = 3, us per epoch, adds against locks: 131,072 vertices at
-// d = 32 93 / 97; 262,144 at d = 64 272 / 156; 67,000 at d = 128 137 / 92; 60,000 at d = 512 285 /
-// 143; 130,000 at d = 36, k = 9 223 / 192), unless there are so few that the launch is bound by one
-// source's chain of round trips, which locks make longer (d = 128: 8,192 vertices 21 / 34, 32,768
-// 70 / 57).
-inline bool worth_locking(int64_t updates, int32_t d) {
+// Whether a launch in which every row is hot takes locks.  `capacity` sources run at a time (C when
+// the device is full), so a launch is sources / capacity rounds.  Adds cost time per block of a
+// row, a lock costs about as much as one round trip however long the row is: what it saves grows
+// with the blocks that the rows in flight have together (131,072 are a full chip at d = 64, 128
+// and 256), and what it costs on top -- the counting, the longer chain of one source -- must spread
+// over some rounds and samples.  Time with locks over time with adds, power law / R-MAT, by rounds:
+//   d = 128, k = 3   1: 1.11, 1.5: 0.92 / 1.04, 2: 0.84 / 0.96, 4: 0.69 / 0.71
+//            k = 1   2: 1.15, 3: - / 0.96, 4: - / 0.86        k = 9   1: 1.05, 1.5: 0.85 / 0.89
+//   d = 64,  k = 3   1: 1.07, 1.75: 0.88 / 0.95, 2.5: 0.79 / 0.90
+//   d = 512, k = 3   0.5: 1.07, 0.9: 0.75 / 0.79               k = 0   1: 0.95, 2: 0.75
+//   d = 68,  k = 3   2: 1.07, 3: 0.95 / 0.99, 6: 0.83          d = 192, k = 3   1.5: 1.02, 2: 0.94
+//   d = 132, k = 9   3: 1.02, 4: 0.96                          k = 1   8: 1.02 / 1.05
+// Rows of three blocks (d <= 48) gain least, their adds being one instruction per row:
+//   d = 36,  k = 3   4: 0.91 / 1.03, 6: 0.85 / 0.93            k = 1   8: 0.97 / 1.08
+inline bool worth_locking(int64_t sources, int64_t samples, int64_t capacity, int32_t d) {
   const int64_t blocks = (d + 15) / 16;
-  return blocks >= 3 && updates * blocks >= 1000000;
+  if (blocks < 3) return false;
+  const double saved = blocks == 3 ? 0.3 : static_cast<double>(blocks * capacity) / 131072.0 - 0.1;
+  return static_cast<double>(sources) * saved >=
+         static_cast<double>(capacity) * (1.0 + 4.0 / static_cast<double>(samples));
 }
+
 // Hubs.  Whoever holds a row keeps the others waiting for about as long as a source takes for one
 // sample, so rows that are drawn too often as positive samples hold up the whole launch.  How
 // often a row is drawn is counted, draw by draw, before the launch: a degree does not tell (many

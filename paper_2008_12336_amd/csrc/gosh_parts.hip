@@ -530,7 +530,7 @@ class Rotation {
                      ? gosh::kHotAll
                      : gosh::kHotBitmap;
       if (mode == gosh::kHotAll && pl.room_for_locks && tune.plain_rows == 0 &&
-          gosh::worth_locking(pair_sources * (samples + 1), pl.d))
+          gosh::worth_locking(pair_sources, samples, std::min<int64_t>(tune.max_waves, gosh::resident_waves()) * gpw, pl.d))
         mode = gosh::kHotLocked;
       if (pl.flags & GOSH_FLAG_PLAIN_STORES) mode = gosh::kHotNone;
       if (pl.flags & GOSH_FLAG_ATOMIC_ADDS) mode = gosh::kHotAll;

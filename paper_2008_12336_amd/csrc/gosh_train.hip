@@ -460,13 +460,14 @@ int launch_epoch(const gosh_csr *g, float *M, int32_t d, int32_t k_neg, float lr
     const int gpw = gosh::SgdLauncher<EpochWork<OffT>>::groups_per_wave(d);
     int64_t waves = std::min<int64_t>((n + gpw - 1) / gpw, max_waves);
     const int64_t in_flight = std::min<int64_t>(waves, gosh::resident_waves()) * gpw;
+    const int64_t capacity = std::min<int64_t>(max_waves, gosh::resident_waves()) * gpw;
     int mode = gosh::kHotBitmap;
     // Locks stand in for the adds of an all-hot launch and for nothing else: with more vertices the
     // degree rule leaves most writes of a skewed graph to plain stores, which are cheaper (k = 3,
     // d = 128, us, stores and adds by degree against locks: R-MAT of 300,000 vertices 246 / 307, of
     // 500,000 445 / 626; power law 437 / 309 and 507 / 655; only uniform graphs gain throughout).
     if (tune.hot_min_degree == 0 && (k_neg + 1) * in_flight * tune.hot_all_inv_eps > n)
-      mode = bits_override == nullptr && tune.plain_rows == 0 && gosh::worth_locking(n * (k_neg + 2), d) && !capturing(st)
+      mode = bits_override == nullptr && tune.plain_rows == 0 && gosh::worth_locking(n, k_neg + 1, capacity, d) && !capturing(st)
                  ? gosh::kHotLocked
                  : gosh::kHotAll;
     if (flags & GOSH_FLAG_PLAIN_STORES) mode = gosh::kHotNone;

@@ -34,3 +34,18 @@ def test_locks_stand_in_for_adds_and_for_nothing_else(n, d, k):
     assert mode_of(n, d, k, G.GOSH_FLAG_ATOMIC_ADDS) == HOT_ALL
     assert mode_of(n, d, k, G.GOSH_FLAG_PLAIN_STORES) == HOT_NONE
     assert mode_of(n, d, k, call=G.gosh_train_epoch_static) == HOT_ALL
+
+
+# one vertex below and at the bound: rounds * (blocks * C / 131,072 - 0.1) >= 1 + 4 / (k + 1)
+@pytest.mark.parametrize("n,d,k", [(36_409, 128, 3), (72_818, 64, 3), (25_487, 128, 9), (8_624, 512, 3), (21_558, 512, 0),
+                                   (218_454, 36, 3), (24_798, 132, 9)])
+def test_small_launches_take_no_locks(n, d, k):
+    """A launch of a few sources is bound by the chain of round trips of one, which locks make
+    longer: up to 1.6 times the time with adds at one round of sources."""
+    assert mode_of(n - 1, d, k) == HOT_ALL
+    assert mode_of(n, d, k) == HOT_LOCKED
+
+
+@pytest.mark.parametrize("d", [4, 16, 32])
+def test_short_rows_take_no_locks(d):
+    assert mode_of(200_000, d, 3) == HOT_ALL

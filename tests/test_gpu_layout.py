@@ -18,7 +18,7 @@ import torch
 import graphgen
 import paper_2008_12336_amd as G
 from oracle import gosh_oracle as O
-from tests.util import csr_from_pairs, rel_err
+from tests.util import HOT_ALL, HOT_LOCKED, csr_from_pairs, last_hot_mode, rel_err
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
@@ -210,10 +210,9 @@ def test_rows_that_straddle_lines_in_sequential_order(d, offset, paths, hot_degr
     assert (room[:offset] == 7.0).all() and (room[offset + n * d:] == 7.0).all()
 
 
-# n (k + 2) updates of rows of ceil(d / 16) blocks: at least a million, so that an epoch on a graph
-# small enough for every row to be written without losses takes row locks
-LOCKED = [(36, 30000, 10), (64, 20000, 11), (100, 12000, 11), (128, 40000, 3), (132, 9000, 11), (260, 8000, 6),
-          (512, 4500, 5)]
+# graphs small enough for every row to be written without losses, and large enough for row locks
+LOCKED = [(36, 150_000, 10), (64, 50_000, 11), (100, 29_000, 11), (128, 40_000, 3), (132, 24_000, 11),
+          (260, 13_500, 6), (512, 7_300, 5)]
 
 
 @pytest.mark.parametrize("d,n,k", LOCKED)
@@ -222,7 +221,6 @@ def test_locked_rows(d, n, k):
     Concurrent: no update is lost, so at a small learning rate every row ends within 2 % of its
     own movement of the sequential result (the bar of the all-atomic epoch); twice in a row, so
     that the locks of the first launch must have been given back."""
-    assert n * (k + 2) * -(-d // 16) >= 1_000_000
     xadj, adj = hub_graph(n, 6 * n, 3)
     g, keep = upload(n, xadj, adj, True)
     M0 = start_matrix(n, d, 5, 0.5)
@@ -231,6 +229,7 @@ def test_locked_rows(d, n, k):
     M = torch.from_numpy(M0).to(DEV)
     G.gosh_train_epoch(g, M, k, 0.1, 77, 0, 1, SEQ_LAYOUT)
     torch.cuda.synchronize()
+    assert last_hot_mode() == HOT_LOCKED
     assert rel_err(M.cpu().numpy(), want) <= TOL
     M = torch.from_numpy(M0).to(DEV)
     for epoch in range(2):
@@ -239,6 +238,7 @@ def test_locked_rows(d, n, k):
         O.train_epoch(xadj, adj, want, k, 1e-3, 77, epoch, 1)
         G.gosh_train_epoch(g, M, k, 1e-3, 77, epoch, 1)
         torch.cuda.synchronize()
+        assert last_hot_mode() == HOT_LOCKED
         step = np.abs(want.astype(np.float64) - before).max(axis=1)
         err = np.abs(M.cpu().numpy().astype(np.float64) - want).max(axis=1)
         ok = err <= 0.02 * step + 2e-7 * np.abs(before).max()
@@ -248,9 +248,10 @@ def test_locked_rows(d, n, k):
 
 @pytest.mark.parametrize("where", ["device", "host"])
 def test_locked_rows_of_a_rotation(where):
-    """The pair kernel with locks (512 columns, 3 parts of 1,200 rows, 21 updates per source and
-    visit), sequential order against the oracle and concurrent to first order."""
-    n, d, k, K, B = 3600, 512, 3, 3, 5
+    """The pair kernel with locks (512 columns, 3 parts of 2,601 rows, 21 updates per source and
+    visit), sequential order against the oracle and concurrent to first order.  The lock words
+    show in the bytes of the call."""
+    n, d, k, K, B = 7801, 512, 3, 3, 5
     xadj, adj = hub_graph(n, 9 * n, 8)
     xt, at = torch.from_numpy(xadj), torch.from_numpy(adj)
     if where == "device":
@@ -262,8 +263,12 @@ def test_locked_rows_of_a_rotation(where):
         M = torch.from_numpy(M0.copy()).to(DEV) if where == "device" else torch.from_numpy(M0.copy()).pin_memory()
         st = G.gosh_train_parts(n, xt, at, M, k, B * K, lr, 7, level=2, force_K=K, B=B, flags=flags)
         torch.cuda.synchronize()
-        assert st["device_bytes"] >= 4 * n
-        got = M.cpu().numpy()
+        assert last_hot_mode() == HOT_LOCKED
+        got = M.cpu().clone().numpy()
+        adds = G.gosh_train_parts(n, xt, at, M, k, B * K, lr, 7, level=2, force_K=K, B=B,
+                                  flags=flags | G.GOSH_FLAG_ATOMIC_ADDS)
+        assert last_hot_mode() == HOT_ALL
+        assert st["device_bytes"] == adds["device_bytes"] + 3 * 4 * 2 * -(-n // K)
         if tol is None:
             assert rel_err(got, want) <= TOL
         else:
