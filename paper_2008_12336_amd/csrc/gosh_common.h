@@ -37,9 +37,12 @@ int hip_fail(hipError_t e, const char *what);
 // gosh_testing(which, value) sets one and returns what it was.
 enum Seam : int32_t {
   kSeamHotMode,  // written by every launch of the training kernels: its HotMode
+  kSeamDeny,     // memory that is not to be had: a sum of the Deny flags
   kSeams
 };
+enum Deny : int64_t { kDenyLocks = 1 };
 int64_t &seam(Seam which);
+inline bool denied(Deny what) { return (seam(kSeamDeny) & what) != 0; }
 
 // Returns from the enclosing function with that status if the call fails.
 #define GOSH_TRY_HIP(call, what)                                 \
@@ -97,7 +100,8 @@ int hot_scratch(size_t bytes, void **out);
 // Per-device words of the training kernels, per row: a lock, zero between launches, and two counts
 // of draws that launches use in turns.  The launch counts in `draws`, which are zero, and clears
 // the first `stale_rows` of `stale`, which the launch before may still be reading until then.
-// Grown on demand and kept until the process ends.
+// Grown on demand and kept until the process ends.  GOSH_ENOMEM if there is no memory: the launch
+// then does without.
 struct LockWords {
   uint32_t *locks, *draws, *stale;
   int64_t stale_rows;

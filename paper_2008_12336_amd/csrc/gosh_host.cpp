@@ -163,13 +163,17 @@ int lock_scratch(int64_t rows, LockWords *out) {
     return fail(GOSH_EHIP, "cannot identify the current device");
   std::lock_guard<std::mutex> lock(g_hot_scratch_mutex);
   Words &w = table[dev];
+  if (denied(kDenyLocks)) return GOSH_ENOMEM;
   if (w.rows < rows) {
     // a smaller block is left alone, since another thread may be about to launch with it: every
     // block is at least twice the one before, so all of them together are no more than the last
     const int64_t want = std::max(rows + rows / 4 + 1024, 2 * w.rows);
     const size_t bytes = static_cast<size_t>(want) * 12;
     void *p = nullptr;
-    if (device_malloc(&p, bytes) != hipSuccess) return fail(GOSH_ENOMEM, "cannot allocate %zu bytes for the row locks", bytes);
+    if (device_malloc(&p, bytes) != hipSuccess) {
+      (void)hipGetLastError();
+      return GOSH_ENOMEM;
+    }
     // ordered before any launch on any stream
     if (hipMemset(p, 0, bytes) != hipSuccess || hipDeviceSynchronize() != hipSuccess) {
       (void)hipGetLastError();

@@ -534,8 +534,13 @@ class Rotation {
         mode = gosh::kHotLocked;
       if (pl.flags & GOSH_FLAG_PLAIN_STORES) mode = gosh::kHotNone;
       if (pl.flags & GOSH_FLAG_ATOMIC_ADDS) mode = gosh::kHotAll;
+      if (mode == gosh::kHotLocked &&
+          (gosh::denied(gosh::kDenyLocks) || gosh::device_malloc(&locks, lock_bytes(n, pl.K)) != hipSuccess)) {
+        (void)hipGetLastError();
+        locks = nullptr;
+        mode = gosh::kHotAll;  // which needs no memory
+      }
       if (mode == gosh::kHotLocked) {
-        GOSH_TRY_HIP(gosh::device_malloc(&locks, lock_bytes(n, pl.K)), "hipMalloc row locks");
         GOSH_TRY_HIP(hipMemsetAsync(locks, 0, lock_bytes(n, pl.K), compute), "clear row locks");
         hot.locks = locks;
         lock_in_flight = in_flight;

@@ -474,13 +474,18 @@ int launch_epoch(const gosh_csr *g, float *M, int32_t d, int32_t k_neg, float lr
     if (flags & GOSH_FLAG_ATOMIC_ADDS) mode = gosh::kHotAll;
     if (mode == gosh::kHotLocked) {
       gosh::LockWords words{};
-      if (int rc = gosh::lock_scratch(n, &words)) return rc;
-      hipLaunchKernelGGL(count_positives_kernel<OffT>, dim3(grid_for(n, 256, 1 << 16)), dim3(256), 0, st, w.s,
-                         words.draws, words.stale, words.stale_rows);
-      if (int rc = gosh::check_launch("count_positives_kernel")) return rc;
-      a.hot.locks = words.locks;
-      a.hot.draws = words.draws;
-      a.hot.most = gosh::most_draws(n, k_neg + 2, in_flight);
+      const int rc = gosh::lock_scratch(n, &words);
+      if (rc == GOSH_ENOMEM) {
+        mode = gosh::kHotAll;  // which needs no memory
+      } else {
+        if (rc != GOSH_OK) return rc;
+        hipLaunchKernelGGL(count_positives_kernel<OffT>, dim3(grid_for(n, 256, 1 << 16)), dim3(256), 0, st, w.s,
+                           words.draws, words.stale, words.stale_rows);
+        if (int rc2 = gosh::check_launch("count_positives_kernel")) return rc2;
+        a.hot.locks = words.locks;
+        a.hot.draws = words.draws;
+        a.hot.most = gosh::most_draws(n, k_neg + 2, in_flight);
+      }
     }
     if (mode == gosh::kHotBitmap) {
       const int64_t min_degree =

@@ -5,8 +5,10 @@ import pytest
 import torch
 
 import paper_2008_12336_amd as G
-from tests.test_gpu_layout import DEV, upload
-from tests.util import HOT_ALL, HOT_BITMAP, HOT_LOCKED, HOT_NONE, last_hot_mode
+from oracle import gosh_oracle as O
+from tests.test_gpu_layout import DEV, SEQ_LAYOUT, TOL, start_matrix, upload
+from tests.util import (DENY_LOCKS, HOT_ALL, HOT_BITMAP, HOT_LOCKED, HOT_NONE, SEAM_DENY, last_hot_mode, rel_err,
+                        seam)
 
 pytestmark = pytest.mark.gpu
 
@@ -49,3 +51,30 @@ def test_small_launches_take_no_locks(n, d, k):
 @pytest.mark.parametrize("d", [4, 16, 32])
 def test_short_rows_take_no_locks(d):
     assert mode_of(200_000, d, 3) == HOT_ALL
+
+
+@pytest.mark.parametrize("in_place", [False, True])
+def test_training_without_memory_for_locks(in_place):
+    """Locks only make a launch faster: where their words cannot be had, it adds as it does without."""
+    n, d, k, K, B = 7_801, 512, 5, 3, 5
+    xadj, adj = ring(n)
+    g, keep = upload(n, xadj, adj, True)
+    M0 = start_matrix(n, d, 3, 0.5)
+    with seam(SEAM_DENY, DENY_LOCKS):
+        want = M0.copy()
+        M = torch.from_numpy(M0.copy()).to(DEV)
+        if in_place:
+            O.train_parts(xadj, adj, want, k, B * K, 0.1, 7, 2, K, B)
+            st = G.gosh_train_parts(n, *keep, M, k, B * K, 0.1, 7, level=2, force_K=K, B=B, flags=SEQ_LAYOUT)
+        else:
+            O.train_epoch(xadj, adj, want, k, 0.1, 7, 0, 1)
+            G.gosh_train_epoch(g, M, k, 0.1, 7, 0, 1, SEQ_LAYOUT)
+        torch.cuda.synchronize()
+        assert last_hot_mode() == HOT_ALL
+        assert rel_err(M.cpu().numpy(), want) <= TOL
+    if in_place:
+        again = G.gosh_train_parts(n, *keep, M, k, B * K, 0.1, 7, level=2, force_K=K, B=B)
+        assert again["device_bytes"] > st["device_bytes"]
+    else:
+        G.gosh_train_epoch(g, M, k, 0.1, 7, 0, 1)
+    assert last_hot_mode() == HOT_LOCKED

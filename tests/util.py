@@ -1,6 +1,8 @@
 """Helpers shared by the tests (graph fixtures, small numpy utilities)."""
 from __future__ import annotations
 
+import contextlib
+
 import numpy as np
 import torch
 
@@ -103,7 +105,8 @@ def conditioned_bar(sensitivity):
 
 
 # Seams of the library for its own tests (gosh_common.h), of the calling thread.
-SEAM_HOT_MODE = 0
+SEAM_HOT_MODE, SEAM_DENY = range(2)
+DENY_LOCKS = 1
 HOT_NONE, HOT_BITMAP, HOT_ALL, HOT_LOCKED = range(4)
 
 
@@ -120,3 +123,12 @@ def set_seam(which, value):
 def last_hot_mode():
     """How the last training launch of this thread wrote its rows."""
     return set_seam(SEAM_HOT_MODE, -1)
+
+
+@contextlib.contextmanager
+def seam(which, value):
+    was = set_seam(which, value)
+    try:
+        yield
+    finally:
+        set_seam(which, was)
