@@ -93,8 +93,8 @@ int matrix_check_read(const CheckResult *result_dev, float *max_abs, int64_t *no
 // A per-device CheckResult owned by the library (allocated on first use, kept).
 int check_scratch(CheckResult **out);
 
-// Per-device scratch for the hot-row bitmap (one bit per vertex), grown on demand and
-// kept until the process ends.  Calls on one device must not overlap on different
+// Per-device scratch for the hot-row bitmap (one bit per vertex), grown on demand and, smaller
+// blocks included, kept until the process ends.  Calls on one device must not overlap on different
 // streams.
 int hot_scratch(size_t bytes, void **out);
 // Per-device words of the training kernels, per row: a lock, zero between launches, and two counts

@@ -136,14 +136,16 @@ int hot_scratch(size_t bytes, void **out) {
   std::lock_guard<std::mutex> lock(g_hot_scratch_mutex);
   HotScratch &h = g_hot_scratch[dev];
   if (h.bytes < bytes) {
-    if (h.ptr) (void)hipFree(h.ptr);
-    h.ptr = nullptr;
-    h.bytes = 0;
-    const size_t want = bytes + bytes / 4 + 4096;
-    if (device_malloc(&h.ptr, want) != hipSuccess) {
+    // a smaller block is left alone: a recorded launch may be replayed with it, and another thread
+    // may be about to launch.  Every block is at least twice the one before, so all of them together
+    // are no more than the last.
+    const size_t want = std::max(bytes + bytes / 4 + 4096, 2 * h.bytes);
+    void *p = nullptr;
+    if (device_malloc(&p, want) != hipSuccess) {
       (void)hipGetLastError();
       return fail(GOSH_ENOMEM, "cannot allocate %zu bytes for the hot-row bitmap", want);
     }
+    h.ptr = p;
     h.bytes = want;
   }
   *out = h.ptr;

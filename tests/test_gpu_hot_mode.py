@@ -78,3 +78,31 @@ def test_training_without_memory_for_locks(in_place):
     else:
         G.gosh_train_epoch(g, M, k, 0.1, 7, 0, 1)
     assert last_hot_mode() == HOT_LOCKED
+
+
+def test_recorded_epoch_is_replayed_after_a_larger_graph_was_trained():
+    """A recorded launch reads the library's bitmap memory whenever it is replayed, also after a larger
+    graph has needed more of it.  Recorded calls take no locks; every replay is one more epoch with
+    adds, which to first order is the sequential one."""
+    n, d, k, lr = 40_000, 128, 3, 1e-4
+    xadj, adj = ring(n)
+    g, keep = upload(n, xadj, adj, True)
+    M = torch.from_numpy(start_matrix(n, d, 5, 0.5)).to(DEV)
+    G.gosh_train_epoch(g, M, k, lr, 77, 0)
+    torch.cuda.synchronize()
+    assert last_hot_mode() == HOT_LOCKED
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        G.gosh_train_epoch(g, M, k, lr, 77, 0)
+    assert last_hot_mode() == HOT_ALL
+    for larger in (3_000_000, 9_000_000):
+        assert mode_of(larger, 32, k) == HOT_BITMAP
+        before = M.cpu().numpy()
+        want = before.copy()
+        O.train_epoch(xadj, adj, want, k, lr, 77, 0, 0)
+        graph.replay()
+        torch.cuda.synchronize()
+        step = np.abs(want.astype(np.float64) - before).max(axis=1)
+        err = np.abs(M.cpu().numpy().astype(np.float64) - want).max(axis=1)
+        assert (err <= 0.02 * step + 2e-7 * np.abs(before).max()).all()
+        G.gosh_train_epoch(g, M, k, lr, 77, 1)
