@@ -176,8 +176,12 @@ int lock_scratch(int64_t rows, LockWords *out) {
       (void)hipGetLastError();
       return GOSH_ENOMEM;
     }
-    // ordered before any launch on any stream
-    if (hipMemset(p, 0, bytes) != hipSuccess || hipDeviceSynchronize() != hipSuccess) {
+    // before any launch on any stream, and behind none: on a stream of its own
+    hipStream_t own = nullptr;
+    const bool cleared = hipStreamCreateWithFlags(&own, hipStreamNonBlocking) == hipSuccess &&
+                         hipMemsetAsync(p, 0, bytes, own) == hipSuccess && hipStreamSynchronize(own) == hipSuccess;
+    if (own) (void)hipStreamDestroy(own);
+    if (!cleared) {
       (void)hipGetLastError();
       (void)hipFree(p);
       return fail(GOSH_EHIP, "cannot clear the row locks");

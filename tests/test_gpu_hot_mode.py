@@ -106,3 +106,28 @@ def test_recorded_epoch_is_replayed_after_a_larger_graph_was_trained():
         err = np.abs(M.cpu().numpy().astype(np.float64) - want).max(axis=1)
         assert (err <= 0.02 * step + 2e-7 * np.abs(before).max()).all()
         G.gosh_train_epoch(g, M, k, lr, 77, 1)
+
+
+def test_first_locks_wait_for_no_other_stream():
+    """The call is asynchronous also where it has to get and clear its lock words first."""
+    n, d, k = 6_000_000, 512, 15
+    G.gosh_set_tuning(hot_all_inv_eps=100_000)  # every row is hot, however many there are
+    try:
+        xadj, adj = ring(n)
+        g, keep = upload(n, xadj, adj, True)
+        M = torch.zeros(n, d, device=DEV)
+        a = torch.randn(8192, 8192, device=DEV)
+        a @ a
+        G.gosh_train_epoch(g, M, k, 1e-3, 1, 0, 0, G.GOSH_FLAG_ATOMIC_ADDS)
+        torch.cuda.synchronize()
+        busy, done = torch.cuda.Stream(), torch.cuda.Event()
+        with torch.cuda.stream(busy):
+            for _ in range(60):  # some 0.4 s
+                a @ a
+            done.record()
+        G.gosh_train_epoch(g, M, k, 1e-3, 1, 0)
+        assert last_hot_mode() == HOT_LOCKED
+        assert not done.query()
+    finally:
+        G.gosh_set_tuning()
+        torch.cuda.synchronize()
