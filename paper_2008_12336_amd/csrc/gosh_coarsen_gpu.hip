@@ -322,8 +322,8 @@ struct StagedCopy {
       if (done[i]) (void)hipEventDestroy(done[i]);
     staging_give(slots);
   }
+  bool available() const { return slots != nullptr; }
   int open() {
-    if (slots == nullptr) return gosh::fail(GOSH_ENOMEM, "cannot allocate pinned staging");
     for (int i = 0; i < 2; ++i)
       GOSH_TRY_HIP(hipEventCreateWithFlags(&done[i], hipEventDisableTiming), "create copy event");
     return GOSH_OK;
@@ -364,6 +364,10 @@ int device_download(DeviceCoarsener *dc, void *dst, const void *src_dev, size_t 
     return GOSH_OK;
   }
   StagedCopy q(dc);
+  if (!q.available()) {
+    GOSH_TRY_HIP(hipMemcpy(dst, src_dev, bytes, hipMemcpyDeviceToHost), "download");
+    return GOSH_OK;
+  }
   if (int rc = q.open()) return rc;
   const size_t piece = piece_bytes_of(bytes), pieces = (bytes + piece - 1) / piece;
   auto len = [&](size_t c) { return std::min(piece, bytes - c * piece); };
@@ -389,6 +393,10 @@ int device_upload(DeviceCoarsener *dc, void *dst_dev, const void *src, size_t by
     return GOSH_OK;
   }
   StagedCopy q(dc);
+  if (!q.available()) {
+    GOSH_TRY_HIP(hipMemcpy(dst_dev, src, bytes, hipMemcpyHostToDevice), "upload");
+    return GOSH_OK;
+  }
   if (int rc = q.open()) return rc;
   const size_t piece = piece_bytes_of(bytes), pieces = (bytes + piece - 1) / piece;
   for (size_t c = 0; c < pieces; ++c) {

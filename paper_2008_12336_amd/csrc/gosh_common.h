@@ -40,7 +40,7 @@ enum Seam : int32_t {
   kSeamDeny,     // memory that is not to be had: a sum of the Deny flags
   kSeams
 };
-enum Deny : int64_t { kDenyLocks = 1 };
+enum Deny : int64_t { kDenyLocks = 1, kDenyStaging = 2 };
 int64_t &seam(Seam which);
 inline bool denied(Deny what) { return (seam(kSeamDeny) & what) != 0; }
 

@@ -203,6 +203,7 @@ size_t block_kept() {
 }
 
 char *staging_take() {
+  if (denied(kDenyStaging)) return nullptr;
   Store &s = store();
   {
     std::lock_guard<std::mutex> lock(s.mutex);

@@ -106,7 +106,7 @@ def conditioned_bar(sensitivity):
 
 # Seams of the library for its own tests (gosh_common.h), of the calling thread.
 SEAM_HOT_MODE, SEAM_DENY = range(2)
-DENY_LOCKS = 1
+DENY_LOCKS, DENY_STAGING = 1, 2
 HOT_NONE, HOT_BITMAP, HOT_ALL, HOT_LOCKED = range(4)
 
 
