@@ -7,8 +7,8 @@
 //
 // Kept blocks are bounded per device (kept_limit), handed out to any thread, given back when an
 // allocation of this library fails, when more would be kept than the bound (oldest first), and
-// on request (block_trim, behind gosh_hierarchy_trim_scratch and _release_device).  A block is
-// kept only after the device has finished what was queued on it, so whoever gets it next may
+// on request (block_trim, behind gosh_hierarchy_trim_scratch and _release_device, which also gives
+// back the kept staging).  A block is kept only after the device has finished what was queued on it, so whoever gets it next may
 // use it on any stream.
 #include <hip/hip_runtime.h>
 
@@ -192,6 +192,7 @@ void block_trim() {
   Store &s = store();
   std::lock_guard<std::mutex> lock(s.mutex);
   (void)drop_kept(s, device);
+  while (s.staging_kept > 0) (void)hipHostFree(s.staging[--s.staging_kept]);
 }
 
 size_t block_kept() {

@@ -13,7 +13,7 @@ namespace gosh {
 
 // Device blocks that outlive a hierarchy (gosh_device_pool.cpp): at least `bytes` on the
 // current device, or null; given back on any thread, whatever device is current; what is kept
-// of them on the current device, freed.
+// of them on the current device, freed, and the staging below.
 void *block_take(size_t bytes);
 void block_give(void *const *blocks, size_t count);
 void block_trim();
