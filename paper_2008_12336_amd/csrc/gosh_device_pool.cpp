@@ -27,14 +27,14 @@ struct Block {
   size_t bytes;
   int device;
 };
-constexpr int kStagingKept = 2;
+constexpr int kStagingKept = 2, kMaxDevices = 64;
 struct Store {
   std::mutex mutex;
   char *staging[kStagingKept] = {};
   int staging_kept = 0;
   std::unordered_map<void *, Block> handed_out;
   std::deque<Block> kept;  // oldest first
-  std::unordered_map<int, size_t> limit;
+  size_t limit[kMaxDevices] = {};  // 0: not known yet
 };
 // Never destroyed: hierarchies may be freed during the end of the process.
 Store &store() {
@@ -44,8 +44,8 @@ Store &store() {
 
 // A 64th of the device's memory.
 size_t kept_limit(Store &s, int device) {
-  const auto known = s.limit.find(device);
-  if (known != s.limit.end()) return known->second;
+  if (device < 0 || device >= kMaxDevices) return 0;
+  if (s.limit[device] != 0) return s.limit[device];
   size_t free_bytes = 0, total = 0;
   if (hipMemGetInfo(&free_bytes, &total) != hipSuccess) {
     (void)hipGetLastError();

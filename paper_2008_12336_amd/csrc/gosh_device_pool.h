@@ -12,8 +12,8 @@
 namespace gosh {
 
 // Device blocks that outlive a hierarchy (gosh_device_pool.cpp): at least `bytes` on the
-// current device, or null; given back on any thread, whatever device is current; what is kept
-// of them on the current device, freed, and the staging below.
+// current device, or null; given back on any thread, whatever device is current (never throws);
+// what is kept of them on the current device, freed, and the staging below.
 void *block_take(size_t bytes);
 void block_give(void *const *blocks, size_t count);
 void block_trim();
@@ -35,10 +35,18 @@ struct Pool {
   };
   std::vector<Block> blocks;
   ~Pool() { trim(); }
-  void trim() {
-    std::vector<void *> all;
-    for (const Block &b : blocks) all.push_back(b.p);
-    block_give(all.data(), all.size());
+  void trim() {  // runs where a hierarchy is freed: needs no host memory
+    constexpr size_t kBatch = 64;
+    void *batch[kBatch];
+    size_t held = 0;
+    for (const Block &b : blocks) {
+      batch[held++] = b.p;
+      if (held == kBatch) {
+        block_give(batch, held);
+        held = 0;
+      }
+    }
+    block_give(batch, held);
     blocks.clear();
   }
   void *take(size_t bytes) {
@@ -52,6 +60,7 @@ struct Pool {
       best->busy = true;
       return best->p;
     }
+    blocks.reserve(blocks.size() + 1);  // throws before there is a block to lose
     void *const p = block_take(bytes);
     if (p == nullptr) return nullptr;
     blocks.push_back(Block{p, bytes, true});
@@ -75,6 +84,7 @@ struct Buffers {
   template <typename T>
   int alloc(T **out, size_t count, const char *what) {
     const size_t bytes = std::max<size_t>(count, 1) * sizeof(T);
+    ptrs.reserve(ptrs.size() + 1);
     void *p = pool.take(bytes);
     if (p == nullptr) return fail(GOSH_ENOMEM, "cannot allocate %zu device bytes for %s", bytes, what);
     ptrs.push_back(p);

@@ -1,8 +1,9 @@
 // The store of device blocks (gosh_device_pool) against a runtime that only keeps books: what is
-// handed out, kept and given back.  No GPU.
+// handed out, kept and given back, with every host allocation failing in turn.  No GPU.
 #include <cstdio>
 #include <cstdlib>
 #include <map>
+#include <new>
 #include <set>
 
 #include "gosh_device_pool.h"
@@ -11,6 +12,7 @@ namespace {
 std::map<void *, size_t> device_blocks;
 std::set<void *> pinned;
 size_t device_total = size_t(64) << 20;
+int64_t allocations_left = -1;  // -1: no limit
 
 [[noreturn]] void broken(const char *what) {
   std::printf("broken: %s\n", what);
@@ -29,26 +31,44 @@ void *plain(size_t bytes) {
   if (p == nullptr) std::abort();
   return p;
 }
+// The books of the runtime are not the library's allocations.
+struct Unlimited {
+  int64_t left = allocations_left;
+  Unlimited() { allocations_left = -1; }
+  ~Unlimited() { allocations_left = left; }
+};
 }  // namespace
+
+void *operator new(size_t bytes) {
+  if (allocations_left == 0) throw std::bad_alloc();
+  if (allocations_left > 0) --allocations_left;
+  return plain(bytes);
+}
+void operator delete(void *p) noexcept { std::free(p); }
+void operator delete(void *p, size_t) noexcept { std::free(p); }
 
 extern "C" {
 hipError_t hipMalloc(void **p, size_t bytes) {
+  Unlimited u;
   if (device_used() + bytes > device_total) return hipErrorOutOfMemory;
   *p = plain(16);
   device_blocks[*p] = bytes;
   return hipSuccess;
 }
 hipError_t hipFree(void *p) {
+  Unlimited u;
   if (p != nullptr && device_blocks.erase(p) != 1) broken("freed what is no block");
   std::free(p);
   return hipSuccess;
 }
 hipError_t hipHostMalloc(void **p, size_t, unsigned) {
+  Unlimited u;
   *p = plain(16);
   pinned.insert(*p);
   return hipSuccess;
 }
 hipError_t hipHostFree(void *p) {
+  Unlimited u;
   if (pinned.erase(p) != 1) broken("freed what is not pinned");
   std::free(p);
   return hipSuccess;
@@ -108,6 +128,18 @@ int main() {
   void *all = nullptr;
   expect(gosh::device_malloc(&all, device_total - 1024) == hipSuccess, "kept blocks make room");
   (void)hipFree(all);
+  // every host allocation of a run fails in turn: nothing ends the process, nothing is lost
+  for (int64_t n = 0; n < 400; ++n) {
+    allocations_left = n;
+    try {
+      run();
+    } catch (const std::bad_alloc &) {
+    }
+    allocations_left = -1;
+    expect(gosh::block_kept() == device_used(), "what is not kept has been freed");
+    gosh::block_trim();
+    expect(device_blocks.empty(), "blocks are lost after a failed host allocation");
+  }
   std::printf("pool ok\n");
   return 0;
 }
