@@ -16,6 +16,7 @@
 #include <vector>
 
 #include "gosh_common.h"
+#include "gosh_device_pool.h"
 
 namespace {
 
@@ -83,6 +84,7 @@ int gosh_matrix_place(int64_t n, int32_t d, uint64_t arena_bytes, float **M_dev,
   GOSH_TRY_HIP(hipMemGetAllocationGranularity(&granularity, &prop, hipMemAllocationGranularityRecommended),
                "hipMemGetAllocationGranularity");
   const size_t piece = std::max<size_t>(size_t{1} << 30, granularity) / granularity * granularity;
+  gosh::block_trim();  // blocks kept from freed hierarchies are free memory
   size_t free_bytes = 0, total_bytes = 0;
   GOSH_TRY_HIP(hipMemGetInfo(&free_bytes, &total_bytes), "hipMemGetInfo");
   const size_t keep_free = size_t{8} << 30;

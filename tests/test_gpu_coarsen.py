@@ -314,3 +314,16 @@ def test_coarsening_without_pinned_staging():
         for got, want in zip(h.graph(1), ref.graph(1)):
             assert np.array_equal(got, want)
     h.free()
+
+
+def test_matrix_placement_counts_kept_blocks_as_free():
+    """gosh_matrix_place asks how much memory is free: blocks kept from freed hierarchies are."""
+    n = 1 << 18
+    csr = graphgen.to_csr(n, graphgen.rmat(18, 1 << 22, 7)).to("cuda:0")
+    kept = G.lib()._ZN4gosh10block_keptEv
+    kept.restype, kept.argtypes = C.c_size_t, []
+    G.gosh_coarsen_device(n, csr.xadj, csr.adj, threshold=500, min_shrink=0.9).free()
+    assert kept() > 0
+    with pytest.raises(G.GoshError, match="no room for an arena"):
+        G.gosh_matrix_place((1 << 31) - 2, 512)
+    assert kept() == 0
