@@ -36,11 +36,12 @@ int hip_fail(hipError_t e, const char *what);
 // Seams for the library's own tests, one set per thread and not part of gosh.h:
 // gosh_testing(which, value) sets one and returns what it was.
 enum Seam : int32_t {
-  kSeamHotMode,  // written by every launch of the training kernels: its HotMode
-  kSeamDeny,     // memory that is not to be had: a sum of the Deny flags
+  kSeamHotMode,    // written by every launch of the training kernels: its HotMode
+  kSeamDeny,       // memory that is not to be had: a sum of the Deny flags
+  kSeamRadixFrom,  // if not 0: long coarse rows of graphs with more columns are sorted by radix
   kSeams
 };
-enum Deny : int64_t { kDenyLocks = 1, kDenyStaging = 2 };
+enum Deny : int64_t { kDenyLocks = 1, kDenyStaging = 2, kDenyRadix = 4 };
 int64_t &seam(Seam which);
 inline bool denied(Deny what) { return (seam(kSeamDeny) & what) != 0; }
 

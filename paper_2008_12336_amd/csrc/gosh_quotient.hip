@@ -15,6 +15,8 @@
 // number of bits below an entry is the place of its sum.  Rows longer than dense_from(), whose
 // sums would fill the LDS many times over, are counted instead: a word of a table per possible
 // neighbour, added up by workgroups that each take a slice of the row and 2^14 columns ("strip").
+// Both grow with the number of columns; where there are many, the entries of the long rows are
+// radix-sorted as (row, column) keys, equal ones added up, and the rest is as after a merge in place.
 //
 // Sorted distinct entries with summed multiplicities are unique, so the arrays are those of
 // the sequential algorithm.  Against a radix sort of 64-bit (row, column) keys of all entries
@@ -45,10 +47,19 @@ constexpr int kGatherRows = 1024;          // rows of a tile that are looked up 
 // in those of a workgroup.
 constexpr int kSortClasses = 5;
 constexpr int kSortMax[kSortClasses] = {64, 128, 256, 512, 2048};
-enum : int { kBitmap = kSortClasses, kDense, kWays };
+enum : int { kBitmap = kSortClasses, kDense, kRadix, kWays };
 constexpr int kPieceBits = 18, kPieceWords = 1 << (kPieceBits - 5);
 constexpr int kStripBits = 14, kStripsPerPiece = 1 << (kPieceBits - kStripBits);
 constexpr int64_t kSlice = 1 << 16;  // entries of a counted segment that one workgroup takes
+// Columns up to which long segments are worth ranking (each reads its entries once per piece and
+// pays for a bitmap per piece, twice) and counting (once per strip).  Beyond, all are sorted, which does
+// not grow with the columns.  Rebuilds, ms, with ranks / counters, by sort, with all entries sorted as
+// keys (the radix sort this file replaced):
+//   2.0 M columns, 288 M entries 19.0, 16.7, 21.7     2.4 M, 535 M 28.0, 29.9, 38.8
+//   3.4 M, 308 M 27.8, 22.3, 22.7                     21.8 M, 536 M 67.7, 35.0, 42.7
+//   8.4 M, 3.6 G 336, 202, 264
+// twenty segments of millions of entries (counted): 0.8 M columns 6.3, 6.6, 6.6; 6.7 M 57, 18, 18
+constexpr int64_t kRankColumns = int64_t{9} << kPieceBits, kCountColumns = int64_t{4} << kPieceBits;
 constexpr int kSumBytes = 30 << 10;  // LDS for the columns and sums of a piece, as many at a time as fit
 
 // Number of segments per way of merging, 1 + the largest column met, slices of the counted ones.
@@ -201,10 +212,13 @@ __global__ __launch_bounds__(256) void gather_kernel(const OffT *__restrict__ xa
 __global__ __launch_bounds__(1024) void classify_segments_kernel(const int64_t *__restrict__ segment, int64_t n_coarse,
                                                                  int32_t *__restrict__ list,
                                                                  int64_t *__restrict__ length,
-                                                                 Slice *__restrict__ slices,
+                                                                 Slice *__restrict__ slices, int64_t rank_columns,
+                                                                 int64_t count_columns,
                                                                  Classes *__restrict__ classes) {
   __shared__ unsigned int count[kWays], base[kWays];
   const int64_t longest_sorted = bitmap_from(classes->columns), longest_ranked = dense_from(classes->columns);
+  const int ranked = classes->columns > rank_columns ? kRadix : kBitmap;
+  const int counted = classes->columns > count_columns ? kRadix : kDense;
   for (int64_t first = blockIdx.x * 1024LL; first < n_coarse; first += gridDim.x * 1024LL) {
     if (threadIdx.x < kWays) count[threadIdx.x] = 0;
     __syncthreads();
@@ -213,10 +227,10 @@ __global__ __launch_bounds__(1024) void classify_segments_kernel(const int64_t *
     unsigned int mine = 0;
     if (a < n_coarse) {
       const int64_t s = segment[a + 1] - segment[a];
-      if (s > longest_sorted) cls = s <= longest_ranked ? kBitmap : kDense;
+      if (s > longest_sorted) cls = s <= longest_ranked ? ranked : counted;
       else if (s > 0)
         for (cls = 0; s > kSortMax[cls];) ++cls;
-      if (cls < 0 || cls >= kBitmap) length[a] = 0;
+      if (cls < 0 || cls >= kBitmap) length[a] = 0;  // (the radix sort assigns, its stand-in adds)
     }
     if (cls >= 0) mine = atomicAdd(&count[cls], 1u);
     __syncthreads();
@@ -664,6 +678,153 @@ __global__ __launch_bounds__(1024) void dense_strips_kernel(const int32_t *__res
   }
 }
 
+// The radix way: the entries of a list of long segments, each segment a row of its own, and where
+// the merged ones belong.  size[i] = entries of the i-th segment, size[count] = 0.
+__global__ __launch_bounds__(256) void radix_sizes_kernel(const int64_t *__restrict__ segment,
+                                                          const int32_t *__restrict__ list, int64_t count,
+                                                          int64_t *__restrict__ size) {
+  for (int64_t i = blockIdx.x * 256LL + threadIdx.x; i <= count; i += gridDim.x * 256LL)
+    size[i] = i < count ? segment[list[i] + 1LL] - segment[list[i]] : 0;
+}
+
+// key = (place in the list, column); an entry inside its cluster gets the largest column of its row.
+template <typename WT, bool WEIGHTED>
+__global__ __launch_bounds__(256) void radix_keys_kernel(const int64_t *__restrict__ segment,
+                                                         const int32_t *__restrict__ list, int64_t count,
+                                                         const int64_t *__restrict__ from, int64_t entries,
+                                                         unsigned column_bits, const uint32_t *__restrict__ column,
+                                                         const WT *__restrict__ weight, uint64_t *__restrict__ key,
+                                                         WT *__restrict__ value) {
+  __shared__ int32_t first_row;
+  const uint64_t inside = (uint64_t{1} << column_bits) - 1;
+  for (int64_t tile = blockIdx.x * static_cast<int64_t>(kGatherTile); tile < entries;
+       tile += gridDim.x * static_cast<int64_t>(kGatherTile)) {
+    __syncthreads();  // the previous tile's row has been read
+    if (threadIdx.x == 0) first_row = row_of_entry<int64_t>(from, 0, static_cast<int32_t>(count - 1), tile);
+    __syncthreads();
+    int32_t r = first_row;
+    for (int64_t e = tile + threadIdx.x; e < std::min(tile + kGatherTile, entries); e += 256) {
+      while (r + 1 < count && from[r + 1] <= e) ++r;  // a tile spans a few rows: all are long
+      const int64_t at = segment[list[r]] + (e - from[r]);
+      const uint32_t c = column[at];
+      key[e] = (static_cast<uint64_t>(r) << column_bits) | (c == kInside ? inside : c);
+      if constexpr (WEIGHTED) value[e] = weight[at];
+    }
+  }
+}
+
+__device__ inline int64_t first_not_below(const uint64_t *keys, int64_t count, uint64_t key) {
+  int64_t lo = 0, hi = count;
+  while (lo < hi) {
+    const int64_t mid = lo + (hi - lo) / 2;
+    if (keys[mid] < key) lo = mid + 1;
+    else hi = mid;
+  }
+  return lo;
+}
+
+// first[i] = place of the first merged entry of the i-th segment; the lengths without what lies
+// inside the clusters.
+__global__ __launch_bounds__(256) void radix_lengths_kernel(const int32_t *__restrict__ list, int64_t count,
+                                                            unsigned column_bits, const uint64_t *__restrict__ merged,
+                                                            const unsigned long long *__restrict__ merged_count,
+                                                            int64_t *__restrict__ first, int64_t *__restrict__ length) {
+  const int64_t n = static_cast<int64_t>(*merged_count);
+  const uint64_t inside = (uint64_t{1} << column_bits) - 1;
+  for (int64_t i = blockIdx.x * 256LL + threadIdx.x; i < count; i += gridDim.x * 256LL) {
+    const uint64_t row = static_cast<uint64_t>(i) << column_bits;
+    first[i] = first_not_below(merged, n, row);
+    length[list[i]] = first_not_below(merged, n, row | inside) - first[i];
+  }
+}
+
+// The merged entries go to the front of their segments, as the sorting networks leave them.
+template <typename WT>
+__global__ __launch_bounds__(256) void radix_place_kernel(const int64_t *__restrict__ segment,
+                                                          const int32_t *__restrict__ list, unsigned column_bits,
+                                                          const uint64_t *__restrict__ merged,
+                                                          const WT *__restrict__ sums,
+                                                          const unsigned long long *__restrict__ merged_count,
+                                                          const int64_t *__restrict__ first,
+                                                          uint32_t *__restrict__ column, WT *__restrict__ weight) {
+  const int64_t n = static_cast<int64_t>(*merged_count);
+  const uint64_t inside = (uint64_t{1} << column_bits) - 1;
+  for (int64_t u = blockIdx.x * 256LL + threadIdx.x; u < n; u += gridDim.x * 256LL) {
+    const uint64_t key = merged[u], c = key & inside;
+    if (c == inside) continue;
+    const int64_t i = static_cast<int64_t>(key >> column_bits), at = segment[list[i]] + (u - first[i]);
+    column[at] = static_cast<uint32_t>(c);
+    weight[at] = sums[u];
+  }
+}
+
+// GOSH_ENOMEM, with nothing changed, if there is no room for the keys.
+template <typename WT, bool WEIGHTED>
+int merge_by_radix(gosh::Pool &pool, const int64_t *segment, const int32_t *list, int64_t count, int64_t columns,
+                   uint32_t *column, WT *weight, int64_t *length) {
+  gosh::Buffers buf(pool);
+  int64_t *size = nullptr, *from = nullptr;
+  uint64_t *keys = nullptr, *sorted = nullptr;
+  WT *values = nullptr, *sorted_values = nullptr;
+  unsigned long long *merged_count = nullptr;
+  if (gosh::denied(gosh::kDenyRadix)) return GOSH_ENOMEM;
+  unsigned column_bits = 1, row_bits = 1;
+  while (((int64_t{1} << column_bits) - 1) < columns) ++column_bits;
+  while ((count >> row_bits) != 0) ++row_bits;
+  if (int rc = buf.alloc(&size, static_cast<size_t>(count) + 1, "long coarse rows")) return rc;
+  if (int rc = buf.alloc(&from, static_cast<size_t>(count) + 1, "long coarse rows")) return rc;
+  if (int rc = buf.alloc(&merged_count, 1, "merged count")) return rc;
+  const int row_blocks = blocks_for(count + 1, 256);
+  hipLaunchKernelGGL(radix_sizes_kernel, dim3(row_blocks), dim3(256), 0, nullptr, segment, list, count, size);
+  size_t scan_bytes = 0, sort_bytes = 0, reduce_bytes = 0;
+  char *temp = nullptr;
+  GOSH_TRY_HIP(rocprim::exclusive_scan(nullptr, scan_bytes, size, from, int64_t(0), static_cast<size_t>(count) + 1,
+                                       rocprim::plus<int64_t>(), nullptr),
+               "long row scan (size query)");
+  if (int rc = buf.alloc(&temp, scan_bytes, "scan workspace")) return rc;
+  GOSH_TRY_HIP(rocprim::exclusive_scan(temp, scan_bytes, size, from, int64_t(0), static_cast<size_t>(count) + 1,
+                                       rocprim::plus<int64_t>(), nullptr),
+               "long row scan");
+  int64_t entries = 0;
+  GOSH_TRY_HIP(hipMemcpy(&entries, from + count, 8, hipMemcpyDeviceToHost), "read long row entries");
+  buf.release(temp);
+  const size_t total = static_cast<size_t>(entries);
+  if (int rc = buf.alloc(&keys, total, "keys of long rows")) return rc;
+  if (int rc = buf.alloc(&sorted, total, "sorted keys of long rows")) return rc;
+  if (int rc = buf.alloc(&values, total, "multiplicities of long rows")) return rc;
+  if constexpr (WEIGHTED)
+    if (int rc = buf.alloc(&sorted_values, total, "sorted multiplicities of long rows")) return rc;
+  auto sort = [&]() -> hipError_t {
+    if constexpr (WEIGHTED)
+      return rocprim::radix_sort_pairs(temp, sort_bytes, keys, sorted, values, sorted_values, total, 0u,
+                                       column_bits + row_bits, nullptr);
+    else
+      return rocprim::radix_sort_keys(temp, sort_bytes, keys, sorted, total, 0u, column_bits + row_bits, nullptr);
+  };
+  auto reduce = [&]() -> hipError_t {  // where the unsorted ones were
+    if constexpr (WEIGHTED)
+      return rocprim::reduce_by_key(temp, reduce_bytes, sorted, sorted_values, total, keys, values, merged_count,
+                                    rocprim::plus<WT>(), rocprim::equal_to<uint64_t>(), nullptr);
+    else
+      return rocprim::reduce_by_key(temp, reduce_bytes, sorted, rocprim::constant_iterator<WT>(1), total, keys, values,
+                                    merged_count, rocprim::plus<WT>(), rocprim::equal_to<uint64_t>(), nullptr);
+  };
+  temp = nullptr;  // asks for the sizes
+  GOSH_TRY_HIP(sort(), "long row sort (size query)");
+  GOSH_TRY_HIP(reduce(), "long row merge (size query)");
+  if (int rc = buf.alloc(&temp, std::max(sort_bytes, reduce_bytes), "sort workspace")) return rc;
+  hipLaunchKernelGGL((radix_keys_kernel<WT, WEIGHTED>), dim3(blocks_for(entries, kGatherTile)), dim3(256), 0, nullptr,
+                     segment, list, count, from, entries, column_bits, column, weight, keys, values);
+  if (int rc = gosh::check_launch("radix_keys_kernel")) return rc;
+  GOSH_TRY_HIP(sort(), "long row sort");
+  GOSH_TRY_HIP(reduce(), "long row merge");
+  hipLaunchKernelGGL(radix_lengths_kernel, dim3(row_blocks), dim3(256), 0, nullptr, list, count, column_bits, keys,
+                     merged_count, size, length);
+  hipLaunchKernelGGL(radix_place_kernel<WT>, dim3(blocks_for(entries, 1024)), dim3(256), 0, nullptr, segment, list,
+                     column_bits, keys, values, merged_count, size, column, weight);
+  return gosh::check_launch("radix_place_kernel");
+}
+
 // Copies the segments that were merged in place, one wavefront each.
 template <typename WT>
 __global__ __launch_bounds__(256) void copy_merged_kernel(const int64_t *__restrict__ segment,
@@ -680,6 +841,24 @@ __global__ __launch_bounds__(256) void copy_merged_kernel(const int64_t *__restr
     const int64_t lo = segment[a], out = xadj_out[a];
     const int64_t size = xadj_out[a + 1] - out;
     for (int64_t e = lane; e < size; e += 64) {
+      adj_out[out + e] = static_cast<int32_t>(column[lo + e]);
+      mult_out[out + e] = static_cast<int64_t>(weight[lo + e]);
+    }
+  }
+}
+
+// The same for segments of any length: gridDim.y workgroups share one.
+template <typename WT>
+__global__ __launch_bounds__(256) void copy_long_kernel(const int64_t *__restrict__ segment,
+                                                        const int32_t *__restrict__ list, int64_t count,
+                                                        const uint32_t *__restrict__ column,
+                                                        const WT *__restrict__ weight,
+                                                        const int64_t *__restrict__ xadj_out,
+                                                        int32_t *__restrict__ adj_out, int64_t *__restrict__ mult_out) {
+  for (int64_t i = blockIdx.x; i < count; i += gridDim.x) {
+    const int32_t a = list[i];
+    const int64_t lo = segment[a], out = xadj_out[a], size = xadj_out[a + 1] - out;
+    for (int64_t e = blockIdx.y * 256LL + threadIdx.x; e < size; e += gridDim.y * 256LL) {
       adj_out[out + e] = static_cast<int32_t>(column[lo + e]);
       mult_out[out + e] = static_cast<int64_t>(weight[lo + e]);
     }
@@ -749,20 +928,29 @@ int quotient(gosh::DeviceCoarsener *dc, const gosh::DeviceLevel &fine, int64_t n
                     static_cast<void *>(lengths), static_cast<void *>(pos), static_cast<void *>(tile_row), static_cast<void *>(temp)})
       buf.release(p);  // what takes them up again is on the same stream
   }
+  const int64_t radix_from = gosh::seam(gosh::kSeamRadixFrom);
   hipLaunchKernelGGL(classify_segments_kernel, dim3(blocks_for(n_coarse, 1024)), dim3(1024), 0, nullptr, segment,
-                     n_coarse, list, length, slices, classes);
+                     n_coarse, list, length, slices, radix_from ? radix_from : kRankColumns,
+                     radix_from ? radix_from : kCountColumns, classes);
   if (int rc = gosh::check_launch("classify_segments_kernel")) return rc;
   Classes c{};
   GOSH_TRY_HIP(hipMemcpy(&c, classes, sizeof(c), hipMemcpyDeviceToHost), "read segment classes");
 
   // merge: in place, or counted
-  const int32_t *bitmap_list = list + kBitmap * n_coarse, *dense_list = list + kDense * n_coarse;
-  const int64_t bitmaps = c.count[kBitmap], denses = c.count[kDense];
+  bool radix_merged = false;  // the segments of the kRadix list are merged in place
+  if (c.count[kRadix] > 0) {
+    const int rc = merge_by_radix<WT, WEIGHTED>(dc->pool, segment, list + kRadix * n_coarse, c.count[kRadix],
+                                                c.columns, column, weight, length);
+    if (rc != GOSH_OK && rc != GOSH_ENOMEM) return rc;
+    radix_merged = rc == GOSH_OK;
+  }
+  const int32_t *dense_list = list + kDense * n_coarse;
   const int64_t pieces = pieces_of(c.columns), strips = pieces * kStripsPerPiece;
-  uint32_t *in_strip = nullptr, *in_dense_strip = nullptr;
-  WT *table = nullptr;
   const int64_t dense_strips = (static_cast<int64_t>(c.columns) + (1 << kStripBits) - 1) >> kStripBits;
+  const int64_t denses = c.count[kDense];
   const int64_t dense_jobs = denses * dense_strips;
+  uint32_t *in_dense_strip = nullptr;
+  WT *table = nullptr;
   if (denses > 0) {
     const int64_t counters = dense_jobs << kStripBits;
     if (int rc = buf.alloc(&table, static_cast<size_t>(counters), "counters of coarse rows")) return rc;
@@ -778,10 +966,18 @@ int quotient(gosh::DeviceCoarsener *dc, const gosh::DeviceLevel &fine, int64_t n
     hipLaunchKernelGGL((dense_strips_kernel<WT, false>), dim3(static_cast<unsigned>(dense_jobs)), dim3(1024), 0, nullptr,
                        dense_list, dense_strips, table, in_dense_strip, length, xadj_out, nullptr, nullptr);
   }
-  if (bitmaps > 0) {
-    if (int rc = buf.alloc(&in_strip, static_cast<size_t>(bitmaps * strips), "strips of coarse rows")) return rc;
-    hipLaunchKernelGGL(count_pieces_kernel, dim3(blocks_for(bitmaps * pieces, 1)), dim3(512), 0, nullptr, segment,
-                       bitmap_list, bitmaps, pieces, static_cast<int64_t>(c.columns), column, in_strip, length);
+  // the bitmap also takes the segments that there was no memory to sort
+  struct Ranked {
+    const int32_t *list;
+    int64_t count;
+    uint32_t *in_strip;
+  } ranked[2] = {{list + kBitmap * n_coarse, c.count[kBitmap], nullptr},
+                 {list + kRadix * n_coarse, radix_merged ? 0 : c.count[kRadix], nullptr}};
+  for (Ranked &r : ranked) {
+    if (r.count == 0) continue;
+    if (int rc = buf.alloc(&r.in_strip, static_cast<size_t>(r.count * strips), "strips of coarse rows")) return rc;
+    hipLaunchKernelGGL(count_pieces_kernel, dim3(blocks_for(r.count * pieces, 1)), dim3(512), 0, nullptr, segment,
+                       r.list, r.count, pieces, static_cast<int64_t>(c.columns), column, r.in_strip, length);
   }
   auto merge_sorted = [&](auto kernel, int cls, int teams) {
     if (c.count[cls] > 0)
@@ -813,10 +1009,17 @@ int quotient(gosh::DeviceCoarsener *dc, const gosh::DeviceLevel &fine, int64_t n
   if (denses > 0)
     hipLaunchKernelGGL((dense_strips_kernel<WT, true>), dim3(static_cast<unsigned>(dense_jobs)), dim3(1024), 0, nullptr,
                        dense_list, dense_strips, table, in_dense_strip, length, xadj_out, coarse.adj, coarse.mult);
-  if (bitmaps > 0)
-    hipLaunchKernelGGL((write_pieces_kernel<WT, WEIGHTED>), dim3(blocks_for(bitmaps * pieces, 1)), dim3(1024), 0,
-                       nullptr, segment, bitmap_list, bitmaps, pieces,
-                       static_cast<int64_t>(c.columns), column, weight, in_strip, xadj_out, coarse.adj, coarse.mult);
+  for (const Ranked &r : ranked)
+    if (r.count > 0)
+      hipLaunchKernelGGL((write_pieces_kernel<WT, WEIGHTED>), dim3(blocks_for(r.count * pieces, 1)), dim3(1024), 0,
+                         nullptr, segment, r.list, r.count, pieces, static_cast<int64_t>(c.columns), column, weight,
+                         r.in_strip, xadj_out, coarse.adj, coarse.mult);
+  if (radix_merged) {
+    const int rows = static_cast<int>(std::min<int64_t>(c.count[kRadix], 65536));
+    hipLaunchKernelGGL(copy_long_kernel<WT>, dim3(rows, std::min(std::max(65536 / rows, 1), 1024)), dim3(256), 0, nullptr,
+                       segment, list + kRadix * n_coarse, static_cast<int64_t>(c.count[kRadix]), column, weight, xadj_out,
+                       coarse.adj, coarse.mult);
+  }
   for (int cls = kSortClasses - 1; cls >= 0; --cls)
     if (c.count[cls] > 0)
       hipLaunchKernelGGL(copy_merged_kernel<WT>, dim3(blocks_for(c.count[cls], 4)), dim3(256), 0, nullptr, segment,

@@ -11,7 +11,7 @@ import graphgen
 import paper_2008_12336_amd as G
 from oracle import gosh_oracle as O
 from tests.test_coarsen import _ring_lattice, assert_same_hierarchy
-from tests.util import DENY_STAGING, SEAM_DENY, csr_from_pairs, seam
+from tests.util import DENY_RADIX, DENY_STAGING, SEAM_DENY, SEAM_RADIX_FROM, csr_from_pairs, seam
 
 pytestmark = pytest.mark.gpu
 
@@ -327,3 +327,79 @@ def test_matrix_placement_counts_kept_blocks_as_free():
     with pytest.raises(G.GoshError, match="no room for an arena"):
         G.gosh_matrix_place((1 << 31) - 2, 512)
     assert kept() == 0
+
+
+def wide_graph(hubs, lengths, seed):
+    """hub_graph for many hubs: the rows of the first ones reach over all of them."""
+    rng = np.random.default_rng(seed)
+    leaves = hubs + np.arange(3 * hubs)
+    second = leaves[rng.random(3 * hubs) < 0.7]
+    u = np.concatenate((np.repeat(np.arange(len(lengths)), lengths), np.arange(hubs), np.repeat(np.arange(hubs), 3),
+                        rng.integers(0, hubs, second.size)))
+    v = np.concatenate((rng.integers(0, hubs, sum(lengths)), (np.arange(hubs) + 1) % hubs, leaves, second))
+    n = 4 * hubs
+    key = np.unique((np.minimum(u, v) * n + np.maximum(u, v))[u != v])
+    return graphgen.to_csr(n, torch.from_numpy(np.stack((key // n, key % n), 1)))
+
+
+def assert_equals_host(csr, levels=None, **kw):
+    n = csr.xadj.numel() - 1
+    h = G.gosh_coarsen_device(n, csr.xadj, csr.adj, **kw)
+    ref = G.gosh_coarsen(n, csr.xadj, csr.adj, **kw)
+    assert h.levels == ref.levels >= (levels or 2)
+    for i in range(h.levels):
+        if i + 1 < h.levels:
+            assert np.array_equal(h.map(i), ref.map(i))
+        for got, want in zip(h.graph(i), ref.graph(i)):
+            assert np.array_equal(got, want)
+        if i:
+            assert np.array_equal(h.mult(i), ref.mult(i))
+    h.free()
+
+
+@pytest.fixture(scope="module")
+def long_rows():
+    """300,000 columns, two pieces of 2^18, and rows on both sides of their border; the longest
+    coarse row has 226,000 entries, four slices of 2^16."""
+    return wide_graph(300_000, [2040, 2060, 9000, 36000, 39000, 70000, 200_000, 420_000], 5)
+
+
+@pytest.mark.parametrize("how", ["ranked and counted", "by radix", "no memory to sort"])
+def test_long_rows_over_several_pieces(long_rows, how):
+    with seam(SEAM_RADIX_FROM, 0 if how == "ranked and counted" else 1), \
+            seam(SEAM_DENY, DENY_RADIX if how == "no memory to sort" else 0):
+        assert_equals_host(long_rows, 4, threshold=4, min_shrink=1.0)
+
+
+def test_rebuild_of_wide_graphs_costs_no_more_than_sorting_their_entries():
+    """Twenty vertices of four million neighbours among seven million coarse ones: reading their rows
+    once per range of columns took three times a sort of all entries."""
+    n, dev = 32_000_000, "cuda:0"
+    g = torch.Generator(device=dev)
+    g.manual_seed(1)
+    draw = lambda hi, m: torch.randint(0, hi, (m,), generator=g, device=dev)
+    u, v = torch.cat((draw(20, 80_000_000), draw(n, 64_000_000))), draw(n, 144_000_000)
+    u, v = u[u != v], v[u != v]
+    key = torch.unique(torch.cat((u * n + v, v * n + u)))
+    del u, v
+    adj = (key % n).to(torch.int32)
+    xadj = torch.searchsorted(key, torch.arange(n + 1, device=dev) * n)
+    key = key[torch.randperm(key.numel(), generator=g, device=dev, dtype=torch.int64)]
+    sort_ms = []
+    for _ in range(2):  # the first one also gets its memory
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        a.record()
+        torch.sort(key)
+        b.record()
+        torch.cuda.synchronize()
+        sort_ms.append(a.elapsed_time(b))
+    del key
+    torch.cuda.empty_cache()
+    build_ms = []
+    for _ in range(2):
+        h = G.gosh_coarsen_device(n, xadj, adj, threshold=10_000, min_shrink=0.8, max_levels=2)
+        assert h.shape(1)[0] > 6_000_000
+        build_ms.append(h.times(0)["build_ms"])
+        h.free()
+    print(f"[wide] rebuild {min(build_ms):.1f} ms, sort of its {adj.numel()} entries {min(sort_ms):.1f} ms")
+    assert min(build_ms) <= 1.25 * min(sort_ms)

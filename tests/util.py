@@ -105,8 +105,8 @@ def conditioned_bar(sensitivity):
 
 
 # Seams of the library for its own tests (gosh_common.h), of the calling thread.
-SEAM_HOT_MODE, SEAM_DENY = range(2)
-DENY_LOCKS, DENY_STAGING = 1, 2
+SEAM_HOT_MODE, SEAM_DENY, SEAM_RADIX_FROM = range(3)
+DENY_LOCKS, DENY_STAGING, DENY_RADIX = 1, 2, 4
 HOT_NONE, HOT_BITMAP, HOT_ALL, HOT_LOCKED = range(4)
 
 
