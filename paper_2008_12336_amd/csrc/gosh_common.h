@@ -41,7 +41,7 @@ enum Seam : int32_t {
   kSeamRadixFrom,  // if not 0: long coarse rows of graphs with more columns are sorted by radix
   kSeams
 };
-enum Deny : int64_t { kDenyLocks = 1, kDenyStaging = 2, kDenyRadix = 4 };
+enum Deny : int64_t { kDenyLocks = 1, kDenyStaging = 2, kDenyRadix = 4, kDenyTable = 8 };
 int64_t &seam(Seam which);
 inline bool denied(Deny what) { return (seam(kSeamDeny) & what) != 0; }
 

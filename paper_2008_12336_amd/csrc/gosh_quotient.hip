@@ -22,7 +22,8 @@
 // the sequential algorithm.  Against a radix sort of 64-bit (row, column) keys of all entries
 // and a reduction of equal keys, which this replaced: 128 M entries of a 4 M-vertex R-MAT graph
 // took 8.9 ms and take 4.4, 117 M weighted entries of its second level 10.5 and 4.2; 8 (wide
-// sums: 12) bytes of scratch per entry, and the table, instead of 32.  A third of it is the gather.
+// sums: 12) bytes of scratch per entry instead of 32, 16 more per entry of a row that is counted and
+// 24 (32) of one that is sorted by radix.  A third of it is the gather.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -87,8 +88,11 @@ __host__ __device__ inline int64_t bitmap_from(int64_t columns) {
 }
 
 // Longest segment whose sums are placed by rank.  Every kSumBytes of sums read the segment again,
-// in one workgroup; the counters of a longer one take up to eight words per entry.
-__host__ __device__ inline int64_t dense_from(int64_t columns) { return std::max<int64_t>(1 << 15, columns / 8); }
+// in one workgroup; the counters of a longer one take at most 16 bytes per entry.
+__host__ __device__ inline int64_t dense_from(int64_t columns, int sum_bytes) {
+  const int64_t strips = (columns + (1 << kStripBits) - 1) >> kStripBits;
+  return std::max<int64_t>(1 << 15, (strips << kStripBits) * sum_bytes / 16);
+}
 
 // A slice of a counted segment: its place in the list, and which of its slices.
 struct Slice {
@@ -213,10 +217,10 @@ __global__ __launch_bounds__(1024) void classify_segments_kernel(const int64_t *
                                                                  int32_t *__restrict__ list,
                                                                  int64_t *__restrict__ length,
                                                                  Slice *__restrict__ slices, int64_t rank_columns,
-                                                                 int64_t count_columns,
+                                                                 int64_t count_columns, int sum_bytes,
                                                                  Classes *__restrict__ classes) {
   __shared__ unsigned int count[kWays], base[kWays];
-  const int64_t longest_sorted = bitmap_from(classes->columns), longest_ranked = dense_from(classes->columns);
+  const int64_t longest_sorted = bitmap_from(classes->columns), longest_ranked = dense_from(classes->columns, sum_bytes);
   const int ranked = classes->columns > rank_columns ? kRadix : kBitmap;
   const int counted = classes->columns > count_columns ? kRadix : kDense;
   for (int64_t first = blockIdx.x * 1024LL; first < n_coarse; first += gridDim.x * 1024LL) {
@@ -931,7 +935,7 @@ int quotient(gosh::DeviceCoarsener *dc, const gosh::DeviceLevel &fine, int64_t n
   const int64_t radix_from = gosh::seam(gosh::kSeamRadixFrom);
   hipLaunchKernelGGL(classify_segments_kernel, dim3(blocks_for(n_coarse, 1024)), dim3(1024), 0, nullptr, segment,
                      n_coarse, list, length, slices, radix_from ? radix_from : kRankColumns,
-                     radix_from ? radix_from : kCountColumns, classes);
+                     radix_from ? radix_from : kCountColumns, static_cast<int>(sizeof(WT)), classes);
   if (int rc = gosh::check_launch("classify_segments_kernel")) return rc;
   Classes c{};
   GOSH_TRY_HIP(hipMemcpy(&c, classes, sizeof(c), hipMemcpyDeviceToHost), "read segment classes");
@@ -947,13 +951,15 @@ int quotient(gosh::DeviceCoarsener *dc, const gosh::DeviceLevel &fine, int64_t n
   const int32_t *dense_list = list + kDense * n_coarse;
   const int64_t pieces = pieces_of(c.columns), strips = pieces * kStripsPerPiece;
   const int64_t dense_strips = (static_cast<int64_t>(c.columns) + (1 << kStripBits) - 1) >> kStripBits;
-  const int64_t denses = c.count[kDense];
+  int64_t denses = c.count[kDense];
   const int64_t dense_jobs = denses * dense_strips;
   uint32_t *in_dense_strip = nullptr;
   WT *table = nullptr;
+  const int64_t counters = dense_jobs << kStripBits;
+  if (denses > 0 && (gosh::denied(gosh::kDenyTable) ||
+                     buf.alloc(&table, static_cast<size_t>(counters), "counters of coarse rows") != GOSH_OK))
+    denses = 0;
   if (denses > 0) {
-    const int64_t counters = dense_jobs << kStripBits;
-    if (int rc = buf.alloc(&table, static_cast<size_t>(counters), "counters of coarse rows")) return rc;
     if (int rc = buf.alloc(&in_dense_strip, static_cast<size_t>(dense_jobs), "strips of coarse rows")) return rc;
     const int64_t units = counters * static_cast<int64_t>(sizeof(WT)) / 16;
     hipLaunchKernelGGL(clear_table_kernel, dim3(blocks_for(units, 256)), dim3(256), 0, nullptr,
@@ -966,12 +972,13 @@ int quotient(gosh::DeviceCoarsener *dc, const gosh::DeviceLevel &fine, int64_t n
     hipLaunchKernelGGL((dense_strips_kernel<WT, false>), dim3(static_cast<unsigned>(dense_jobs)), dim3(1024), 0, nullptr,
                        dense_list, dense_strips, table, in_dense_strip, length, xadj_out, nullptr, nullptr);
   }
-  // the bitmap also takes the segments that there was no memory to sort
+  // the bitmap also takes the segments that there was no memory to sort or to count
   struct Ranked {
     const int32_t *list;
     int64_t count;
     uint32_t *in_strip;
-  } ranked[2] = {{list + kBitmap * n_coarse, c.count[kBitmap], nullptr},
+  } ranked[3] = {{list + kBitmap * n_coarse, c.count[kBitmap], nullptr},
+                 {dense_list, denses > 0 ? 0 : c.count[kDense], nullptr},
                  {list + kRadix * n_coarse, radix_merged ? 0 : c.count[kRadix], nullptr}};
   for (Ranked &r : ranked) {
     if (r.count == 0) continue;

@@ -11,7 +11,7 @@ import graphgen
 import paper_2008_12336_amd as G
 from oracle import gosh_oracle as O
 from tests.test_coarsen import _ring_lattice, assert_same_hierarchy
-from tests.util import DENY_RADIX, DENY_STAGING, SEAM_DENY, SEAM_RADIX_FROM, csr_from_pairs, seam
+from tests.util import DENY_RADIX, DENY_STAGING, DENY_TABLE, SEAM_DENY, SEAM_RADIX_FROM, csr_from_pairs, seam
 
 pytestmark = pytest.mark.gpu
 
@@ -364,10 +364,14 @@ def long_rows():
     return wide_graph(300_000, [2040, 2060, 9000, 36000, 39000, 70000, 200_000, 420_000], 5)
 
 
-@pytest.mark.parametrize("how", ["ranked and counted", "by radix", "no memory to sort"])
-def test_long_rows_over_several_pieces(long_rows, how):
-    with seam(SEAM_RADIX_FROM, 0 if how == "ranked and counted" else 1), \
-            seam(SEAM_DENY, DENY_RADIX if how == "no memory to sort" else 0):
+# SEAM_RADIX_FROM, SEAM_DENY
+WAYS = {"ranked and counted": (0, 0), "by radix": (1, 0), "no memory to sort": (1, DENY_RADIX),
+        "no memory to count": (0, DENY_TABLE)}
+
+
+@pytest.mark.parametrize("way", sorted(WAYS))
+def test_long_rows_over_several_pieces(long_rows, way):
+    with seam(SEAM_RADIX_FROM, WAYS[way][0]), seam(SEAM_DENY, WAYS[way][1]):
         assert_equals_host(long_rows, 4, threshold=4, min_shrink=1.0)
 
 

@@ -106,7 +106,7 @@ def conditioned_bar(sensitivity):
 
 # Seams of the library for its own tests (gosh_common.h), of the calling thread.
 SEAM_HOT_MODE, SEAM_DENY, SEAM_RADIX_FROM = range(3)
-DENY_LOCKS, DENY_STAGING, DENY_RADIX = 1, 2, 4
+DENY_LOCKS, DENY_STAGING, DENY_RADIX, DENY_TABLE = 1, 2, 4, 8
 HOT_NONE, HOT_BITMAP, HOT_ALL, HOT_LOCKED = range(4)
 
 
