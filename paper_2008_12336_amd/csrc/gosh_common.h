@@ -39,6 +39,9 @@ enum Seam : int32_t {
   kSeamHotMode,    // written by every launch of the training kernels: its HotMode
   kSeamDeny,       // memory that is not to be had: a sum of the Deny flags
   kSeamRadixFrom,  // if not 0: long coarse rows of graphs with more columns are sorted by radix
+  kSeamWideSums,   // if not 0: multiplicities are summed in 64 bits from this weight on
+  kSeamLockTries,  // if not 0: tries of a row lock before an update is added without it
+  kSeamLocksHeld,  // if not 0: every lock of an epoch is held (1) or free (2) when its launch begins
   kSeams
 };
 enum Deny : int64_t { kDenyLocks = 1, kDenyStaging = 2, kDenyRadix = 4, kDenyTable = 8 };

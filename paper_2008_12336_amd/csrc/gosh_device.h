@@ -273,15 +273,18 @@ struct SgdArgs {
   int32_t k_neg;    // sample t of a source is a positive iff t % (k_neg + 1) == 0
   int32_t samples;  // samples per source: k_neg + 1 per round
   float lr;
+  int32_t max_tries;  // of a row lock
   int64_t sources_per_block;  // consecutive sources that one workgroup walks (a multiple of
                               // the sources that its wavefronts take per turn)
 };
 
 constexpr int kChunk = 4;  // sample rows in flight per source
-// Tries of a lock before an update is added without it.  Every holder lets go after its own
-// memory accesses and waits for no other lock meanwhile, so this is never reached in practice; it
-// bounds the kernel's time whatever the lock words hold.
+// Tries of a lock before an update is added without it, and may be lost to the holder's store like
+// any update of the lock-free scheme.  Every holder lets go after its own memory accesses and waits
+// for no other lock meanwhile, and a row that many want is a hub, so this is not reached; it bounds
+// the kernel's time whatever the lock words hold.
 constexpr int32_t kMaxTries = 1 << 14;
+inline int32_t lock_tries() { return seam(kSeamLockTries) ? static_cast<int32_t>(seam(kSeamLockTries)) : kMaxTries; }
 
 // Atomic adds of whole rows with 128-bit units, one row at a time by the whole wavefront.
 // A memory-side fp32 atomic costs one operation per instruction and line it touches, full or
@@ -580,7 +583,7 @@ __device__ __forceinline__ void sgd_walk(const W &w, const SgdArgs &a) {
           const int32_t slot = want ? w.sample_slot(idx, id) : 0;
           if (__ballot(want) == 0) break;  // the same for the whole wavefront
           const bool locked = try_lock(want && !hub, slot);
-          const bool add = want && (hub || (!locked && tries >= kMaxTries));
+          const bool add = want && (hub || (!locked && tries >= a.max_tries));
           const bool apply = locked || add;
           float *const row = apply ? w.sample_row(idx, id) : src_row;
 #pragma unroll
@@ -714,7 +717,7 @@ __device__ __forceinline__ void sgd_walk(const W &w, const SgdArgs &a) {
       // the source's change, added to its row as it is now
       const bool hub = live && src_word > a.hot.most;
       bool locked = false;
-      for (int32_t tries = 0; tries < kMaxTries; ++tries) {
+      for (int32_t tries = 0; tries < a.max_tries; ++tries) {
         if (__ballot(live && !hub && !locked) == 0) break;  // the same for the whole wavefront
         if (try_lock(live && !hub && !locked, src_slot)) {
           locked = true;

@@ -188,6 +188,10 @@ int lock_scratch(int64_t rows, LockWords *out) {
     }
     w = Words{static_cast<uint32_t *>(p), want, {0, 0}, 0};
   }
+  if (const int64_t held = seam(kSeamLocksHeld)) {
+    if (hipMemset(w.base, held == 1, static_cast<size_t>(w.rows) * 4) != hipSuccess || hipDeviceSynchronize() != hipSuccess)
+      return fail(GOSH_EHIP, "cannot set the row locks");
+  }
   w.turn ^= 1;
   *out = LockWords{w.base, w.base + w.rows * (1 + w.turn), w.base + w.rows * (2 - w.turn), w.counted[w.turn ^ 1]};
   w.counted[w.turn] = rows;

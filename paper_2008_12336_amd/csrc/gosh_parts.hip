@@ -794,6 +794,7 @@ class Rotation {
     args.d = pl.d;
     args.k_neg = pl.k_neg;
     args.samples = samples;
+    args.max_tries = gosh::lock_tries();
     args.lr = gosh_lr(pl.lr0, v.rot, pl.rotations);
     const int timer = static_cast<int>(vi % kTimers);
     if (k_pending[timer]) {

@@ -1070,7 +1070,8 @@ int device_rebuild(DeviceCoarsener *dc, const DeviceLevel &fine, int64_t n_coars
     return GOSH_OK;
   }
   const bool weighted = fine.mult != nullptr;
-  if (fine.weight < kWideSumsFrom)
+  const int64_t wide_from = seam(kSeamWideSums) ? seam(kSeamWideSums) : kWideSumsFrom;
+  if (fine.weight < wide_from)
     return weighted ? quotient_by_offsets<uint32_t, true>(dc, fine, n_coarse, coarse, xadj_out)
                     : quotient_by_offsets<uint32_t, false>(dc, fine, n_coarse, coarse, xadj_out);
   return weighted ? quotient_by_offsets<unsigned long long, true>(dc, fine, n_coarse, coarse, xadj_out)

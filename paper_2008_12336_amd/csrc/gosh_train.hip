@@ -447,6 +447,7 @@ int launch_epoch(const gosh_csr *g, float *M, int32_t d, int32_t k_neg, float lr
   a.k_neg = k_neg;
   a.samples = k_neg + 1;
   a.lr = lr;
+  a.max_tries = gosh::lock_tries();
   a.hot = gosh::HotSet{nullptr, gosh::kHotNone, nullptr};
   const int64_t max_waves = tune.max_waves;
   if (concurrent_paths) {

@@ -11,7 +11,7 @@ import graphgen
 import paper_2008_12336_amd as G
 from oracle import gosh_oracle as O
 from tests.test_coarsen import _ring_lattice, assert_same_hierarchy
-from tests.util import DENY_RADIX, DENY_STAGING, DENY_TABLE, SEAM_DENY, SEAM_RADIX_FROM, csr_from_pairs, seam
+from tests.util import DENY_RADIX, DENY_STAGING, DENY_TABLE, SEAM_DENY, SEAM_RADIX_FROM, SEAM_WIDE_SUMS, csr_from_pairs, seam
 
 pytestmark = pytest.mark.gpu
 
@@ -231,19 +231,11 @@ def hub_graph(hubs, edges_of, seed):
     return graphgen.to_csr(nxt, torch.tensor(sorted(pairs), dtype=torch.int64))
 
 
-@pytest.mark.parametrize("lengths", [range(20, 44), [*range(140, 250, 2), 1024], [2000, 2040, 2100, 9000, 17000, 40000]])
-def test_coarse_rows_of_every_way_of_merging(lengths):
-    """Rows around the lengths at which the rebuild changes its way (64, 128, 256, 512 entries: one
-    to eight per lane of a wavefront; 2,048: a workgroup; then a bitmap; from 32,768 counters),
-    level by level with growing multiplicities, against gosh_coarsen."""
-    lengths = list(lengths)
-    hubs = max(64, 3 * max(lengths))
-    edges = [lengths[a] if a < len(lengths) else 3 for a in range(hubs)]
-    csr = hub_graph(hubs, edges, 5)
+def assert_equals_host(csr, levels=None, **kw):
     n = csr.xadj.numel() - 1
-    h = G.gosh_coarsen_device(n, csr.xadj, csr.adj, threshold=4, min_shrink=1.0)
-    ref = G.gosh_coarsen(n, csr.xadj, csr.adj, threshold=4, min_shrink=1.0)
-    assert h.levels == ref.levels >= 3
+    h = G.gosh_coarsen_device(n, csr.xadj, csr.adj, **kw)
+    ref = G.gosh_coarsen(n, csr.xadj, csr.adj, **kw)
+    assert h.levels == ref.levels >= (levels or 2)
     for i in range(h.levels):
         if i + 1 < h.levels:
             assert np.array_equal(h.map(i), ref.map(i))
@@ -251,6 +243,20 @@ def test_coarse_rows_of_every_way_of_merging(lengths):
             assert np.array_equal(got, want)
         if i:
             assert np.array_equal(h.mult(i), ref.mult(i))
+    h.free()
+
+
+@pytest.mark.parametrize("wide_sums", [0, 1])
+@pytest.mark.parametrize("lengths", [range(20, 44), [*range(140, 250, 2), 1024], [2000, 2040, 2100, 9000, 17000, 40000]])
+def test_coarse_rows_of_every_way_of_merging(lengths, wide_sums):
+    """Rows around the lengths at which the rebuild changes its way (64, 128, 256, 512 entries: one
+    to eight per lane of a wavefront; 2,048: a workgroup; then a bitmap; from 32,768 counters),
+    level by level with growing multiplicities, against gosh_coarsen."""
+    lengths = list(lengths)
+    hubs = max(64, 3 * max(lengths))
+    edges = [lengths[a] if a < len(lengths) else 3 for a in range(hubs)]
+    with seam(SEAM_WIDE_SUMS, wide_sums):
+        assert_equals_host(hub_graph(hubs, edges, 5), 3, threshold=4, min_shrink=1.0)
 
 
 def test_blocks_of_freed_hierarchies_are_reused_bounded_and_given_back():
@@ -342,21 +348,6 @@ def wide_graph(hubs, lengths, seed):
     return graphgen.to_csr(n, torch.from_numpy(np.stack((key // n, key % n), 1)))
 
 
-def assert_equals_host(csr, levels=None, **kw):
-    n = csr.xadj.numel() - 1
-    h = G.gosh_coarsen_device(n, csr.xadj, csr.adj, **kw)
-    ref = G.gosh_coarsen(n, csr.xadj, csr.adj, **kw)
-    assert h.levels == ref.levels >= (levels or 2)
-    for i in range(h.levels):
-        if i + 1 < h.levels:
-            assert np.array_equal(h.map(i), ref.map(i))
-        for got, want in zip(h.graph(i), ref.graph(i)):
-            assert np.array_equal(got, want)
-        if i:
-            assert np.array_equal(h.mult(i), ref.mult(i))
-    h.free()
-
-
 @pytest.fixture(scope="module")
 def long_rows():
     """300,000 columns, two pieces of 2^18, and rows on both sides of their border; the longest
@@ -369,9 +360,12 @@ WAYS = {"ranked and counted": (0, 0), "by radix": (1, 0), "no memory to sort": (
         "no memory to count": (0, DENY_TABLE)}
 
 
+@pytest.mark.parametrize("wide_sums", [0, 1])
 @pytest.mark.parametrize("way", sorted(WAYS))
-def test_long_rows_over_several_pieces(long_rows, way):
-    with seam(SEAM_RADIX_FROM, WAYS[way][0]), seam(SEAM_DENY, WAYS[way][1]):
+def test_long_rows_over_several_pieces(long_rows, way, wide_sums):
+    """Every way of merging long rows, with 32-bit sums and with the 64-bit ones of graphs of 2^32
+    entries and more (other LDS sizes, exchanges and atomics)."""
+    with seam(SEAM_RADIX_FROM, WAYS[way][0]), seam(SEAM_DENY, WAYS[way][1]), seam(SEAM_WIDE_SUMS, wide_sums):
         assert_equals_host(long_rows, 4, threshold=4, min_shrink=1.0)
 
 

@@ -7,8 +7,9 @@ import torch
 
 import paper_2008_12336_amd as G
 from oracle import gosh_oracle as O
+from tests.test_gpu_hot_mode import ring
 from tests.test_gpu_layout import DEV, SEQ_LAYOUT, TOL, say, start_matrix, upload
-from tests.util import rel_err
+from tests.util import HOT_ALL, HOT_LOCKED, SEAM_LOCK_TRIES, SEAM_LOCKS_HELD, last_hot_mode, rel_err, seam
 
 pytestmark = pytest.mark.gpu
 
@@ -33,6 +34,19 @@ def milliseconds(run):
         torch.cuda.synchronize()
         times.append(a.elapsed_time(b))
     return min(times)
+
+
+def assert_first_order(M, before, want, g, k, epoch):
+    """Every row within 2 % of its own movement of the sequential result, and what the roundings of
+    that many updates of a row can add up to."""
+    step = np.abs(want.astype(np.float64) - before).max(axis=1)
+    err = np.abs(M.cpu().numpy().astype(np.float64) - want).max(axis=1)
+    say(f"[contended] d={M.shape[1]}: worst err/step {np.max(err / np.maximum(step, 1e-30)):.3e}")
+    ids = torch.empty(g.n * (k + 1), dtype=torch.int32, device=DEV)
+    G.gosh_sample_epoch(g, k, 77, epoch, 1, ids)
+    ids = ids.cpu().numpy()
+    updates = np.bincount(ids[ids >= 0], minlength=g.n) + k + 2
+    assert (err <= 0.02 * step + updates * 2.0 ** -23 * np.abs(before).max()).all()
 
 
 @pytest.mark.parametrize("sinks", [1, 40])
@@ -88,12 +102,61 @@ def test_rows_drawn_often_lose_no_update(d, n, k):
         O.train_epoch(xadj, adj, want, k, 1e-5, 77, epoch, 1)
         G.gosh_train_epoch(g, M, k, 1e-5, 77, epoch, 1)
         torch.cuda.synchronize()
-        step = np.abs(want.astype(np.float64) - before).max(axis=1)
-        err = np.abs(M.cpu().numpy().astype(np.float64) - want).max(axis=1)
-        say(f"[contended] d={d}: worst err/step {np.max(err / np.maximum(step, 1e-30)):.3e}")
-        # first order, and what the roundings of that many updates of a row can add up to
-        ids = torch.empty(n * (k + 1), dtype=torch.int32, device=DEV)
-        G.gosh_sample_epoch(g, k, 77, epoch, 1, ids)
-        ids = ids.cpu().numpy()
-        updates = np.bincount(ids[ids >= 0], minlength=n) + k + 2
-        assert (err <= 0.02 * step + updates * 2.0 ** -23 * np.abs(before).max()).all()
+        assert_first_order(M, before, want, g, k, epoch)
+
+
+@pytest.mark.parametrize("d,n,k", [(64, 50_000, 11), (100, 29_000, 11), (128, 40_000, 3), (260, 13_500, 6)])
+def test_updates_whose_lock_cannot_be_had_are_added(d, n, k):
+    """Every lock held when the launch begins and nobody to let go: the tries end and every update is
+    added, the source's own change too.  As nothing is stored then, nothing is lost: the sequential
+    result in sequential order and, concurrent, the bar of the all-atomic epoch."""
+    xadj, adj = sink_graph(n, 30, 4, 9)
+    g, keep = upload(n, xadj, adj, False)
+    M0 = start_matrix(n, d, 5, 0.5)
+    try:
+        with seam(SEAM_LOCK_TRIES, 2), seam(SEAM_LOCKS_HELD, 1):
+            for lr, flags in ((0.02, SEQ_LAYOUT), (1e-5, 0)):
+                want = M0.copy()
+                O.train_epoch(xadj, adj, want, k, lr, 77, 0, 1)
+                M = torch.from_numpy(M0).to(DEV)
+                G.gosh_train_epoch(g, M, k, lr, 77, 0, 1, flags)
+                torch.cuda.synchronize()
+                assert last_hot_mode() == HOT_LOCKED
+                if flags:
+                    assert rel_err(M.cpu().numpy(), want) <= TOL
+                else:
+                    assert_first_order(M, M0, want, g, k, 0)
+    finally:
+        with seam(SEAM_LOCKS_HELD, 2):
+            G.gosh_train_epoch(g, M, k, 1e-5, 77, 0, 1)
+            torch.cuda.synchronize()
+
+
+@pytest.mark.parametrize("d,n", [(64, 185_000), (100, 106_000), (128, 92_000), (512, 22_000)])
+def test_infinities_and_nan_under_locks(d, n):
+    """Rows that hold what is no number spread it as they do with adds, in sequential order entry by
+    entry: the same entries finite, and those the same numbers.  No negatives and a ring, so that it
+    does not reach everywhere."""
+    rng = np.random.default_rng(2)
+    xadj, adj = ring(n)
+    g, keep = upload(n, xadj, adj, False)
+    M0 = start_matrix(n, d, 5, 0.5)
+    for v, x in zip(rng.choice(n, 40, replace=False), [np.nan, np.inf, -np.inf, 3e38] * 10):
+        M0[v, rng.integers(0, d)] = x
+    got = []
+    G.gosh_set_tuning(hot_all_inv_eps=64)  # every row is hot also without negatives
+    try:
+        for flags in (SEQ_LAYOUT, SEQ_LAYOUT | G.GOSH_FLAG_ATOMIC_ADDS):
+            M = torch.from_numpy(M0.copy()).to(DEV)
+            G.gosh_train_epoch(g, M, 0, 1e-3, 77, 0, 1, flags)
+            torch.cuda.synchronize()
+            assert last_hot_mode() == (HOT_LOCKED if flags == SEQ_LAYOUT else HOT_ALL)
+            got.append(M.cpu().numpy())
+    finally:
+        G.gosh_set_tuning()
+    finite = [np.isfinite(x) for x in got]
+    hit = (~finite[0]).any(axis=1).sum()
+    say(f"[contended] d={d}: {hit} rows with entries that are no numbers")
+    assert np.array_equal(*finite) and 40 <= hit < n / 2
+    ok = finite[0] & (np.abs(got[1]) < 1e3)
+    assert rel_err(np.where(ok, got[0], 0), np.where(ok, got[1], 0)) <= TOL
