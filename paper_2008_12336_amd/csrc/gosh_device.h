@@ -196,11 +196,16 @@ struct HotSet {
   const uint32_t *bits;  // one bit per vertex when mode is kHotBitmap (hot); in the other modes still
                          // a readable device word (the kernel reads word 0 blindly)
   int32_t mode;
-  // in kHotLocked mode, a word each per row: a lock, 0 before and after a launch, and how often the
-  // row is drawn (see most_draws); a hub is a row of which that is above `most`
-  uint32_t *locks;
-  const uint32_t *draws;
-  uint32_t most;
+};
+
+// What a launch in kHotLocked mode needs besides.  A word each per row: a lock, 0 before and after
+// the launch, and how often the row is drawn (see most_draws); a hub is a row of which that is above
+// `most`.  An argument of its own: the other kernels start a little sooner without it.
+struct LockSet {
+  uint32_t *locks = nullptr;
+  const uint32_t *draws = nullptr;
+  uint32_t most = 0;
+  int32_t max_tries = 0;  // of a lock
 };
 
 // Whether a launch in which every row is hot takes locks.  `capacity` sources run at a time (C when
@@ -220,9 +225,10 @@ struct HotSet {
 inline bool worth_locking(int64_t sources, int64_t samples, int64_t capacity, int32_t d) {
   const int64_t blocks = (d + 15) / 16;
   if (blocks < 3) return false;
-  const double saved = blocks == 3 ? 0.3 : static_cast<double>(blocks * capacity) / 131072.0 - 0.1;
+  const double full = static_cast<double>(blocks * capacity) / 131072.0;
+  const double saved = blocks == 3 ? 0.3 : std::min(full, full * full);
   return static_cast<double>(sources) * saved >=
-         static_cast<double>(capacity) * (1.0 + 4.0 / static_cast<double>(samples));
+         static_cast<double>(capacity) * (0.9 + 3.6 / static_cast<double>(samples));
 }
 
 // Hubs.  Whoever holds a row keeps the others waiting for about as long as a source takes for one
@@ -273,7 +279,6 @@ struct SgdArgs {
   int32_t k_neg;    // sample t of a source is a positive iff t % (k_neg + 1) == 0
   int32_t samples;  // samples per source: k_neg + 1 per round
   float lr;
-  int32_t max_tries;  // of a row lock
   int64_t sources_per_block;  // consecutive sources that one workgroup walks (a multiple of
                               // the sources that its wavefronts take per turn)
 };
@@ -391,7 +396,7 @@ struct ChunkPos {
 // more to locks that are held longer: 67,000 vertices at d = 128 89 -> 101 us, 262,144 at d = 64
 // 154 -> 186; only the longest rows gain, 60,000 at d = 512 141 -> 130.)
 template <class P, int LPG, int UPL, class W, bool SEQ, bool LOCKED>
-__device__ __forceinline__ void sgd_walk(const W &w, const SgdArgs &a) {
+__device__ __forceinline__ void sgd_walk(const W &w, const SgdArgs &a, const LockSet &lock) {
   constexpr int kGroupsPerWave = 64 / LPG;
   constexpr int kPasses = (kChunk + LPG - 1) / LPG;  // sampler passes per chunk (lane q takes sample q)
   constexpr int F = P::F;
@@ -477,14 +482,14 @@ __device__ __forceinline__ void sgd_walk(const W &w, const SgdArgs &a) {
   auto release = [&]() {
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     if (held_lock >= 0 && gl == 0)
-      __hip_atomic_store(a.hot.locks + held_lock, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      __hip_atomic_store(lock.locks + held_lock, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     held_lock = -1;
   };
   // One try at a lock; true in the whole group if it was free.
   auto try_lock = [&](bool want, int32_t slot) -> bool {
     bool mine = false;
     if (want && gl == 0)
-      mine = __hip_atomic_exchange(a.hot.locks + slot, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0u;
+      mine = __hip_atomic_exchange(lock.locks + slot, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0u;
     release();
     return ((__ballot(mine) >> (lane & ~(LPG - 1))) & 1u) != 0;
   };
@@ -513,7 +518,7 @@ __device__ __forceinline__ void sgd_walk(const W &w, const SgdArgs &a) {
 #pragma unroll
     for (int i = 0; i < UPL; ++i) s[i] = P::load(src_row + readable(column(src_row, i)));
     const int32_t src_slot = LOCKED ? w.source_slot(idx) : 0;
-    const uint32_t src_word = LOCKED ? a.hot.draws[src_slot] : bits[use_bitmap ? (src >> 5) : 0];
+    const uint32_t src_word = LOCKED ? lock.draws[src_slot] : bits[use_bitmap ? (src >> 5) : 0];
     bool fresh = true;
 
     ChunkPos cur{idx_raw, 0, 0};
@@ -539,7 +544,7 @@ __device__ __forceinline__ void sgd_walk(const W &w, const SgdArgs &a) {
 #pragma unroll
           for (int i = 0; i < UPL; ++i) r[q][i] = P::load(row + readable(column(row, i)));
         }
-        if constexpr (LOCKED) word[q] = a.hot.draws[valid[q] ? w.sample_slot(idx, v[q]) : 0];
+        if constexpr (LOCKED) word[q] = lock.draws[valid[q] ? w.sample_slot(idx, v[q]) : 0];
         else word[q] = bits[(use_bitmap && valid[q]) ? (v[q] >> 5) : 0];
       }
       // While they are in flight: the ids of the next chunk (its offsets arrived a chunk
@@ -577,13 +582,13 @@ __device__ __forceinline__ void sgd_walk(const W &w, const SgdArgs &a) {
               at = q;
               id = v[q];
               positive = is_pos[q];
-              hub = word[q] > a.hot.most;
+              hub = word[q] > lock.most;
             }
           const bool want = id >= 0;
           const int32_t slot = want ? w.sample_slot(idx, id) : 0;
           if (__ballot(want) == 0) break;  // the same for the whole wavefront
           const bool locked = try_lock(want && !hub, slot);
-          const bool add = want && (hub || (!locked && tries >= a.max_tries));
+          const bool add = want && (hub || (!locked && tries >= lock.max_tries));
           const bool apply = locked || add;
           float *const row = apply ? w.sample_row(idx, id) : src_row;
 #pragma unroll
@@ -715,9 +720,9 @@ __device__ __forceinline__ void sgd_walk(const W &w, const SgdArgs &a) {
     }
     if constexpr (LOCKED) {
       // the source's change, added to its row as it is now
-      const bool hub = live && src_word > a.hot.most;
+      const bool hub = live && src_word > lock.most;
       bool locked = false;
-      for (int32_t tries = 0; tries < a.max_tries; ++tries) {
+      for (int32_t tries = 0; tries < lock.max_tries; ++tries) {
         if (__ballot(live && !hub && !locked) == 0) break;  // the same for the whole wavefront
         if (try_lock(live && !hub && !locked, src_slot)) {
           locked = true;
@@ -774,11 +779,11 @@ __device__ __forceinline__ void sgd_walk(const W &w, const SgdArgs &a) {
 
 template <class P, int LPG, int UPL, class W, bool SEQ>
 __global__ __launch_bounds__(256) void sgd_kernel(W w, SgdArgs a) {
-  sgd_walk<P, LPG, UPL, W, SEQ, false>(w, a);
+  sgd_walk<P, LPG, UPL, W, SEQ, false>(w, a, LockSet{});
 }
 template <class P, int LPG, int UPL, class W, bool SEQ>
-__global__ __launch_bounds__(256) void sgd_locked_kernel(W w, SgdArgs a) {
-  sgd_walk<P, LPG, UPL, W, SEQ, true>(w, a);
+__global__ __launch_bounds__(256) void sgd_locked_kernel(W w, SgdArgs a, LockSet lock) {
+  sgd_walk<P, LPG, UPL, W, SEQ, true>(w, a, lock);
 }
 
 // Whether the access instructions of lanes at columns 0, 1, 2, ... touch no more 64-byte blocks
@@ -799,7 +804,8 @@ inline bool rows_at_lines(const float *M, int32_t d) { return reinterpret_cast<u
 template <class W>
 struct SgdLauncher {
   template <class P, int LPG, int UPL>
-  static void run(const W &w, SgdArgs a, int64_t count, bool seq, int64_t max_waves, hipStream_t st) {
+  static void run(const W &w, SgdArgs a, const LockSet &lock, int64_t count, bool seq, int64_t max_waves,
+                  hipStream_t st) {
     constexpr int kWavesPerBlock = 4;
     constexpr int kGroupsPerWave = 64 / LPG;
     constexpr int64_t kPerTurn = kWavesPerBlock * kGroupsPerWave;  // sources a workgroup takes per turn
@@ -811,8 +817,9 @@ struct SgdLauncher {
     const int blocks = static_cast<int>(blocks64);
     const bool locked = a.hot.mode == kHotLocked;
     if constexpr (!std::is_same_v<P, RowPlain128>) {
-      if (locked && seq) hipLaunchKernelGGL((sgd_locked_kernel<P, LPG, UPL, W, true>), dim3(1), dim3(64), 0, st, w, a);
-      else if (locked) hipLaunchKernelGGL((sgd_locked_kernel<P, LPG, UPL, W, false>), dim3(blocks), dim3(256), 0, st, w, a);
+      if (locked && seq) hipLaunchKernelGGL((sgd_locked_kernel<P, LPG, UPL, W, true>), dim3(1), dim3(64), 0, st, w, a, lock);
+      else if (locked)
+        hipLaunchKernelGGL((sgd_locked_kernel<P, LPG, UPL, W, false>), dim3(blocks), dim3(256), 0, st, w, a, lock);
       if (locked) return;
     }
     if (seq) hipLaunchKernelGGL((sgd_kernel<P, LPG, UPL, W, true>), dim3(1), dim3(64), 0, st, w, a);
@@ -828,28 +835,28 @@ struct SgdLauncher {
   // Lane groups per wavefront in concurrent mode (to size the launch and the hot-row rule).
   static int groups_per_wave(int32_t d) { return 64 / pow2_lanes(d / 4); }
 
-  static void launch(const W &w, const SgdArgs &a, int64_t count, bool seq, bool plain_rows,
+  static void launch(const W &w, const SgdArgs &a, const LockSet &lock, int64_t count, bool seq, bool plain_rows,
                      int64_t max_waves, hipStream_t st) {
     const int d = a.d;
     if (plain_rows) {
-      if (d > 256) return run<RowPlain128, 64, 2>(w, a, count, seq, max_waves, st);
+      if (d > 256) return run<RowPlain128, 64, 2>(w, a, lock, count, seq, max_waves, st);
       switch (pow2_lanes(d / 4)) {
-        case 64: return run<RowPlain128, 64, 1>(w, a, count, seq, max_waves, st);
-        case 32: return run<RowPlain128, 32, 1>(w, a, count, seq, max_waves, st);
-        case 16: return run<RowPlain128, 16, 1>(w, a, count, seq, max_waves, st);
-        case 8: return run<RowPlain128, 8, 1>(w, a, count, seq, max_waves, st);
-        case 4: return run<RowPlain128, 4, 1>(w, a, count, seq, max_waves, st);
-        case 2: return run<RowPlain128, 2, 1>(w, a, count, seq, max_waves, st);
-        default: return run<RowPlain128, 1, 1>(w, a, count, seq, max_waves, st);
+        case 64: return run<RowPlain128, 64, 1>(w, a, lock, count, seq, max_waves, st);
+        case 32: return run<RowPlain128, 32, 1>(w, a, lock, count, seq, max_waves, st);
+        case 16: return run<RowPlain128, 16, 1>(w, a, lock, count, seq, max_waves, st);
+        case 8: return run<RowPlain128, 8, 1>(w, a, lock, count, seq, max_waves, st);
+        case 4: return run<RowPlain128, 4, 1>(w, a, lock, count, seq, max_waves, st);
+        case 2: return run<RowPlain128, 2, 1>(w, a, lock, count, seq, max_waves, st);
+        default: return run<RowPlain128, 1, 1>(w, a, lock, count, seq, max_waves, st);
       }
     }
     if (d <= 64) {
       switch (pow2_lanes(d / 4)) {
-        case 16: return run<RowAgent128, 16, 1>(w, a, count, seq, max_waves, st);
-        case 8: return run<RowAgent128, 8, 1>(w, a, count, seq, max_waves, st);
-        case 4: return run<RowAgent128, 4, 1>(w, a, count, seq, max_waves, st);
-        case 2: return run<RowAgent128, 2, 1>(w, a, count, seq, max_waves, st);
-        default: return run<RowAgent128, 1, 1>(w, a, count, seq, max_waves, st);
+        case 16: return run<RowAgent128, 16, 1>(w, a, lock, count, seq, max_waves, st);
+        case 8: return run<RowAgent128, 8, 1>(w, a, lock, count, seq, max_waves, st);
+        case 4: return run<RowAgent128, 4, 1>(w, a, lock, count, seq, max_waves, st);
+        case 2: return run<RowAgent128, 2, 1>(w, a, lock, count, seq, max_waves, st);
+        default: return run<RowAgent128, 1, 1>(w, a, lock, count, seq, max_waves, st);
       }
     }
     // Rows that straddle lines.  Measured before and after on 2^20 vertices (a mix of stores and
@@ -859,13 +866,13 @@ struct SgdLauncher {
     // 4,018 / 923.  At 132 half the lanes idle and the longer code costs more than the blocks
     // saved, unless every write is an atomic add.
     if (!w.rows_at_lines() && (d <= 128 || d > 192 || a.hot.mode >= kHotAll)) {
-      if (d > 256) return run<RowAgentLine, 64, 8>(w, a, count, seq, max_waves, st);
-      if (d > 128) return run<RowAgentLine, 64, 4>(w, a, count, seq, max_waves, st);
-      return run<RowAgentLine, 32, 4>(w, a, count, seq, max_waves, st);
+      if (d > 256) return run<RowAgentLine, 64, 8>(w, a, lock, count, seq, max_waves, st);
+      if (d > 128) return run<RowAgentLine, 64, 4>(w, a, lock, count, seq, max_waves, st);
+      return run<RowAgentLine, 32, 4>(w, a, lock, count, seq, max_waves, st);
     }
-    if (d > 256) return run<RowAgent32, 64, 8>(w, a, count, seq, max_waves, st);
-    if (d > 128) return run<RowAgent32, 64, 4>(w, a, count, seq, max_waves, st);
-    return run<RowAgent32, 32, 4>(w, a, count, seq, max_waves, st);
+    if (d > 256) return run<RowAgent32, 64, 8>(w, a, lock, count, seq, max_waves, st);
+    if (d > 128) return run<RowAgent32, 64, 4>(w, a, lock, count, seq, max_waves, st);
+    return run<RowAgent32, 32, 4>(w, a, lock, count, seq, max_waves, st);
   }
 };
 

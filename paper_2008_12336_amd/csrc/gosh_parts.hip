@@ -494,7 +494,7 @@ class Rotation {
   uint32_t *hot_bits_dev = nullptr;
   uint32_t *locks = nullptr;     // a lock per row of a visit, then two times its draws, in turns
   int64_t lock_in_flight = 0;    // sources in flight that the hub rule counts with
-  gosh::HotSet hot{nullptr, gosh::kHotNone, nullptr};
+  gosh::HotSet hot{nullptr, gosh::kHotNone};
   gosh::CheckResult *check = nullptr;  // divergence check, accumulated on the outbound stream
   hipStream_t compute = nullptr, copy = nullptr, copy_out = nullptr;
   std::vector<hipEvent_t> chunk_flushed, slot_ready, slot_used, pool_ready, pool_used, staging_done, k_begin, k_end;
@@ -542,7 +542,6 @@ class Rotation {
       }
       if (mode == gosh::kHotLocked) {
         GOSH_TRY_HIP(hipMemsetAsync(locks, 0, lock_bytes(n, pl.K), compute), "clear row locks");
-        hot.locks = locks;
         lock_in_flight = in_flight;
       }
       if (mode == gosh::kHotBitmap) {
@@ -794,7 +793,6 @@ class Rotation {
     args.d = pl.d;
     args.k_neg = pl.k_neg;
     args.samples = samples;
-    args.max_tries = gosh::lock_tries();
     args.lr = gosh_lr(pl.lr0, v.rot, pl.rotations);
     const int timer = static_cast<int>(vi % kTimers);
     if (k_pending[timer]) {
@@ -804,17 +802,17 @@ class Rotation {
       st.kernel_ms += ms;
       k_pending[timer] = 0;
     }
+    gosh::LockSet lock;
     if (hot.mode == gosh::kHotLocked) {
       const int64_t rows = visit_rows(pl.g->n, pl.K);
       uint32_t *const draws = locks + rows * (1 + vi % 2);
       const int blocks = static_cast<int>(std::min<int64_t>((rows + 255) / 256, 65536));
       hipLaunchKernelGGL(count_pool_kernel, dim3(blocks), dim3(256), 0, compute, w, draws, locks + rows * (2 - vi % 2), rows);
       if (int rc = gosh::check_launch("count_pool_kernel")) return rc;
-      args.hot.draws = draws;
-      args.hot.most = gosh::most_draws(w.count(), per_round, lock_in_flight);
+      lock = gosh::LockSet{locks, draws, gosh::most_draws(w.count(), per_round, lock_in_flight), gosh::lock_tries()};
     }
     GOSH_TRY_HIP(hipEventRecord(k_begin[timer], compute), "hipEventRecord");
-    gosh::SgdLauncher<PairWork>::launch(w, args, w.count(), seq, tune.plain_rows != 0 || !concurrent_paths,
+    gosh::SgdLauncher<PairWork>::launch(w, args, lock, w.count(), seq, tune.plain_rows != 0 || !concurrent_paths,
                                         tune.max_waves, compute);
     if (int rc = gosh::check_launch("sgd_kernel (pair)")) return rc;
     GOSH_TRY_HIP(hipEventRecord(k_end[timer], compute), "hipEventRecord");

@@ -447,8 +447,8 @@ int launch_epoch(const gosh_csr *g, float *M, int32_t d, int32_t k_neg, float lr
   a.k_neg = k_neg;
   a.samples = k_neg + 1;
   a.lr = lr;
-  a.max_tries = gosh::lock_tries();
-  a.hot = gosh::HotSet{nullptr, gosh::kHotNone, nullptr};
+  a.hot = gosh::HotSet{nullptr, gosh::kHotNone};
+  gosh::LockSet lock;
   const int64_t max_waves = tune.max_waves;
   if (concurrent_paths) {
     // Sources in flight C, and the hot-row rule.  A vertex is hot if its expected
@@ -483,9 +483,7 @@ int launch_epoch(const gosh_csr *g, float *M, int32_t d, int32_t k_neg, float lr
         hipLaunchKernelGGL(count_positives_kernel<OffT>, dim3(grid_for(n, 256, 1 << 16)), dim3(256), 0, st, w.s,
                            words.draws, words.stale, words.stale_rows);
         if (int rc2 = gosh::check_launch("count_positives_kernel")) return rc2;
-        a.hot.locks = words.locks;
-        a.hot.draws = words.draws;
-        a.hot.most = gosh::most_draws(n, k_neg + 2, in_flight);
+        lock = gosh::LockSet{words.locks, words.draws, gosh::most_draws(n, k_neg + 2, in_flight), gosh::lock_tries()};
       }
     }
     if (mode == gosh::kHotBitmap) {
@@ -513,7 +511,7 @@ int launch_epoch(const gosh_csr *g, float *M, int32_t d, int32_t k_neg, float lr
     a.hot.bits = static_cast<const uint32_t *>(bits);
   }
   const bool plain_rows = tune.plain_rows != 0 || (seq && !concurrent_paths);
-  gosh::SgdLauncher<EpochWork<OffT>>::launch(w, a, n, seq, plain_rows, max_waves, st);
+  gosh::SgdLauncher<EpochWork<OffT>>::launch(w, a, lock, n, seq, plain_rows, max_waves, st);
   return gosh::check_launch("sgd_kernel (epoch)");
 }
 

@@ -81,7 +81,7 @@ def test_rotation_does_not_queue_up_at_a_sink():
     assert ms[0] <= 4 * ms[G.GOSH_FLAG_ATOMIC_ADDS]
 
 
-@pytest.mark.parametrize("d,n,k", [(36, 40_000, 10), (128, 40_000, 3)])
+@pytest.mark.parametrize("d,n,k", [(36, 140_000, 10), (128, 40_000, 3)])
 def test_rows_drawn_often_lose_no_update(d, n, k):
     """Sinks that thousands of sources draw, beside rows under locks: in sequential order the
     sequential result; concurrent, to first order (the bar of the all-atomic epoch, see
