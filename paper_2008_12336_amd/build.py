@@ -12,7 +12,7 @@ LIB = os.path.join(HERE, "libgosh.so")
 EXAMPLE_SRC = os.path.join(HERE, "examples", "embed_example.cpp")
 EXAMPLE = os.path.join(HERE, "examples", "embed_example")
 
-SOURCES = ["gosh_host.cpp", "gosh_coarsen.cpp", "gosh_sampler.cpp", "gosh_coarsen_gpu.hip", "gosh_quotient.hip", "gosh_device_pool.cpp", "gosh_train.hip", "gosh_embed.hip", "gosh_parts.hip", "gosh_place.hip"]
+SOURCES = ["gosh_host.cpp", "gosh_coarsen.cpp", "gosh_sampler.cpp", "gosh_coarsen_gpu.hip", "gosh_quotient.hip", "gosh_quotient_radix32.hip", "gosh_quotient_radix64.hip", "gosh_device_pool.cpp", "gosh_train.hip", "gosh_embed.hip", "gosh_parts.hip", "gosh_place.hip"]
 
 FLAGS = [
     "--offload-arch=gfx950",
