@@ -104,12 +104,12 @@ int hot_scratch(size_t bytes, void **out);
 // Per-device words of the training kernels, per row: a lock, zero between launches, and two counts
 // of draws that launches use in turns.  The launch counts in `draws`, which are zero, and clears
 // the first `stale_rows` of `stale`, which the launch before may still be reading until then.
-// Grown on demand and kept until the process ends.  GOSH_ENOMEM if there is no memory: the launch
-// then does without.
+// Grown on demand, cleared on `stream` (a hipStream_t) and kept until the process ends.  GOSH_ENOMEM
+// if there is no memory: the launch then does without.
 struct LockWords {
   uint32_t *locks, *draws, *stale;
   int64_t stale_rows;
 };
-int lock_scratch(int64_t rows, LockWords *out);
+int lock_scratch(int64_t rows, void *stream, LockWords *out);
 
 }  // namespace gosh

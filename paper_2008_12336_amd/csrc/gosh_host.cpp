@@ -152,7 +152,7 @@ int hot_scratch(size_t bytes, void **out) {
   return GOSH_OK;
 }
 
-int lock_scratch(int64_t rows, LockWords *out) {
+int lock_scratch(int64_t rows, void *stream, LockWords *out) {
   struct Words {
     uint32_t *base = nullptr;
     int64_t rows = 0;         // locks, then two times draws, that many each
@@ -176,11 +176,9 @@ int lock_scratch(int64_t rows, LockWords *out) {
       (void)hipGetLastError();
       return GOSH_ENOMEM;
     }
-    // before any launch on any stream, and behind none: on a stream of its own
-    hipStream_t own = nullptr;
-    const bool cleared = hipStreamCreateWithFlags(&own, hipStreamNonBlocking) == hipSuccess &&
-                         hipMemsetAsync(p, 0, bytes, own) == hipSuccess && hipStreamSynchronize(own) == hipSuccess;
-    if (own) (void)hipStreamDestroy(own);
+    // before the launch that asks; the caller orders later ones behind that.  (A stream made for the
+    // clear alone cost the first locked launch of a process 4 ms.)
+    const bool cleared = hipMemsetAsync(p, 0, bytes, static_cast<hipStream_t>(stream)) == hipSuccess;
     if (!cleared) {
       (void)hipGetLastError();
       (void)hipFree(p);

@@ -475,7 +475,7 @@ int launch_epoch(const gosh_csr *g, float *M, int32_t d, int32_t k_neg, float lr
     if (flags & GOSH_FLAG_ATOMIC_ADDS) mode = gosh::kHotAll;
     if (mode == gosh::kHotLocked) {
       gosh::LockWords words{};
-      const int rc = gosh::lock_scratch(n, &words);
+      const int rc = gosh::lock_scratch(n, st, &words);
       if (rc == GOSH_ENOMEM) {
         mode = gosh::kHotAll;  // which needs no memory
       } else {
