@@ -66,8 +66,8 @@ typedef struct {
 #define GOSH_FLAG_CONCURRENT_LAYOUT 64u /* debug, with GOSH_FLAG_SEQUENTIAL: the one lane group
                                      that walks the sources runs the concurrent kernel as it
                                      is shipped -- its lane-to-column layout, its device-scope
-                                     row accesses, its hot-row rule with the atomic-add and the
-                                     plain-store write paths -- instead of the plain 128-bit
+                                     row accesses, its hot-row rule with the atomic-add, plain-store
+                                     and row-lock write paths -- instead of the plain 128-bit
                                      layout, so that exactly that code can be compared with a
                                      sequential reference.  No effect without
                                      GOSH_FLAG_SEQUENTIAL */
@@ -111,8 +111,9 @@ typedef struct {
                                 Default 2^18 */
   int64_t hot_inv_eps;       /* a vertex is hot if deg * C / nnz > 1 / hot_inv_eps, C = sources
                                 in flight.  Default 64 */
-  int64_t hot_all_inv_eps;   /* every row is hot if (k_neg + 1) * C / n > 1 / hot_all_inv_eps;
-                                0 switches that rule off.  Default 4 */
+  int64_t hot_all_inv_eps;   /* every row is hot if (k_neg + 1) * C / n > 1 / hot_all_inv_eps
+                                (written under locks then where that pays, see
+                                gosh_train_epoch); 0 switches that rule off.  Default 4 */
   int64_t hot_min_degree;    /* > 0: skip both rules; a vertex is hot iff its degree is at
                                 least this.  Default 0 */
   int64_t pair_level_min_n;  /* GOSH_FLAG_PAIR_LEVELS: smallest part, in vertices.
@@ -186,22 +187,26 @@ int gosh_coarsen(const gosh_csr *g0_host, int64_t threshold, double min_shrink,
  * that device, where gosh_embed / gosh_embed_host read it without another upload, and the
  * host arrays behind gosh_hierarchy_graph / _map / _mult are downloaded on first request.
  * A graph whose marking does not resolve in a bounded number of rounds (long chains of
- * equal degrees) is marked on the host instead.  Device memory: about 24 bytes per entry
- * of G_0 while running; afterwards 12 bytes per entry
- * of all levels, and the run's scratch blocks (about 8 bytes per entry of G_0), which stay
+ * equal degrees) is marked on the host instead.  Device memory per entry of G_0 while running:
+ * scratch of about 8 bytes (12 from 2^32 entries on), 16 more per entry of coarse rows that
+ * are counted or 24 (32) of those that are radix-sorted -- both only rows of thousands of
+ * entries, and only if there is room -- and up to 12 for G_1; afterwards 12 bytes per entry of
+ * all levels but the first, and the scratch blocks, which stay
  * with the hierarchy until gosh_hierarchy_trim_scratch, gosh_hierarchy_release_device or
  * gosh_hierarchy_free, because freeing them at once would slow the host link down for whatever
  * follows (the driver clears freed memory in the background).  For the same reason
  * gosh_hierarchy_free keeps device blocks for the next hierarchy, at most a 64th of the
- * device's memory per process; they are given back when an allocation of this library needs
- * them, and by either of the other two calls.
+ * device's memory per process, and up to 128 MB of pinned memory for the copies of pageable
+ * arrays.  The blocks are given back when an allocation of this library needs them (other
+ * allocators of the process cannot have them), and with the pinned memory by either of the other
+ * two calls.
  * GOSH_ENOMEM / GOSH_EHIP if the device cannot.  Blocking; null stream. */
 int gosh_coarsen_device(const gosh_csr *g0, int64_t threshold, double min_shrink,
                         int32_t max_levels, int32_t n_threads, gosh_hierarchy **out);
 
 /* Returns to the driver the scratch blocks a device-built hierarchy still holds from its
  * construction and, whatever h is (NULL allowed), the blocks kept from freed hierarchies on the
- * current device.  The levels stay where they are. */
+ * current device, and the kept pinned memory.  The levels stay where they are. */
 int gosh_hierarchy_trim_scratch(gosh_hierarchy *h);
 
 /* Brings every array of a device-built hierarchy to the host and frees its device copies
@@ -262,18 +267,24 @@ int gosh_sample_epoch(const gosh_csr *g_dev, int32_t k_neg, uint64_t seed, uint3
  *   g = lr_epoch * (b - sigmoid(M[src] . M[v]));  M[src] += g*M[v];  M[v] += g*M[src]
  * (the second axpy uses the already updated source row; b = 1 for the positive, 0 for
  * negatives).  No positive update for a vertex without neighbours; a negative equal
- * to the source applies no update.  Sources run concurrently without locks (Sec. 3.1);
- * the launch is the epoch barrier.  With GOSH_FLAG_SEQUENTIAL the sources are taken one
+ * to the source applies no update.  Sources run concurrently and no source waits for another's
+ * turn (Sec. 3.1); the launch is the epoch barrier.  With GOSH_FLAG_SEQUENTIAL the sources are taken one
  * by one in ascending id, which is deterministic.  In concurrent mode the sources are
  * handed out in ascending id too (workgroups start in the order of their index and each walks
  * a block of consecutive sources), so an epoch sweeps the graph in the order of the sequential
  * one, a window of concurrently running sources wide.  The default write path is a
  * mix: rows likely to be held by several wavefronts at once (every row of a small
  * graph, high-degree vertices of a large one) receive atomic adds of the step, the
- * others plain stores; GOSH_FLAG_PLAIN_STORES / GOSH_FLAG_ATOMIC_ADDS force one kind.
- * The mix uses a per-device scratch bitmap owned by the library (n bits, allocated on
- * first use), so concurrent-mode calls on one device must not overlap on different
- * streams.
+ * others plain stores.  Where every row would be added to and rows are long enough (d > 32) and
+ * sources many enough, each row is written under a lock of its own instead, except those that
+ * the epoch draws often, which are still added to; GOSH_FLAG_PLAIN_STORES / GOSH_FLAG_ATOMIC_ADDS
+ * force one kind.  No update is lost to adds or locks (but an update whose lock cannot be had in
+ * 2^14 tries is added without it).
+ * The library owns the memory for this, per device: a bitmap (n bits) or lock words and counts
+ * (12 bytes per vertex), allocated on first use and when a larger graph comes, smaller blocks
+ * being kept.  All calls share it, so concurrent-mode calls on one device must not overlap on
+ * different streams.  Without memory for lock words, and while the stream is being captured, the
+ * launch adds.
  * g_dev: CSR arrays on the device.  M_dev: device matrix, updated in place.
  * (Where M_dev lies matters on this device: random row traffic inside one of the three HBM
  * ranks runs at about 5.2 TB/s, across two at about 6.2 TB/s; gosh_matrix_place allocates a
@@ -285,10 +296,11 @@ int gosh_train_epoch(const gosh_csr *g_dev, float *M_dev, int32_t d, int32_t k_n
 
 /* gosh_train_epoch for callers that cannot allocate device memory: code under HIP graph
  * capture, tight serving loops, harnesses that forbid hipMalloc.  The same epoch with the
- * same arguments, results and error behaviour, except that the hot-row bitmap -- the one
- * buffer gosh_train_epoch allocates (on first use, and again when a larger graph comes) --
- * lives in a fixed array inside the library's code object: GOSH_STATIC_MAX_N bits = 8 MiB of
- * device memory on every GPU the library is loaded on, held until the process ends.  The
+ * same arguments and error behaviour, except that it takes no row locks -- where
+ * gosh_train_epoch does, this call adds: no update is lost either, and it takes up to twice as
+ * long -- and that the hot-row bitmap lives in a fixed array inside the library's code
+ * object: GOSH_STATIC_MAX_N bits = 8 MiB of device memory on every GPU the library is loaded
+ * on, held until the process ends.  The
  * call allocates and frees nothing, on the device or the host, and takes graphs of at most
  * GOSH_STATIC_MAX_N vertices (GOSH_EINVAL beyond).  The bitmap is rewritten by every call
  * that uses it (nothing of a previous call is relied on), and all calls on one GPU share it:
@@ -416,7 +428,8 @@ typedef struct {
   int64_t rotations;     /* ceil(epochs / (B*K)), at least 1 */
   int64_t pair_visits;   /* rotations * K(K+1)/2 pair kernels */
   int64_t updates;       /* updates of Alg. 1 attempted (sources * B * (k_neg+1) per visit) */
-  uint64_t device_bytes; /* part slots + sample pools + hot-row bitmap (+ row locks, if used) */
+  uint64_t device_bytes; /* part slots + sample pools + hot-row bitmap (+ 12 bytes for each row
+                            of two parts, if they are locked) */
   uint64_t bytes_h2d;    /* parts and pools copied to the device */
   uint64_t bytes_d2h;    /* parts copied back */
   double kernel_ms;      /* sum of the pair kernels' durations (HIP events) */
@@ -484,7 +497,8 @@ int gosh_parts_sample_pair(const gosh_csr *g_host, int32_t K, int32_t pa, int32_
  * 1.2-1.4x cheaper than an epoch of Alg. 3 (a source row is loaded once per B rounds, and
  * the negatives of a visit fall into one part).
  * device_budget_bytes: cap for slots + pools + bitmap (0 only together with force_K > 0,
- * or with a device matrix).  P_gpu >= 2 (paper: 3), S_gpu >= 1 (paper: 4), B >= 1
+ * or with a device matrix); rows are locked, as in gosh_train_epoch, only where the words for
+ * that fit under the cap too and can be had.  P_gpu >= 2 (paper: 3), S_gpu >= 1 (paper: 4), B >= 1
  * (paper: 5).  force_K > 0 overrides the part count.  flags as for gosh_train_epoch
  * (GOSH_FLAG_SEQUENTIAL: every pair kernel runs on one wavefront, sources in order), plus
  * GOSH_FLAG_BLOCKED_ORDER.

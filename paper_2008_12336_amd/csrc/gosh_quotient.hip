@@ -23,7 +23,7 @@
 // and a reduction of equal keys, which this replaced: 128 M entries of a 4 M-vertex R-MAT graph
 // took 8.9 ms and take 4.4, 117 M weighted entries of its second level 10.5 and 4.2; 8 (wide
 // sums: 12) bytes of scratch per entry instead of 32, 16 more per entry of a row that is counted and
-// 24 (weighted: 32) of one that is sorted by radix.  A third of it is the gather.
+// 24 (wide sums: 32) of one that is sorted by radix.  A third of it is the gather.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
