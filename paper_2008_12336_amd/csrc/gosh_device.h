@@ -6,6 +6,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <cmath>
 #include <cstdint>
 #include <type_traits>
 
@@ -211,24 +212,38 @@ struct LockSet {
 // Whether a launch in which every row is hot takes locks.  `capacity` sources run at a time (C when
 // the device is full), so a launch is sources / capacity rounds.  Adds cost time per block of a
 // row, a lock costs about as much as one round trip however long the row is: what it saves grows
-// with the blocks that the rows in flight have together (131,072 are a full chip at d = 64, 128
-// and 256), and what it costs on top -- the counting, the longer chain of one source -- must spread
-// over some rounds and samples.  Time with locks over time with adds, power law / R-MAT, by rounds:
-//   d = 128, k = 3   1: 1.11, 1.5: 0.92 / 1.04, 2: 0.84 / 0.96, 4: 0.69 / 0.71
-//            k = 1   2: 1.15, 3: - / 0.96, 4: - / 0.86        k = 9   1: 1.05, 1.5: 0.85 / 0.89
-//   d = 64,  k = 3   1: 1.07, 1.75: 0.88 / 0.95, 2.5: 0.79 / 0.90
-//   d = 512, k = 3   0.5: 1.07, 0.9: 0.75 / 0.79               k = 0   1: 0.95, 2: 0.75
-//   d = 68,  k = 3   2: 1.07, 3: 0.95 / 0.99, 6: 0.83          d = 192, k = 3   1.5: 1.02, 2: 0.94
-//   d = 132, k = 9   3: 1.02, 4: 0.96                          k = 1   8: 1.02 / 1.05
-// Rows of three blocks (d <= 48) gain least, their adds being one instruction per row:
-//   d = 36,  k = 3   4: 0.91 / 1.03, 6: 0.85 / 0.93            k = 1   8: 0.97 / 1.08
+// with what the rows in flight have together (131,072 blocks are a full chip at d = 64, 128 and
+// 256), and what it costs on top -- the counting, the longer chain of one source -- must spread
+// over some rounds and samples.  Rows that start inside a block share lines with their neighbours:
+// they count by their columns, and barely pay where half of a lane group is idle.  With few negatives
+// many of the rows drawn are positives, of which R-MAT graphs have few, and such launches must be
+// larger.  Time with locks over time with adds, power law / R-MAT, by rounds, and the rule's edge:
+//   d = 128, k = 9   1.5: 0.86 / 0.90                (1.3)     k = 3   2: 0.83 / 0.94        (1.8)
+//            k = 1   3: 0.84 / 0.93                  (2.7)     d = 192, k = 3  4: 0.75 / 0.78  (3.2)
+//   d = 80,  k = 3   6: 0.94 / 0.91                  (4.6)     d = 384, k = 9  1: 0.78 / 0.79  (0.8)
+//   d = 64,  k = 3   2: 0.83 / 0.93                  (1.8)     k = 1   3: 0.84 / 1.07, 4: 0.83 / 1.05  (3.6)
+//   d = 52,  k = 3   1.8: 0.93 / 1.07, 2.5: 0.83 / 0.91  (2.2)  k = 1  3: 0.91 / 1.12, 4: 0.86 / 1.09  (4.4)
+//   d = 100, k = 9   2.5: 0.91 / 0.95 (2.3)    k = 3   2.5: 0.97 / 1.02, 3: 0.91 / 0.94      (3.3)
+//            k = 1   4: 0.99 / 1.07, 6: 0.95 / 0.98  (6.7)
+//   d = 76,  k = 9   3.6: 1.03 / 1.05, 6: 0.94 / 0.96 (4.6)    k = 2   6: 1.05 / 1.09        (8.8)
+//   d = 68,  k = 9   4: 1.08 / 1.11, 8: 0.98 / 0.98 (7.4)      k = 3   6: 1.06 / 1.14, 12: 0.98 / 0.96 (10.6)
+//   d = 132, k = 9   4: 1.07 / 1.09, 8: 0.99 / 0.99 (7.4)      k = 3   6: 1.01 / 1.04, 12: 0.96 / 0.99 (10.6)
+//   d = 260, k = 9   1.5: 1.04 / 1.05, 2.5: 0.96 / 0.95 (2.1)  k = 3   2: 0.99 / 1.04, 3: 0.94 / 0.96  (3.0)
+//   d = 36,  k = 3   4: 0.91 / 1.03, 6: 0.85 / 0.90  (6.0), three blocks, which adds do in one instruction
 inline bool worth_locking(int64_t sources, int64_t samples, int64_t capacity, int32_t d) {
   const int64_t blocks = (d + 15) / 16;
   if (blocks < 3) return false;
-  const double full = static_cast<double>(blocks * capacity) / 131072.0;
-  const double saved = blocks == 3 ? 0.3 : std::min(full, full * full);
-  return static_cast<double>(sources) * saved >=
-         static_cast<double>(capacity) * (0.9 + 3.6 / static_cast<double>(samples));
+  const bool aligned = d % 16 == 0;
+  double full = static_cast<double>(d * capacity) / (131072.0 * 16);
+  if (d > 256 && !aligned) full *= 0.8;  // fewer wavefronts: more registers per row
+  const double saved = blocks == 3 ? 0.3
+                       : aligned   ? std::min(full, full * full)
+                       : d <= 64   ? full
+                       : full < 0.58 ? 0.17
+                                     : std::min(full, full * full * std::sqrt(full));
+  const double per_sample = 1.0 / static_cast<double>(samples);
+  const double rounds = std::max(0.9 + 3.6 * per_sample, aligned && d > 64 ? 0.0 : 7.2 * per_sample);
+  return static_cast<double>(sources) * saved >= static_cast<double>(capacity) * rounds;
 }
 
 // Hubs.  Whoever holds a row keeps the others waiting for about as long as a source takes for one

@@ -43,9 +43,10 @@ def test_locks_stand_in_for_adds_and_for_nothing_else(n, d, k):
     assert mode_of(n, d, k, call=G.gosh_train_epoch_static) == HOT_ALL
 
 
-# one vertex below and at the bound: rounds * saved >= 0.9 + 3.6 / (k + 1)
+# one vertex below and at the bound: rounds * saved >= 0.9 + 3.6 / (k + 1), and more with one negative
 @pytest.mark.parametrize("n,d,k", [(29_492, 128, 3), (58_983, 64, 3), (20_644, 128, 9), (7_373, 512, 3), (18_432, 512, 0),
-                                   (196_609, 36, 3), (32_623, 132, 9)])
+                                   (196_609, 36, 3), (60_718, 132, 9), (54_667, 100, 3), (117_965, 64, 1),
+                                   (24_781, 260, 3), (44_237, 128, 1), (72_594, 52, 3)])
 def test_small_launches_take_no_locks(n, d, k):
     """A launch of a few sources is bound by the chain of round trips of one, which locks make
     longer: up to 1.6 times the time with adds at one round of sources."""

@@ -211,8 +211,8 @@ def test_rows_that_straddle_lines_in_sequential_order(d, offset, paths, hot_degr
 
 
 # graphs small enough for every row to be written without losses, and large enough for row locks
-LOCKED = [(36, 150_000, 10), (64, 50_000, 11), (100, 29_000, 11), (128, 40_000, 3), (132, 32_000, 11),
-          (260, 13_500, 6), (512, 7_300, 5)]
+LOCKED = [(36, 150_000, 10), (64, 50_000, 11), (100, 37_000, 11), (128, 40_000, 3), (132, 58_000, 11),
+          (260, 20_000, 6), (512, 7_300, 5)]
 
 
 @pytest.mark.parametrize("d,n,k", LOCKED)
