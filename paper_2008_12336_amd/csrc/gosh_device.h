@@ -402,16 +402,8 @@ struct ChunkPos {
 // (its step is forced to zero, its store is skipped).  All reads of a chunk are therefore
 // issued back to back and waited for once, which is what keeps their latencies overlapped;
 // with predicated reads the compiler splits the code into blocks and waits in each.
-// LOCKED: the rows are locked (see kHotLocked).  A chunk's samples are then taken one after
-// another, each group at its own pace: try the lock of the next one (one exchange, never waited
-// for), read the row if it was free, update, write back.  The previous row's lock is released
-// behind the wait for that exchange, which is also the wait for the row's stores.  A group holds one
-// lock while it tries another but never waits for one, so no two can wait for each other.  (Trying
-// the lock of the row after the next together with each row saves a round trip per row and loses
-// more to locks that are held longer: 67,000 vertices at d = 128 89 -> 101 us, 262,144 at d = 64
-// 154 -> 186; only the longest rows gain, 60,000 at d = 512 141 -> 130.)
-template <class P, int LPG, int UPL, class W, bool SEQ, bool LOCKED>
-__device__ __forceinline__ void sgd_walk(const W &w, const SgdArgs &a, const LockSet &lock) {
+template <class P, int LPG, int UPL, class W, bool SEQ>
+__device__ __forceinline__ void sgd_walk(const W &w, const SgdArgs &a) {
   constexpr int kGroupsPerWave = 64 / LPG;
   constexpr int kPasses = (kChunk + LPG - 1) / LPG;  // sampler passes per chunk (lane q takes sample q)
   constexpr int F = P::F;
@@ -438,7 +430,7 @@ __device__ __forceinline__ void sgd_walk(const W &w, const SgdArgs &a, const Loc
   const int64_t first = first_of_wave + (SEQ ? 0 : lane / LPG);
   const int32_t d = a.d;
   const int32_t per_round = a.k_neg + 1;
-  const bool use_bitmap = !LOCKED && a.hot.mode == kHotBitmap;
+  const bool use_bitmap = a.hot.mode == kHotBitmap;
   const bool all_hot = a.hot.mode == kHotAll;
   const uint32_t *const bits = a.hot.bits;  // always a readable word, also without a bitmap
 
@@ -492,23 +484,6 @@ __device__ __forceinline__ void sgd_walk(const W &w, const SgdArgs &a, const Loc
     return w.stage1(live ? pos.idx : 0, live);
   };
 
-  // The lock this group holds (slot, -1 none); its release, behind everything issued so far.
-  int32_t held_lock = -1;
-  auto release = [&]() {
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    if (held_lock >= 0 && gl == 0)
-      __hip_atomic_store(lock.locks + held_lock, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    held_lock = -1;
-  };
-  // One try at a lock; true in the whole group if it was free.
-  auto try_lock = [&](bool want, int32_t slot) -> bool {
-    bool mine = false;
-    if (want && gl == 0)
-      mine = __hip_atomic_exchange(lock.locks + slot, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0u;
-    release();
-    return ((__ballot(mine) >> (lane & ~(LPG - 1))) & 1u) != 0;
-  };
-
   // Pipeline prologue: the ids of the group's first chunk and the offsets of its second.
   int32_t mine[kPasses];
   Pre pre_next;
@@ -532,8 +507,7 @@ __device__ __forceinline__ void sgd_walk(const W &w, const SgdArgs &a, const Loc
     U s[UPL], s_before[UPL];
 #pragma unroll
     for (int i = 0; i < UPL; ++i) s[i] = P::load(src_row + readable(column(src_row, i)));
-    const int32_t src_slot = LOCKED ? w.source_slot(idx) : 0;
-    const uint32_t src_word = LOCKED ? lock.draws[src_slot] : bits[use_bitmap ? (src >> 5) : 0];
+    const uint32_t src_word = bits[use_bitmap ? (src >> 5) : 0];
     bool fresh = true;
 
     ChunkPos cur{idx_raw, 0, 0};
@@ -548,19 +522,16 @@ __device__ __forceinline__ void sgd_walk(const W &w, const SgdArgs &a, const Loc
         for (int q = 0; q < LPG && p * LPG + q < kChunk; ++q) v[p * LPG + q] = __shfl(mine[p], q, LPG);
 
       // Request every row of the chunk (a missing sample reads the source row instead).
-      U r[LOCKED ? 1 : kChunk][UPL];
-      uint32_t word[kChunk];  // of the bitmap, or of the draws
+      U r[kChunk][UPL];
+      uint32_t word[kChunk];
       bool valid[kChunk];
 #pragma unroll
       for (int q = 0; q < kChunk; ++q) {
         valid[q] = live && v[q] >= 0 && v[q] != src;  // a sample that hits the source applies no update
-        if constexpr (!LOCKED) {
-          const float *row = valid[q] ? w.sample_row(idx, v[q]) : src_row;
+        const float *row = valid[q] ? w.sample_row(idx, v[q]) : src_row;
 #pragma unroll
-          for (int i = 0; i < UPL; ++i) r[q][i] = P::load(row + readable(column(row, i)));
-        }
-        if constexpr (LOCKED) word[q] = lock.draws[valid[q] ? w.sample_slot(idx, v[q]) : 0];
-        else word[q] = bits[(use_bitmap && valid[q]) ? (v[q] >> 5) : 0];
+        for (int i = 0; i < UPL; ++i) r[q][i] = P::load(row + readable(column(row, i)));
+        word[q] = bits[(use_bitmap && valid[q]) ? (v[q] >> 5) : 0];
       }
       // While they are in flight: the ids of the next chunk (its offsets arrived a chunk
       // ago) and the offsets of the chunk after it.
@@ -584,78 +555,6 @@ __device__ __forceinline__ void sgd_walk(const W &w, const SgdArgs &a, const Loc
       }
       held_in_order();
       fresh = false;
-      if constexpr (LOCKED) {
-        release();
-        int next = 0;  // first sample of the chunk that this group has not applied yet
-        for (int32_t tries = 0;; ++tries) {
-          int32_t id = -1;
-          int at = kChunk;
-          bool positive = false, hub = false;
-#pragma unroll
-          for (int q = kChunk - 1; q >= 0; --q)
-            if (q >= next && valid[q]) {
-              at = q;
-              id = v[q];
-              positive = is_pos[q];
-              hub = word[q] > lock.most;
-            }
-          const bool want = id >= 0;
-          const int32_t slot = want ? w.sample_slot(idx, id) : 0;
-          if (__ballot(want) == 0) break;  // the same for the whole wavefront
-          const bool locked = try_lock(want && !hub, slot);
-          const bool add = want && (hub || (!locked && tries >= lock.max_tries));
-          const bool apply = locked || add;
-          float *const row = apply ? w.sample_row(idx, id) : src_row;
-#pragma unroll
-          for (int i = 0; i < UPL; ++i) r[0][i] = P::load(row + readable(column(row, i)));
-          P::wait_all();
-          float partial = 0.f;
-#pragma unroll
-          for (int i = 0; i < UPL; ++i) {
-            P::settle(r[0][i]);
-            if constexpr (P::kAligned) s[i].v[0] = held[column(row, i)];
-#pragma unroll
-            for (int c = 0; c < F; ++c) {
-              r[0][i].v[c] = column(row, i) < d ? r[0][i].v[c] : 0.f;
-              partial = fmaf(s[i].v[c], r[0][i].v[c], partial);
-            }
-          }
-          const float x = group_sum<LPG>(partial);
-          const float g = apply ? a.lr * ((positive ? 1.f : 0.f) - 1.f / (1.f + expf(-x))) : 0.f;
-#pragma unroll
-          for (int i = 0; i < UPL; ++i)
-#pragma unroll
-            for (int c = 0; c < F; ++c) {
-              s[i].v[c] = fmaf(g, r[0][i].v[c], s[i].v[c]);
-              r[0][i].v[c] = fmaf(g, s[i].v[c], r[0][i].v[c]);
-            }
-          if constexpr (P::kAligned) {
-#pragma unroll
-            for (int i = 0; i < UPL; ++i) held[column(row, i)] = s[i].v[0];
-            held_in_order();
-          }
-          if (locked) {  // uniform over the group; only writes inside
-#pragma unroll
-            for (int i = 0; i < UPL; ++i)
-              if (column(row, i) < d) P::store(row + column(row, i), r[0][i]);
-          }
-          if constexpr (P::kWaveAtomics) {
-            U step;
-#pragma unroll
-            for (int c = 0; c < F; ++c) step.v[c] = g * s[0].v[c];
-            add_rows_as_a_wave<LPG>(add, row, step, d, lane);
-          } else if (add) {
-#pragma unroll
-            for (int i = 0; i < UPL; ++i)
-#pragma unroll
-              for (int c = 0; c < F; ++c)
-                if (column(row, i) < d) atomic_step(row + column(row, i) + c, g * s[i].v[c]);
-          }
-          held_lock = locked ? slot : -1;
-          next = apply ? at + 1 : next;
-        }
-        continue;
-      }
 #pragma unroll
       for (int q = 0; q < kChunk; ++q) {
         const float *const row = valid[q] ? w.sample_row(idx, v[q]) : src_row;
@@ -733,43 +632,6 @@ __device__ __forceinline__ void sgd_walk(const W &w, const SgdArgs &a, const Loc
       for (int i = 0; i < UPL; ++i) s[i].v[0] = held[column(src_row, i)];
       held_in_order();
     }
-    if constexpr (LOCKED) {
-      // the source's change, added to its row as it is now
-      const bool hub = live && src_word > lock.most;
-      bool locked = false;
-      for (int32_t tries = 0; tries < lock.max_tries; ++tries) {
-        if (__ballot(live && !hub && !locked) == 0) break;  // the same for the whole wavefront
-        if (try_lock(live && !hub && !locked, src_slot)) {
-          locked = true;
-          U now[UPL];
-#pragma unroll
-          for (int i = 0; i < UPL; ++i) now[i] = P::load(src_row + readable(column(src_row, i)));
-          P::wait_all();
-#pragma unroll
-          for (int i = 0; i < UPL; ++i) {
-            P::settle(now[i]);
-#pragma unroll
-            for (int c = 0; c < F; ++c) now[i].v[c] += s[i].v[c] - s_before[i].v[c];
-            if (column(src_row, i) < d) P::store(src_row + column(src_row, i), now[i]);
-          }
-          held_lock = src_slot;
-        }
-      }
-      const bool add = live && !locked;
-      if constexpr (P::kWaveAtomics) {
-        U step;
-#pragma unroll
-        for (int c = 0; c < F; ++c) step.v[c] = s[0].v[c] - s_before[0].v[c];
-        add_rows_as_a_wave<LPG>(add, src_row, step, d, lane);
-      } else if (add) {
-#pragma unroll
-        for (int i = 0; i < UPL; ++i)
-#pragma unroll
-          for (int c = 0; c < F; ++c)
-            if (column(src_row, i) < d) atomic_step(src_row + column(src_row, i) + c, s[i].v[c] - s_before[i].v[c]);
-      }
-      continue;
-    }
     const bool src_hot = live && (all_hot || ((src_word >> (src & 31)) & 1u));
     if (live && !src_hot) {
 #pragma unroll
@@ -789,16 +651,329 @@ __device__ __forceinline__ void sgd_walk(const W &w, const SgdArgs &a, const Loc
           if (column(src_row, i) < d) atomic_step(src_row + column(src_row, i) + c, s[i].v[c] - s_before[i].v[c]);
     }
   }
-  if constexpr (LOCKED) release();
+}
+
+// Workgroups of sgd_locked_kernel.  One wavefront each: one that ends makes room for the next at once,
+// not when three others end too (67,000 x 128, k = 3: 83.1 -> 78.3 us; a rotation of 4 x 500,000 rows
+// 41.1 -> 40.6 ms).  Rows that straddle lines are left at four and at six wavefronts per SIMD: more
+// sources in flight are faster (333,337 x 100, k = 9: 909 -> 888 us) but take their turns further from
+// the order of Alg. 3 (distance from it in 64 bits 3.1e-4 -> 4.9e-4; it was 3.0e-4 with chunks of four).
+template <class P>
+constexpr int kLockedThreads = P::kAligned ? 256 : 64;
+// Wavefronts per SIMD that the registers must allow.  Longer rows need what they need.
+template <class P, int UPL>
+constexpr int kLockedWaves = UPL * P::F > 4 ? 1 : P::kAligned ? 6 : 7;
+
+// Waits for all outstanding accesses to memory, and lets the compiler know that it has.
+__device__ __forceinline__ void wait_memory() {
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0), nothing else
+  asm volatile("" ::: "memory");
+}
+
+// The same epoch or visit with every row written under a lock (see kHotLocked); template arguments as
+// in sgd_walk.  The samples of a source are taken one after another, each group at its own pace, in
+// chunks of at most LPG whose ids lie one to a lane: a chunk's ids are drawn while the chunk before it
+// runs, one round of Philox for up to LPG samples.  A row takes two round trips: the exchange of its
+// lock (never waited for; behind it the stores of the row before have arrived, and that row's lock is
+// given back), then the read of the row.  A group holds one lock while it tries another but never waits
+// for one, so no two can wait for each other.
+//
+// What bounds it is the latency of those round trips (70 to 80 % of a wavefront's time), so the layout is
+// made for few registers: the source row as it was read lies in LDS, ids and hub flags are a register
+// each and not one per sample, places are 32-bit.  With chunks of four samples as in sgd_walk, five to
+// six wavefronts per SIMD, 67,000 x 128, k = 3 took 93.3 us, now 75.5 with the counting of the draws;
+// 333,337 x 100, k = 9 1,046, now 909; a rotation of 4 x 500,000 rows at d = 128 47.4 ms, now 40.6 (4.1 G
+// rows/s; visits of 2 x 58,000 rows, which the memory-side cache holds, 5.8 G).
+// The source row is read with the first sample's, where that can be: earlier it is older (67,000 x 128:
+// distance from the sequential epoch 2.96e-4, so 2.88e-4, for the same time).
+// What lost: the lock of the next row asked for while a row is read (one round trip per row, but then a
+// lock is held while another is not to be had: 67,000 x 128 98 -> 1,200 us, rotations 1.5 to 2.5 times
+// as long); versions in the lock words, which let a row be read beside its lock (140 us: a load from a
+// line that others write words of costs more than the round trip, also where the versions lie apart);
+// eight wavefronts per SIMD by spilling (878 -> 945 us at 333,337 x 100).
+template <class P, int LPG, int UPL, class W, bool SEQ>
+__device__ __forceinline__ void sgd_locked_walk(const W &w, const SgdArgs &a, const LockSet &lock) {
+  constexpr int kGroupsPerWave = 64 / LPG;
+  constexpr int F = P::F;
+  using U = Unit<F>;
+  // Whether the source row is read with the first sample's row or, where loads are written out, before
+  // it with the lock: the wait for them must follow in the code too.
+  constexpr bool kLate = !P::kWaveAtomics;
+  using Pre = typename W::Pre;
+  using Mask = std::conditional_t<(LPG > 32), uint64_t, uint32_t>;  // a bit per lane of the group
+  const int lane = threadIdx.x & 63;
+  const int gl = lane & (LPG - 1);
+  if (SEQ && (threadIdx.x >= 64 || blockIdx.x != 0)) return;
+  const bool group_on = !SEQ || lane < LPG;
+
+  // A workgroup walks a block of consecutive sources, as in sgd_walk.  (Rotations gain 3 % when the turns
+  // of a workgroup lie the grid's width apart, but that takes the sources of both parts of a visit up
+  // side by side instead of one part's after the other's.)  Sources fit 31 bits, as vertices do, and so
+  // does what follows the last ones.
+  constexpr uint32_t kWaves = SEQ ? 1 : kLockedThreads<P> / 64;
+  const uint32_t per_block = static_cast<uint32_t>(a.sources_per_block);
+  const uint32_t block_lo = SEQ ? 0 : blockIdx.x * per_block;
+  const uint32_t count = static_cast<uint32_t>(w.count());
+  const uint32_t n = SEQ ? count : std::min(count, block_lo + per_block);
+  const uint32_t first_of_wave = block_lo + (SEQ ? 0 : threadIdx.x / 64 * kGroupsPerWave);
+  const uint32_t stride = SEQ ? 1 : kWaves * kGroupsPerWave;
+  const uint32_t first = first_of_wave + (SEQ ? 0 : lane / LPG);
+  const int32_t d = a.d;
+  const int32_t per_round = a.k_neg + 1;
+
+  constexpr int kSlots = LPG * UPL;
+  static_assert(!P::kAligned || (F == 1 && (kSlots & (kSlots - 1)) == 0), "slots wrap around by masking");
+  auto column = [&](const float *row, int i) -> int32_t {
+    if constexpr (P::kAligned) {
+      const int32_t behind_line = static_cast<int32_t>(reinterpret_cast<uintptr_t>(row) >> 2) & 31;
+      return (gl + i * LPG - behind_line) & (kSlots - 1);
+    } else {
+      return (gl + i * LPG) * F;
+    }
+  };
+  auto readable = [&](int32_t c) { return c < d ? c : d - F; };
+  // the source row by column; the entries past d stay zero
+  __shared__ float held_rows[P::kAligned ? kLockedThreads<P> / LPG * kSlots : 1];
+  float *const held = held_rows + (P::kAligned ? threadIdx.x / LPG * kSlots : 0);
+  auto held_in_order = [] {  // the wavefront's LDS accesses take effect in program order; keep that order
+    if constexpr (P::kAligned) __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  };
+  // the source row as it was read, later its change; every lane uses its own entries only
+  __shared__ float kept_rows[kLockedThreads<P> * UPL * F];
+  auto kept = [&](int i, int c) -> float & { return kept_rows[(i * F + c) * kLockedThreads<P> + threadIdx.x]; };
+
+  auto in_group = [&](bool x) -> Mask {
+    return static_cast<Mask>(__ballot(x) >> (lane & ~(LPG - 1))) & static_cast<Mask>(~uint64_t{0} >> (64 - LPG));
+  };
+  auto first_of = [](Mask m) -> int { return LPG > 32 ? __builtin_ctzll(m) : __builtin_ctz(static_cast<uint32_t>(m)); };
+
+  const bool whole = d == kSlots * F;
+  auto store_row = [&](float *row, const U (&u)[UPL]) {
+    if (!P::kAligned && whole) {
+#pragma unroll
+      for (int i = 0; i < UPL; ++i) P::store(row + (gl + i * LPG) * F, u[i]);
+    } else {
+#pragma unroll
+      for (int i = 0; i < UPL; ++i)
+        if (column(row, i) < d) P::store(row + column(row, i), u[i]);
+    }
+  };
+
+  // Lane gl draws sample t0 + gl of source idx (-1 = none).
+  auto draw_ids = [&](uint32_t idx, int32_t t0, const Pre &pre) -> int32_t {
+    const bool live = group_on && idx < n;
+    const bool any_live = __ballot(live) != 0;  // the same for the whole wavefront: a jump, not a mask
+    const uint32_t i = live ? idx : 0;
+    const int32_t id = w.source_id(i);
+    const bool want = live && t0 + gl < a.samples;
+    const int32_t t = want ? t0 + gl : 0;
+    uint64_t r = 0;
+    if (any_live) r = w.draw(i, id, t);
+    const int32_t v = w.stage2(i, id, t, want, t % per_round == 0, pre, r);
+    return v == id ? -1 : v;  // a sample that hits the source applies no update
+  };
+  auto offsets_for = [&](uint32_t idx) {
+    const bool live = group_on && idx < n;
+    return w.stage1(live ? idx : 0, live);
+  };
+
+  // The lock to let go (slot, -1 none) behind the next wait.
+  int32_t held_slot = -1;
+  auto wait_and_release = [&]() {
+    P::wait_all();
+    wait_memory();
+    if (held_slot >= 0 && gl == 0)
+      __hip_atomic_store(lock.locks + held_slot, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    held_slot = -1;
+  };
+  // One try at a lock: what its word was (0 = the lock was free and is now held).
+  auto try_lock = [&](bool ask, int32_t slot) -> uint32_t {
+    uint32_t old = 1;
+    if (ask && gl == 0) old = __hip_atomic_exchange(lock.locks + slot, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return old;
+  };
+
+  // Pipeline prologue: the ids of the group's first chunk, the offsets of its second.
+  int32_t mine = draw_ids(first, 0, offsets_for(first));
+  const bool one_chunk = a.samples <= LPG;
+  Pre pre_next = offsets_for(one_chunk ? first + stride : first);
+  const uint32_t first_idx = group_on && first < n ? first : 0;
+  uint32_t draws = lock.draws[mine >= 0 ? w.sample_slot(first_idx, mine) : 0];  // of the lane's sample
+
+  for (uint32_t base = first_of_wave; base < n; base += stride) {
+    const uint32_t idx_raw = first + (base - first_of_wave);
+    const bool live = group_on && idx_raw < n;
+    const uint32_t idx = live ? idx_raw : 0;
+    float *const src_row = w.source_row(idx);
+    const int32_t src_slot = w.source_slot(idx);
+    const uint32_t src_draws = lock.draws[src_slot];
+    U s[UPL];
+    auto read_source = [&] {
+#pragma unroll
+      for (int i = 0; i < UPL; ++i) s[i] = P::load(src_row + readable(column(src_row, i)));
+    };
+    auto keep_source = [&] {  // behind a wait
+#pragma unroll
+      for (int i = 0; i < UPL; ++i) {
+        P::settle(s[i]);
+        const bool inside = column(src_row, i) < d;
+#pragma unroll
+        for (int c = 0; c < F; ++c) {
+          s[i].v[c] = inside ? s[i].v[c] : 0.f;
+          kept(i, c) = s[i].v[c];
+        }
+        if constexpr (P::kAligned) held[column(src_row, i)] = s[i].v[0];
+      }
+      held_in_order();
+    };
+    for (int32_t t0 = 0; t0 < a.samples; t0 += LPG) {
+      const bool last = t0 + LPG >= a.samples;
+      const uint32_t idx_ahead = last ? idx_raw + stride : idx_raw;
+      const int32_t t0_ahead = last ? 0 : t0 + LPG;
+      Mask todo = in_group(mine >= 0);  // samples of the chunk that this group has not applied yet
+      const Mask hubs = in_group(draws > lock.most);
+      const Mask positives = in_group((t0 + gl) % per_round == 0);
+      int32_t mine_ahead = -1;
+      int32_t id = __shfl(mine, todo ? first_of(todo) : 0, LPG);
+      for (int32_t tries = 0;; ++tries) {
+        const bool want = todo != 0;
+        if (tries > 0 && __ballot(want) == 0) break;  // the same for the whole wavefront
+        const int q = want ? first_of(todo) : 0;
+        const bool hub = want && ((hubs >> q) & 1u) != 0;
+        const int32_t slot = want ? w.sample_slot(idx, id) : 0;
+        const uint32_t word = try_lock(want && !hub, slot);
+        const bool fresh = t0 == 0 && tries == 0;  // the source row has not been read yet
+        if (fresh && !kLate) read_source();
+        if (tries == 0) {
+          mine_ahead = draw_ids(idx_ahead, t0_ahead, pre_next);
+          pre_next = offsets_for(t0_ahead + LPG >= a.samples ? idx_ahead + stride : idx_ahead);
+        }
+        wait_and_release();
+        if (fresh && !kLate) keep_source();
+        const bool locked = __shfl(word, 0, LPG) == 0;
+        const bool add = want && (hub || (!locked && tries >= lock.max_tries));
+        const bool apply = locked || add;
+        float *const row = apply ? w.sample_row(idx, id) : src_row;
+        U r[UPL];
+        if (apply)
+#pragma unroll
+          for (int i = 0; i < UPL; ++i) r[i] = P::load(row + readable(column(row, i)));
+        if (fresh && kLate) read_source();
+        if (tries == 0)
+          draws = lock.draws[mine_ahead >= 0 ? w.sample_slot(group_on && idx_ahead < n ? idx_ahead : 0, mine_ahead) : 0];
+        P::wait_all();
+        if (fresh && kLate) keep_source();
+
+        float partial = 0.f;
+#pragma unroll
+        for (int i = 0; i < UPL; ++i) {
+          P::settle(r[i]);
+          if constexpr (P::kAligned) s[i].v[0] = held[column(row, i)];
+#pragma unroll
+          for (int c = 0; c < F; ++c) {
+            r[i].v[c] = apply && column(row, i) < d ? r[i].v[c] : 0.f;  // no step leaves the source as it is, infinities too
+            partial = fmaf(s[i].v[c], r[i].v[c], partial);
+          }
+        }
+        const float x = group_sum<LPG>(partial);
+        const float label = ((positives >> q) & 1u) ? 1.f : 0.f;
+        const float g = apply ? a.lr * (label - 1.f / (1.f + expf(-x))) : 0.f;
+#pragma unroll
+        for (int i = 0; i < UPL; ++i)
+#pragma unroll
+          for (int c = 0; c < F; ++c) {
+            s[i].v[c] = fmaf(g, r[i].v[c], s[i].v[c]);
+            r[i].v[c] = fmaf(g, s[i].v[c], r[i].v[c]);
+          }
+        if constexpr (P::kAligned) {
+#pragma unroll
+          for (int i = 0; i < UPL; ++i) held[column(row, i)] = s[i].v[0];
+          held_in_order();
+        }
+        if (locked) {  // uniform over the group; only writes inside
+          store_row(row, r);
+          held_slot = slot;
+        }
+        if constexpr (P::kWaveAtomics) {
+          U step;
+#pragma unroll
+          for (int c = 0; c < F; ++c) step.v[c] = g * s[0].v[c];
+          add_rows_as_a_wave<LPG>(add, row, step, d, lane);
+        } else if (add) {
+#pragma unroll
+          for (int i = 0; i < UPL; ++i)
+#pragma unroll
+            for (int c = 0; c < F; ++c)
+              if (column(row, i) < d) atomic_step(row + column(row, i) + c, g * s[i].v[c]);
+        }
+        if (apply) {
+          todo &= todo - 1;
+          id = __shfl(mine, todo ? first_of(todo) : 0, LPG);
+        }
+      }
+      mine = mine_ahead;
+    }
+
+    // The source's change, added to its row as it is now.
+    if constexpr (P::kAligned) {
+#pragma unroll
+      for (int i = 0; i < UPL; ++i) s[i].v[0] = held[column(src_row, i)];
+      held_in_order();
+    }
+#pragma unroll
+    for (int i = 0; i < UPL; ++i)
+#pragma unroll
+      for (int c = 0; c < F; ++c) kept(i, c) = s[i].v[c] - kept(i, c);
+    const bool hub = src_draws > lock.most;
+    bool add = live;
+    bool todo_src = live && !hub;
+    for (int32_t tries = 0;; ++tries) {
+      if (tries > 0 && __ballot(todo_src) == 0) break;  // the same for the whole wavefront
+      const uint32_t word = try_lock(todo_src, src_slot);
+      wait_and_release();
+      const bool locked = __shfl(word, 0, LPG) == 0;
+      U now[UPL];
+      if (locked)
+#pragma unroll
+        for (int i = 0; i < UPL; ++i) now[i] = P::load(src_row + readable(column(src_row, i)));
+      P::wait_all();
+#pragma unroll
+      for (int i = 0; i < UPL; ++i) {
+        P::settle(now[i]);
+#pragma unroll
+        for (int c = 0; c < F; ++c) now[i].v[c] += kept(i, c);
+      }
+      if (locked) {
+        store_row(src_row, now);
+        held_slot = src_slot;
+      }
+      todo_src = todo_src && !locked && tries < lock.max_tries;
+      add = add && !locked;
+    }
+    if constexpr (P::kWaveAtomics) {
+      U step;
+#pragma unroll
+      for (int c = 0; c < F; ++c) step.v[c] = kept(0, c);
+      add_rows_as_a_wave<LPG>(add, src_row, step, d, lane);
+    } else if (add) {
+#pragma unroll
+      for (int i = 0; i < UPL; ++i)
+#pragma unroll
+        for (int c = 0; c < F; ++c)
+          if (column(src_row, i) < d) atomic_step(src_row + column(src_row, i) + c, kept(i, c));
+    }
+  }
+  wait_and_release();
 }
 
 template <class P, int LPG, int UPL, class W, bool SEQ>
 __global__ __launch_bounds__(256) void sgd_kernel(W w, SgdArgs a) {
-  sgd_walk<P, LPG, UPL, W, SEQ, false>(w, a, LockSet{});
+  sgd_walk<P, LPG, UPL, W, SEQ>(w, a);
 }
 template <class P, int LPG, int UPL, class W, bool SEQ>
-__global__ __launch_bounds__(256) void sgd_locked_kernel(W w, SgdArgs a, LockSet lock) {
-  sgd_walk<P, LPG, UPL, W, SEQ, true>(w, a, lock);
+__global__ __launch_bounds__(kLockedThreads<P>, (kLockedWaves<P, UPL>)) void sgd_locked_kernel(W w, SgdArgs a, LockSet lock) {
+  sgd_locked_walk<P, LPG, UPL, W, SEQ>(w, a, lock);
 }
 
 // Whether the access instructions of lanes at columns 0, 1, 2, ... touch no more 64-byte blocks
@@ -821,20 +996,20 @@ struct SgdLauncher {
   template <class P, int LPG, int UPL>
   static void run(const W &w, SgdArgs a, const LockSet &lock, int64_t count, bool seq, int64_t max_waves,
                   hipStream_t st) {
-    constexpr int kWavesPerBlock = 4;
+    const bool locked = a.hot.mode == kHotLocked && !std::is_same_v<P, RowPlain128>;
+    const int waves_per_block = locked ? kLockedThreads<P> / 64 : 4;
     constexpr int kGroupsPerWave = 64 / LPG;
-    constexpr int64_t kPerTurn = kWavesPerBlock * kGroupsPerWave;  // sources a workgroup takes per turn
-    const int64_t turns = std::max<int64_t>((count + kPerTurn - 1) / kPerTurn, 1);
-    const int64_t max_blocks = std::max<int64_t>(max_waves / kWavesPerBlock, 1);
+    const int64_t per_turn = waves_per_block * kGroupsPerWave;  // sources a workgroup takes per turn
+    const int64_t turns = std::max<int64_t>((count + per_turn - 1) / per_turn, 1);
+    const int64_t max_blocks = std::max<int64_t>(max_waves / waves_per_block, 1);
     const int64_t per_block = (turns + max_blocks - 1) / max_blocks;  // turns of one workgroup
     const int64_t blocks64 = (turns + per_block - 1) / per_block;
-    a.sources_per_block = per_block * kPerTurn;
+    a.sources_per_block = per_block * per_turn;
     const int blocks = static_cast<int>(blocks64);
-    const bool locked = a.hot.mode == kHotLocked;
     if constexpr (!std::is_same_v<P, RowPlain128>) {
       if (locked && seq) hipLaunchKernelGGL((sgd_locked_kernel<P, LPG, UPL, W, true>), dim3(1), dim3(64), 0, st, w, a, lock);
       else if (locked)
-        hipLaunchKernelGGL((sgd_locked_kernel<P, LPG, UPL, W, false>), dim3(blocks), dim3(256), 0, st, w, a, lock);
+        hipLaunchKernelGGL((sgd_locked_kernel<P, LPG, UPL, W, false>), dim3(blocks), dim3(kLockedThreads<P>), 0, st, w, a, lock);
       if (locked) return;
     }
     if (seq) hipLaunchKernelGGL((sgd_kernel<P, LPG, UPL, W, true>), dim3(1), dim3(64), 0, st, w, a);

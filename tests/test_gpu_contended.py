@@ -160,3 +160,40 @@ def test_infinities_and_nan_under_locks(d, n):
     assert np.array_equal(*finite) and 40 <= hit < n / 2
     ok = finite[0] & (np.abs(got[1]) < 1e3)
     assert rel_err(np.where(ok, got[0], 0), np.where(ok, got[1], 0)) <= TOL
+
+
+@pytest.mark.parametrize("d,n,k", [(64, 45_000, 15), (36, 140_000, 15), (100, 37_000, 15)])
+def test_locked_epoch_with_as_many_samples_as_lanes_or_more(d, n, k):
+    """A source's samples are taken in chunks of a lane group's size (16 for d <= 64, 32 for d <= 128):
+    chunks that are just full, and half empty.  The sequential result; concurrent, to first order."""
+    xadj, adj = sink_graph(n, 30, 4, 9)
+    g, keep = upload(n, xadj, adj, True)
+    M0 = start_matrix(n, d, 5, 0.5)
+    for lr, flags in ((0.02, SEQ_LAYOUT), (1e-5, 0)):
+        want = M0.copy()
+        O.train_epoch(xadj, adj, want, k, lr, 77, 0, 1)
+        M = torch.from_numpy(M0).to(DEV)
+        G.gosh_train_epoch(g, M, k, lr, 77, 0, 1, flags)
+        torch.cuda.synchronize()
+        assert last_hot_mode() == HOT_LOCKED
+        if flags:
+            assert rel_err(M.cpu().numpy(), want) <= TOL
+        else:
+            assert_first_order(M, M0, want, g, k, 0)
+
+
+@pytest.mark.parametrize("d,n,k,B", [(64, 20_000, 3, 5), (64, 20_000, 15, 1), (100, 16_000, 3, 8), (128, 9_000, 3, 9),
+                                     (260, 7_500, 12, 5)])
+def test_locked_visits_of_several_chunks(d, n, k, B):
+    """Visits whose sources take more samples than a lane group has lanes: a last chunk of 4 of 16, one
+    full, one full of 32, 4 of 32 and 1 of 64.  Sequential order against the oracle."""
+    xadj, adj = sink_graph(n, 30, 4, 9)
+    xt, at = torch.from_numpy(xadj).to(DEV), torch.from_numpy(adj).to(DEV)
+    M0 = start_matrix(n, d, 5, 0.5)
+    want = M0.copy()
+    O.train_parts(xadj, adj, want, k, B, 0.02, 77, 0, K=1, B=B)
+    M = torch.from_numpy(M0).to(DEV)
+    G.gosh_train_parts(n, xt, at, M, k, B, 0.02, 77, force_K=1, B=B, flags=SEQ_LAYOUT)
+    torch.cuda.synchronize()
+    assert last_hot_mode() == HOT_LOCKED
+    assert rel_err(M.cpu().numpy(), want) <= TOL
