@@ -91,6 +91,10 @@ struct CheckResult {
   uint32_t pad;
   unsigned long long nonfinite;
 };
+// Where kernels on the current device reach `bytes` of host memory at p, or null unless all of it is
+// pinned.
+void *pinned_on_device(void *p, size_t bytes);
+
 int matrix_check_clear(CheckResult *result_dev, hipStream_t st);
 int matrix_check_add(const float *rows_dev, int64_t floats, CheckResult *result_dev, hipStream_t st);
 int matrix_check_read(const CheckResult *result_dev, float *max_abs, int64_t *nonfinite, hipStream_t st);

@@ -288,6 +288,35 @@ __device__ __forceinline__ void count_draws(int32_t at, uint32_t *draws) {
   else if (mine != 0) atomicAdd(draws + at, mine);
 }
 
+// Largest finite |entry| (the bits of a non-negative finite float order like the float) and the number of
+// non-finite entries that a lane, then its wavefront, has looked at.
+struct EntryCheck {
+  uint32_t top = 0, bad = 0;
+  __device__ __forceinline__ void look(const Float4 &x) {
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      const uint32_t mag = __float_as_uint(x[c]) & 0x7FFFFFFFu;
+      const bool finite = mag < 0x7F800000u;
+      top = finite ? max(top, mag) : top;
+      bad += finite ? 0u : 1u;
+    }
+  }
+  __device__ __forceinline__ void reduce_wave() {
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) {
+      top = max(top, static_cast<uint32_t>(__shfl_xor(static_cast<int>(top), off, 64)));
+      bad += static_cast<uint32_t>(__shfl_xor(static_cast<int>(bad), off, 64));
+    }
+  }
+  template <class Result>
+  __device__ __forceinline__ void add_to(Result *out) const {
+    // the word only grows: a stale value can only cost an atomic that was not needed
+    if (top > __hip_atomic_load(&out->max_bits, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+      atomicMax(&out->max_bits, top);
+    if (bad) atomicAdd(&out->nonfinite, static_cast<unsigned long long>(bad));
+  }
+};
+
 struct SgdArgs {
   HotSet hot;
   int32_t d;

@@ -76,6 +76,19 @@ int check_device_span(const void *p, size_t bytes, const char *what) {
   return GOSH_OK;
 }
 
+void *pinned_on_device(void *p, size_t bytes) {
+  hipPointerAttribute_t attr;
+  hipDeviceptr_t base = nullptr;
+  size_t size = 0;
+  if (hipPointerGetAttributes(&attr, p) != hipSuccess || attr.type != hipMemoryTypeHost || attr.devicePointer == nullptr ||
+      hipMemGetAddressRange(&base, &size, attr.devicePointer) != hipSuccess) {
+    (void)hipGetLastError();
+    return nullptr;
+  }
+  const char *const end = static_cast<const char *>(attr.devicePointer) + bytes;
+  return end <= static_cast<const char *>(base) + size ? attr.devicePointer : nullptr;
+}
+
 int check_device_csr(const gosh_csr *g) {
   if (int rc = check_device_span(g->xadj, static_cast<size_t>(g->n + 1) * (g->xadj_is64 ? 8 : 4), "xadj")) return rc;
   if (g->nnz > 0)

@@ -193,6 +193,53 @@ __global__ __launch_bounds__(256) void count_pool_kernel(PairWork w, uint32_t *_
   }
 }
 
+// A part swap in one pass: every unit of the slot is written to its place on the host and replaced by
+// the new part's, both over the host link, whose directions are busy at once from the first unit to the
+// last.  What leaves is checked for divergence on the way.
+// Bound by the link.  Copies of pieces on two streams (an upload behind the write-back of the same
+// bytes) spend a piece's time before the first upload and 10 to 40 us between pieces: 30 MB each way
+// took 0.80 ms like that, and smaller pieces more.  Workgroups of one wavefront, since one of four would
+// wait for four places on a CU at a time while a training kernel of such workgroups runs.
+// Few of them: 40 keep the link busy, more hold up the training kernel beside them (a rotation of
+// 524,288 x 128 under 96 MB: copies 38.6 ms; 16 workgroups 40.8, 24 37.1, 32 36.6, 40 36.0, 64 41.2,
+// 128 44.3; 1 M x 256 under 460 MB: 111 ms; 122, 115, 107, 104, 106, 116; 6 M x 128 under 1.7 GB 231 -> 220).
+constexpr int kSwapUnits = 8;  // in flight per lane and direction
+constexpr int kSwapBlocks = 40;
+__global__ __launch_bounds__(64) void swap_part_kernel(gosh::Float4 *__restrict__ slot, gosh::Float4 *__restrict__ old_host,
+                                                       int64_t old_units, const gosh::Float4 *__restrict__ new_host,
+                                                       int64_t new_units, gosh::CheckResult *__restrict__ out) {
+  const int64_t units = std::max(old_units, new_units);
+  gosh::EntryCheck check;
+  for (int64_t base = blockIdx.x * (64LL * kSwapUnits); base < units; base += gridDim.x * (64LL * kSwapUnits)) {
+    gosh::Float4 leaves[kSwapUnits], comes[kSwapUnits];
+#pragma unroll
+    for (int q = 0; q < kSwapUnits; ++q) {
+      const int64_t i = base + q * 64 + threadIdx.x;
+      leaves[q] = slot[std::min(i, old_units - 1)];
+    }
+#pragma unroll
+    for (int q = 0; q < kSwapUnits; ++q) {
+      const int64_t i = base + q * 64 + threadIdx.x;
+      comes[q] = __builtin_nontemporal_load(new_host + std::min(i, new_units - 1));
+    }
+#pragma unroll
+    for (int q = 0; q < kSwapUnits; ++q) {
+      const int64_t i = base + q * 64 + threadIdx.x;
+      if (i < old_units) {
+        check.look(leaves[q]);
+        __builtin_nontemporal_store(leaves[q], old_host + i);
+      }
+    }
+#pragma unroll
+    for (int q = 0; q < kSwapUnits; ++q) {
+      const int64_t i = base + q * 64 + threadIdx.x;
+      if (i < new_units) slot[i] = comes[q];
+    }
+  }
+  check.reduce_wave();
+  if (threadIdx.x == 0) check.add_to(out);
+}
+
 struct HostCsr {
   const gosh_csr *g;
   int64_t begin(int64_t v) const {
@@ -402,8 +449,12 @@ class Rotation {
       GOSH_TRY_HIP(hipEventCreate(&k_begin[t]), "hipEventCreate");
       GOSH_TRY_HIP(hipEventCreate(&k_end[t]), "hipEventCreate");
     }
+    if (!pl.matrix_on_device)
+      host_rows = static_cast<float *>(gosh::pinned_on_device(pl.M_host, static_cast<size_t>(pl.g->n) * pl.d * 4));
     GOSH_TRY_HIP(gosh::device_malloc(&check, sizeof(gosh::CheckResult)), "hipMalloc check result");
     if (int rc = gosh::matrix_check_clear(check, copy_out)) return rc;
+    GOSH_TRY_HIP(hipEventRecord(arrived, copy_out), "hipEventRecord");
+    GOSH_TRY_HIP(hipStreamWaitEvent(copy, arrived, 0), "hipStreamWaitEvent");  // swaps add to the check
     if (int rc = build_hot_set()) return rc;
     if (!graph_on_device) sampler = std::thread([this] { sampler_loop(); });
     return GOSH_OK;
@@ -489,6 +540,7 @@ class Rotation {
   int64_t npairs = 0, visits = 0;
 
   std::vector<float *> slot;
+  float *host_rows = nullptr;  // the host matrix as kernels reach it, or null
   std::vector<int32_t *> dpool, staging;
   std::vector<int32_t> slot_part;
   uint32_t *hot_bits_dev = nullptr;
@@ -657,7 +709,7 @@ class Rotation {
     const size_t new_bytes = static_cast<size_t>(L.size(p)) * d * 4;
     float *new_host = pl.M_host + static_cast<int64_t>(L.lo(p)) * d;
     if (slot_part[victim] >= 0) {
-      // Write the old part back on the outbound stream and bring the new one in on the
+      // Where kernels cannot reach the host matrix: write the old part back on the outbound stream and bring the new one in on the
       // inbound stream, piece by piece: the upload of a piece waits only for the
       // write-back of the same bytes of the slot.  A later upload of the old part must
       // see its host bytes; it is queued on the inbound stream after these waits, the
@@ -665,6 +717,21 @@ class Rotation {
       const int32_t old = slot_part[victim];
       const size_t old_bytes = static_cast<size_t>(L.size(old)) * d * 4;
       float *old_host = pl.M_host + static_cast<int64_t>(L.lo(old)) * d;
+      if (host_rows != nullptr && old_bytes > 0 && new_bytes > 0) {
+        const int64_t old_units = static_cast<int64_t>(old_bytes / 16), new_units = static_cast<int64_t>(new_bytes / 16);
+        const int64_t turns = (std::max(old_units, new_units) + 64 * kSwapUnits - 1) / (64 * kSwapUnits);
+        const int blocks = static_cast<int>(std::min<int64_t>(turns, kSwapBlocks));
+        GOSH_TRY_HIP(hipStreamWaitEvent(copy, slot_used[victim], 0), "hipStreamWaitEvent");
+        hipLaunchKernelGGL(swap_part_kernel, dim3(blocks), dim3(64), 0, copy, reinterpret_cast<gosh::Float4 *>(slot[victim]),
+                           reinterpret_cast<gosh::Float4 *>(host_rows + static_cast<int64_t>(L.lo(old)) * d), old_units,
+                           reinterpret_cast<const gosh::Float4 *>(host_rows + static_cast<int64_t>(L.lo(p)) * d), new_units,
+                           check);
+        if (int rc = gosh::check_launch("swap_part_kernel")) return rc;
+        st.bytes_d2h += old_bytes;
+        st.bytes_h2d += new_bytes;
+        GOSH_TRY_HIP(hipEventRecord(slot_ready[victim], copy), "hipEventRecord");
+        return GOSH_OK;
+      }
       const size_t longest = std::max(old_bytes, new_bytes);
       size_t piece = (longest + kSwapChunks - 1) / kSwapChunks;
       piece = std::max<size_t>((piece + 255) / 256 * 256, size_t(8) << 20);
@@ -775,10 +842,6 @@ class Rotation {
 
   int launch_pair(int64_t vi, const Visit &v, int sa, int sb) {
     const int ps = static_cast<int>(vi % S);
-    if (!pl.matrix_on_device) {
-      GOSH_TRY_HIP(hipStreamWaitEvent(compute, slot_ready[sa], 0), "hipStreamWaitEvent");
-      GOSH_TRY_HIP(hipStreamWaitEvent(compute, slot_ready[sb], 0), "hipStreamWaitEvent");
-    }
     GOSH_TRY_HIP(hipStreamWaitEvent(compute, pool_ready[ps], 0), "hipStreamWaitEvent");
     PairWork w{};
     w.a_lo = L.lo(v.a); w.a_n = L.size(v.a); w.b_lo = L.lo(v.b); w.b_n = L.size(v.b);
@@ -810,6 +873,12 @@ class Rotation {
       hipLaunchKernelGGL(count_pool_kernel, dim3(blocks), dim3(256), 0, compute, w, draws, locks + rows * (2 - vi % 2), rows);
       if (int rc = gosh::check_launch("count_pool_kernel")) return rc;
       lock = gosh::LockSet{locks, draws, gosh::most_draws(w.count(), per_round, lock_in_flight), gosh::lock_tries()};
+    }
+    // The counting needs no rows: queued ahead of the wait for them it runs beside the part swap (its few
+    // workgroups take 20 to 80 us there, 5 alone).
+    if (!pl.matrix_on_device) {
+      GOSH_TRY_HIP(hipStreamWaitEvent(compute, slot_ready[sa], 0), "hipStreamWaitEvent");
+      GOSH_TRY_HIP(hipStreamWaitEvent(compute, slot_ready[sb], 0), "hipStreamWaitEvent");
     }
     GOSH_TRY_HIP(hipEventRecord(k_begin[timer], compute), "hipEventRecord");
     gosh::SgdLauncher<PairWork>::launch(w, args, lock, w.count(), seq, tune.plain_rows != 0 || !concurrent_paths,

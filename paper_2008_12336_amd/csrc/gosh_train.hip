@@ -348,16 +348,7 @@ constexpr int kCheckBlocks = 2048;
 __global__ __launch_bounds__(256) void matrix_check_kernel(const Float4 *__restrict__ M, int64_t total4,
                                                            gosh::CheckResult *__restrict__ out) {
   constexpr int kUnits = kCheckTile / 256;
-  uint32_t top = 0, bad = 0;
-  auto look = [&](const Float4 &x) {
-#pragma unroll
-    for (int c = 0; c < 4; ++c) {
-      const uint32_t mag = __float_as_uint(x[c]) & 0x7FFFFFFFu;
-      const bool finite = mag < 0x7F800000u;
-      top = finite ? max(top, mag) : top;
-      bad += finite ? 0u : 1u;
-    }
-  };
+  gosh::EntryCheck check;
   const int64_t tiles = (total4 + kCheckTile - 1) / kCheckTile;
   for (int64_t t = blockIdx.x; t < tiles; t += gridDim.x) {
     const int64_t first = (tiles - 1 - t) * kCheckTile + threadIdx.x;
@@ -366,29 +357,22 @@ __global__ __launch_bounds__(256) void matrix_check_kernel(const Float4 *__restr
 #pragma unroll
       for (int q = 0; q < kUnits; ++q) x[q] = __builtin_nontemporal_load(M + first + q * 256);
 #pragma unroll
-      for (int q = 0; q < kUnits; ++q) look(x[q]);
+      for (int q = 0; q < kUnits; ++q) check.look(x[q]);
     } else {
-      for (int64_t i = first; i < total4; i += 256) look(__builtin_nontemporal_load(M + i));
+      for (int64_t i = first; i < total4; i += 256) check.look(__builtin_nontemporal_load(M + i));
     }
   }
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) {
-    top = max(top, static_cast<uint32_t>(__shfl_xor(static_cast<int>(top), off, 64)));
-    bad += static_cast<uint32_t>(__shfl_xor(static_cast<int>(bad), off, 64));
-  }
+  check.reduce_wave();
   __shared__ uint32_t tops[4], bads[4];
   if ((threadIdx.x & 63) == 0) {
-    tops[threadIdx.x >> 6] = top;
-    bads[threadIdx.x >> 6] = bad;
+    tops[threadIdx.x >> 6] = check.top;
+    bads[threadIdx.x >> 6] = check.bad;
   }
   __syncthreads();
   if (threadIdx.x == 0) {
-    top = max(max(tops[0], tops[1]), max(tops[2], tops[3]));
-    const unsigned long long all_bad = static_cast<unsigned long long>(bads[0]) + bads[1] + bads[2] + bads[3];
-    // the word only grows: a stale value can only cost an atomic that was not needed
-    if (top > __hip_atomic_load(&out->max_bits, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
-      atomicMax(&out->max_bits, top);
-    if (all_bad) atomicAdd(&out->nonfinite, all_bad);
+    check.top = max(max(tops[0], tops[1]), max(tops[2], tops[3]));
+    check.bad = bads[0] + bads[1] + bads[2] + bads[3];
+    check.add_to(out);
   }
 }
 

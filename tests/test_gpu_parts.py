@@ -326,3 +326,35 @@ def test_matrix_in_device_memory_is_trained_in_place(graph_on_device, order_flag
     assert st["K"] == 16 and np.array_equal(M_dev.cpu().numpy(), M0)
     G.gosh_train_parts(n, xadj, adj, M_dev, k, epochs, 0.05, 7, flags=order_flag)
     assert torch.isfinite(M_dev).all()
+
+
+@pytest.mark.parametrize("n,d,K,P,blocked", [(1001, 36, 5, 2, False), (1001, 36, 5, 3, True), (770, 4, 7, 3, False), (4099, 128, 6, 3, False),
+                                             (21, 8, 6, 2, False)])
+def test_swaps_of_pinned_and_pageable_matrices_agree(n, d, K, P, blocked):
+    """A part of a pinned matrix is swapped by one kernel, one of a pageable matrix by copies: the same
+    rows to the bit in sequential order, short and empty last parts among them, and the same entries
+    reported that are no numbers."""
+    c = graph(n, 6 * n, 3)
+    rng = np.random.default_rng(7)
+    M0 = rng.standard_normal((n, d)).astype(np.float32) * np.float32(0.1)
+    flags = G.GOSH_FLAG_SEQUENTIAL | (G.GOSH_FLAG_BLOCKED_ORDER if blocked else 0)
+    for spoilt in (False, True):
+        if spoilt:
+            M0[n // 2, d // 2], M0[n - 1, 0] = np.inf, np.nan
+        got, stats = [], []
+        for pinned in (True, False):
+            M = torch.from_numpy(M0.copy())
+            M = M.pin_memory() if pinned else M
+            run = lambda: G.gosh_train_parts(n, c.xadj, c.adj, M, 2, 2 * K, 0.02, 5, P_gpu=P, force_K=K, B=2, flags=flags)
+            if spoilt:
+                with pytest.raises(G.GoshError) as e:
+                    run()
+                assert e.value.code == G.GOSH_EDIVERGED
+                stats.append(e.value.stats)
+            else:
+                stats.append(run())
+            got.append(M.clone().numpy())
+        assert np.array_equal(got[0].view(np.int32), got[1].view(np.int32)) if not spoilt else \
+            np.array_equal(np.isfinite(got[0]), np.isfinite(got[1]))
+        for key in ("max_abs", "nonfinite", "bytes_h2d", "bytes_d2h"):
+            assert stats[0][key] == stats[1][key]
