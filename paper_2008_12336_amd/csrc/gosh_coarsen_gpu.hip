@@ -68,32 +68,54 @@ __global__ __launch_bounds__(256) void rank_kernel(const uint32_t *__restrict__ 
   }
 }
 
-// First classification, one wavefront per vertex: needs no knowledge of other decisions.
-template <typename OffT>
+// Lanes per vertex of classify_kernel and join_kernel.  Both look at the entries of vertices of at most
+// mean degree, after a chain of dependent reads (rank, offsets, entry, rank or status), and are bound by
+// that chain: with a wavefront per vertex most lanes have no entry and few vertices are in flight.  Fewer
+// lanes pay until the vertices no longer fill the device.  us with 64 / 16 / 8 / 4 lanes, both kernels:
+//   4.2 M vertices, R-MAT, mean degree 30: 1,430 / 868 / 774 / 724    its next level, mean above 100: 421 / 152 / 109 / 84
+//   2.1 M, power law: 2,200 / 1,720 / 1,465 / 1,160                   1 M, uniform: 440 / 344 / 294 / 238
+//   the last one's next levels, each about a tenth: 288 / 192 / 177 / 196, 82 / 59 / 68 / 98, 24 / 50 / 80 / 140
+inline int lanes_per_vertex(int64_t n, int64_t nnz) {
+  int lanes = n >= (int64_t{1} << 20) ? 4 : n >= (int64_t{1} << 16) ? 8 : n >= (int64_t{1} << 13) ? 16 : 64;
+  while (lanes < 64 && lanes * 64 * n < nnz) lanes *= 2;  // at most 64 entries of a mean row to a lane
+  return lanes;
+}
+
+// First classification, LANES lanes per vertex: needs no knowledge of other decisions.
+template <typename OffT, int LANES>
 __global__ __launch_bounds__(256) void classify_kernel(const OffT *__restrict__ xadj,
                                                        const int32_t *__restrict__ adj,
                                                        const uint32_t *__restrict__ rk, int64_t n,
                                                        int32_t *__restrict__ status,
                                                        int32_t *__restrict__ pending,
                                                        unsigned long long *__restrict__ pending_count) {
-  const int lane = threadIdx.x & 63;
-  for (int64_t v = first_wave(); v < n; v += wave_count()) {
-    const uint32_t r = rk[v];
-    int32_t st = kHub;
+  constexpr int kPerWave = 64 / LANES;
+  const int lane = threadIdx.x & 63, gl = lane & (LANES - 1), group = lane & ~(LANES - 1);
+  for (int64_t base = first_wave() * kPerWave; base < n; base += wave_count() * kPerWave) {
+    const int64_t v = base + lane / LANES;
+    const uint32_t r = v < n ? rk[v] : kHighBit;
+    bool high_neighbour = false, predecessor = false;
     if (!(r & kHighBit)) {
-      bool high_neighbour = false, predecessor = false;
       const int64_t begin = static_cast<int64_t>(xadj[v]), end = static_cast<int64_t>(xadj[v + 1]);
-      for (int64_t e = begin + lane; e < end; e += 64) {
+      for (int64_t e = begin + gl; e < end; e += LANES) {
         const uint32_t ru = rk[adj[e]];
         high_neighbour |= (ru & kHighBit) != 0;
         predecessor |= (ru & kRankMask) < r;
       }
-      if (__ballot(high_neighbour) != 0) st = kTaken;
-      else if (__ballot(predecessor) != 0) st = kUndecided;
     }
-    if (lane == 0) {
-      status[v] = st;
-      if (st == kUndecided) pending[atomicAdd(pending_count, 1ull)] = static_cast<int32_t>(v);
+    const uint64_t of_group = ~uint64_t{0} >> (64 - LANES) << group;
+    const bool taken = (__ballot(high_neighbour) & of_group) != 0;
+    const bool undecided = !taken && (__ballot(predecessor) & of_group) != 0;
+    if (gl == 0 && v < n) status[v] = taken ? kTaken : undecided ? kUndecided : kHub;
+    // one atomic per wavefront: thousands on one word follow one another
+    const bool lists = gl == 0 && v < n && undecided;
+    const uint64_t listed = __ballot(lists);
+    if (listed != 0) {
+      const int leader = __builtin_ctzll(listed);
+      unsigned long long at = 0;
+      if (lane == leader) at = atomicAdd(pending_count, static_cast<unsigned long long>(__popcll(listed)));
+      at = __shfl(at, leader, 64) + __popcll(listed & ((uint64_t{1} << lane) - 1));
+      if (lists) pending[at] = static_cast<int32_t>(v);
     }
   }
 }
@@ -146,31 +168,34 @@ __global__ __launch_bounds__(256) void number_hubs_kernel(const int32_t *__restr
     if (flags[t]) map[order[t]] = index[t];
 }
 
-// Every taken vertex joins its first hub in the order, one wavefront per vertex.  The
+// Every taken vertex joins its first hub in the order, LANES lanes per vertex.  The
 // hubs' own entries of map (read here) were written by the launch before this one; this
 // launch writes only entries of taken vertices.
-template <typename OffT>
+template <typename OffT, int LANES>
 __global__ __launch_bounds__(256) void join_kernel(const OffT *__restrict__ xadj,
                                                    const int32_t *__restrict__ adj,
                                                    const uint32_t *__restrict__ rk,
                                                    const int32_t *__restrict__ status,
                                                    const int32_t *__restrict__ order, int64_t n,
                                                    int32_t *map) {
-  const int lane = threadIdx.x & 63;
-  for (int64_t v = first_wave(); v < n; v += wave_count()) {
-    if (status[v] != kTaken) continue;
-    const uint32_t r = rk[v];
+  constexpr int kPerWave = 64 / LANES;
+  const int lane = threadIdx.x & 63, gl = lane & (LANES - 1);
+  for (int64_t base = first_wave() * kPerWave; base < n; base += wave_count() * kPerWave) {
+    const int64_t v = base + lane / LANES;
     uint32_t best = kRankMask;
-    const int64_t begin = static_cast<int64_t>(xadj[v]), end = static_cast<int64_t>(xadj[v + 1]);
-    for (int64_t e = begin + lane; e < end; e += 64) {
-      const int32_t u = adj[e];
-      const uint32_t ru = rk[u] & kRankMask;
-      if (ru < r && ru < best && status[u] == kHub) best = ru;
+    if (v < n && status[v] == kTaken) {
+      const uint32_t r = rk[v];
+      const int64_t begin = static_cast<int64_t>(xadj[v]), end = static_cast<int64_t>(xadj[v + 1]);
+      for (int64_t e = begin + gl; e < end; e += LANES) {
+        const int32_t u = adj[e];
+        const uint32_t ru = rk[u] & kRankMask;
+        if (ru < r && ru < best && status[u] == kHub) best = ru;
+      }
     }
-    for (int offset = 32; offset > 0; offset >>= 1) best = min(best, __shfl_xor(best, offset, 64));
+    for (int offset = LANES / 2; offset > 0; offset >>= 1) best = min(best, __shfl_xor(best, offset, 64));
     // a taken vertex has a hub before it, so best is a valid position; the guard keeps a
     // broken invariant from turning into a wild read
-    if (lane == 0 && best < static_cast<uint32_t>(n)) map[v] = map[order[best]];
+    if (gl == 0 && best < static_cast<uint32_t>(n)) map[v] = map[order[best]];
   }
 }
 
@@ -463,9 +488,19 @@ int mark_impl(DeviceCoarsener *dc, DeviceLevel &fine, int64_t *n_coarse, bool *d
   if (int rc = buf.alloc(&still, static_cast<size_t>(n), "pending list")) return rc;
   if (int rc = buf.alloc(&counters, 2, "pending counters")) return rc;
   GOSH_TRY_HIP(hipMemset(counters, 0, 16), "clear counters");
-  const int wave_blocks = blocks_for(n, 4);  // four wavefronts (vertices) per block
-  hipLaunchKernelGGL(classify_kernel<OffT>, dim3(wave_blocks), dim3(256), 0, nullptr, xadj, adj, rk, n, status,
-                     pending, counters);
+  const int lanes = lanes_per_vertex(n, nnz);
+  const auto classify = lanes == 4    ? classify_kernel<OffT, 4>
+                        : lanes == 8  ? classify_kernel<OffT, 8>
+                        : lanes == 16 ? classify_kernel<OffT, 16>
+                        : lanes == 32 ? classify_kernel<OffT, 32>
+                                      : classify_kernel<OffT, 64>;
+  const auto join = lanes == 4    ? join_kernel<OffT, 4>
+                    : lanes == 8  ? join_kernel<OffT, 8>
+                    : lanes == 16 ? join_kernel<OffT, 16>
+                    : lanes == 32 ? join_kernel<OffT, 32>
+                                  : join_kernel<OffT, 64>;
+  const int group_blocks = blocks_for(n, 256 / lanes);
+  hipLaunchKernelGGL(classify, dim3(group_blocks), dim3(256), 0, nullptr, xadj, adj, rk, n, status, pending, counters);
   if (int rc = gosh::check_launch("classify_kernel")) return rc;
   unsigned long long count = 0;
   GOSH_TRY_HIP(hipMemcpy(&count, counters, 8, hipMemcpyDeviceToHost), "read pending count");
@@ -516,8 +551,7 @@ int mark_impl(DeviceCoarsener *dc, DeviceLevel &fine, int64_t *n_coarse, bool *d
     if (int rc = persistent(&fine.map, static_cast<size_t>(n), "map")) return rc;
   hipLaunchKernelGGL(number_hubs_kernel, dim3(flat_blocks), dim3(256), 0, nullptr, flags, index, order, n, fine.map);
   if (int rc = gosh::check_launch("number_hubs_kernel")) return rc;
-  hipLaunchKernelGGL(join_kernel<OffT>, dim3(wave_blocks), dim3(256), 0, nullptr, xadj, adj, rk, status, order, n,
-                     fine.map);
+  hipLaunchKernelGGL(join, dim3(group_blocks), dim3(256), 0, nullptr, xadj, adj, rk, status, order, n, fine.map);
   if (int rc = gosh::check_launch("join_kernel")) return rc;
   GOSH_TRY_HIP(hipDeviceSynchronize(), "marking");
   *n_coarse = static_cast<int64_t>(last_flag) + last_index;

@@ -401,3 +401,13 @@ def test_rebuild_of_wide_graphs_costs_no_more_than_sorting_their_entries():
         h.free()
     print(f"[wide] rebuild {min(build_ms):.1f} ms, sort of its {adj.numel()} entries {min(sort_ms):.1f} ms")
     assert min(build_ms) <= 1.25 * min(sort_ms)
+
+
+@pytest.mark.parametrize("n,per_vertex", [(8191, 3), (8192, 3), (8195, 600), (65_535, 2), (65_541, 4), (65_536, 300),
+                                          ((1 << 20) - 1, 2), ((1 << 20) + 3, 3)])
+def test_marking_with_few_lanes_per_vertex(n, per_vertex):
+    """The marking kernels give a vertex 4, 8, 16 or 64 lanes by the vertices of a level, more where its
+    rows are long: both sides of each border, vertices that do not fill the last wavefront, rows
+    of many turns."""
+    edges = graphgen.chung_lu(n, per_vertex * n, 11)
+    assert_equals_host(graphgen.to_csr(n, edges), threshold=500, min_shrink=0.9)
