@@ -217,19 +217,21 @@ struct LockSet {
 // over some rounds and samples.  Rows that start inside a block share lines with their neighbours:
 // they count by their columns, and barely pay where half of a lane group is idle.  With few negatives
 // many of the rows drawn are positives, of which R-MAT graphs have few, and such launches must be
-// larger.  Time with locks over time with adds, power law / R-MAT, by rounds, and the rule's edge:
-//   d = 128, k = 9   1.5: 0.86 / 0.90                (1.3)     k = 3   2: 0.83 / 0.94        (1.8)
-//            k = 1   3: 0.84 / 0.93                  (2.7)     d = 192, k = 3  4: 0.75 / 0.78  (3.2)
-//   d = 80,  k = 3   6: 0.94 / 0.91                  (4.6)     d = 384, k = 9  1: 0.78 / 0.79  (0.8)
-//   d = 64,  k = 3   2: 0.83 / 0.93                  (1.8)     k = 1   3: 0.84 / 1.07, 4: 0.83 / 1.05  (3.6)
-//   d = 52,  k = 3   1.8: 0.93 / 1.07, 2.5: 0.83 / 0.91  (2.2)  k = 1  3: 0.91 / 1.12, 4: 0.86 / 1.09  (4.4)
-//   d = 100, k = 9   2.5: 0.91 / 0.95 (2.3)    k = 3   2.5: 0.97 / 1.02, 3: 0.91 / 0.94      (3.3)
-//            k = 1   4: 0.99 / 1.07, 6: 0.95 / 0.98  (6.7)
-//   d = 76,  k = 9   3.6: 1.03 / 1.05, 6: 0.94 / 0.96 (4.6)    k = 2   6: 1.05 / 1.09        (8.8)
-//   d = 68,  k = 9   4: 1.08 / 1.11, 8: 0.98 / 0.98 (7.4)      k = 3   6: 1.06 / 1.14, 12: 0.98 / 0.96 (10.6)
-//   d = 132, k = 9   4: 1.07 / 1.09, 8: 0.99 / 0.99 (7.4)      k = 3   6: 1.01 / 1.04, 12: 0.96 / 0.99 (10.6)
-//   d = 260, k = 9   1.5: 1.04 / 1.05, 2.5: 0.96 / 0.95 (2.1)  k = 3   2: 0.99 / 1.04, 3: 0.94 / 0.96  (3.0)
-//   d = 36,  k = 3   4: 0.91 / 1.03, 6: 0.85 / 0.90  (6.0), three blocks, which adds do in one instruction
+// larger.  The edge lies where a kernel of chunks of four samples broke even; sgd_locked_walk does so
+// earlier where rows straddle lines or leave lanes idle.  Time with locks over time with adds, power
+// law / R-MAT with m = 10 n, by rounds, and the rule's edge:
+//   d = 128, k = 9   1.5: 0.64 / 0.72                (1.3)     k = 3   2: 0.68 / 0.75        (1.8)
+//            k = 1   3: 0.66 / 0.83                  (2.7)     d = 192, k = 3  4: 0.61 / 0.66  (3.2)
+//   d = 80,  k = 3   6: 0.75 / 0.78                  (4.6)     d = 384, k = 9  1: 0.62 / 0.66  (0.8)
+//   d = 64,  k = 3   2: 0.76 / 0.99                  (1.8)     k = 1   3: 0.75 / 1.07, 4: 0.71 / 1.01  (3.6)
+//   d = 52,  k = 3   1.8: 0.83 / 1.07, 2.5: 0.74 / 0.88  (2.2)  k = 1  3: 0.80 / 1.07, 4: 0.75 / 1.00  (4.4)
+//   d = 100, k = 9   2.5: 0.69 / 0.76 (2.3)    k = 3   2.5: 0.80 / 0.94, 3: 0.76 / 0.85      (3.3)
+//            k = 1   4: 0.84 / 1.02, 6: 0.78 / 0.85  (6.7)
+//   d = 76,  k = 9   3.6: 0.77 / 0.80, 6: 0.70 / 0.68 (4.6)    k = 2   6: 0.87 / 0.87        (8.8)
+//   d = 68,  k = 9   4: 0.82 / 0.85, 8: 0.73 / 0.74 (7.4)      k = 3   6: 0.89 / 0.87, 12: 0.81 / 0.79 (10.6)
+//   d = 132, k = 9   4: 0.80 / 0.80, 8: 0.72 / 0.71 (7.4)      k = 3   6: 0.85 / 0.89, 12: 0.79 / 0.81 (10.6)
+//   d = 260, k = 9   1.5: 0.79 / 0.80, 2.5: 0.70 / 0.71 (2.1)  k = 3   2: 0.80 / 0.84, 3: 0.74 / 0.78  (3.0)
+//   d = 36,  k = 3   4: 0.81 / 0.99, 6: 0.74 / 0.86  (6.0), three blocks, which adds do in one instruction
 inline bool worth_locking(int64_t sources, int64_t samples, int64_t capacity, int32_t d) {
   const int64_t blocks = (d + 15) / 16;
   if (blocks < 3) return false;
@@ -258,7 +260,7 @@ inline bool worth_locking(int64_t sources, int64_t samples, int64_t capacity, in
 // or if more than kMostAtOnce of 64 consecutive sources draw it, which start at the same time.
 // Shares of 2 / 8 / 16 on 200,000 x 128, us: stars of ten leaves in a row 504 / 374 / 375, R-MAT
 // 231 / 228 / 226, power law 230 / 226 / 226; at 67,000 with a bound of 1 instead of 2 every fourth
-// row is a hub.  Counting takes 6 us of 95 at 67,000 x 128.
+// row is a hub.  Counting takes 6 us of 76 at 67,000 x 128.
 constexpr int64_t kHubShare = 8;
 constexpr uint32_t kMostAtOnce = 2;
 constexpr uint32_t kDrawnAtOnce = 0x80000000u;  // flag in a word of draws
