@@ -684,16 +684,26 @@ __device__ __forceinline__ void sgd_walk(const W &w, const SgdArgs &a) {
   }
 }
 
-// Workgroups of sgd_locked_kernel.  One wavefront each: one that ends makes room for the next at once,
-// not when three others end too (67,000 x 128, k = 3: 83.1 -> 78.3 us; a rotation of 4 x 500,000 rows
-// 41.1 -> 40.6 ms).  Rows that straddle lines are left at four and at six wavefronts per SIMD: more
-// sources in flight are faster (333,337 x 100, k = 9: 909 -> 888 us) but take their turns further from
-// the order of Alg. 3 (distance from it in 64 bits 3.1e-4 -> 4.9e-4; it was 3.0e-4 with chunks of four).
-template <class P>
-constexpr int kLockedThreads = P::kAligned ? 256 : 64;
-// Wavefronts per SIMD that the registers must allow.  Longer rows need what they need.
-template <class P, int UPL>
-constexpr int kLockedWaves = UPL * P::F > 4 ? 1 : P::kAligned ? 6 : 7;
+// Workgroups of sgd_locked_kernel: one wavefront, which makes room for the next when it ends and not
+// when three others end too; long rows, of which few fit a CU, stay at four.
+template <int UPL>
+constexpr int kLockedThreads = UPL > 4 ? 256 : 64;
+// Wavefronts per SIMD, no fewer (the registers allow them without scratch) and no more.  More sources in
+// flight are faster, but a source then works on a copy of its row that is further behind, and the result
+// lies further from the sequential order of Alg. 3: these counts keep it where chunks of four samples in
+// workgroups of four had it.  Sources of a visit hold their rows for B rounds.  Relative distance from
+// the sequential result, and us: with chunks of four / up to seven wavefronts per SIMD / these counts
+//   epoch 67,000 x 128, k = 3       2.66e-4 / 2.87e-4 / 2.67e-4      101 /     80 /     83
+//   epoch 262,144 x 64, k = 3       1.98e-4 / 2.14e-4 / 1.98e-4      178 /    158 /    164
+//   epoch 333,337 x 100, k = 9      2.92e-4 / 3.11e-4 / 2.89e-4    1,003 /    828 /    860
+//   epoch 60,000 x 260, k = 9       3.70e-4 / 4.18e-4 / 3.65e-4      492 /    355 /    424
+//   visits, in place 2 M x 128      8.77e-5 / 1.02e-4 / 8.65e-5   47,400 / 40,900 / 42,800
+//   visits, in place 262,147 x 100  5.85e-5 / 6.91e-5 / 5.85e-5    3,510 /  2,620 /  2,960
+//   visits, in place 400,001 x 64   1.60e-4 / 1.79e-4 / 1.53e-4    4,880 /  4,320 /  4,700
+//   visits, in place 100,001 x 512  6.09e-5 / 8.18e-5 / 5.40e-5    3,150 /  3,060 /  3,150
+//   visits, in place 300,001 x 128  3.11e-5 / 4.00e-5 / 3.38e-5    2,220 /  1,930 /  1,970  (R-MAT)
+template <class P, int UPL, class W>
+constexpr int kLockedWaves = UPL > 4 ? (P::kAligned || W::kLongTurns ? 3 : 4) : (P::kAligned ? 5 : 6) - (W::kLongTurns ? 1 : 0);
 
 // Waits for all outstanding accesses to memory, and lets the compiler know that it has.
 __device__ __forceinline__ void wait_memory() {
@@ -742,7 +752,7 @@ __device__ __forceinline__ void sgd_locked_walk(const W &w, const SgdArgs &a, co
   // of a workgroup lie the grid's width apart, but that takes the sources of both parts of a visit up
   // side by side instead of one part's after the other's.)  Sources fit 31 bits, as vertices do, and so
   // does what follows the last ones.
-  constexpr uint32_t kWaves = SEQ ? 1 : kLockedThreads<P> / 64;
+  constexpr uint32_t kWaves = SEQ ? 1 : kLockedThreads<UPL> / 64;
   const uint32_t per_block = static_cast<uint32_t>(a.sources_per_block);
   const uint32_t block_lo = SEQ ? 0 : blockIdx.x * per_block;
   const uint32_t count = static_cast<uint32_t>(w.count());
@@ -765,14 +775,14 @@ __device__ __forceinline__ void sgd_locked_walk(const W &w, const SgdArgs &a, co
   };
   auto readable = [&](int32_t c) { return c < d ? c : d - F; };
   // the source row by column; the entries past d stay zero
-  __shared__ float held_rows[P::kAligned ? kLockedThreads<P> / LPG * kSlots : 1];
+  __shared__ float held_rows[P::kAligned ? kLockedThreads<UPL> / LPG * kSlots : 1];
   float *const held = held_rows + (P::kAligned ? threadIdx.x / LPG * kSlots : 0);
   auto held_in_order = [] {  // the wavefront's LDS accesses take effect in program order; keep that order
     if constexpr (P::kAligned) __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
   };
   // the source row as it was read, later its change; every lane uses its own entries only
-  __shared__ float kept_rows[kLockedThreads<P> * UPL * F];
-  auto kept = [&](int i, int c) -> float & { return kept_rows[(i * F + c) * kLockedThreads<P> + threadIdx.x]; };
+  __shared__ float kept_rows[kLockedThreads<UPL> * UPL * F];
+  auto kept = [&](int i, int c) -> float & { return kept_rows[(i * F + c) * kLockedThreads<UPL> + threadIdx.x]; };
 
   auto in_group = [&](bool x) -> Mask {
     return static_cast<Mask>(__ballot(x) >> (lane & ~(LPG - 1))) & static_cast<Mask>(~uint64_t{0} >> (64 - LPG));
@@ -1003,7 +1013,9 @@ __global__ __launch_bounds__(256) void sgd_kernel(W w, SgdArgs a) {
   sgd_walk<P, LPG, UPL, W, SEQ>(w, a);
 }
 template <class P, int LPG, int UPL, class W, bool SEQ>
-__global__ __launch_bounds__(kLockedThreads<P>, (kLockedWaves<P, UPL>)) void sgd_locked_kernel(W w, SgdArgs a, LockSet lock) {
+__global__ __launch_bounds__(kLockedThreads<UPL>)
+    __attribute__((amdgpu_waves_per_eu((kLockedWaves<P, UPL, W>), (kLockedWaves<P, UPL, W>)))) void
+    sgd_locked_kernel(W w, SgdArgs a, LockSet lock) {
   sgd_locked_walk<P, LPG, UPL, W, SEQ>(w, a, lock);
 }
 
@@ -1028,7 +1040,7 @@ struct SgdLauncher {
   static void run(const W &w, SgdArgs a, const LockSet &lock, int64_t count, bool seq, int64_t max_waves,
                   hipStream_t st) {
     const bool locked = a.hot.mode == kHotLocked && !std::is_same_v<P, RowPlain128>;
-    const int waves_per_block = locked ? kLockedThreads<P> / 64 : 4;
+    const int waves_per_block = locked ? kLockedThreads<UPL> / 64 : 4;
     constexpr int kGroupsPerWave = 64 / LPG;
     const int64_t per_turn = waves_per_block * kGroupsPerWave;  // sources a workgroup takes per turn
     const int64_t turns = std::max<int64_t>((count + per_turn - 1) / per_turn, 1);
@@ -1040,7 +1052,7 @@ struct SgdLauncher {
     if constexpr (!std::is_same_v<P, RowPlain128>) {
       if (locked && seq) hipLaunchKernelGGL((sgd_locked_kernel<P, LPG, UPL, W, true>), dim3(1), dim3(64), 0, st, w, a, lock);
       else if (locked)
-        hipLaunchKernelGGL((sgd_locked_kernel<P, LPG, UPL, W, false>), dim3(blocks), dim3(kLockedThreads<P>), 0, st, w, a, lock);
+        hipLaunchKernelGGL((sgd_locked_kernel<P, LPG, UPL, W, false>), dim3(blocks), dim3(kLockedThreads<UPL>), 0, st, w, a, lock);
       if (locked) return;
     }
     if (seq) hipLaunchKernelGGL((sgd_kernel<P, LPG, UPL, W, true>), dim3(1), dim3(64), 0, st, w, a);

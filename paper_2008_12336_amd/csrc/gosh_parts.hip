@@ -41,6 +41,7 @@ __host__ __device__ inline uint32_t level_word(uint32_t level, uint32_t pair_ind
 // rounds of 1 + k_neg samples: the positive of round r comes from its pool entry, the
 // negatives are uniform over the partner part.
 struct PairWork {
+  static constexpr bool kLongTurns = true;  // a source takes B rounds of samples
   int32_t a_lo, a_n, b_lo, b_n;  // vertex id ranges of the two parts
   float *a_rows, *b_rows;        // device slots holding their rows
   const int32_t *pool_a;         // a_n * B positives for the sources of a

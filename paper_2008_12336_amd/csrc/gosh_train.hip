@@ -70,6 +70,7 @@ __global__ __launch_bounds__(256) void sample_epoch_kernel(SamplerArgs a, int32_
 // source, sample t is draw t of that source, rows live in one matrix.
 template <typename OffT>
 struct EpochWork {
+  static constexpr bool kLongTurns = false;  // a source takes one round of samples
   SamplerArgs s;
   float *M;
   int32_t d;

@@ -1,0 +1,64 @@
+"""How far concurrent training under row locks ends from the sequential order of Alg. 3 and Alg. 5.
+
+A source works on its own copy of its row for its whole turn, and turns run side by side, so the result
+depends on how many sources are in flight (and on how evenly they advance).  The distances here are
+relative 2-norms from the oracle's sequential result after one epoch or rotation at the first learning
+rate of a schedule; two runs differ by one or two percent of them."""
+import numpy as np
+import pytest
+import torch
+
+import graphgen
+import paper_2008_12336_amd as G
+from oracle import gosh_oracle as O
+from tests.test_gpu_layout import DEV, say, upload
+from tests.util import HOT_LOCKED, csr_numpy, last_hot_mode
+
+pytestmark = pytest.mark.gpu
+
+
+def inputs(n, m, d, seed):
+    xadj, adj = csr_numpy(graphgen.to_csr(n, graphgen.chung_lu(n, m, seed)))
+    M0 = np.random.default_rng(seed).standard_normal((n, d), dtype=np.float32) * np.float32(d ** -0.5)
+    return xadj, adj, M0
+
+
+def distance(M, want):
+    want = want.astype(np.float64)
+    return float(np.linalg.norm(M.cpu().numpy() - want) / np.linalg.norm(want))
+
+
+# most: halfway between the larger of what the present kernel and chunks of four samples give, and what one
+# or two wavefronts more per SIMD give: 2.73e-4 and 2.92e-4, 3.82e-4 and 4.31e-4
+@pytest.mark.parametrize("n,d,k,most", [(67_000, 128, 3, 2.82e-4), (60_000, 260, 9, 4.06e-4)])
+def test_locked_epochs_stay_near_the_sequential_order(n, d, k, most):
+    xadj, adj, M0 = inputs(n, 10 * n, d, 3)
+    g, keep = upload(n, xadj, adj, False)
+    want = M0.copy()
+    O.train_epoch(xadj, adj, want, k, 0.025, 7, 0, 0)
+    for _ in range(2):
+        M = torch.from_numpy(M0).to(DEV)
+        G.gosh_train_epoch(g, M, k, 0.025, 7, 0, 0)
+        torch.cuda.synchronize()
+        assert last_hot_mode() == HOT_LOCKED
+        far = distance(M, want)
+        say(f"[order] epoch n={n} d={d} k={k}: {far:.3e}")
+        assert far <= most
+
+
+# in the same way: 5.97e-5 and 7.99e-5, 6.11e-5 and 8.79e-5, 7.48e-5 and 8.88e-5
+@pytest.mark.parametrize("n,d,most", [(150_001, 256, 7.0e-5), (100_001, 512, 7.4e-5), (150_001, 100, 8.2e-5)])
+def test_locked_visits_stay_near_the_sequential_order(n, d, most):
+    k, K, B = 3, 2, 5
+    xadj, adj, M0 = inputs(n, 10 * n, d, 3)
+    xt, at = torch.from_numpy(xadj).to(DEV), torch.from_numpy(adj).to(DEV)
+    want = M0.copy()
+    O.train_parts(xadj, adj, want, k, 1, 0.005, 7, 0, K, B)
+    for _ in range(2):
+        M = torch.from_numpy(M0).to(DEV)
+        G.gosh_train_parts(n, xt, at, M, k, 1, 0.005, 7, force_K=K, B=B)
+        torch.cuda.synchronize()
+        assert last_hot_mode() == HOT_LOCKED
+        far = distance(M, want)
+        say(f"[order] visits in place n={n} d={d}: {far:.3e}")
+        assert far <= most
