@@ -207,6 +207,7 @@ struct LockSet {
   const uint32_t *draws = nullptr;
   uint32_t most = 0;
   int32_t max_tries = 0;  // of a lock
+  int32_t waves_per_cu = 0;  // wavefronts of the launch that a CU may hold (0: kLockedWaves alone decides)
 };
 
 // Whether a launch in which every row is hot takes locks.  `capacity` sources run at a time (C when
@@ -1036,6 +1037,17 @@ inline bool rows_at_lines(const float *M, int32_t d) { return reinterpret_cast<u
 // `a.sources_per_block` is filled in here from `count`.
 template <class W>
 struct SgdLauncher {
+  // LDS of a locked workgroup beyond what it uses, so that no more than `waves` wavefronts fit a CU.
+  template <class P, int LPG, int UPL>
+  static unsigned lds_for(int waves) {
+    if (waves == 0) return 0;
+    constexpr int kThreads = kLockedThreads<UPL>;
+    constexpr unsigned kOwn = 4 * kThreads * UPL * P::F + (P::kAligned ? 4 * kThreads * UPL : 4);
+    constexpr unsigned kPerCu = 160 * 1024, kGranule = 1280;
+    const unsigned share = kPerCu / std::max(waves / (kThreads / 64), 1) / kGranule * kGranule;
+    return share > kOwn ? share - kOwn : 0;
+  }
+
   template <class P, int LPG, int UPL>
   static void run(const W &w, SgdArgs a, const LockSet &lock, int64_t count, bool seq, int64_t max_waves,
                   hipStream_t st) {
@@ -1052,7 +1064,8 @@ struct SgdLauncher {
     if constexpr (!std::is_same_v<P, RowPlain128>) {
       if (locked && seq) hipLaunchKernelGGL((sgd_locked_kernel<P, LPG, UPL, W, true>), dim3(1), dim3(64), 0, st, w, a, lock);
       else if (locked)
-        hipLaunchKernelGGL((sgd_locked_kernel<P, LPG, UPL, W, false>), dim3(blocks), dim3(kLockedThreads<UPL>), 0, st, w, a, lock);
+        hipLaunchKernelGGL((sgd_locked_kernel<P, LPG, UPL, W, false>), dim3(blocks), dim3(kLockedThreads<UPL>),
+                           (lds_for<P, LPG, UPL>(lock.waves_per_cu)), st, w, a, lock);
       if (locked) return;
     }
     if (seq) hipLaunchKernelGGL((sgd_kernel<P, LPG, UPL, W, true>), dim3(1), dim3(64), 0, st, w, a);

@@ -199,33 +199,29 @@ __global__ __launch_bounds__(256) void count_pool_kernel(PairWork w, uint32_t *_
 // last.  What leaves is checked for divergence on the way.
 // Bound by the link.  Copies of pieces on two streams (an upload behind the write-back of the same
 // bytes) spend a piece's time before the first upload and 10 to 40 us between pieces: 30 MB each way
-// took 0.80 ms like that, and smaller pieces more.  Workgroups of one wavefront, since one of four would
-// wait for four places on a CU at a time while a training kernel of such workgroups runs.
-// Few of them: 40 keep the link busy, more hold up the training kernel beside them (a rotation of
-// 524,288 x 128 under 96 MB: copies 38.6 ms; 16 workgroups 40.8, 24 37.1, 32 36.6, 40 36.0, 64 41.2,
-// 128 44.3; 1 M x 256 under 460 MB: 111 ms; 122, 115, 107, 104, 106, 116; 6 M x 128 under 1.7 GB 231 -> 220).
+// took 0.80 ms like that, and smaller pieces more.  See Rotation::plan_swaps for where it runs.
 constexpr int kSwapUnits = 8;  // in flight per lane and direction
-constexpr int kSwapBlocks = 40;
-__global__ __launch_bounds__(64) void swap_part_kernel(gosh::Float4 *__restrict__ slot, gosh::Float4 *__restrict__ old_host,
-                                                       int64_t old_units, const gosh::Float4 *__restrict__ new_host,
-                                                       int64_t new_units, gosh::CheckResult *__restrict__ out) {
+__global__ __launch_bounds__(128) void swap_part_kernel(gosh::Float4 *__restrict__ slot, gosh::Float4 *__restrict__ old_host,
+                                                        int64_t old_units, const gosh::Float4 *__restrict__ new_host,
+                                                        int64_t new_units, gosh::CheckResult *__restrict__ out) {
   const int64_t units = std::max(old_units, new_units);
+  const int64_t lanes = blockDim.x, per_turn = lanes * kSwapUnits;
   gosh::EntryCheck check;
-  for (int64_t base = blockIdx.x * (64LL * kSwapUnits); base < units; base += gridDim.x * (64LL * kSwapUnits)) {
+  for (int64_t base = blockIdx.x * per_turn; base < units; base += gridDim.x * per_turn) {
     gosh::Float4 leaves[kSwapUnits], comes[kSwapUnits];
 #pragma unroll
     for (int q = 0; q < kSwapUnits; ++q) {
-      const int64_t i = base + q * 64 + threadIdx.x;
+      const int64_t i = base + q * lanes + threadIdx.x;
       leaves[q] = slot[std::min(i, old_units - 1)];
     }
 #pragma unroll
     for (int q = 0; q < kSwapUnits; ++q) {
-      const int64_t i = base + q * 64 + threadIdx.x;
+      const int64_t i = base + q * lanes + threadIdx.x;
       comes[q] = __builtin_nontemporal_load(new_host + std::min(i, new_units - 1));
     }
 #pragma unroll
     for (int q = 0; q < kSwapUnits; ++q) {
-      const int64_t i = base + q * 64 + threadIdx.x;
+      const int64_t i = base + q * lanes + threadIdx.x;
       if (i < old_units) {
         check.look(leaves[q]);
         __builtin_nontemporal_store(leaves[q], old_host + i);
@@ -233,12 +229,12 @@ __global__ __launch_bounds__(64) void swap_part_kernel(gosh::Float4 *__restrict_
     }
 #pragma unroll
     for (int q = 0; q < kSwapUnits; ++q) {
-      const int64_t i = base + q * 64 + threadIdx.x;
+      const int64_t i = base + q * lanes + threadIdx.x;
       if (i < new_units) slot[i] = comes[q];
     }
   }
   check.reduce_wave();
-  if (threadIdx.x == 0) check.add_to(out);
+  if ((threadIdx.x & 63) == 0) check.add_to(out);
 }
 
 struct HostCsr {
@@ -450,13 +446,12 @@ class Rotation {
       GOSH_TRY_HIP(hipEventCreate(&k_begin[t]), "hipEventCreate");
       GOSH_TRY_HIP(hipEventCreate(&k_end[t]), "hipEventCreate");
     }
-    if (!pl.matrix_on_device)
-      host_rows = static_cast<float *>(gosh::pinned_on_device(pl.M_host, static_cast<size_t>(pl.g->n) * pl.d * 4));
     GOSH_TRY_HIP(gosh::device_malloc(&check, sizeof(gosh::CheckResult)), "hipMalloc check result");
     if (int rc = gosh::matrix_check_clear(check, copy_out)) return rc;
     GOSH_TRY_HIP(hipEventRecord(arrived, copy_out), "hipEventRecord");
     GOSH_TRY_HIP(hipStreamWaitEvent(copy, arrived, 0), "hipStreamWaitEvent");  // swaps add to the check
     if (int rc = build_hot_set()) return rc;
+    plan_swaps();
     if (!graph_on_device) sampler = std::thread([this] { sampler_loop(); });
     return GOSH_OK;
   }
@@ -541,7 +536,9 @@ class Rotation {
   int64_t npairs = 0, visits = 0;
 
   std::vector<float *> slot;
-  float *host_rows = nullptr;  // the host matrix as kernels reach it, or null
+  float *host_rows = nullptr;  // the host matrix as kernels reach it, where they swap the parts
+  int swap_threads = 0, swap_blocks = 0;
+  int locked_waves_per_cu = 0;  // see LockSet
   std::vector<int32_t *> dpool, staging;
   std::vector<int32_t> slot_part;
   uint32_t *hot_bits_dev = nullptr;
@@ -642,6 +639,43 @@ class Rotation {
     return GOSH_OK;
   }
 
+  // How the parts of a host matrix move, and how many wavefronts a visit under locks has beside that.
+  //
+  // A wavefront that waits for the host link holds up the others of its CU (loads return in order there),
+  // so swaps by kernel slow the visits beside them and spread the pace of their sources, the further the
+  // more CUs they run on: with 40 workgroups of one wavefront beside visits under locks a rotation ended
+  // 1.7 times as far from the sequential order as with copies.  There the kernel is 16 workgroups of two,
+  // which fit beside 16 wavefronts of the visit per CU at once.  Visits that store without locks show no
+  // such distance (3.1e-3 either way) and leave no registers for two.  ms and distance with chunks of four
+  // samples beside copies / copies beside 18 wavefronts per CU / the kernel beside 16, 20 samples a source:
+  //   524,288 x 128 under 96 MB   40.5, 1.64e-4 / 38.6, 1.69e-4 / 36.4, 1.64e-4
+  //   700,001 x 64 under 70 MB    26.0, 1.96e-4 / 25.1, 1.82e-4 / 24.6, 1.76e-4
+  //   2^20 x 256 under 460 MB      133, 8.0e-5  /  129, 8.1e-5  /  124, 7.4e-5
+  // It pays where the link is the longer side of a visit.  The link takes 24 ns per KB of a part's row; a
+  // visit changes 2 (samples + 1) rows for it, 0.4 ns per KB under locks (0.6 where rows straddle lines,
+  // 0.3 as stores, 0.8 as adds), and in the blocked order a part that comes in meets several others.
+  // Copies / the kernel, ms: locked, 524,288 x 128 with 8 samples 34.3 / 33.2, 30 42.4 / 42.4, 40 48.8 / 52.2,
+  // 100 96.7 / 105.4; 700,001 x 64 with 30 28.8 / 29.7; 524,289 x 100 with 20 30.9 / 30.7; adds, 3 M x 32 53.4 /
+  // 54.5, 1.4 M x 8 21.5 / 22.5; stores, 20 samples, 6 M x 128 254 / 245, 10 M x 32 85.8 / 77.3, 3 M x 100 84.1 /
+  // 79.4.  Parts of some GB the copies move faster: 1.7 GB 833 / 803 ms, 2.6 GB (65 M x 128 under 8 GB) 5.31 /
+  // 5.48 s.
+  static constexpr int64_t kSwapMostBytes = int64_t{7} << 28;
+  static constexpr int kBesideCopies = 18, kBesideSwaps = 16;  // wavefronts of a locked visit per CU
+  void plan_swaps() {
+    gosh::seam(gosh::kSeamSwaps) = 0;
+    if (pl.matrix_on_device) return;
+    const bool locked = hot.mode == gosh::kHotLocked;
+    const int64_t partners = (pl.flags & GOSH_FLAG_BLOCKED_ORDER) ? std::max(1, pl.order_P - 2) : 1;
+    const bool straddle = locked && !gosh::rows_at_lines(slot[0], pl.d);
+    const int64_t short_rows = std::max(32 / pl.d, 1);  // a row costs the memory system a line at least
+    const bool link_is_longer = hot.mode != gosh::kHotAll && samples * partners * short_rows * (straddle ? 3 : 2) < 60;
+    if (link_is_longer && L.part_rows * pl.d * 4 <= kSwapMostBytes)
+      host_rows = static_cast<float *>(gosh::pinned_on_device(pl.M_host, static_cast<size_t>(pl.g->n) * pl.d * 4));
+    swap_threads = locked ? 128 : 64;
+    swap_blocks = locked ? 16 : 40;
+    locked_waves_per_cu = host_rows != nullptr ? kBesideSwaps : kBesideCopies;
+  }
+
   // Sampler thread (host graph only): pools of positives, at most NS visits ahead of their
   // release.
   void sampler_loop() {
@@ -710,29 +744,33 @@ class Rotation {
     const size_t new_bytes = static_cast<size_t>(L.size(p)) * d * 4;
     float *new_host = pl.M_host + static_cast<int64_t>(L.lo(p)) * d;
     if (slot_part[victim] >= 0) {
-      // Where kernels cannot reach the host matrix: write the old part back on the outbound stream and bring the new one in on the
-      // inbound stream, piece by piece: the upload of a piece waits only for the
-      // write-back of the same bytes of the slot.  A later upload of the old part must
-      // see its host bytes; it is queued on the inbound stream after these waits, the
-      // last of which covers the whole write-back.
       const int32_t old = slot_part[victim];
       const size_t old_bytes = static_cast<size_t>(L.size(old)) * d * 4;
       float *old_host = pl.M_host + static_cast<int64_t>(L.lo(old)) * d;
       if (host_rows != nullptr && old_bytes > 0 && new_bytes > 0) {
+        // One kernel on the inbound stream, behind the last kernel that used the slot.  What it writes to the
+        // host is there before anything later on that stream reads it.
         const int64_t old_units = static_cast<int64_t>(old_bytes / 16), new_units = static_cast<int64_t>(new_bytes / 16);
-        const int64_t turns = (std::max(old_units, new_units) + 64 * kSwapUnits - 1) / (64 * kSwapUnits);
-        const int blocks = static_cast<int>(std::min<int64_t>(turns, kSwapBlocks));
+        const int64_t per_turn = static_cast<int64_t>(swap_threads) * kSwapUnits;
+        const int64_t turns = (std::max(old_units, new_units) + per_turn - 1) / per_turn;
+        const int blocks = static_cast<int>(std::min<int64_t>(turns, swap_blocks));
         GOSH_TRY_HIP(hipStreamWaitEvent(copy, slot_used[victim], 0), "hipStreamWaitEvent");
-        hipLaunchKernelGGL(swap_part_kernel, dim3(blocks), dim3(64), 0, copy, reinterpret_cast<gosh::Float4 *>(slot[victim]),
+        hipLaunchKernelGGL(swap_part_kernel, dim3(blocks), dim3(swap_threads), 0, copy,
+                           reinterpret_cast<gosh::Float4 *>(slot[victim]),
                            reinterpret_cast<gosh::Float4 *>(host_rows + static_cast<int64_t>(L.lo(old)) * d), old_units,
                            reinterpret_cast<const gosh::Float4 *>(host_rows + static_cast<int64_t>(L.lo(p)) * d), new_units,
                            check);
         if (int rc = gosh::check_launch("swap_part_kernel")) return rc;
+        ++gosh::seam(gosh::kSeamSwaps);
         st.bytes_d2h += old_bytes;
         st.bytes_h2d += new_bytes;
         GOSH_TRY_HIP(hipEventRecord(slot_ready[victim], copy), "hipEventRecord");
         return GOSH_OK;
       }
+      // Otherwise: write the old part back on the outbound stream and bring the new one in on the
+      // inbound stream, piece by piece: the upload of a piece waits only for the write-back of the
+      // same bytes of the slot.  A later upload of the old part must see its host bytes; it is queued
+      // on the inbound stream after these waits, the last of which covers the whole write-back.
       const size_t longest = std::max(old_bytes, new_bytes);
       size_t piece = (longest + kSwapChunks - 1) / kSwapChunks;
       piece = std::max<size_t>((piece + 255) / 256 * 256, size_t(8) << 20);
@@ -873,7 +911,8 @@ class Rotation {
       const int blocks = static_cast<int>(std::min<int64_t>((rows + 255) / 256, 65536));
       hipLaunchKernelGGL(count_pool_kernel, dim3(blocks), dim3(256), 0, compute, w, draws, locks + rows * (2 - vi % 2), rows);
       if (int rc = gosh::check_launch("count_pool_kernel")) return rc;
-      lock = gosh::LockSet{locks, draws, gosh::most_draws(w.count(), per_round, lock_in_flight), gosh::lock_tries()};
+      lock = gosh::LockSet{locks, draws, gosh::most_draws(w.count(), per_round, lock_in_flight), gosh::lock_tries(),
+                           locked_waves_per_cu};
     }
     // The counting needs no rows: queued ahead of the wait for them it runs beside the part swap (its few
     // workgroups take 20 to 80 us there, 5 alone).

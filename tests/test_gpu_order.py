@@ -12,7 +12,7 @@ import graphgen
 import paper_2008_12336_amd as G
 from oracle import gosh_oracle as O
 from tests.test_gpu_layout import DEV, say, upload
-from tests.util import HOT_LOCKED, csr_numpy, last_hot_mode
+from tests.util import HOT_LOCKED, SEAM_SWAPS, csr_numpy, last_hot_mode, set_seam
 
 pytestmark = pytest.mark.gpu
 
@@ -61,4 +61,28 @@ def test_locked_visits_stay_near_the_sequential_order(n, d, most):
         assert last_hot_mode() == HOT_LOCKED
         far = distance(M, want)
         say(f"[order] visits in place n={n} d={d}: {far:.3e}")
+        assert far <= most
+
+
+# by_kernel: whether kernels swap the parts; most: halfway between the larger of what there is now and what
+# chunks of four samples beside copies gave, and what seven wavefronts per SIMD beside swaps by 40 workgroups
+# gave: 1.47e-4 and 2.16e-4, 2.47e-4 and 2.87e-4, 1.27e-4 and 1.95e-4, 2.73e-4 and 3.61e-4, 1.36e-4 and 1.97e-4
+@pytest.mark.parametrize("n,d,k,by_kernel,most", [(250_000, 128, 3, True, 1.82e-4), (250_000, 64, 3, True, 2.67e-4),
+                                                  (150_000, 256, 3, True, 1.61e-4), (250_000, 128, 9, False, 3.17e-4),
+                                                  (250_000, 100, 3, False, 1.67e-4)])
+def test_locked_rotations_stay_near_the_sequential_order(n, d, k, by_kernel, most):
+    """Parts of a pinned matrix on their way through the device beside the visits: what moves them must not
+    hold up some sources and not others."""
+    K, B = 5, 5
+    xadj, adj, M0 = inputs(n, 10 * n, d, 3)
+    xt, at = torch.from_numpy(xadj).to(DEV), torch.from_numpy(adj).to(DEV)
+    want = M0.copy()
+    O.train_parts(xadj, adj, want, k, 1, 0.005, 7, 0, K, B)
+    for _ in range(2):
+        M = torch.from_numpy(M0).pin_memory()
+        G.gosh_train_parts(n, xt, at, M, k, 1, 0.005, 7, force_K=K, P_gpu=3, B=B)
+        assert last_hot_mode() == HOT_LOCKED
+        assert (set_seam(SEAM_SWAPS, 0) > 0) == by_kernel
+        far = distance(M, want)
+        say(f"[order] rotation n={n} d={d} k={k}: {far:.3e}")
         assert far <= most

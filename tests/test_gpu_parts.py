@@ -9,7 +9,7 @@ import graphgen
 import paper_2008_12336_amd as G
 from oracle import gosh_oracle as O
 from tests.linkpred import aucroc, make_eval_sets
-from tests.util import conditioned_bar, oracle_sensitivity, rel_err
+from tests.util import SEAM_SWAPS, conditioned_bar, oracle_sensitivity, rel_err, set_seam
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
@@ -358,3 +358,76 @@ def test_swaps_of_pinned_and_pageable_matrices_agree(n, d, K, P, blocked):
             np.array_equal(np.isfinite(got[0]), np.isfinite(got[1]))
         for key in ("max_abs", "nonfinite", "bytes_h2d", "bytes_d2h"):
             assert stats[0][key] == stats[1][key]
+
+
+def run_both_ways(n, d, K, P, k, B, flags, M_of, seed=3):
+    """A rotation of a matrix made by M_of and of a pageable one: rows, statistics and kernel swaps of both."""
+    c = graph(n, 6 * n, seed)
+    M0 = np.random.default_rng(seed).standard_normal((n, d)).astype(np.float32) * np.float32(0.1)
+    out = []
+    for make in (M_of, lambda rows: torch.from_numpy(rows.copy())):
+        M = make(M0)
+        st = G.gosh_train_parts(n, c.xadj, c.adj, M, k, 2 * B * K, 0.02, 5, P_gpu=P, force_K=K, B=B, flags=flags)
+        out.append((M.clone().numpy(), st, set_seam(SEAM_SWAPS, 0)))
+    return out
+
+
+@pytest.mark.parametrize("n,d,K,P,k,B,flags,by_kernel", [
+    (1001, 36, 5, 2, 2, 2, 0, True),
+    (1001, 36, 40, 3, 2, 2, 0, True),    # 26 rows a part: the last but one has 13, the last none
+    (9, 8, 4, 3, 0, 2, 0, True),         # 3 rows a part, the last empty
+    (770, 4, 7, 3, 2, 1, 0, True),       # rows shorter than a line: up to 3 samples
+    (770, 4, 7, 3, 3, 1, 0, False),
+    (600, 64, 6, 3, 6, 4, 0, True),      # 28 samples and 30
+    (600, 64, 6, 3, 9, 3, 0, False),
+    (600, 64, 6, 4, 6, 2, G.GOSH_FLAG_BLOCKED_ORDER, True),   # blocks of two parts: 2 * 14 and 2 * 16 samples
+    (600, 64, 6, 4, 7, 2, G.GOSH_FLAG_BLOCKED_ORDER, False),
+])
+def test_where_kernels_swap_parts(n, d, K, P, k, B, flags, by_kernel):
+    """A kernel swaps the parts of a pinned matrix where the link is the longer side of a visit, copies do
+    elsewhere and for pageable matrices: the same rows to the bit in sequential order."""
+    pinned, pageable = run_both_ways(n, d, K, P, k, B, flags | G.GOSH_FLAG_SEQUENTIAL, lambda rows: torch.from_numpy(rows.copy()).pin_memory())
+    assert (pinned[2] > 0) == by_kernel and pageable[2] == 0
+    assert np.array_equal(pinned[0].view(np.int32), pageable[0].view(np.int32))
+    for key in ("max_abs", "nonfinite", "bytes_h2d", "bytes_d2h"):
+        assert pinned[1][key] == pageable[1][key]
+
+
+def test_atomic_adds_leave_the_parts_to_copies():
+    out = run_both_ways(1001, 36, 5, 2, 2, 2, G.GOSH_FLAG_ATOMIC_ADDS, lambda rows: torch.from_numpy(rows.copy()).pin_memory())
+    assert out[0][2] == 0 and out[1][2] == 0
+    assert np.abs(out[0][0] - out[1][0]).max() < 1e-2
+
+
+@pytest.mark.parametrize("before,behind", [(4, 60), (4096, 0), (20, 1 << 16)])
+def test_a_matrix_inside_a_pinned_allocation(before, behind):
+    """A matrix that begins some floats into its allocation, 16-byte aligned but not at a line: the same rows
+    as a pageable one, and nothing around it written."""
+    n, d = 1001, 36
+    whole = torch.full((before + n * d + behind,), 7.5).pin_memory()
+
+    def inside(rows):
+        M = whole[before:before + n * d].view(n, d)
+        M.copy_(torch.from_numpy(rows))
+        return M
+
+    out = run_both_ways(n, d, 5, 2, 2, 2, G.GOSH_FLAG_SEQUENTIAL, inside)
+    assert out[0][2] > 0
+    assert np.array_equal(out[0][0].view(np.int32), out[1][0].view(np.int32))
+    assert (whole[:before] == 7.5).all() and (whole[before + n * d:] == 7.5).all()
+
+
+def test_a_matrix_that_ends_where_its_pinned_allocation_ends():
+    import ctypes
+    hip = G.lib()  # its own HIP runtime
+    n, d = 1001, 36
+    p = ctypes.c_void_p()
+    torch.cuda.synchronize()
+    assert hip.hipHostMalloc(ctypes.byref(p), ctypes.c_size_t(n * d * 4), ctypes.c_uint(0)) == 0
+    try:
+        M = torch.frombuffer((ctypes.c_float * (n * d)).from_address(p.value), dtype=torch.float32).view(n, d)
+        out = run_both_ways(n, d, 5, 2, 2, 2, G.GOSH_FLAG_SEQUENTIAL, lambda rows: M.copy_(torch.from_numpy(rows)))
+        assert out[0][2] > 0
+        assert np.array_equal(out[0][0].view(np.int32), out[1][0].view(np.int32))
+    finally:
+        assert hip.hipHostFree(p) == 0

@@ -105,7 +105,8 @@ def conditioned_bar(sensitivity):
 
 
 # Seams of the library for its own tests (gosh_common.h), of the calling thread.
-(SEAM_HOT_MODE, SEAM_DENY, SEAM_RADIX_FROM, SEAM_WIDE_SUMS, SEAM_LOCK_TRIES, SEAM_LOCKS_HELD) = range(6)
+(SEAM_HOT_MODE, SEAM_DENY, SEAM_RADIX_FROM, SEAM_WIDE_SUMS, SEAM_LOCK_TRIES, SEAM_LOCKS_HELD,
+ SEAM_SWAPS) = range(7)
 DENY_LOCKS, DENY_STAGING, DENY_RADIX, DENY_TABLE = 1, 2, 4, 8
 HOT_NONE, HOT_BITMAP, HOT_ALL, HOT_LOCKED = range(4)
 
