@@ -197,3 +197,33 @@ def test_locked_visits_of_several_chunks(d, n, k, B):
     torch.cuda.synchronize()
     assert last_hot_mode() == HOT_LOCKED
     assert rel_err(M.cpu().numpy(), want) <= TOL
+
+
+@pytest.mark.parametrize("d,n,k,B", [(64, 40_000, 3, 5), (64, 40_000, 15, 2), (36, 125_000, 3, 5), (100, 32_000, 3, 9), (128, 18_000, 3, 9),
+                                     (200, 16_000, 6, 10), (260, 15_000, 12, 5)])
+def test_concurrent_visits_of_several_chunks(d, n, k, B):
+    """All groups of all wavefronts at work, each with a lock, the next chunk's ids and its counts of draws
+    carried over a chunk's border at its own pace (20 or 32 samples of 16 lanes, 36 of 32, 65 or 70 of 64):
+    two parts, two rotations in one call, so that locks and counts left behind would show.  To first order,
+    as in assert_first_order.  (An epoch has at most 16 samples and, under locks, at least 16 lanes.)"""
+    K, lr = 2, 1e-5
+    xadj, adj = sink_graph(n, 30, 4, 9)
+    xt, at = torch.from_numpy(xadj).to(DEV), torch.from_numpy(adj).to(DEV)
+    M0 = start_matrix(n, d, 5, 0.5)
+    want = M0.copy()
+    O.train_parts(xadj, adj, want, k, 2 * B * K, lr, 77, 0, K, B)
+    M = torch.from_numpy(M0).to(DEV)
+    st = G.gosh_train_parts(n, xt, at, M, k, 2 * B * K, lr, 77, force_K=K, B=B)
+    torch.cuda.synchronize()
+    assert last_hot_mode() == HOT_LOCKED and st["rotations"] == 2
+    updates = np.full(n, 2.0 * K)  # a source's own change is added once a visit
+    narrow = np.zeros((n, 4), dtype=np.float32)
+    for rotation in range(2):
+        for q, (pa, pb) in enumerate(O.pair_order(K)):
+            ids = O.train_pair(xadj, adj, narrow, k, B, K, pa, pb, 0.0, 77, rotation, 0, q, want_stream=True)
+            updates += np.bincount(ids[ids >= 0], minlength=n)
+    updates += 2 * K * B * (k + 1)  # the roundings of the copy that the source works on
+    step = np.abs(want.astype(np.float64) - M0).max(axis=1)
+    err = np.abs(M.cpu().numpy().astype(np.float64) - want).max(axis=1)
+    say(f"[contended] visits d={d} k={k} B={B}: worst err/step {np.max(err / np.maximum(step, 1e-30)):.3e}")
+    assert (err <= 0.02 * step + updates * 2.0 ** -23 * np.abs(M0).max()).all()
