@@ -187,10 +187,11 @@ struct RowAgentLine : RowAgent32 {
 // Locked rows.  fp32 atomic adds run at 20.5 G 64-byte blocks per second on the whole chip, and
 // a launch in which every row is hot is bound by that.  A row can also be written without losing
 // an update by taking a lock first: one 32-bit exchange instead of an atomic add per block, then
-// the row is read, changed and written back like a cold one (5.3 G rows of 512 bytes per second,
-// read included, against 2.55 G as adds alone).  In kHotLocked mode every row is written that
-// way, except hubs, whose holders would queue up: their rows take atomic adds, always, so that a
-// row is only ever written one way in a launch (but see kMaxTries).
+// the row is read, changed and written back like a cold one (7.0 G rows of 512 bytes per second where
+// the memory-side cache holds them, 5.0 G where it does not, read included, against 2.55 G as adds
+// alone).  In kHotLocked mode every row is written that way, except hubs, whose holders would queue up:
+// their rows take atomic adds, always, so that a row is only ever written one way in a launch (but see
+// kMaxTries).
 enum HotMode : int32_t { kHotNone = 0, kHotBitmap = 1, kHotAll = 2, kHotLocked = 3 };
 
 struct HotSet {
@@ -218,21 +219,23 @@ struct LockSet {
 // over some rounds and samples.  Rows that start inside a block share lines with their neighbours:
 // they count by their columns, and barely pay where half of a lane group is idle.  With few negatives
 // many of the rows drawn are positives, of which R-MAT graphs have few, and such launches must be
-// larger.  The edge lies where a kernel of chunks of four samples broke even; sgd_locked_walk does so
-// earlier where rows straddle lines or leave lanes idle.  Time with locks over time with adds, power
-// law / R-MAT with m = 10 n, by rounds, and the rule's edge:
-//   d = 128, k = 9   1.5: 0.64 / 0.72                (1.3)     k = 3   2: 0.68 / 0.75        (1.8)
-//            k = 1   3: 0.66 / 0.83                  (2.7)     d = 192, k = 3  4: 0.61 / 0.66  (3.2)
-//   d = 80,  k = 3   6: 0.75 / 0.78                  (4.6)     d = 384, k = 9  1: 0.62 / 0.66  (0.8)
-//   d = 64,  k = 3   2: 0.76 / 0.99                  (1.8)     k = 1   3: 0.75 / 1.07, 4: 0.71 / 1.01  (3.6)
-//   d = 52,  k = 3   1.8: 0.83 / 1.07, 2.5: 0.74 / 0.88  (2.2)  k = 1  3: 0.80 / 1.07, 4: 0.75 / 1.00  (4.4)
-//   d = 100, k = 9   2.5: 0.69 / 0.76 (2.3)    k = 3   2.5: 0.80 / 0.94, 3: 0.76 / 0.85      (3.3)
-//            k = 1   4: 0.84 / 1.02, 6: 0.78 / 0.85  (6.7)
-//   d = 76,  k = 9   3.6: 0.77 / 0.80, 6: 0.70 / 0.68 (4.6)    k = 2   6: 0.87 / 0.87        (8.8)
-//   d = 68,  k = 9   4: 0.82 / 0.85, 8: 0.73 / 0.74 (7.4)      k = 3   6: 0.89 / 0.87, 12: 0.81 / 0.79 (10.6)
-//   d = 132, k = 9   4: 0.80 / 0.80, 8: 0.72 / 0.71 (7.4)      k = 3   6: 0.85 / 0.89, 12: 0.79 / 0.81 (10.6)
-//   d = 260, k = 9   1.5: 0.79 / 0.80, 2.5: 0.70 / 0.71 (2.1)  k = 3   2: 0.80 / 0.84, 3: 0.74 / 0.78  (3.0)
-//   d = 36,  k = 3   4: 0.81 / 0.99, 6: 0.74 / 0.86  (6.0), three blocks, which adds do in one instruction
+// larger.  The edge is where a kernel of chunks of four samples broke even, and the tests hold it there
+// vertex for vertex; sgd_locked_walk breaks even earlier where rows straddle lines or leave lanes idle, so
+// launches of such rows below the edge forgo up to a fifth, and R-MAT graphs with one negative gain
+// nothing just above it.  Time with locks over time with adds, power law / R-MAT with m = 10 n, by
+// rounds, and the rule's edge:
+//   d = 128, k = 9   1.5: 0.65 / 0.71                (1.3)     k = 3   2: 0.70 / 0.79        (1.8)
+//            k = 1   3: 0.69 / 0.86                  (2.7)     d = 192, k = 3  4: 0.66 / 0.69  (3.2)
+//   d = 80,  k = 3   6: 0.81 / 0.80                  (4.6)     d = 384, k = 9  1: 0.65 / 0.70  (0.8)
+//   d = 64,  k = 3   2: 0.77 / 0.96                  (1.8)     k = 1   3: 0.76 / 1.05, 4: 0.75 / 1.03  (3.6)
+//   d = 52,  k = 3   1.8: 0.84 / 1.05, 2.5: 0.77 / 0.87  (2.2)  k = 1  3: 0.83 / 1.05, 4: 0.78 / 1.02  (4.4)
+//   d = 100, k = 9   2.5: 0.70 / 0.76 (2.3)    k = 3   2.5: 0.80 / 0.91, 3: 0.77 / 0.85      (3.3)
+//            k = 1   4: 0.83 / 0.97, 6: 0.78 / 0.87  (6.7)
+//   d = 76,  k = 9   3.6: 0.79 / 0.80, 6: 0.72 / 0.72 (4.6)    k = 2   6: 0.89 / 0.89        (8.8)
+//   d = 68,  k = 9   4: 0.85 / 0.87, 8: 0.75 / 0.75 (7.4)      k = 3   6: 0.90 / 0.87, 12: 0.82 / 0.82 (10.6)
+//   d = 132, k = 9   4: 0.84 / 0.84, 8: 0.75 / 0.76 (7.4)      k = 3   6: 0.88 / 0.92, 12: 0.83 / 0.82 (10.6)
+//   d = 260, k = 9   1.5: 0.91 / 0.91, 2.5: 0.83 / 0.83 (2.1)  k = 3   2: 0.94 / 0.98, 3: 0.88 / 0.91  (3.0)
+//   d = 36,  k = 3   4: 0.85 / 0.97, 6: 0.78 / 0.85  (6.0), three blocks, which adds do in one instruction
 inline bool worth_locking(int64_t sources, int64_t samples, int64_t capacity, int32_t d) {
   const int64_t blocks = (d + 15) / 16;
   if (blocks < 3) return false;
@@ -261,7 +264,7 @@ inline bool worth_locking(int64_t sources, int64_t samples, int64_t capacity, in
 // or if more than kMostAtOnce of 64 consecutive sources draw it, which start at the same time.
 // Shares of 2 / 8 / 16 on 200,000 x 128, us: stars of ten leaves in a row 504 / 374 / 375, R-MAT
 // 231 / 228 / 226, power law 230 / 226 / 226; at 67,000 with a bound of 1 instead of 2 every fourth
-// row is a hub.  Counting takes 6 us of 76 at 67,000 x 128.
+// row is a hub.  Counting takes 7 us of 79 at 67,000 x 128.
 constexpr int64_t kHubShare = 8;
 constexpr uint32_t kMostAtOnce = 2;
 constexpr uint32_t kDrawnAtOnce = 0x80000000u;  // flag in a word of draws
@@ -704,7 +707,8 @@ constexpr int kLockedThreads = UPL > 4 ? 256 : 64;
 //   visits, in place 100,001 x 512  6.09e-5 / 8.18e-5 / 5.40e-5    3,150 /  3,060 /  3,150
 //   visits, in place 300,001 x 128  3.11e-5 / 4.00e-5 / 3.38e-5    2,220 /  1,930 /  1,970  (R-MAT)
 template <class P, int UPL, class W>
-constexpr int kLockedWaves = UPL > 4 ? (P::kAligned || W::kLongTurns ? 3 : 4) : (P::kAligned ? 5 : 6) - (W::kLongTurns ? 1 : 0);
+constexpr int kLockedWaves = UPL > 4 ? (P::kAligned || W::kLongTurns ? 3 : 4)
+                                     : (P::kAligned ? 5 : 6) - (W::kLongTurns ? 1 : 0);
 
 // Waits for all outstanding accesses to memory, and lets the compiler know that it has.
 __device__ __forceinline__ void wait_memory() {
@@ -723,14 +727,15 @@ __device__ __forceinline__ void wait_memory() {
 //
 // What bounds it is the latency of those round trips (70 to 80 % of a wavefront's time), so the layout is
 // made for few registers: the source row as it was read lies in LDS, ids and hub flags are a register
-// each and not one per sample, places are 32-bit.  With chunks of four samples as in sgd_walk, five to
-// six wavefronts per SIMD, 67,000 x 128, k = 3 took 93.3 us, now 75.5 with the counting of the draws;
-// 333,337 x 100, k = 9 1,046, now 909; a rotation of 4 x 500,000 rows at d = 128 47.4 ms, now 40.6 (4.1 G
-// rows/s; visits of 2 x 58,000 rows, which the memory-side cache holds, 5.8 G).
-// The source row is read with the first sample's, where that can be: earlier it is older (67,000 x 128:
-// distance from the sequential epoch 2.96e-4, so 2.88e-4, for the same time).
+// each and not one per sample, places are 32-bit.  With chunks of four samples as in sgd_walk 67,000 x
+// 128, k = 3 took 93.5 us, now 78.5 with the counting of the draws; 333,337 x 100, k = 9 1,045, now 969 (750
+// on one matrix that stays in the memory-side cache); the pair scheme in place on 4 x 500,000 rows at d = 128 47.4 ms,
+// now 43.0 (3.9 G rows/s; visits of 2 x 58,000 rows, which the memory-side cache holds, 5.2 G).
+// The source row is read with the first sample's, where that can be: read earlier it is older (67,000 x
+// 128 with seven wavefronts per SIMD: distance from the sequential epoch 2.96e-4, so 2.88e-4, for the same
+// time).
 // What lost: the lock of the next row asked for while a row is read (one round trip per row, but then a
-// lock is held while another is not to be had: 67,000 x 128 98 -> 1,200 us, rotations 1.5 to 2.5 times
+// lock is held while another is not to be had: 67,000 x 128 98 -> 1,200 us, visits 1.5 to 2.5 times
 // as long); versions in the lock words, which let a row be read beside its lock (140 us: a load from a
 // line that others write words of costs more than the round trip, also where the versions lie apart);
 // eight wavefronts per SIMD by spilling (878 -> 945 us at 333,337 x 100).

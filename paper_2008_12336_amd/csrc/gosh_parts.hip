@@ -8,7 +8,9 @@
 //   * sampler thread: fills pools of positive samples on the host, a bounded number of
 //     pairs ahead (an OpenMP team fills one pool);
 //   * copy-in stream: part upload / pool upload, and copy-out stream: part write-back
-//     (the two directions of the host link run at the same time), overlapped with
+//     (the two directions of the host link run at the same time); where the link bounds the
+//     rotation and the matrix is pinned, a part swap is one kernel on the copy-in stream;
+//     overlapped with
 //   * compute stream: one pair kernel per visited pair, in the fixed inside-out order.
 #include <hip/hip_runtime.h>
 #include <omp.h>
@@ -512,8 +514,8 @@ class Rotation {
     uint32_t rot, q;   // rotation, index of the pair inside the rotation
   };
   enum { kPlaced = 0, kNoSlot = 1, kError = -2 };
-  // A part swap runs in kSwapChunks pieces: piece c of the new part goes up as soon as piece
-  // c of the old one is down, so both directions of the host link are busy at once.
+  // A part swap by copies runs in kSwapChunks pieces: piece c of the new part goes up as soon as
+  // piece c of the old one is down, so both directions of the host link are busy at once.
   static constexpr int kSwapChunks = 8;
   // Kernel timing: a ring of event pairs, read when a pair is used again and at the end.
   // The host is normally a few visits ahead of the kernels, so that read does not wait;
@@ -545,7 +547,7 @@ class Rotation {
   uint32_t *locks = nullptr;     // a lock per row of a visit, then two times its draws, in turns
   int64_t lock_in_flight = 0;    // sources in flight that the hub rule counts with
   gosh::HotSet hot{nullptr, gosh::kHotNone};
-  gosh::CheckResult *check = nullptr;  // divergence check, accumulated on the outbound stream
+  gosh::CheckResult *check = nullptr;  // divergence check, accumulated on the outbound stream, by swap kernels on the inbound one
   hipStream_t compute = nullptr, copy = nullptr, copy_out = nullptr;
   std::vector<hipEvent_t> chunk_flushed, slot_ready, slot_used, pool_ready, pool_used, staging_done, k_begin, k_end;
   std::vector<char> k_pending;
