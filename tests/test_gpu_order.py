@@ -28,9 +28,9 @@ def distance(M, want):
     return float(np.linalg.norm(M.cpu().numpy() - want) / np.linalg.norm(want))
 
 
-# most: halfway between the larger of what the present kernel and chunks of four samples give, and what one
-# or two wavefronts more per SIMD give: 2.73e-4 and 2.92e-4, 3.82e-4 and 4.31e-4
-@pytest.mark.parametrize("n,d,k,most", [(67_000, 128, 3, 2.82e-4), (60_000, 260, 9, 4.06e-4)])
+# most: between the larger of what the present kernel and chunks of four samples give, and what one or two
+# wavefronts more per SIMD give: 2.75e-4 and 2.92e-4, 3.82e-4 and 4.31e-4
+@pytest.mark.parametrize("n,d,k,most", [(67_000, 128, 3, 2.86e-4), (60_000, 260, 9, 4.06e-4)])
 def test_locked_epochs_stay_near_the_sequential_order(n, d, k, most):
     xadj, adj, M0 = inputs(n, 10 * n, d, 3)
     g, keep = upload(n, xadj, adj, False)
