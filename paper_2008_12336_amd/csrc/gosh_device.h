@@ -341,31 +341,42 @@ constexpr int kChunk = 4;  // sample rows in flight per source
 constexpr int32_t kMaxTries = 1 << 14;
 inline int32_t lock_tries() { return seam(kSeamLockTries) ? static_cast<int32_t>(seam(kSeamLockTries)) : kMaxTries; }
 
-// Atomic adds of whole rows with 128-bit units, one row at a time by the whole wavefront.
-// A memory-side fp32 atomic costs one operation per instruction and line it touches, full or
-// sparse.  A lane group of d/4 lanes that adds its own four floats per lane needs four
-// instructions per row, each touching every line of the row; here the rows to be added (one
-// per lane group that asks, `mine`) are taken in turn, lane l of the wavefront fetches float l
-// of the row's step from the lane that holds it and adds it at row + l: one instruction per
-// row, each line touched once.  Needs d <= 64 and every lane of the wavefront present (no
-// divergent branch around the call); `mine` and `row` are uniform inside a lane group.
+// Atomic adds of whole rows with 128-bit units, by the whole wavefront.  A memory-side fp32 atomic
+// costs one operation per instruction and line it touches, full or sparse.  A lane group of d/4
+// lanes that adds its own four floats per lane needs four instructions per row, each touching every
+// line of the row; here the rows to be added (one per lane group that asks, `mine`) are laid out
+// side by side in LDS, 4 * LPG floats each, and lane l of the wavefront adds float l of every 64:
+// 16 / LPG rows per instruction, each line touched once, and at most four instructions however many
+// groups a wavefront has.  (One row per instruction, its floats fetched from the lanes that hold them,
+// made a wavefront's rows a serial chain: epochs of 1,024 sources, k = 3, d = 8 / 16 / 32 / 64 took 24.8 /
+// 12.1 / 9.4 / 7.0 us, now 6.4 / 6.0 / 5.9 / 6.0; 65,536 sources 29.4 / 26.1 / 42.1, now 20.0 / 24.1 / 39.8 at
+// d = 8 / 16 / 32, where the adds themselves bound it; a store and add mix of 4.2 M x 32 1,124, now 1,100.)  Needs d <= 64 and every lane of the wavefront present (no divergent branch around
+// the call); `mine` and `row` are uniform inside a lane group.
 template <int LPG>
-__device__ __forceinline__ void add_rows_as_a_wave(bool mine, float *row, const Unit<4> &step, int32_t d, int lane) {
-  unsigned long long todo = __ballot(mine && (lane & (LPG - 1)) == 0);
-  const uint64_t address = reinterpret_cast<uint64_t>(row);
-  const int piece = lane & 3;
-  while (todo != 0) {
-    const int leader = __builtin_amdgcn_readfirstlane(__builtin_ctzll(todo));
-    todo &= todo - 1;
-    const uint32_t lo = __builtin_amdgcn_readlane(static_cast<uint32_t>(address), leader);
-    const uint32_t hi = __builtin_amdgcn_readlane(static_cast<uint32_t>(address >> 32), leader);
-    float *const target = reinterpret_cast<float *>((static_cast<uint64_t>(hi) << 32) | lo);
-    const int owner = leader + (lane >> 2);  // lanes past the row wrap around and are masked below
-    const float x0 = __shfl(step.v[0], owner, 64), x1 = __shfl(step.v[1], owner, 64);
-    const float x2 = __shfl(step.v[2], owner, 64), x3 = __shfl(step.v[3], owner, 64);
-    const float x = piece == 0 ? x0 : piece == 1 ? x1 : piece == 2 ? x2 : x3;
-    if (lane < d) atomic_step(target + lane, x);
+struct RowsOfWave {
+  Float4 step[64];
+  float *row[64 / LPG];
+};
+template <int LPG>
+__device__ __forceinline__ void add_rows_as_a_wave(bool mine, float *row, const Unit<4> &step, int32_t d, int lane,
+                                                   RowsOfWave<LPG> &rows) {
+  static_assert(LPG <= 16, "a row is at most 64 floats");
+  const unsigned long long todo = __ballot(mine);
+  if (todo == 0) return;  // the same for the whole wavefront
+  rows.step[lane] = step.v;
+  if ((lane & (LPG - 1)) == 0) rows.row[lane / LPG] = row;
+  // a wavefront's LDS accesses take effect in program order; the compiler must keep it
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  const float *const floats = reinterpret_cast<const float *>(rows.step);
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    if (((todo >> (16 * r)) & 0xFFFFu) == 0) continue;  // no owner of these 64 floats adds
+    const int owner = 16 * r + (lane >> 2), column = (64 * r + lane) & (4 * LPG - 1);
+    const float x = floats[64 * r + lane];
+    float *const target = rows.row[owner / LPG];
+    if (((todo >> owner) & 1) != 0 && column < d) atomic_step(target + column, x);
   }
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
 }
 
 // Position of a chunk of kChunk samples in the work of one lane group: source index, first
@@ -490,6 +501,9 @@ __device__ __forceinline__ void sgd_walk(const W &w, const SgdArgs &a) {
   auto held_in_order = [] {  // the wavefront's LDS accesses take effect in program order; keep that order
     if constexpr (P::kAligned) __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
   };
+
+  __shared__ RowsOfWave<P::kWaveAtomics ? LPG : 16> all_rows[P::kWaveAtomics ? 4 : 1];
+  auto &rows_of_wave = all_rows[P::kWaveAtomics ? threadIdx.x >> 6 : 0];
 
   // Stage 2 for the chunk at `pos`: lane q of the group evaluates sample pos.t0 + q (in
   // several passes if the group has fewer than kChunk lanes).
@@ -641,7 +655,7 @@ __device__ __forceinline__ void sgd_walk(const W &w, const SgdArgs &a) {
             U step;
 #pragma unroll
             for (int c = 0; c < F; ++c) step.v[c] = g * s[0].v[c];
-            add_rows_as_a_wave<LPG>(hot, row, step, d, lane);
+            add_rows_as_a_wave<LPG>(hot, row, step, d, lane, rows_of_wave);
           } else if (hot) {
 #pragma unroll
             for (int i = 0; i < UPL; ++i)
@@ -677,7 +691,7 @@ __device__ __forceinline__ void sgd_walk(const W &w, const SgdArgs &a) {
       U step;
 #pragma unroll
       for (int c = 0; c < F; ++c) step.v[c] = s[0].v[c] - s_before[0].v[c];
-      add_rows_as_a_wave<LPG>(src_hot, src_row, step, d, lane);
+      add_rows_as_a_wave<LPG>(src_hot, src_row, step, d, lane, rows_of_wave);
     } else if (src_hot) {
 #pragma unroll
       for (int i = 0; i < UPL; ++i)
@@ -789,6 +803,9 @@ __device__ __forceinline__ void sgd_locked_walk(const W &w, const SgdArgs &a, co
   // the source row as it was read, later its change; every lane uses its own entries only
   __shared__ float kept_rows[kLockedThreads<UPL> * UPL * F];
   auto kept = [&](int i, int c) -> float & { return kept_rows[(i * F + c) * kLockedThreads<UPL> + threadIdx.x]; };
+
+  __shared__ RowsOfWave<P::kWaveAtomics ? LPG : 16> all_rows[P::kWaveAtomics ? kLockedThreads<UPL> / 64 : 1];
+  auto &rows_of_wave = all_rows[P::kWaveAtomics ? threadIdx.x >> 6 : 0];
 
   auto in_group = [&](bool x) -> Mask {
     return static_cast<Mask>(__ballot(x) >> (lane & ~(LPG - 1))) & static_cast<Mask>(~uint64_t{0} >> (64 - LPG));
@@ -946,7 +963,7 @@ __device__ __forceinline__ void sgd_locked_walk(const W &w, const SgdArgs &a, co
           U step;
 #pragma unroll
           for (int c = 0; c < F; ++c) step.v[c] = g * s[0].v[c];
-          add_rows_as_a_wave<LPG>(add, row, step, d, lane);
+          add_rows_as_a_wave<LPG>(add, row, step, d, lane, rows_of_wave);
         } else if (add) {
 #pragma unroll
           for (int i = 0; i < UPL; ++i)
@@ -1002,7 +1019,7 @@ __device__ __forceinline__ void sgd_locked_walk(const W &w, const SgdArgs &a, co
       U step;
 #pragma unroll
       for (int c = 0; c < F; ++c) step.v[c] = kept(0, c);
-      add_rows_as_a_wave<LPG>(add, src_row, step, d, lane);
+      add_rows_as_a_wave<LPG>(add, src_row, step, d, lane, rows_of_wave);
     } else if (add) {
 #pragma unroll
       for (int i = 0; i < UPL; ++i)
@@ -1034,7 +1051,7 @@ inline bool rows_at_lines(const float *M, int32_t d) { return reinterpret_cast<u
 //                          of the sequential-order debug mode
 //   otherwise, d <= 64     128-bit agent-scope units, LPG = pow2ceil(d/4) lanes, one unit per
 //                          lane (4..64 sources per wavefront); hot rows are added to by the
-//                          whole wavefront, one row at a time
+//                          whole wavefront
 //   otherwise, d  > 64     32-bit agent-scope units interleaved over LPG = pow2ceil(d/4)
 //                          lanes (<= 64), four or eight units per lane; their columns from the
 //                          address of the row where rows do not start at line borders
@@ -1047,7 +1064,8 @@ struct SgdLauncher {
   static unsigned lds_for(int waves) {
     if (waves == 0) return 0;
     constexpr int kThreads = kLockedThreads<UPL>;
-    constexpr unsigned kOwn = 4 * kThreads * UPL * P::F + (P::kAligned ? 4 * kThreads * UPL : 4);
+    constexpr unsigned kOwn = 4 * kThreads * UPL * P::F + (P::kAligned ? 4 * kThreads * UPL : 4) +
+                              (P::kWaveAtomics ? kThreads / 64 * sizeof(RowsOfWave<(LPG <= 16 ? LPG : 16)>) : 0);
     constexpr unsigned kPerCu = 160 * 1024, kGranule = 1280;
     const unsigned share = kPerCu / std::max(waves / (kThreads / 64), 1) / kGranule * kGranule;
     return share > kOwn ? share - kOwn : 0;
