@@ -46,7 +46,9 @@ using gosh::kGatherTile;
 using gosh::kInside;
 using gosh::row_of_entry;
 
-constexpr int kGatherRows = 1024;          // rows of a tile that are looked up in LDS
+constexpr int kGatherRows = 1024;          // rows of a tile that are looked up in LDS,
+constexpr int kTileRows = 4096;            // among at most so many
+constexpr int64_t kNarrowFrom = 1 << 19;   // vertices whose map no L2 holds beside the streams
 // Longest segments that are sorted in the registers of a wavefront, 1, 2, 4 or 8 per lane, and
 // in those of a workgroup.
 constexpr int kSortClasses = 5;
@@ -102,19 +104,17 @@ struct Slice {
   int32_t row, part;
 };
 
-// len[t] = degree of the t-th vertex in cluster order, len[n] = 0.
+// len[t] = degree of the t-th vertex in cluster order, len[n] = 0; begin[t] = its first entry.
 template <typename OffT>
 __global__ __launch_bounds__(256) void row_lengths_kernel(const OffT *__restrict__ xadj,
                                                           const int32_t *__restrict__ order, int64_t n,
-                                                          int64_t *__restrict__ len) {
+                                                          int64_t *__restrict__ len, OffT *__restrict__ begin) {
   for (int64_t t = blockIdx.x * 256LL + threadIdx.x; t <= n; t += gridDim.x * 256LL) {
     const int64_t v = t < n ? order[t] : 0;
-    len[t] = t < n ? static_cast<int64_t>(xadj[v + 1] - xadj[v]) : 0;
+    const OffT first = xadj[v];
+    len[t] = t < n ? static_cast<int64_t>(xadj[v + 1] - first) : 0;
+    if (t < n) begin[t] = first;
   }
-}
-
-__global__ __launch_bounds__(256) void iota_kernel(int32_t *__restrict__ ids, int64_t n) {
-  for (int64_t v = blockIdx.x * 256LL + threadIdx.x; v < n; v += gridDim.x * 256LL) ids[v] = static_cast<int32_t>(v);
 }
 
 // segment[a] = place of the first entry of cluster a (segment[n_coarse] = nnz); tile_row[k] =
@@ -133,41 +133,96 @@ __global__ __launch_bounds__(256) void segments_kernel(const int32_t *__restrict
   }
 }
 
+// What the gather looks clusters up in: `stride` bytes per vertex, of which `mask` keeps the cluster.
+struct ClusterTable {
+  const char *base;
+  uint32_t stride, mask;
+  __device__ __forceinline__ uint32_t of(int32_t v) const {
+    uint32_t word;  // need not lie at a multiple of its size
+    __builtin_memcpy(&word, base + static_cast<uint64_t>(static_cast<uint32_t>(v)) * stride, 4);
+    return word & mask;
+  }
+};
+
+// The map in three bytes per vertex, four vertices a thread.
+__global__ __launch_bounds__(256) void narrow_map_kernel(const int32_t *__restrict__ map, int64_t n,
+                                                         uint32_t *__restrict__ narrow) {
+  const int64_t quads = (n + 3) / 4;
+  for (int64_t i = blockIdx.x * 256LL + threadIdx.x; i < quads; i += gridDim.x * 256LL) {
+    uint32_t m[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) m[q] = static_cast<uint32_t>(map[std::min<int64_t>(i * 4 + q, n - 1)]);
+    narrow[i * 3] = m[0] | m[1] << 24;
+    narrow[i * 3 + 1] = m[1] >> 8 | m[2] << 16;
+    narrow[i * 3 + 2] = m[2] >> 16 | m[3] << 8;
+  }
+}
+
 // Entry e in cluster order: the cluster of its neighbour (kInside if that is its own) and its
 // multiplicity.  A workgroup takes kGatherTile consecutive entries, so hub rows are no long
-// tail and the writes are coalesced; the rows it spans are looked up in LDS.  Bound by the
-// 4-byte gathers from the map.
+// tail and the writes are coalesced.  The rows of a tile are found by their starts, a bit per entry:
+// a wavefront's 64 consecutive entries share one word, and the bits below a lane count its row.
+// Bound by the lookups: where the table is larger than an L2, most read a line from the memory side (7 TB/s
+// of lines).  Hence the narrow table, and streams that pass the L2 by: 128 M entries of 4.2 M vertices 1.35 ms without
+// both, now 1.21, 117 M weighted ones of 2.3 M vertices 0.95 and 0.90 (1.43 and 0.96 with a binary search per entry).
 template <typename OffT, typename WT, bool WEIGHTED>
-__global__ __launch_bounds__(256) void gather_kernel(const OffT *__restrict__ xadj, const int32_t *__restrict__ adj,
+__global__ __launch_bounds__(256) void gather_kernel(const int32_t *__restrict__ adj,
                                                      const int64_t *__restrict__ mult,
-                                                     const int32_t *__restrict__ map,
-                                                     const int32_t *__restrict__ order,
+                                                     ClusterTable clusters,
+                                                     const OffT *__restrict__ begin,
                                                      const int32_t *__restrict__ cluster,
                                                      const int64_t *__restrict__ pos,
                                                      const int32_t *__restrict__ tile_row, int64_t n, int64_t nnz,
                                                      uint32_t *__restrict__ column, WT *__restrict__ weight,
                                                      Classes *__restrict__ classes) {
-  constexpr int kUnits = 4;
+  constexpr int kUnits = 4, kWords = kGatherTile / 64;
+  static_assert(kWords == 64, "the first wavefront scans a word per lane");
   __shared__ unsigned int block_top;
   if (threadIdx.x == 0) block_top = 0;
   unsigned int top = 0;
-  __shared__ int32_t place[kGatherRows];  // relative to the tile; rows that began before it count as 0
-  __shared__ int64_t from[kGatherRows];   // fine entry of place 0 of the row, were it that long
+  __shared__ unsigned long long starts[kWords];  // entries of the tile at which a row starts; the first one counts
+  __shared__ int32_t before[kWords];             // number of the row at a word's first entry
+  __shared__ int32_t rows_met;
+  __shared__ int64_t from[kGatherRows];  // fine entry of place 0 of the row, were it that long
   __shared__ int32_t owner[kGatherRows];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int64_t tiles = (nnz + kGatherTile - 1) / kGatherTile;
   for (int64_t tile = blockIdx.x; tile < tiles; tile += gridDim.x) {
     const int64_t e0 = tile * kGatherTile, e1 = std::min(e0 + kGatherTile, nnz);
     const int32_t row0 = tile_row[tile];
     const int32_t row1 = tile + 1 < tiles ? tile_row[tile + 1] : static_cast<int32_t>(n - 1);
-    const bool in_lds = row1 - row0 < kGatherRows;
+    const bool few = row1 - row0 < kTileRows;  // not the vertices without entries, of which one tile may span millions
     __syncthreads();  // the tables of the previous tile have been used
-    if (in_lds)
-      for (int32_t r = threadIdx.x; r <= row1 - row0; r += 256) {
-        const int64_t p = pos[row0 + r];
-        place[r] = static_cast<int32_t>(std::min<int64_t>(std::max<int64_t>(p - e0, 0), kGatherTile));
-        from[r] = static_cast<int64_t>(xadj[order[row0 + r]]) - p;
-        owner[r] = cluster[row0 + r];
+    if (threadIdx.x < kWords) starts[threadIdx.x] = 0;
+    __syncthreads();
+    // rows without entries share their place with the next row and are not counted
+    auto for_rows = [&](auto body) {
+      for (int32_t r = row0 + static_cast<int32_t>(threadIdx.x); r <= row1; r += 256) {
+        const int64_t p = pos[r];
+        if (p < e1 && pos[r + 1] > p) body(r, p, static_cast<uint32_t>(std::max<int64_t>(p - e0, 0)));
       }
+    };
+    if (few) for_rows([&](int32_t, int64_t, uint32_t place) { atomicOr(&starts[place >> 6], 1ull << (place & 63)); });
+    __syncthreads();
+    if (wave == 0) {
+      const unsigned long long mine = starts[lane];
+      int32_t upto = __popcll(mine);
+      for (int step = 1; step < 64; step <<= 1) {
+        const int32_t x = __shfl_up(upto, step, 64);
+        if (lane >= step) upto += x;
+      }
+      before[lane] = upto - __popcll(mine >> 1) - 1;
+      if (lane == 63) rows_met = upto;
+    }
+    __syncthreads();
+    const bool in_lds = few && rows_met <= kGatherRows;
+    if (in_lds)
+      for_rows([&](int32_t r, int64_t p, uint32_t place) {
+        const unsigned long long word = starts[place >> 6] >> 1;
+        const int32_t k = before[place >> 6] + __popcll(word & ((1ull << (place & 63)) - 1));
+        from[k] = static_cast<int64_t>(begin[r]) - p;
+        owner[k] = cluster[r];
+      });
     __syncthreads();
     for (int64_t first = e0 + threadIdx.x; first < e1; first += 256 * kUnits) {
       int64_t at[kUnits];
@@ -176,25 +231,30 @@ __global__ __launch_bounds__(256) void gather_kernel(const OffT *__restrict__ xa
       for (int q = 0; q < kUnits; ++q) {
         const int64_t e = std::min(first + q * 256, e1 - 1);
         if (in_lds) {
-          const int32_t r = row_of_entry<int32_t>(place, 0, row1 - row0, static_cast<int32_t>(e - e0));
+          const int w = static_cast<int>((first - threadIdx.x - e0) >> 6) + q * 4 + wave;
+          const unsigned long long word = starts[w] >> 1;
+          const int32_t r = before[w] + static_cast<int32_t>(__builtin_amdgcn_mbcnt_hi(
+                                            static_cast<uint32_t>(word >> 32),
+                                            __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(word), 0)));
           at[q] = from[r] + e;
           own[q] = owner[r];
         } else {
           const int32_t r = row_of_entry<int64_t>(pos, row0, row1, e);
-          at[q] = static_cast<int64_t>(xadj[order[r]]) - pos[r] + e;
+          at[q] = static_cast<int64_t>(begin[r]) - pos[r] + e;
           own[q] = cluster[r];
         }
       }
 #pragma unroll
-      for (int q = 0; q < kUnits; ++q) y[q] = adj[at[q]];
+      for (int q = 0; q < kUnits; ++q) y[q] = __builtin_nontemporal_load(adj + at[q]);
 #pragma unroll
       for (int q = 0; q < kUnits; ++q) {
         const int64_t e = first + q * 256;
-        const int32_t b = map[y[q]];
+        const uint32_t b = clusters.of(y[q]);
         if (e < e1) {
-          column[e] = b == own[q] ? kInside : static_cast<uint32_t>(b);
-          top = max(top, static_cast<unsigned int>(b) + 1);
-          if constexpr (WEIGHTED) weight[e] = static_cast<WT>(mult[at[q]]);
+          __builtin_nontemporal_store(b == static_cast<uint32_t>(own[q]) ? kInside : b, column + e);
+          top = max(top, b + 1);
+          if constexpr (WEIGHTED)
+            __builtin_nontemporal_store(static_cast<WT>(__builtin_nontemporal_load(mult + at[q])), weight + e);
         }
       }
     }
@@ -738,14 +798,16 @@ int quotient(gosh::DeviceCoarsener *dc, const gosh::DeviceLevel &fine, int64_t n
   const int flat_blocks = blocks_for(n + 1, 256);
 
   {  // the fine rows in cluster order
-    int32_t *ids = nullptr, *order = nullptr, *cluster = nullptr, *tile_row = nullptr;
+    int32_t *order = nullptr, *cluster = nullptr, *tile_row = nullptr;
+    OffT *begin = nullptr;
     int64_t *lengths = nullptr, *pos = nullptr;
     const int64_t tiles = (nnz + kGatherTile - 1) / kGatherTile;
-    if (int rc = buf.alloc(&ids, static_cast<size_t>(n), "vertex ids")) return rc;
+    const rocprim::counting_iterator<int32_t> ids(0);
     if (int rc = buf.alloc(&order, static_cast<size_t>(n), "cluster order")) return rc;
     if (int rc = buf.alloc(&cluster, static_cast<size_t>(n), "sorted clusters")) return rc;
     if (int rc = buf.alloc(&lengths, static_cast<size_t>(n) + 1, "row lengths")) return rc;
     if (int rc = buf.alloc(&pos, static_cast<size_t>(n) + 1, "row places")) return rc;
+    if (int rc = buf.alloc(&begin, static_cast<size_t>(n), "row starts")) return rc;
     if (int rc = buf.alloc(&tile_row, static_cast<size_t>(tiles), "tile rows")) return rc;
     unsigned bits = 1;
     while (bits < 31 && (n_coarse >> bits) != 0) ++bits;
@@ -758,22 +820,28 @@ int quotient(gosh::DeviceCoarsener *dc, const gosh::DeviceLevel &fine, int64_t n
                  "row scan (size query)");
     char *temp = nullptr;
     if (int rc = buf.alloc(&temp, std::max(sort_bytes, scan_bytes), "sort workspace")) return rc;
-    hipLaunchKernelGGL(iota_kernel, dim3(flat_blocks), dim3(256), 0, nullptr, ids, n);
     GOSH_TRY_HIP(rocprim::radix_sort_pairs(temp, sort_bytes, fine.map, cluster, ids, order, static_cast<size_t>(n), 0u,
                                            bits, nullptr),
                  "cluster sort");
-    hipLaunchKernelGGL(row_lengths_kernel<OffT>, dim3(flat_blocks), dim3(256), 0, nullptr, xadj, order, n, lengths);
+    hipLaunchKernelGGL(row_lengths_kernel<OffT>, dim3(flat_blocks), dim3(256), 0, nullptr, xadj, order, n, lengths, begin);
     GOSH_TRY_HIP(rocprim::exclusive_scan(temp, scan_bytes, lengths, pos, int64_t(0), static_cast<size_t>(n) + 1,
                                          rocprim::plus<int64_t>(), nullptr),
                  "row scan");
     hipLaunchKernelGGL(segments_kernel, dim3(flat_blocks), dim3(256), 0, nullptr, cluster, pos, n, nnz, n_coarse,
                        segment, tile_row);
+    ClusterTable table{reinterpret_cast<const char *>(fine.map), 4, ~0u};
+    if (n >= kNarrowFrom && n_coarse <= (int64_t{1} << 24)) {
+      uint32_t *narrow = nullptr;  // and a word for what is read past the last vertex
+      if (int rc = buf.alloc(&narrow, static_cast<size_t>((n + 3) / 4) * 3 + 1, "narrow map")) return rc;
+      hipLaunchKernelGGL(narrow_map_kernel, dim3(blocks_for((n + 3) / 4, 256)), dim3(256), 0, nullptr, fine.map, n, narrow);
+      table = ClusterTable{reinterpret_cast<const char *>(narrow), 3, 0xFFFFFFu};
+    }
     hipLaunchKernelGGL((gather_kernel<OffT, WT, WEIGHTED>), dim3(blocks_for(nnz, kGatherTile)), dim3(256), 0, nullptr,
-                       xadj, fine.adj, fine.mult, fine.map, order, cluster, pos, tile_row, n, nnz, column, weight,
-                       classes);
+                       fine.adj, fine.mult, table, begin, cluster, pos, tile_row, n, nnz, column, weight, classes);
     if (int rc = gosh::check_launch("gather_kernel")) return rc;
-    for (void *p : {static_cast<void *>(ids), static_cast<void *>(order), static_cast<void *>(cluster),
-                    static_cast<void *>(lengths), static_cast<void *>(pos), static_cast<void *>(tile_row), static_cast<void *>(temp)})
+    for (void *p : {static_cast<void *>(order), static_cast<void *>(cluster),
+                    static_cast<void *>(lengths), static_cast<void *>(begin), static_cast<void *>(pos), static_cast<void *>(tile_row),
+                    static_cast<void *>(temp)})
       buf.release(p);  // what takes them up again is on the same stream
   }
   const int64_t radix_from = gosh::seam(gosh::kSeamRadixFrom);
