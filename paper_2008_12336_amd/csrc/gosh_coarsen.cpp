@@ -412,7 +412,10 @@ int ensure_host_mult_impl(gosh_hierarchy &h, gosh_hierarchy::Level &l) {
   if (l.host_mult || !l.has_mult) return GOSH_OK;
   if (l.dev.mult == nullptr) return gosh::fail(GOSH_EINVAL, "multiplicities have neither a host nor a device copy");
   l.mult.resize(static_cast<size_t>(l.nnz));
-  if (int rc = gosh::device_download(h.dc, l.mult.data(), l.dev.mult, static_cast<size_t>(l.nnz) * 8)) return rc;
+  const size_t count = static_cast<size_t>(l.nnz);
+  if (int rc = l.dev.mult_is64 ? gosh::device_download(h.dc, l.mult.data(), l.dev.mult, count * 8)
+                               : gosh::device_download_widened(h.dc, l.mult.data(), l.dev.mult, count))
+    return rc;
   l.host_mult = true;
   return GOSH_OK;
 }

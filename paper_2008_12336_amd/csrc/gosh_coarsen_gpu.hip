@@ -332,6 +332,16 @@ int device_level_set_map(DeviceLevel &level, const int32_t *map_host) {
 
 namespace {
 
+// Ascending, so that `from` may be the second half of `to`.
+void widen_words(char *to, const char *from, size_t count) {
+  for (size_t i = 0; i < count; ++i) {
+    uint32_t word;
+    memcpy(&word, from + 4 * i, 4);
+    const int64_t wide = static_cast<int64_t>(word);
+    memcpy(to + 8 * i, &wide, 8);
+  }
+}
+
 // Copies between pageable host memory and the device through two pinned slots, so that the
 // DMA of one piece overlaps the host-side copy of the next, which all threads share (on a
 // download that also spreads the page faults of a fresh destination over the threads).
@@ -354,13 +364,17 @@ struct StagedCopy {
     return GOSH_OK;
   }
   char *slot(size_t c) const { return slots + (c & 1) * kStagingBytes; }
-  void host_copy(char *to, const char *from, size_t bytes) const {
+  // `to` gets the 32-bit words of `from` as 64-bit ones where `widen` is set.
+  void host_copy(char *to, const char *from, size_t bytes, bool widen = false) const {
     const int64_t len = static_cast<int64_t>(bytes);
     const int64_t grain = int64_t(1) << 18;
     const int64_t grains = (len + grain - 1) / grain;
 #pragma omp parallel for num_threads(threads) schedule(static)
-    for (int64_t g = 0; g < grains; ++g)
-      memcpy(to + g * grain, from + g * grain, static_cast<size_t>(std::min(grain, len - g * grain)));
+    for (int64_t g = 0; g < grains; ++g) {
+      const size_t part = static_cast<size_t>(std::min(grain, len - g * grain));
+      if (widen) widen_words(to + 2 * g * grain, from + g * grain, part / 4);
+      else memcpy(to + g * grain, from + g * grain, part);
+    }
   }
 };
 
@@ -382,23 +396,19 @@ bool is_pinned_host(const void *p) {
 
 }  // namespace
 
-int device_download(DeviceCoarsener *dc, void *dst, const void *src_dev, size_t bytes) {
-  if (bytes == 0) return GOSH_OK;
-  if (dc == nullptr || bytes < kStagedFrom) {
-    GOSH_TRY_HIP(hipMemcpy(dst, src_dev, bytes, hipMemcpyDeviceToHost), "download");
-    return GOSH_OK;
-  }
+namespace {
+
+// Through the staging, if there is any and it pays: *done says so.
+int staged_download(DeviceCoarsener *dc, char *dst, const char *src_dev, size_t bytes, bool widen, bool *done) {
+  *done = false;
+  if (dc == nullptr || bytes < kStagedFrom) return GOSH_OK;
   StagedCopy q(dc);
-  if (!q.available()) {
-    GOSH_TRY_HIP(hipMemcpy(dst, src_dev, bytes, hipMemcpyDeviceToHost), "download");
-    return GOSH_OK;
-  }
+  if (!q.available()) return GOSH_OK;
   if (int rc = q.open()) return rc;
   const size_t piece = piece_bytes_of(bytes), pieces = (bytes + piece - 1) / piece;
   auto len = [&](size_t c) { return std::min(piece, bytes - c * piece); };
   auto start = [&](size_t c) -> hipError_t {
-    hipError_t e = hipMemcpyAsync(q.slot(c), static_cast<const char *>(src_dev) + c * piece, len(c),
-                                  hipMemcpyDeviceToHost, nullptr);
+    hipError_t e = hipMemcpyAsync(q.slot(c), src_dev + c * piece, len(c), hipMemcpyDeviceToHost, nullptr);
     return e != hipSuccess ? e : hipEventRecord(q.done[c & 1], nullptr);
   };
   GOSH_TRY_HIP(start(0), "start download");
@@ -406,8 +416,31 @@ int device_download(DeviceCoarsener *dc, void *dst, const void *src_dev, size_t 
     // slot (c + 1) & 1 was emptied in the previous iteration
     if (c + 1 < pieces) GOSH_TRY_HIP(start(c + 1), "start download");
     GOSH_TRY_HIP(hipEventSynchronize(q.done[c & 1]), "wait for download");
-    q.host_copy(static_cast<char *>(dst) + c * piece, q.slot(c), len(c));
+    q.host_copy(dst + c * piece * (widen ? 2 : 1), q.slot(c), len(c), widen);
   }
+  *done = true;
+  return GOSH_OK;
+}
+
+}  // namespace
+
+int device_download(DeviceCoarsener *dc, void *dst, const void *src_dev, size_t bytes) {
+  if (bytes == 0) return GOSH_OK;
+  bool done = false;
+  if (int rc = staged_download(dc, static_cast<char *>(dst), static_cast<const char *>(src_dev), bytes, false, &done))
+    return rc;
+  if (!done) GOSH_TRY_HIP(hipMemcpy(dst, src_dev, bytes, hipMemcpyDeviceToHost), "download");
+  return GOSH_OK;
+}
+
+int device_download_widened(DeviceCoarsener *dc, int64_t *dst, const void *src_dev, size_t count) {
+  if (count == 0) return GOSH_OK;
+  char *const to = reinterpret_cast<char *>(dst);
+  bool done = false;
+  if (int rc = staged_download(dc, to, static_cast<const char *>(src_dev), count * 4, true, &done)) return rc;
+  if (done) return GOSH_OK;
+  GOSH_TRY_HIP(hipMemcpy(to + count * 4, src_dev, count * 4, hipMemcpyDeviceToHost), "download");
+  widen_words(to, to + count * 4, count);
   return GOSH_OK;
 }
 

@@ -68,7 +68,8 @@ struct DeviceLevel {
   int32_t xadj_is64 = 1;
   void *xadj = nullptr;     // n + 1 offsets
   int32_t *adj = nullptr;   // nnz neighbours
-  int64_t *mult = nullptr;  // nnz multiplicities (coarse levels only)
+  void *mult = nullptr;     // nnz multiplicities (coarse levels only), 32 or 64 bits each
+  int32_t mult_is64 = 0;
   int32_t *map = nullptr;   // n cluster ids (every level but the last)
   bool borrowed_graph = false;  // xadj and adj belong to the caller (a device-resident G_0)
   bool present() const { return xadj != nullptr; }
@@ -112,6 +113,8 @@ int device_rebuild(DeviceCoarsener *dc, const DeviceLevel &fine, int64_t n_coars
 // Copies between pageable host memory and the device through the run's pinned staging,
 // the host side of every piece shared by all threads.
 int device_download(DeviceCoarsener *dc, void *dst, const void *src_dev, size_t bytes);
+// The same of 32-bit words that become 64-bit ones on the way.
+int device_download_widened(DeviceCoarsener *dc, int64_t *dst, const void *src_dev, size_t count);
 int device_upload(DeviceCoarsener *dc, void *dst_dev, const void *src, size_t bytes);
 
 // What the multilevel driver needs of a hierarchy without forcing host copies: the shape

@@ -43,6 +43,7 @@ enum Seam : int32_t {
   kSeamLockTries,  // if not 0: tries of a row lock before an update is added without it
   kSeamLocksHeld,  // if not 0: every lock of an epoch is held (1) or free (2) when its launch begins
   kSeamSwaps,      // written by every rotation: how many part swaps a kernel made
+  kSeamWeightBits, // if not 0: at most so many bits of a weight lie beside its column while rows are merged
   kSeams
 };
 enum Deny : int64_t { kDenyLocks = 1, kDenyStaging = 2, kDenyRadix = 4, kDenyTable = 8 };

@@ -6,7 +6,7 @@
 // one pass over the entries writes the cluster of each neighbour there.  What is left is to
 // sort each coarse row ("segment") by itself and to merge equal entries.  Three ways, by the
 // length S of the segment:
-//   S <= 512            one wavefront, bitonic in registers
+//   S <= 1,024          one wavefront, bitonic in registers
 //   S <= bitmap_from()  one workgroup, the same
 //   longer              no comparisons: a bitmap in LDS with a bit per possible neighbour, 2^18
 //                       ("piece") at a time, whose set bits are the merged row in order
@@ -18,12 +18,14 @@
 // Both grow with the number of columns; where there are many, the entries of the long rows are
 // radix-sorted as (row, column) keys, equal ones added up, and the rest is as after a merge in place.
 //
+// An entry is one word, its weight beside its column (Packing), from the gather to the copy.
+//
 // Sorted distinct entries with summed multiplicities are unique, so the arrays are those of
-// the sequential algorithm.  Against a radix sort of 64-bit (row, column) keys of all entries
-// and a reduction of equal keys, which this replaced: 128 M entries of a 4 M-vertex R-MAT graph
-// took 8.9 ms and take 4.4, 117 M weighted entries of its second level 10.5 and 4.2; 8 (wide
-// sums: 12) bytes of scratch per entry instead of 32, 16 more per entry of a row that is counted and
-// 24 (wide sums: 32) of one that is sorted by radix.  A third of it is the gather.
+// the sequential algorithm.  128 M entries of a 4 M-vertex R-MAT graph and the 117 M weighted ones of its
+// second level take 5.2 ms together (7.5 with weights in arrays of their own, pairs sorted by compare and select, and
+// a wavefront per segment to copy; 19.4 as a radix sort of 64-bit (row, column) keys of all entries).
+// 8 (wide sums: 12) bytes of scratch per entry, 16 more per entry of a row that is counted and 24 (wide sums: 32)
+// of one that is sorted by radix.  A third of it is the gather.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -44,15 +46,16 @@ using gosh::persistent;
 
 using gosh::kGatherTile;
 using gosh::kInside;
+using gosh::Packing;
 using gosh::row_of_entry;
 
 constexpr int kGatherRows = 1024;          // rows of a tile that are looked up in LDS,
 constexpr int kTileRows = 4096;            // among at most so many
 constexpr int64_t kNarrowFrom = 1 << 19;   // vertices whose map no L2 holds beside the streams
-// Longest segments that are sorted in the registers of a wavefront, 1, 2, 4 or 8 per lane, and
-// in those of a workgroup.
-constexpr int kSortClasses = 5;
-constexpr int kSortMax[kSortClasses] = {64, 128, 256, 512, 2048};
+// Longest segments that are sorted in the registers of a wavefront, 1, 2, 4, 8 or 16 per lane, and
+// in those of a workgroup, 8 or 16 per lane.
+constexpr int kSortClasses = 7;
+constexpr int kSortMax[kSortClasses] = {64, 128, 256, 512, 1024, 2048, 4096};
 enum : int { kBitmap = kSortClasses, kDense, kRadix, kWays };
 constexpr int kPieceBits = 18, kPieceWords = 1 << (kPieceBits - 5);
 constexpr int kStripBits = 14, kStripsPerPiece = 1 << (kPieceBits - kStripBits);
@@ -87,9 +90,10 @@ __host__ __device__ inline int64_t pieces_of(int64_t columns) {
 }
 
 // Longest segment that is sorted: the bitmap costs a fixed time per 2^14 columns, as much as
-// sorting about 160 entries, and longer ones have no network.
+// sorting about 300 entries, and longer ones have no network.  (7,300 segments of 2,049 to 4,096 entries among
+// 280,000 or 500,000 columns: about 0.4 ms as bitmaps, written included, 0.15 to 0.19 sorted.)
 __host__ __device__ inline int64_t bitmap_from(int64_t columns) {
-  return std::min<int64_t>(kSortMax[kSortClasses - 1], std::max<int64_t>(512, ((columns >> kStripBits) + 1) * 160));
+  return std::min<int64_t>(kSortMax[kSortClasses - 1], std::max<int64_t>(512, ((columns >> kStripBits) + 1) * 300));
 }
 
 // Longest segment whose sums are placed by rank.  Every kSumBytes of sums read the segment again,
@@ -97,6 +101,21 @@ __host__ __device__ inline int64_t bitmap_from(int64_t columns) {
 __host__ __device__ inline int64_t dense_from(int64_t columns, int sum_bytes) {
   const int64_t strips = (columns + (1 << kStripBits) - 1) >> kStripBits;
   return std::max<int64_t>(1 << 15, (strips << kStripBits) * sum_bytes / 16);
+}
+
+// How the long segments of a graph are merged: the bounds above, as far as they are not forced.
+struct Ways {
+  int64_t rank_columns, count_columns;
+  int sum_bytes;
+};
+__host__ __device__ inline int way_of_long(int64_t size, int64_t columns, const Ways &w) {
+  if (size <= dense_from(columns, w.sum_bytes)) return columns > w.rank_columns ? kRadix : kBitmap;
+  return columns > w.count_columns ? kRadix : kDense;
+}
+// Segments longer than this are sorted by radix.
+inline int64_t radix_above(int64_t columns, const Ways &w) {
+  if (columns > w.rank_columns) return bitmap_from(columns);
+  return columns > w.count_columns ? dense_from(columns, w.sum_bytes) : INT64_MAX;
 }
 
 // A slice of a counted segment: its place in the list, and which of its slices.
@@ -158,84 +177,105 @@ __global__ __launch_bounds__(256) void narrow_map_kernel(const int32_t *__restri
   }
 }
 
+// Which row the entries of a tile lie in: a bit per entry at which a row starts (the tile's first entry counts).
+// 64 consecutive entries, a wavefront's, share one word, and the bits up to a lane count its row.
+constexpr int kTileWords = kGatherTile / 64;
+struct RowStarts {
+  unsigned long long after[kTileWords];  // the word without its first bit, shifted down by it
+  int32_t before[kTileWords];            // number of the row at a word's first entry
+  int32_t met;                           // rows of the tile
+  // Number of the row at entry 64 * word + lane.
+  __device__ __forceinline__ int32_t row(int word) const {
+    const unsigned long long w = after[word];
+    return before[word] + static_cast<int32_t>(__builtin_amdgcn_mbcnt_hi(
+                              static_cast<uint32_t>(w >> 32), __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(w), 0)));
+  }
+};
+
+// Fills the table for the entries [e0, e1) of the rows row0 .. row1, which start at pos, and calls
+// fill(number, row, pos[row]) for each of them.  Rows without entries share their place with the next row and
+// are no rows of the tile.  False if there are too many for tables of kGatherRows, or so many without entries
+// that one search per entry costs less: fill has not been called.  The whole workgroup of 256 threads.
+template <class Fill>
+__device__ __forceinline__ bool lay_out_rows(RowStarts &t, const int64_t *__restrict__ pos, int32_t row0, int32_t row1,
+                                             int64_t e0, int64_t e1, Fill fill) {
+  static_assert(kTileWords == 64, "the first wavefront scans a word per lane");
+  const int lane = threadIdx.x & 63;
+  __syncthreads();  // the tables of the previous tile have been used
+  if (row1 - row0 >= kTileRows) return false;
+  if (threadIdx.x < kTileWords) t.after[threadIdx.x] = 0;
+  __syncthreads();
+  auto for_rows = [&](auto body) {
+    for (int32_t r = row0 + static_cast<int32_t>(threadIdx.x); r <= row1; r += 256) {
+      const int64_t p = pos[r];
+      if (p < e1 && pos[r + 1] > p) body(r, p, static_cast<uint32_t>(std::max<int64_t>(p - e0, 0)));
+    }
+  };
+  for_rows([&](int32_t, int64_t, uint32_t place) { atomicOr(&t.after[place >> 6], 1ull << (place & 63)); });
+  __syncthreads();
+  if (threadIdx.x < 64) {
+    const unsigned long long mine = t.after[lane];
+    int32_t upto = __popcll(mine);
+    for (int step = 1; step < 64; step <<= 1) {
+      const int32_t x = __shfl_up(upto, step, 64);
+      if (lane >= step) upto += x;
+    }
+    t.after[lane] = mine >> 1;
+    t.before[lane] = upto - __popcll(mine >> 1) - 1;
+    if (lane == 63) t.met = upto;
+  }
+  __syncthreads();
+  if (t.met > kGatherRows) return false;
+  for_rows([&](int32_t r, int64_t p, uint32_t place) {
+    fill(t.before[place >> 6] + __popcll(t.after[place >> 6] & ((1ull << (place & 63)) - 1)), r, p);
+  });
+  __syncthreads();
+  return true;
+}
+
 // Entry e in cluster order: the cluster of its neighbour (kInside if that is its own) and its
 // multiplicity.  A workgroup takes kGatherTile consecutive entries, so hub rows are no long
-// tail and the writes are coalesced.  The rows of a tile are found by their starts, a bit per entry:
-// a wavefront's 64 consecutive entries share one word, and the bits below a lane count its row.
-// Bound by the lookups: where the table is larger than an L2, most read a line from the memory side (7 TB/s
-// of lines).  Hence the narrow table, and streams that pass the L2 by: 128 M entries of 4.2 M vertices 1.35 ms without
-// both, now 1.21, 117 M weighted ones of 2.3 M vertices 0.95 and 0.90 (1.43 and 0.96 with a binary search per entry).
+// tail and the writes are coalesced.  Bound by the lookups: where the table is larger than an L2, most read a
+// line from the memory side (7 TB/s of lines).  Hence the narrow table, and streams that pass the L2 by: 128 M
+// entries of 4.2 M vertices 1.35 ms without both, now 1.21 (1.43 with a binary search per entry besides).
 template <typename OffT, typename WT, bool WEIGHTED>
 __global__ __launch_bounds__(256) void gather_kernel(const int32_t *__restrict__ adj,
-                                                     const int64_t *__restrict__ mult,
+                                                     const WT *__restrict__ mult,
                                                      ClusterTable clusters,
                                                      const OffT *__restrict__ begin,
                                                      const int32_t *__restrict__ cluster,
                                                      const int64_t *__restrict__ pos,
                                                      const int32_t *__restrict__ tile_row, int64_t n, int64_t nnz,
-                                                     uint32_t *__restrict__ column, WT *__restrict__ weight,
-                                                     Classes *__restrict__ classes) {
-  constexpr int kUnits = 4, kWords = kGatherTile / 64;
-  static_assert(kWords == 64, "the first wavefront scans a word per lane");
+                                                     Packing pack, uint32_t *__restrict__ entry,
+                                                     WT *__restrict__ weight, Classes *__restrict__ classes) {
+  constexpr int kUnits = 4;
   __shared__ unsigned int block_top;
   if (threadIdx.x == 0) block_top = 0;
   unsigned int top = 0;
-  __shared__ unsigned long long starts[kWords];  // entries of the tile at which a row starts; the first one counts
-  __shared__ int32_t before[kWords];             // number of the row at a word's first entry
-  __shared__ int32_t rows_met;
+  __shared__ RowStarts rows;
   __shared__ int64_t from[kGatherRows];  // fine entry of place 0 of the row, were it that long
   __shared__ int32_t owner[kGatherRows];
-  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int64_t tiles = (nnz + kGatherTile - 1) / kGatherTile;
   for (int64_t tile = blockIdx.x; tile < tiles; tile += gridDim.x) {
     const int64_t e0 = tile * kGatherTile, e1 = std::min(e0 + kGatherTile, nnz);
     const int32_t row0 = tile_row[tile];
     const int32_t row1 = tile + 1 < tiles ? tile_row[tile + 1] : static_cast<int32_t>(n - 1);
-    const bool few = row1 - row0 < kTileRows;  // not the vertices without entries, of which one tile may span millions
-    __syncthreads();  // the tables of the previous tile have been used
-    if (threadIdx.x < kWords) starts[threadIdx.x] = 0;
-    __syncthreads();
-    // rows without entries share their place with the next row and are not counted
-    auto for_rows = [&](auto body) {
-      for (int32_t r = row0 + static_cast<int32_t>(threadIdx.x); r <= row1; r += 256) {
-        const int64_t p = pos[r];
-        if (p < e1 && pos[r + 1] > p) body(r, p, static_cast<uint32_t>(std::max<int64_t>(p - e0, 0)));
-      }
-    };
-    if (few) for_rows([&](int32_t, int64_t, uint32_t place) { atomicOr(&starts[place >> 6], 1ull << (place & 63)); });
-    __syncthreads();
-    if (wave == 0) {
-      const unsigned long long mine = starts[lane];
-      int32_t upto = __popcll(mine);
-      for (int step = 1; step < 64; step <<= 1) {
-        const int32_t x = __shfl_up(upto, step, 64);
-        if (lane >= step) upto += x;
-      }
-      before[lane] = upto - __popcll(mine >> 1) - 1;
-      if (lane == 63) rows_met = upto;
-    }
-    __syncthreads();
-    const bool in_lds = few && rows_met <= kGatherRows;
-    if (in_lds)
-      for_rows([&](int32_t r, int64_t p, uint32_t place) {
-        const unsigned long long word = starts[place >> 6] >> 1;
-        const int32_t k = before[place >> 6] + __popcll(word & ((1ull << (place & 63)) - 1));
-        from[k] = static_cast<int64_t>(begin[r]) - p;
-        owner[k] = cluster[r];
-      });
-    __syncthreads();
-    for (int64_t first = e0 + threadIdx.x; first < e1; first += 256 * kUnits) {
+    const bool in_lds = lay_out_rows(rows, pos, row0, row1, e0, e1, [&](int32_t k, int32_t r, int64_t p) {
+      from[k] = static_cast<int64_t>(begin[r]) - p;
+      owner[k] = cluster[r];
+    });
+    for (int step = 0; step < kGatherTile / 256; step += kUnits) {
+      const int64_t first = e0 + step * 256 + threadIdx.x;
+      if (first >= e1) break;
       int64_t at[kUnits];
       int32_t own[kUnits], y[kUnits];
+      WT w[WEIGHTED ? kUnits : 1];
 #pragma unroll
       for (int q = 0; q < kUnits; ++q) {
         const int64_t e = std::min(first + q * 256, e1 - 1);
         if (in_lds) {
-          const int w = static_cast<int>((first - threadIdx.x - e0) >> 6) + q * 4 + wave;
-          const unsigned long long word = starts[w] >> 1;
-          const int32_t r = before[w] + static_cast<int32_t>(__builtin_amdgcn_mbcnt_hi(
-                                            static_cast<uint32_t>(word >> 32),
-                                            __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(word), 0)));
+          const int32_t r = rows.row((step + q) * 4 + wave);
           at[q] = from[r] + e;
           own[q] = owner[r];
         } else {
@@ -245,16 +285,22 @@ __global__ __launch_bounds__(256) void gather_kernel(const int32_t *__restrict__
         }
       }
 #pragma unroll
-      for (int q = 0; q < kUnits; ++q) y[q] = __builtin_nontemporal_load(adj + at[q]);
+      for (int q = 0; q < kUnits; ++q) {
+        y[q] = __builtin_nontemporal_load(adj + at[q]);
+        if constexpr (WEIGHTED) w[q] = __builtin_nontemporal_load(mult + at[q]);
+      }
 #pragma unroll
       for (int q = 0; q < kUnits; ++q) {
         const int64_t e = first + q * 256;
         const uint32_t b = clusters.of(y[q]);
         if (e < e1) {
-          __builtin_nontemporal_store(b == static_cast<uint32_t>(own[q]) ? kInside : b, column + e);
           top = max(top, b + 1);
-          if constexpr (WEIGHTED)
-            __builtin_nontemporal_store(static_cast<WT>(__builtin_nontemporal_load(mult + at[q])), weight + e);
+          uint32_t word = b;
+          if constexpr (WEIGHTED) {
+            word = pack.entry(b, w[q]);
+            if (w[q] >= pack.top) weight[e] = w[q];
+          }
+          __builtin_nontemporal_store(b == static_cast<uint32_t>(own[q]) ? kInside : word, entry + e);
         }
       }
     }
@@ -267,13 +313,10 @@ __global__ __launch_bounds__(256) void gather_kernel(const int32_t *__restrict__
 __global__ __launch_bounds__(1024) void classify_segments_kernel(const int64_t *__restrict__ segment, int64_t n_coarse,
                                                                  int32_t *__restrict__ list,
                                                                  int64_t *__restrict__ length,
-                                                                 Slice *__restrict__ slices, int64_t rank_columns,
-                                                                 int64_t count_columns, int sum_bytes,
+                                                                 Slice *__restrict__ slices, Ways ways,
                                                                  Classes *__restrict__ classes) {
   __shared__ unsigned int count[kWays], base[kWays];
-  const int64_t longest_sorted = bitmap_from(classes->columns), longest_ranked = dense_from(classes->columns, sum_bytes);
-  const int ranked = classes->columns > rank_columns ? kRadix : kBitmap;
-  const int counted = classes->columns > count_columns ? kRadix : kDense;
+  const int64_t columns = classes->columns, longest_sorted = bitmap_from(columns);
   for (int64_t first = blockIdx.x * 1024LL; first < n_coarse; first += gridDim.x * 1024LL) {
     if (threadIdx.x < kWays) count[threadIdx.x] = 0;
     __syncthreads();
@@ -282,7 +325,7 @@ __global__ __launch_bounds__(1024) void classify_segments_kernel(const int64_t *
     unsigned int mine = 0;
     if (a < n_coarse) {
       const int64_t s = segment[a + 1] - segment[a];
-      if (s > longest_sorted) cls = s <= longest_ranked ? ranked : counted;
+      if (s > longest_sorted) cls = way_of_long(s, columns, ways);
       else if (s > 0)
         for (cls = 0; s > kSortMax[cls];) ++cls;
       if (cls < 0 || cls >= kBitmap) length[a] = 0;  // (the radix sort assigns, its stand-in adds)
@@ -319,75 +362,105 @@ __device__ __forceinline__ unsigned long long lane_xor(unsigned long long x) {
          lane_xor<MASK>(static_cast<uint32_t>(x));
 }
 
-// One stage (distance J, in blocks of K) of a bitonic network over the elements first + r,
-// r < R, of consecutive lanes; distances below 64 R.  Equal keys stay where they are on both sides.
-template <int K, int J, int R, bool WEIGHTED, typename WT>
-__device__ __forceinline__ void bitonic_stage(uint32_t (&key)[R], WT (&w)[R], uint32_t first) {
-  if constexpr (J < R) {
+// Median of three: the smaller of a and b beside 0, the larger beside ~0.
+__device__ __forceinline__ uint32_t med3(uint32_t a, uint32_t b, uint32_t c) {
+  uint32_t m;
+  asm("v_med3_u32 %0, %1, %2, %3" : "=v"(m) : "v"(a), "v"(b), "v"(c));
+  return m;
+}
+
+// ~0 where the bit is set in `index`, else 0.
+template <int BIT>
+__device__ __forceinline__ uint32_t spread(uint32_t index) {
+  static_assert(BIT > 0 && (BIT & (BIT - 1)) == 0, "one bit");
+  return static_cast<uint32_t>(static_cast<int32_t>(index << __builtin_clz(BIT)) >> 31);
+}
+
+// One stage (distance J, in blocks of K of TOP) of a bitonic network over the elements index * R + r,
+// r < R, of consecutive lanes; distances below 64 R.  Which of two elements stays is the third operand of a
+// median, so a stage costs an instruction per element, and one more to fetch the other from another lane.
+template <int K, int J, int TOP, int R>
+__device__ __forceinline__ void key_stage(uint32_t (&key)[R], uint32_t index) {
+  if constexpr (J >= R) {
+    uint32_t larger = spread<J / R>(index);
+    if constexpr (K < TOP) larger ^= spread<K / R>(index);
+#pragma unroll
+    for (int r = 0; r < R; ++r) key[r] = med3(key[r], lane_xor<J / R>(key[r]), larger);
+  } else {
 #pragma unroll
     for (int r = 0; r < R; ++r)
       if ((r & J) == 0) {
-        const bool up = ((first + r) & K) == 0;
-        if ((key[r] > key[r | J]) == up && key[r] != key[r | J]) {
-          const uint32_t k = key[r];
-          key[r] = key[r | J];
-          key[r | J] = k;
-          if constexpr (WEIGHTED) {
-            const WT x = w[r];
-            w[r] = w[r | J];
-            w[r | J] = x;
-          }
+        const uint32_t x = key[r], y = key[r | J];
+        if constexpr (K >= TOP || K < R) {
+          const bool up = K >= TOP || (r & K) == 0;
+          key[r] = up ? min(x, y) : max(x, y);
+          key[r | J] = up ? max(x, y) : min(x, y);
+        } else {
+          const uint32_t larger = spread<K / R>(index);
+          key[r] = med3(x, y, larger);
+          key[r | J] = med3(x, y, ~larger);
         }
       }
-  } else {
-    const bool keep_small = ((first & J) == 0) == ((first & K) == 0);
-#pragma unroll
-    for (int r = 0; r < R; ++r) {
-      const uint32_t other = lane_xor<J / R>(key[r]);
-      if constexpr (WEIGHTED) {
-        const WT other_w = lane_xor<J / R>(w[r]);
-        const bool take = keep_small ? other < key[r] : other > key[r];
-        key[r] = take ? other : key[r];
-        w[r] = take ? other_w : w[r];
-      } else {
-        key[r] = keep_small ? min(key[r], other) : max(key[r], other);
-      }
-    }
   }
 }
-template <int K, int J, int R, bool WEIGHTED, typename WT>
-__device__ __forceinline__ void bitonic_merge(uint32_t (&key)[R], WT (&w)[R], uint32_t first) {
-  bitonic_stage<K, J, R, WEIGHTED>(key, w, first);
-  if constexpr (J > 1) bitonic_merge<K, J / 2, R, WEIGHTED>(key, w, first);
+template <int K, int J, int TOP, int R>
+__device__ __forceinline__ void key_merge(uint32_t (&key)[R], uint32_t index) {
+  key_stage<K, J, TOP>(key, index);
+  if constexpr (J > 1) key_merge<K, J / 2, TOP>(key, index);
 }
-template <int K, int TOP, int R, bool WEIGHTED, typename WT>
-__device__ __forceinline__ void bitonic_blocks(uint32_t (&key)[R], WT (&w)[R], uint32_t first) {
-  bitonic_merge<K, K / 2, R, WEIGHTED>(key, w, first);
-  if constexpr (K < TOP) bitonic_blocks<K * 2, TOP, R, WEIGHTED>(key, w, first);
+template <int K, int LAST, int TOP, int R>
+__device__ __forceinline__ void key_blocks(uint32_t (&key)[R], uint32_t index) {
+  key_merge<K, K / 2, TOP>(key, index);
+  if constexpr (K < LAST) key_blocks<K * 2, LAST, TOP>(key, index);
+}
+
+// Inclusive sum over the lanes below and this one.
+__device__ __forceinline__ uint32_t sum_upto_lane(uint32_t x, int) {
+  auto step = [&](auto move) { x += static_cast<uint32_t>(move(static_cast<int>(x))); };
+  step([](int v) { return __builtin_amdgcn_update_dpp(0, v, 0x111, 0xF, 0xF, false); });  // row_shr 1
+  step([](int v) { return __builtin_amdgcn_update_dpp(0, v, 0x112, 0xF, 0xF, false); });
+  step([](int v) { return __builtin_amdgcn_update_dpp(0, v, 0x114, 0xF, 0xF, false); });
+  step([](int v) { return __builtin_amdgcn_update_dpp(0, v, 0x118, 0xF, 0xF, false); });
+  step([](int v) { return __builtin_amdgcn_update_dpp(0, v, 0x142, 0xA, 0xF, false); });  // row_bcast 15
+  step([](int v) { return __builtin_amdgcn_update_dpp(0, v, 0x143, 0xC, 0xF, false); });  // row_bcast 31
+  return x;
+}
+__device__ __forceinline__ unsigned long long sum_upto_lane(unsigned long long x, int lane) {
+#pragma unroll
+  for (int step = 1; step < 64; step <<= 1) {
+    const unsigned long long y = __shfl_up(x, step, 64);
+    if (lane >= step) x += y;
+  }
+  return x;
+}
+__device__ __forceinline__ int32_t lanes_below(unsigned long long mask) {
+  return static_cast<int32_t>(__builtin_amdgcn_mbcnt_hi(static_cast<uint32_t>(mask >> 32),
+                                                        __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(mask), 0)));
 }
 
 // Segments of at most WAVES * 64 * R entries, WAVES wavefronts each: a bitonic network over the
 // registers of the lanes (R consecutive elements per lane; between wavefronts through LDS),
 // then equal columns are merged in place.  The sum of a run is the difference of the running
-// sums at its end and at the end of the run before.  Bound by the network's instructions: 67 M
-// entries in segments of 65 to 2,048 take 0.70 ms, weighted 1.18 ms (with the keys in LDS and a
-// barrier per stage, bound by latency, those up to 1,024 alone took 1.46 and 1.86 ms).
+// sums at its end and at the end of the run before.  An entry is sorted as the word it is held in, weight
+// included; what a word does not hold of a weight is added to the sum of its column afterwards.  Bound by the network's
+// instructions: 74 M entries in segments of up to 2,048 take 0.38 ms, 65 M weighted ones 0.37 (0.66 and 1.00 with
+// columns and weights sorted as pairs by compare and select).
 template <int R, int WAVES, typename WT, bool WEIGHTED>
 __global__ __launch_bounds__(256) void merge_sorted_kernel(const int64_t *__restrict__ segment,
                                                            const int32_t *__restrict__ list, int64_t count,
-                                                           uint32_t *__restrict__ column, WT *__restrict__ weight,
-                                                           int64_t *__restrict__ length) {
+                                                           Packing pack, uint32_t *__restrict__ entries,
+                                                           WT *__restrict__ weight, int64_t *__restrict__ length) {
   static_assert(WAVES == 1 || WAVES == 4, "a wavefront or a workgroup");
   constexpr int kWave = 64 * R, kAll = kWave * WAVES;
   constexpr int kTeams = 4 / WAVES;  // segments a workgroup works at
-  __shared__ uint32_t swap_key[WAVES > 1 ? kAll : 1];
-  __shared__ WT swap_w[WAVES > 1 && WEIGHTED ? kAll : 1];
-  __shared__ WT run_end[kTeams][kAll];  // running sum at the end of each run
+  __shared__ uint32_t run_column[kTeams][kAll];  // of each run; between wavefronts: what they exchange
+  __shared__ WT run_end[kTeams][kAll];           // running sum at the end of each run
   __shared__ int wave_heads[4];
   __shared__ WT wave_sum[4];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, team = wave / WAVES;
+  __shared__ uint32_t wave_last[4];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), team = wave / WAVES;
   const int member = wave % WAVES;  // wavefront within the team
-  const uint32_t first = (member * 64 + lane) * R;
+  const uint32_t index = member * 64 + lane, first = index * R;
   // a team takes the segments team, team + teams, ...; with several teams there are no barriers
   auto team_sync = [] {
     if constexpr (WAVES > 1) {
@@ -401,135 +474,148 @@ __global__ __launch_bounds__(256) void merge_sorted_kernel(const int64_t *__rest
     const int32_t a = list[i];
     const int64_t lo = segment[a];
     const uint32_t size = static_cast<uint32_t>(segment[a + 1] - lo);
+    uint32_t *const entry = entries + lo;
     uint32_t key[R];
     WT w[R];
+    bool held_apart = false;
 #pragma unroll
     for (int r = 0; r < R; ++r) {
       // lane-consecutive loads; where an element starts does not matter to a sort
       const uint32_t e = member * kWave + r * 64 + lane;
-      key[r] = e < size ? column[lo + e] : kInside;
-      w[r] = WT(1);
-      if constexpr (WEIGHTED) w[r] = e < size ? weight[lo + e] : WT(0);
+      key[r] = e < size ? entry[e] : kInside;
+      if constexpr (WEIGHTED) held_apart |= key[r] != kInside && (key[r] & pack.top) == pack.top;
     }
-    bitonic_blocks<2, kWave, R, WEIGHTED>(key, w, first);
+    bool apart = false;  // whether the segment has weights that its words do not hold
+    if constexpr (WEIGHTED) {
+      if constexpr (WAVES == 1) apart = __ballot(held_apart) != 0;
+      else apart = __syncthreads_or(held_apart) != 0;
+    }
+    key_blocks<2, kWave, kAll>(key, index);
     if constexpr (WAVES == 4) {
+      uint32_t *const swap = run_column[0];
+      auto across = [&](uint32_t larger, int partner) {
+        __syncthreads();
 #pragma unroll
-      for (int k = 2 * kWave; k <= kAll; k *= 2) {
+        for (int r = 0; r < R; ++r) swap[r * 256 + threadIdx.x] = key[r];
+        __syncthreads();
 #pragma unroll
-        for (int j = k / 2; j >= kWave; j /= 2) {
-          __syncthreads();
+        for (int r = 0; r < R; ++r) key[r] = med3(key[r], swap[r * 256 + partner], larger);
+      };
+      across(spread<64>(index) ^ spread<128>(index), threadIdx.x ^ 64);
+      key_merge<2 * kWave, kWave / 2, kAll>(key, index);
+      across(spread<128>(index), threadIdx.x ^ 128);
+      across(spread<64>(index), threadIdx.x ^ 64);
+      key_merge<4 * kWave, kWave / 2, kAll>(key, index);
+    }
 #pragma unroll
-          for (int r = 0; r < R; ++r) {
-            swap_key[r * 256 + threadIdx.x] = key[r];
-            if constexpr (WEIGHTED) swap_w[r * 256 + threadIdx.x] = w[r];
-          }
-          __syncthreads();
-          const bool keep_small = ((first & j) == 0) == ((first & k) == 0);
-          const int partner = threadIdx.x ^ (j / R);
-#pragma unroll
-          for (int r = 0; r < R; ++r) {
-            const uint32_t other = swap_key[r * 256 + partner];
-            const bool take = keep_small ? other < key[r] : other > key[r];
-            key[r] = take ? other : key[r];
-            if constexpr (WEIGHTED) w[r] = take ? swap_w[r * 256 + partner] : w[r];
-          }
-        }
-        if (k == 2 * kWave) bitonic_merge<2 * kWave, kWave / 2, R, WEIGHTED>(key, w, first);
-        else bitonic_merge<4 * kWave, kWave / 2, R, WEIGHTED>(key, w, first);
-      }
-      __syncthreads();
-      if (lane == 63) swap_key[wave] = key[R - 1];  // the element before the next wavefront's first
+    for (int r = 0; r < R; ++r) {
+      w[r] = WEIGHTED ? static_cast<WT>(key[r] & pack.top) : WT(1);
+      if constexpr (WEIGHTED) key[r] = pack.column(key[r]);
+    }
+    // heads of runs: a column that differs from the one before; what lies inside the cluster is at the end
+    if constexpr (WAVES == 4) {
+      if (lane == 63) wave_last[wave] = key[R - 1];
       __syncthreads();
     }
     uint32_t before = __shfl_up(key[R - 1], 1, 64);
-    if (lane == 0) before = kInside;  // nothing equals it that counts
-    if constexpr (WAVES == 4)
-      if (lane == 0 && wave > 0) before = swap_key[wave - 1];
-    // heads and running sums: over the lane's elements, the lanes, the team's wavefronts
-    bool head[R];
-    int heads = 0;
+    if (lane == 0) before = member > 0 ? wave_last[wave - 1] : kInside;
+    int rank = -1, distinct = 0;  // of the run that the element before belongs to
     WT sum = 0;
 #pragma unroll
     for (int r = 0; r < R; ++r) {
-      head[r] = key[r] != kInside && key[r] != (r == 0 ? before : key[r - 1]);
-      heads += head[r];
-      sum += key[r] != kInside ? w[r] : WT(0);
+      const unsigned long long heads = __ballot(key[r] != kInside && key[r] != (r == 0 ? before : key[r - 1]));
+      rank += lanes_below(heads);
+      distinct += __popcll(heads);
+      if constexpr (WEIGHTED) sum += key[r] != kInside ? w[r] : WT(0);
     }
-    int upto = heads;
-    WT sum_upto = sum;
-#pragma unroll
-    for (int step = 1; step < 64; step <<= 1) {
-      const int h = __shfl_up(upto, step, 64);
-      const WT s = __shfl_up(sum_upto, step, 64);
-      if (lane >= step) {
-        upto += h;
-        sum_upto += s;
-      }
+    WT running = static_cast<WT>(first);  // of the entries before; ones, unless they have weights
+    if constexpr (WEIGHTED) {
+      const WT upto = sum_upto_lane(sum, lane);
+      running = upto - sum;
+      if constexpr (WAVES == 4)
+        if (lane == 63) wave_sum[wave] = upto;
     }
-    int rank = upto - heads - 1;  // of the run that the element before belongs to
-    WT running = sum_upto - sum;
-    int distinct = __shfl(upto, 63, 64);
     if constexpr (WAVES == 4) {
-      if (lane == 63) {
-        wave_heads[wave] = upto;
-        wave_sum[wave] = sum_upto;
-      }
+      if (lane == 63) wave_heads[wave] = distinct;
       __syncthreads();
       distinct = 0;
       for (int q = 0; q < 4; ++q) {
         if (q < wave) {
           rank += wave_heads[q];
-          running += wave_sum[q];
+          if constexpr (WEIGHTED) running += wave_sum[q];
         }
         distinct += wave_heads[q];
       }
     }
 #pragma unroll
     for (int r = 0; r < R; ++r) {
-      if (head[r]) {
+      if (key[r] != (r == 0 ? before : key[r - 1])) {
         if (rank >= 0) run_end[team][rank] = running;  // the run before ends here
-        ++rank;
-        column[lo + rank] = key[r];  // every column of the segment is in registers
+        if (key[r] != kInside) run_column[team][++rank] = key[r];
       }
       running += key[r] != kInside ? w[r] : WT(0);
     }
-    const uint32_t last = first + R - 1;  // the team's last lane knows the end of the last run
-    if (last == kAll - 1 && rank >= 0) run_end[team][rank] = running;
+    // the team's last lane knows the end of the last run, if nothing inside the cluster follows it
+    if (first + R == kAll && key[R - 1] != kInside) run_end[team][rank] = running;
     team_sync();
-    for (int c = member * 64 + lane; c < distinct; c += 64 * WAVES)
-      weight[lo + c] = run_end[team][c] - (c > 0 ? run_end[team][c - 1] : WT(0));
+    if (WEIGHTED && apart) {  // the sums themselves in place of their ends, and what the words left out
+      WT sums[R];
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        const int c = r * 64 * WAVES + index;
+        sums[r] = c < distinct ? run_end[team][c] - (c > 0 ? run_end[team][c - 1] : WT(0)) : WT(0);
+      }
+      team_sync();
+#pragma unroll
+      for (int r = 0; r < R; ++r)
+        if (r * 64 * WAVES + static_cast<int>(index) < distinct) run_end[team][r * 64 * WAVES + index] = sums[r];
+      team_sync();
+      for (uint32_t e = index; e < size; e += 64 * WAVES) {  // the segment is as it was until the loop below
+        const uint32_t word = entry[e];
+        if (word == kInside || (word & pack.top) != pack.top) continue;
+        const int c = row_of_entry<uint32_t>(run_column[team], 0, distinct - 1, pack.column(word));
+        atomicAdd(&run_end[team][c], static_cast<WT>(weight[lo + e] - pack.top));
+      }
+      team_sync();
+    }
+    for (int c = index; c < distinct; c += 64 * WAVES) {
+      const WT total = run_end[team][c] - (c > 0 && !apart ? run_end[team][c - 1] : WT(0));
+      entry[c] = pack.entry(run_column[team][c], total);
+      if (total >= pack.top) weight[lo + c] = total;
+    }
     if (first == 0) length[a] = distinct;
     team_sync();
   }
 }
 
-// Calls body(entry, column) for the entries [lo, hi) with the workgroup's threads side by side,
+// Calls body(entry, word, column) for the entries [lo, hi) with the workgroup's threads side by side,
 // eight requested before the first is used: a workgroup has its compute unit nearly to itself
 // and would otherwise wait for memory once per entry and thread (counting 55 M entries in 9,000
 // segments: 110 us, 690 us one by one).
 template <class Body>
-__device__ __forceinline__ void for_entries(const uint32_t *__restrict__ column, int64_t lo, int64_t hi, Body body) {
+__device__ __forceinline__ void for_entries(const uint32_t *__restrict__ entry, Packing pack, int64_t lo, int64_t hi,
+                                            Body body) {
   constexpr int kAhead = 8;
   const int64_t step = blockDim.x;
   for (int64_t first = lo + threadIdx.x; first < hi; first += kAhead * step) {
     uint32_t b[kAhead];
 #pragma unroll
-    for (int q = 0; q < kAhead; ++q) b[q] = column[std::min(first + q * step, hi - 1)];
+    for (int q = 0; q < kAhead; ++q) b[q] = entry[std::min(first + q * step, hi - 1)];
 #pragma unroll
     for (int q = 0; q < kAhead; ++q)
-      if (first + q * step < hi) body(first + q * step, b[q]);
+      if (first + q * step < hi) body(first + q * step, b[q], pack.column(b[q]));
   }
 }
 
 // Marks the columns of a piece of a segment in the bitmap.  Returns the number of its words.
-__device__ inline int mark_piece(const uint32_t *__restrict__ column, int64_t lo, int64_t hi, int64_t piece,
+__device__ inline int mark_piece(const uint32_t *__restrict__ entry, Packing pack, int64_t lo, int64_t hi, int64_t piece,
                                  int64_t columns, uint32_t *bits) {
   const uint32_t base = static_cast<uint32_t>(piece << kPieceBits);
   const int words = static_cast<int>(std::min<int64_t>(kPieceWords, (columns - base + 31) / 32));
   const uint32_t width = static_cast<uint32_t>(words) * 32u;
   for (int w = threadIdx.x; w < kPieceWords; w += blockDim.x) bits[w] = 0;
   __syncthreads();
-  for_entries(column, lo, hi, [&](int64_t, uint32_t b) {
+  for_entries(entry, pack, lo, hi, [&](int64_t, uint32_t, uint32_t b) {
     b -= base;  // columns of other pieces, and kInside, are past the bitmap
     if (b < width) atomicOr(&bits[b >> 5], 1u << (b & 31));
   });
@@ -541,7 +627,7 @@ __device__ inline int mark_piece(const uint32_t *__restrict__ column, int64_t lo
 __global__ __launch_bounds__(512) void count_pieces_kernel(const int64_t *__restrict__ segment,
                                                            const int32_t *__restrict__ list, int64_t count,
                                                            int64_t pieces, int64_t columns,
-                                                           const uint32_t *__restrict__ column,
+                                                           const uint32_t *__restrict__ entry, Packing pack,
                                                            uint32_t *__restrict__ in_strip,
                                                            int64_t *__restrict__ length) {
   constexpr int kStripWords = kPieceWords / kStripsPerPiece;
@@ -551,7 +637,7 @@ __global__ __launch_bounds__(512) void count_pieces_kernel(const int64_t *__rest
   for (int64_t job = blockIdx.x; job < count * pieces; job += gridDim.x) {
     const int32_t a = list[job / pieces];
     if (threadIdx.x == 0) total = 0;
-    mark_piece(column, segment[a], segment[a + 1], job % pieces, columns, bits);
+    mark_piece(entry, pack, segment[a], segment[a + 1], job % pieces, columns, bits);
     for (int strip = wave; strip < kStripsPerPiece; strip += 8) {
       uint32_t mine = 0;
       for (int w = lane; w < kStripWords; w += 64) mine += __popc(bits[strip * kStripWords + w]);
@@ -582,12 +668,12 @@ template <typename WT, bool WEIGHTED>
 __global__ __launch_bounds__(1024) void write_pieces_kernel(const int64_t *__restrict__ segment,
                                                             const int32_t *__restrict__ list, int64_t count,
                                                             int64_t pieces, int64_t columns,
-                                                            const uint32_t *__restrict__ column,
+                                                            const uint32_t *__restrict__ entry, Packing pack,
                                                             const WT *__restrict__ weight,
                                                             const uint32_t *__restrict__ in_strip,
                                                             const int64_t *__restrict__ xadj_out,
                                                             int32_t *__restrict__ adj_out,
-                                                            int64_t *__restrict__ mult_out) {
+                                                            WT *__restrict__ mult_out) {
   constexpr uint32_t kSums = kSumBytes / (sizeof(WT) + 4);
   constexpr int kPairs = kPieceWords / 2, kPerThread = kPairs / 1024;
   __shared__ unsigned long long bits[kPairs];
@@ -603,7 +689,7 @@ __global__ __launch_bounds__(1024) void write_pieces_kernel(const int64_t *__res
     const int64_t lo = segment[a], hi = segment[a + 1];
     __syncthreads();  // the previous piece is done with the LDS
     if (threadIdx.x == 0) earlier = 0;
-    const uint32_t width = 32u * mark_piece(column, lo, hi, piece, columns, reinterpret_cast<uint32_t *>(bits));
+    const uint32_t width = 32u * mark_piece(entry, pack, lo, hi, piece, columns, reinterpret_cast<uint32_t *>(bits));
     add_strips(in_strip + which * pieces * kStripsPerPiece, piece * kStripsPerPiece, &earlier);
     // exclusive scan of the set bits: kPerThread pairs per thread, then over the workgroup
     const int p0 = threadIdx.x * kPerThread;
@@ -632,20 +718,20 @@ __global__ __launch_bounds__(1024) void write_pieces_kernel(const int64_t *__res
       const uint32_t here = std::min(kSums, distinct - first);
       for (uint32_t c = threadIdx.x; c < here; c += 1024) sums[c] = 0;
       __syncthreads();
-      for_entries(column, lo, hi, [&](int64_t e, uint32_t b) {
+      for_entries(entry, pack, lo, hi, [&](int64_t e, uint32_t word, uint32_t b) {
         b -= base;
         if (b < width) {
           const uint32_t c = below[b >> 6] + __popcll(bits[b >> 6] & ((1ull << (b & 63)) - 1)) - first;
           if (c < here) {
             found[c] = base + b;  // by every entry of that column alike
-            atomicAdd(&sums[c], WEIGHTED ? weight[e] : WT(1));
+            atomicAdd(&sums[c], WEIGHTED ? pack.weight(word, weight, e) : WT(1));
           }
         }
       });
       __syncthreads();
       for (uint32_t c = threadIdx.x; c < here; c += 1024) {
         adj_out[out + first + c] = static_cast<int32_t>(found[c]);
-        mult_out[out + first + c] = static_cast<int64_t>(sums[c]);
+        mult_out[out + first + c] = sums[c];
       }
       __syncthreads();
     }
@@ -665,7 +751,7 @@ __global__ __launch_bounds__(1024) void count_dense_kernel(const int64_t *__rest
                                                            const int32_t *__restrict__ list,
                                                            const Slice *__restrict__ slices, int64_t first_strip,
                                                            int64_t strips,
-                                                           const uint32_t *__restrict__ column,
+                                                           const uint32_t *__restrict__ entry, Packing pack,
                                                            const WT *__restrict__ weight, WT *__restrict__ table) {
   constexpr int kWidth = 1 << kStripBits;
   __shared__ WT sums[kWidth];
@@ -676,9 +762,9 @@ __global__ __launch_bounds__(1024) void count_dense_kernel(const int64_t *__rest
   const uint32_t base = static_cast<uint32_t>(strip << kStripBits);
   for (int c = threadIdx.x; c < kWidth; c += 1024) sums[c] = 0;
   __syncthreads();
-  for_entries(column, lo, hi, [&](int64_t e, uint32_t b) {
+  for_entries(entry, pack, lo, hi, [&](int64_t e, uint32_t word, uint32_t b) {
     b -= base;  // columns of other strips, and kInside, are past the counters
-    if (b < static_cast<uint32_t>(kWidth)) atomicAdd(&sums[b], WEIGHTED ? weight[e] : WT(1));
+    if (b < static_cast<uint32_t>(kWidth)) atomicAdd(&sums[b], WEIGHTED ? pack.weight(word, weight, e) : WT(1));
   });
   __syncthreads();
   WT *const row = table + (slice.row * strips + strip) * kWidth;
@@ -695,7 +781,7 @@ __global__ __launch_bounds__(1024) void dense_strips_kernel(const int32_t *__res
                                                             int64_t *__restrict__ length,
                                                             const int64_t *__restrict__ xadj_out,
                                                             int32_t *__restrict__ adj_out,
-                                                            int64_t *__restrict__ mult_out) {
+                                                            WT *__restrict__ mult_out) {
   constexpr int kWidth = 1 << kStripBits, kPerWave = kWidth / 16;
   __shared__ uint32_t wave_total[16];
   __shared__ unsigned long long earlier;
@@ -726,49 +812,76 @@ __global__ __launch_bounds__(1024) void dense_strips_kernel(const int32_t *__res
       if (sum != 0) {
         const int64_t at = out + __popcll(set & ((1ull << lane) - 1));
         adj_out[at] = static_cast<int32_t>((strip << kStripBits) + wave * kPerWave + c);
-        mult_out[at] = static_cast<int64_t>(sum);
+        mult_out[at] = sum;
       }
       out += __popcll(set);
     }
   }
 }
 
-// Copies the segments that were merged in place, one wavefront each.
-template <typename WT>
-__global__ __launch_bounds__(256) void copy_merged_kernel(const int64_t *__restrict__ segment,
-                                                          const int32_t *__restrict__ list, int64_t count,
-                                                          const uint32_t *__restrict__ column,
-                                                          const WT *__restrict__ weight,
-                                                          const int64_t *__restrict__ xadj_out,
-                                                          int32_t *__restrict__ adj_out,
-                                                          int64_t *__restrict__ mult_out) {
-  const int lane = threadIdx.x & 63;
-  const int64_t waves = (gridDim.x * 256LL) >> 6;
-  for (int64_t i = (blockIdx.x * 256LL + threadIdx.x) >> 6; i < count; i += waves) {
-    const int32_t a = list[i];
-    const int64_t lo = segment[a], out = xadj_out[a];
-    const int64_t size = xadj_out[a + 1] - out;
-    for (int64_t e = lane; e < size; e += 64) {
-      adj_out[out + e] = static_cast<int32_t>(column[lo + e]);
-      mult_out[out + e] = static_cast<int64_t>(weight[lo + e]);
-    }
+// tile_row[k] = coarse row that holds entry k * kGatherTile of the coarse graph.
+__global__ __launch_bounds__(256) void coarse_tiles_kernel(const int64_t *__restrict__ xadj_out, int64_t n_coarse,
+                                                           int32_t *__restrict__ tile_row) {
+  for (int64_t a = blockIdx.x * 256LL + threadIdx.x; a < n_coarse; a += gridDim.x * 256LL) {
+    const int64_t lo = xadj_out[a], hi = xadj_out[a + 1];
+    for (int64_t k = (lo + kGatherTile - 1) / kGatherTile; k * kGatherTile < hi; ++k) tile_row[k] = static_cast<int32_t>(a);
   }
 }
 
-// The same for segments of any length: gridDim.y workgroups share one.
+// Copies the segments that were merged in place, those of up to `sorted_to` or more than `radix_from`
+// entries, to the coarse graph.  A workgroup takes kGatherTile consecutive entries of that: with a wavefront per
+// segment, bound by the chain of reads before its first entry, 96 M entries took 500 us, now 297.
 template <typename WT>
-__global__ __launch_bounds__(256) void copy_long_kernel(const int64_t *__restrict__ segment,
-                                                        const int32_t *__restrict__ list, int64_t count,
-                                                        const uint32_t *__restrict__ column,
-                                                        const WT *__restrict__ weight,
-                                                        const int64_t *__restrict__ xadj_out,
-                                                        int32_t *__restrict__ adj_out, int64_t *__restrict__ mult_out) {
-  for (int64_t i = blockIdx.x; i < count; i += gridDim.x) {
-    const int32_t a = list[i];
-    const int64_t lo = segment[a], out = xadj_out[a], size = xadj_out[a + 1] - out;
-    for (int64_t e = blockIdx.y * 256LL + threadIdx.x; e < size; e += gridDim.y * 256LL) {
-      adj_out[out + e] = static_cast<int32_t>(column[lo + e]);
-      mult_out[out + e] = static_cast<int64_t>(weight[lo + e]);
+__global__ __launch_bounds__(256) void copy_merged_kernel(const int64_t *__restrict__ segment, int64_t sorted_to,
+                                                          int64_t radix_from, const int32_t *__restrict__ tile_row,
+                                                          int64_t n_coarse, int64_t nnz_coarse,
+                                                          const uint32_t *__restrict__ entry, Packing pack,
+                                                          const WT *__restrict__ weight,
+                                                          const int64_t *__restrict__ xadj_out,
+                                                          int32_t *__restrict__ adj_out,
+                                                          WT *__restrict__ mult_out) {
+  constexpr int kUnits = 8;
+  constexpr int64_t kElsewhere = INT64_MIN;
+  __shared__ RowStarts rows;
+  __shared__ int64_t from[kGatherRows];  // entry of place 0 of the row, were it that long
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  auto start_of = [&](int32_t a, int64_t p) -> int64_t {
+    const int64_t lo = segment[a], size = segment[a + 1] - lo;
+    return size <= sorted_to || size > radix_from ? lo - p : kElsewhere;
+  };
+  const int64_t tiles = (nnz_coarse + kGatherTile - 1) / kGatherTile;
+  for (int64_t tile = blockIdx.x; tile < tiles; tile += gridDim.x) {
+    const int64_t e0 = tile * kGatherTile, e1 = std::min(e0 + kGatherTile, nnz_coarse);
+    const int32_t row0 = tile_row[tile];
+    const int32_t row1 = tile + 1 < tiles ? tile_row[tile + 1] : static_cast<int32_t>(n_coarse - 1);
+    const bool in_lds = lay_out_rows(rows, xadj_out, row0, row1, e0, e1,
+                                     [&](int32_t k, int32_t a, int64_t p) { from[k] = start_of(a, p); });
+    for (int step = 0; step < kGatherTile / 256; step += kUnits) {
+      const int64_t first = e0 + step * 256 + threadIdx.x;
+      if (first >= e1) break;
+      int64_t at[kUnits];
+      uint32_t word[kUnits];
+#pragma unroll
+      for (int q = 0; q < kUnits; ++q) {
+        const int64_t e = std::min(first + q * 256, e1 - 1);
+        int64_t start;
+        if (in_lds) {
+          start = from[rows.row((step + q) * 4 + wave)];
+        } else {
+          const int32_t a = row_of_entry<int64_t>(xadj_out, row0, row1, e);
+          start = start_of(a, xadj_out[a]);
+        }
+        at[q] = start == kElsewhere || first + q * 256 >= e1 ? -1 : start + e;
+      }
+#pragma unroll
+      for (int q = 0; q < kUnits; ++q) word[q] = __builtin_nontemporal_load(entry + std::max<int64_t>(at[q], 0));
+#pragma unroll
+      for (int q = 0; q < kUnits; ++q)
+        if (at[q] >= 0) {
+          const int64_t e = first + q * 256;
+          __builtin_nontemporal_store(static_cast<int32_t>(pack.column(word[q])), adj_out + e);
+          __builtin_nontemporal_store(pack.weight(word[q], weight, at[q]), mult_out + e);
+        }
     }
   }
 }
@@ -780,13 +893,14 @@ int quotient(gosh::DeviceCoarsener *dc, const gosh::DeviceLevel &fine, int64_t n
              int64_t *xadj_out) {
   const int64_t n = fine.n, nnz = fine.nnz;
   const OffT *xadj = static_cast<const OffT *>(fine.xadj);
+  const Packing pack = Packing::for_columns(n_coarse), held = WEIGHTED ? pack : Packing{0, 0};  // merged, and before
   gosh::Buffers buf(dc->pool);
-  uint32_t *column = nullptr;
+  uint32_t *entry = nullptr;
   WT *weight = nullptr;
   int64_t *segment = nullptr, *length = nullptr;
   int32_t *list = nullptr;
   Classes *classes = nullptr;
-  if (int rc = buf.alloc(&column, static_cast<size_t>(nnz), "columns")) return rc;
+  if (int rc = buf.alloc(&entry, static_cast<size_t>(nnz), "entries")) return rc;
   if (int rc = buf.alloc(&weight, static_cast<size_t>(nnz), "multiplicities")) return rc;
   if (int rc = buf.alloc(&segment, static_cast<size_t>(n_coarse) + 1, "coarse rows")) return rc;
   if (int rc = buf.alloc(&length, static_cast<size_t>(n_coarse) + 1, "coarse row lengths")) return rc;
@@ -837,7 +951,8 @@ int quotient(gosh::DeviceCoarsener *dc, const gosh::DeviceLevel &fine, int64_t n
       table = ClusterTable{reinterpret_cast<const char *>(narrow), 3, 0xFFFFFFu};
     }
     hipLaunchKernelGGL((gather_kernel<OffT, WT, WEIGHTED>), dim3(blocks_for(nnz, kGatherTile)), dim3(256), 0, nullptr,
-                       fine.adj, fine.mult, table, begin, cluster, pos, tile_row, n, nnz, column, weight, classes);
+                       fine.adj, static_cast<const WT *>(fine.mult), table, begin, cluster, pos, tile_row, n, nnz, pack, entry, weight,
+                       classes);
     if (int rc = gosh::check_launch("gather_kernel")) return rc;
     for (void *p : {static_cast<void *>(order), static_cast<void *>(cluster),
                     static_cast<void *>(lengths), static_cast<void *>(begin), static_cast<void *>(pos), static_cast<void *>(tile_row),
@@ -845,9 +960,9 @@ int quotient(gosh::DeviceCoarsener *dc, const gosh::DeviceLevel &fine, int64_t n
       buf.release(p);  // what takes them up again is on the same stream
   }
   const int64_t radix_from = gosh::seam(gosh::kSeamRadixFrom);
+  const Ways ways{radix_from ? radix_from : kRankColumns, radix_from ? radix_from : kCountColumns, static_cast<int>(sizeof(WT))};
   hipLaunchKernelGGL(classify_segments_kernel, dim3(blocks_for(n_coarse, 1024)), dim3(1024), 0, nullptr, segment,
-                     n_coarse, list, length, slices, radix_from ? radix_from : kRankColumns,
-                     radix_from ? radix_from : kCountColumns, static_cast<int>(sizeof(WT)), classes);
+                     n_coarse, list, length, slices, ways, classes);
   if (int rc = gosh::check_launch("classify_segments_kernel")) return rc;
   Classes c{};
   GOSH_TRY_HIP(hipMemcpy(&c, classes, sizeof(c), hipMemcpyDeviceToHost), "read segment classes");
@@ -856,7 +971,7 @@ int quotient(gosh::DeviceCoarsener *dc, const gosh::DeviceLevel &fine, int64_t n
   bool radix_merged = false;  // the segments of the kRadix list are merged in place
   if (c.count[kRadix] > 0) {
     const int rc = gosh::merge_by_radix<WT, WEIGHTED>(dc->pool, segment, list + kRadix * n_coarse, c.count[kRadix],
-                                                c.columns, column, weight, length);
+                                                c.columns, pack, entry, weight, length);
     if (rc != GOSH_OK && rc != GOSH_ENOMEM) return rc;
     radix_merged = rc == GOSH_OK;
   }
@@ -880,7 +995,7 @@ int quotient(gosh::DeviceCoarsener *dc, const gosh::DeviceLevel &fine, int64_t n
     for (int64_t first = 0; first < dense_strips; first += 65535)
       hipLaunchKernelGGL((count_dense_kernel<WT, WEIGHTED>),
                          dim3(c.slices, static_cast<unsigned>(std::min<int64_t>(dense_strips - first, 65535))), dim3(1024), 0,
-                         nullptr, segment, dense_list, slices, first, dense_strips, column, weight, table);
+                         nullptr, segment, dense_list, slices, first, dense_strips, entry, held, weight, table);
     hipLaunchKernelGGL((dense_strips_kernel<WT, false>), dim3(static_cast<unsigned>(dense_jobs)), dim3(1024), 0, nullptr,
                        dense_list, dense_strips, table, in_dense_strip, length, xadj_out, nullptr, nullptr);
   }
@@ -896,14 +1011,16 @@ int quotient(gosh::DeviceCoarsener *dc, const gosh::DeviceLevel &fine, int64_t n
     if (r.count == 0) continue;
     if (int rc = buf.alloc(&r.in_strip, static_cast<size_t>(r.count * strips), "strips of coarse rows")) return rc;
     hipLaunchKernelGGL(count_pieces_kernel, dim3(blocks_for(r.count * pieces, 1)), dim3(512), 0, nullptr, segment,
-                       r.list, r.count, pieces, static_cast<int64_t>(c.columns), column, r.in_strip, length);
+                       r.list, r.count, pieces, static_cast<int64_t>(c.columns), entry, held, r.in_strip, length);
   }
   auto merge_sorted = [&](auto kernel, int cls, int teams) {
     if (c.count[cls] > 0)
       hipLaunchKernelGGL(kernel, dim3(blocks_for(c.count[cls], teams)), dim3(256), 0, nullptr, segment,
-                         list + cls * n_coarse, static_cast<int64_t>(c.count[cls]), column, weight, length);
+                         list + cls * n_coarse, static_cast<int64_t>(c.count[cls]), pack, entry, weight, length);
   };
-  merge_sorted(merge_sorted_kernel<8, 4, WT, WEIGHTED>, 4, 1);
+  merge_sorted(merge_sorted_kernel<16, 4, WT, WEIGHTED>, 6, 1);
+  merge_sorted(merge_sorted_kernel<8, 4, WT, WEIGHTED>, 5, 1);
+  merge_sorted(merge_sorted_kernel<16, 1, WT, WEIGHTED>, 4, 4);
   merge_sorted(merge_sorted_kernel<8, 1, WT, WEIGHTED>, 3, 4);
   merge_sorted(merge_sorted_kernel<4, 1, WT, WEIGHTED>, 2, 4);
   merge_sorted(merge_sorted_kernel<2, 1, WT, WEIGHTED>, 1, 4);
@@ -924,26 +1041,28 @@ int quotient(gosh::DeviceCoarsener *dc, const gosh::DeviceLevel &fine, int64_t n
   }
   GOSH_TRY_HIP(hipMemcpy(&coarse.nnz, xadj_out + n_coarse, 8, hipMemcpyDeviceToHost), "read coarse size");
   if (int rc = persistent(&coarse.adj, static_cast<size_t>(coarse.nnz), "coarse adjacency")) return rc;
-  if (int rc = persistent(&coarse.mult, static_cast<size_t>(coarse.nnz), "coarse multiplicities")) return rc;
+  WT *mult_out = nullptr;
+  if (int rc = persistent(&mult_out, static_cast<size_t>(coarse.nnz), "coarse multiplicities")) return rc;
+  coarse.mult = mult_out;
+  coarse.mult_is64 = sizeof(WT) == 8;
   if (denses > 0)
     hipLaunchKernelGGL((dense_strips_kernel<WT, true>), dim3(static_cast<unsigned>(dense_jobs)), dim3(1024), 0, nullptr,
-                       dense_list, dense_strips, table, in_dense_strip, length, xadj_out, coarse.adj, coarse.mult);
+                       dense_list, dense_strips, table, in_dense_strip, length, xadj_out, coarse.adj, mult_out);
   for (const Ranked &r : ranked)
     if (r.count > 0)
       hipLaunchKernelGGL((write_pieces_kernel<WT, WEIGHTED>), dim3(blocks_for(r.count * pieces, 1)), dim3(1024), 0,
-                         nullptr, segment, r.list, r.count, pieces, static_cast<int64_t>(c.columns), column, weight,
-                         r.in_strip, xadj_out, coarse.adj, coarse.mult);
-  if (radix_merged) {
-    const int rows = static_cast<int>(std::min<int64_t>(c.count[kRadix], 65536));
-    hipLaunchKernelGGL(copy_long_kernel<WT>, dim3(rows, std::min(std::max(65536 / rows, 1), 1024)), dim3(256), 0, nullptr,
-                       segment, list + kRadix * n_coarse, static_cast<int64_t>(c.count[kRadix]), column, weight, xadj_out,
-                       coarse.adj, coarse.mult);
+                         nullptr, segment, r.list, r.count, pieces, static_cast<int64_t>(c.columns), entry, held,
+                         weight, r.in_strip, xadj_out, coarse.adj, mult_out);
+  if (coarse.nnz > 0) {
+    const int64_t tiles = (coarse.nnz + kGatherTile - 1) / kGatherTile;
+    int32_t *tile_row = nullptr;
+    if (int rc = buf.alloc(&tile_row, static_cast<size_t>(tiles), "tile rows")) return rc;
+    hipLaunchKernelGGL(coarse_tiles_kernel, dim3(blocks_for(n_coarse, 256)), dim3(256), 0, nullptr, xadj_out, n_coarse,
+                       tile_row);
+    hipLaunchKernelGGL(copy_merged_kernel<WT>, dim3(blocks_for(coarse.nnz, kGatherTile)), dim3(256), 0, nullptr, segment,
+                       bitmap_from(c.columns), radix_merged ? radix_above(c.columns, ways) : INT64_MAX, tile_row, n_coarse,
+                       coarse.nnz, entry, pack, weight, xadj_out, coarse.adj, mult_out);
   }
-  for (int cls = kSortClasses - 1; cls >= 0; --cls)
-    if (c.count[cls] > 0)
-      hipLaunchKernelGGL(copy_merged_kernel<WT>, dim3(blocks_for(c.count[cls], 4)), dim3(256), 0, nullptr, segment,
-                         list + cls * n_coarse, static_cast<int64_t>(c.count[cls]), column, weight, xadj_out, coarse.adj,
-                         coarse.mult);
   if (int rc = gosh::check_launch("coarse rows")) return rc;
   GOSH_TRY_HIP(hipDeviceSynchronize(), "coarse CSR");
   return GOSH_OK;
@@ -971,6 +1090,9 @@ int device_rebuild(DeviceCoarsener *dc, const DeviceLevel &fine, int64_t n_coars
   coarse.n = n_coarse;
   coarse.weight = fine.weight;
   coarse.xadj_is64 = 1;
+  const bool weighted = fine.mult != nullptr;
+  const int64_t wide_from = seam(kSeamWideSums) ? seam(kSeamWideSums) : kWideSumsFrom;
+  const bool wide = weighted ? fine.mult_is64 : fine.weight >= wide_from;
   int64_t *xadj_out = nullptr;
   if (int rc = persistent(&xadj_out, static_cast<size_t>(n_coarse) + 1, "coarse offsets")) return rc;
   coarse.xadj = xadj_out;
@@ -978,12 +1100,10 @@ int device_rebuild(DeviceCoarsener *dc, const DeviceLevel &fine, int64_t n_coars
     coarse.nnz = 0;
     GOSH_TRY_HIP(hipMemset(xadj_out, 0, (static_cast<size_t>(n_coarse) + 1) * 8), "clear coarse offsets");
     if (int rc = persistent(&coarse.adj, 0, "coarse adjacency")) return rc;
-    if (int rc = persistent(&coarse.mult, 0, "coarse multiplicities")) return rc;
-    return GOSH_OK;
+    coarse.mult_is64 = wide;
+    return persistent(reinterpret_cast<uint64_t **>(&coarse.mult), 0, "coarse multiplicities");
   }
-  const bool weighted = fine.mult != nullptr;
-  const int64_t wide_from = seam(kSeamWideSums) ? seam(kSeamWideSums) : kWideSumsFrom;
-  if (fine.weight < wide_from)
+  if (!wide)
     return weighted ? quotient_by_offsets<uint32_t, true>(dc, fine, n_coarse, coarse, xadj_out)
                     : quotient_by_offsets<uint32_t, false>(dc, fine, n_coarse, coarse, xadj_out);
   return weighted ? quotient_by_offsets<unsigned long long, true>(dc, fine, n_coarse, coarse, xadj_out)

@@ -26,7 +26,8 @@ template <typename WT, bool WEIGHTED>
 __global__ __launch_bounds__(256) void radix_keys_kernel(const int64_t *__restrict__ segment,
                                                          const int32_t *__restrict__ list, int64_t count,
                                                          const int64_t *__restrict__ from, int64_t entries,
-                                                         unsigned column_bits, const uint32_t *__restrict__ column,
+                                                         unsigned column_bits, Packing pack,
+                                                         const uint32_t *__restrict__ entry,
                                                          const WT *__restrict__ weight, uint64_t *__restrict__ key,
                                                          WT *__restrict__ value) {
   __shared__ int32_t first_row;
@@ -40,9 +41,9 @@ __global__ __launch_bounds__(256) void radix_keys_kernel(const int64_t *__restri
     for (int64_t e = tile + threadIdx.x; e < std::min(tile + kGatherTile, entries); e += 256) {
       while (r + 1 < count && from[r + 1] <= e) ++r;  // a tile spans a few rows: all are long
       const int64_t at = segment[list[r]] + (e - from[r]);
-      const uint32_t c = column[at];
+      const uint32_t word = entry[at], c = WEIGHTED ? pack.column(word) : word;
       key[e] = (static_cast<uint64_t>(r) << column_bits) | (c == kInside ? inside : c);
-      if constexpr (WEIGHTED) value[e] = weight[at];
+      if constexpr (WEIGHTED) value[e] = c == kInside ? WT(0) : pack.weight(word, weight, at);
     }
   }
 }
@@ -79,16 +80,16 @@ __global__ __launch_bounds__(256) void radix_place_kernel(const int64_t *__restr
                                                           const uint64_t *__restrict__ merged,
                                                           const WT *__restrict__ sums,
                                                           const unsigned long long *__restrict__ merged_count,
-                                                          const int64_t *__restrict__ first,
-                                                          uint32_t *__restrict__ column, WT *__restrict__ weight) {
+                                                          const int64_t *__restrict__ first, Packing pack,
+                                                          uint32_t *__restrict__ entry, WT *__restrict__ weight) {
   const int64_t n = static_cast<int64_t>(*merged_count);
   const uint64_t inside = (uint64_t{1} << column_bits) - 1;
   for (int64_t u = blockIdx.x * 256LL + threadIdx.x; u < n; u += gridDim.x * 256LL) {
     const uint64_t key = merged[u], c = key & inside;
     if (c == inside) continue;
     const int64_t i = static_cast<int64_t>(key >> column_bits), at = segment[list[i]] + (u - first[i]);
-    column[at] = static_cast<uint32_t>(c);
-    weight[at] = sums[u];
+    entry[at] = pack.entry(static_cast<uint32_t>(c), sums[u]);
+    if (sums[u] >= pack.top) weight[at] = sums[u];
   }
 }
 
@@ -96,7 +97,7 @@ __global__ __launch_bounds__(256) void radix_place_kernel(const int64_t *__restr
 
 template <typename WT, bool WEIGHTED>
 int merge_by_radix(Pool &pool, const int64_t *segment, const int32_t *list, int64_t count, int64_t columns,
-                   uint32_t *column, WT *weight, int64_t *length) {
+                   Packing pack, uint32_t *entry, WT *weight, int64_t *length) {
   Buffers buf(pool);
   int64_t *size = nullptr, *from = nullptr;
   uint64_t *keys = nullptr, *sorted = nullptr;
@@ -149,14 +150,14 @@ int merge_by_radix(Pool &pool, const int64_t *segment, const int32_t *list, int6
   GOSH_TRY_HIP(reduce(), "long row merge (size query)");
   if (int rc = buf.alloc(&temp, std::max(sort_bytes, reduce_bytes), "sort workspace")) return rc;
   hipLaunchKernelGGL((radix_keys_kernel<WT, WEIGHTED>), dim3(blocks_for(entries, kGatherTile)), dim3(256), 0, nullptr,
-                     segment, list, count, from, entries, column_bits, column, weight, keys, values);
+                     segment, list, count, from, entries, column_bits, pack, entry, weight, keys, values);
   if (int rc = gosh::check_launch("radix_keys_kernel")) return rc;
   GOSH_TRY_HIP(sort(), "long row sort");
   GOSH_TRY_HIP(reduce(), "long row merge");
   hipLaunchKernelGGL(radix_lengths_kernel, dim3(row_blocks), dim3(256), 0, nullptr, list, count, column_bits, keys,
                      merged_count, size, length);
   hipLaunchKernelGGL(radix_place_kernel<WT>, dim3(blocks_for(entries, 1024)), dim3(256), 0, nullptr, segment, list,
-                     column_bits, keys, values, merged_count, size, column, weight);
+                     column_bits, keys, values, merged_count, size, pack, entry, weight);
   return gosh::check_launch("radix_place_kernel");
 }
 

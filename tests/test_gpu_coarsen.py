@@ -11,7 +11,7 @@ import graphgen
 import paper_2008_12336_amd as G
 from oracle import gosh_oracle as O
 from tests.test_coarsen import _ring_lattice, assert_same_hierarchy
-from tests.util import DENY_RADIX, DENY_STAGING, DENY_TABLE, SEAM_DENY, SEAM_RADIX_FROM, SEAM_WIDE_SUMS, csr_from_pairs, seam
+from tests.util import SEAM_WEIGHT_BITS, DENY_RADIX, DENY_STAGING, DENY_TABLE, SEAM_DENY, SEAM_RADIX_FROM, SEAM_WIDE_SUMS, csr_from_pairs, seam
 
 pytestmark = pytest.mark.gpu
 
@@ -411,3 +411,24 @@ def test_marking_with_few_lanes_per_vertex(n, per_vertex):
     of many turns."""
     edges = graphgen.chung_lu(n, per_vertex * n, 11)
     assert_equals_host(graphgen.to_csr(n, edges), threshold=500, min_shrink=0.9)
+
+
+@pytest.mark.parametrize("weight_bits,wide_sums,radix_from", [(1, 0, 0), (3, 0, 0), (3, 1, 0), (2, 0, 1)])
+@pytest.mark.parametrize("lengths", [[*range(120, 140), *range(1000, 1040, 3)], [2040, 2050, 4090, 4100, 9000, 40000]])
+def test_weights_beside_and_apart_from_their_columns(lengths, weight_bits, wide_sums, radix_from):
+    """Multiplicities that fit the bits a column leaves, and such as do not, up to none: the seam takes the
+    bits away that graphs of 2^28 clusters lack.  Rows of the sorting networks around 1,024 and 4,096 entries,
+    of the bitmap, the counters and the radix sort."""
+    hubs = max(64, 3 * max(lengths))
+    edges = [lengths[a] if a < len(lengths) else 3 for a in range(hubs)]
+    with seam(SEAM_WIDE_SUMS, wide_sums), seam(SEAM_WEIGHT_BITS, weight_bits), seam(SEAM_RADIX_FROM, radix_from):
+        assert_equals_host(hub_graph(hubs, edges, 5), 3, threshold=4, min_shrink=1.0)
+
+
+@pytest.mark.parametrize("n,linked,m", [
+    (30_000, 30_000, 20_000),   # rows of one entry and without: more than a tile's tables hold
+    (16_003, 9_003, 36_011),    # tiles of some hundred rows, the last one spans thousands without entries
+    ((1 << 19) + 5, (1 << 19) + 5, 900_000)])  # clusters looked up in three bytes per vertex
+def test_rows_of_a_tile(n, linked, m):
+    """The tables by which the gather and the copy of the merged rows find the row of an entry."""
+    assert_equals_host(graphgen.to_csr(n, graphgen.er_gnm(linked, m, 3)), threshold=10, min_shrink=1.0)
