@@ -26,11 +26,13 @@
 #include "gosh_coarsen_internal.h"
 #include "gosh_common.h"
 #include "gosh_device_pool.h"
+#include "gosh_quotient.h"
 
 namespace {
 
 using gosh::blocks_for;
 using gosh::persistent;
+using gosh::raise_by_block;
 
 constexpr uint32_t kHighBit = 0x80000000u;   // set in rk[v] when deg(v) is above the mean
 constexpr uint32_t kRankMask = 0x7FFFFFFFu;  // rk[v] & kRankMask = position of v in the order
@@ -46,24 +48,21 @@ __device__ inline void store_status(int32_t *p, int32_t v) {
   __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// key = 2^31 - 1 - degree: ascending keys are descending degrees; stable => ties by id.
+// key = largest degree - degree: ascending keys are descending degrees; stable => ties by id.
 template <typename OffT>
-__global__ __launch_bounds__(256) void degree_keys_kernel(const OffT *__restrict__ xadj, int64_t n,
-                                                          uint32_t *__restrict__ keys,
-                                                          int32_t *__restrict__ ids) {
-  for (int64_t v = blockIdx.x * 256LL + threadIdx.x; v < n; v += gridDim.x * 256LL) {
-    keys[v] = kRankMask - static_cast<uint32_t>(xadj[v + 1] - xadj[v]);
-    ids[v] = static_cast<int32_t>(v);
-  }
+__global__ __launch_bounds__(256) void degree_keys_kernel(const OffT *__restrict__ xadj, int64_t n, uint32_t top,
+                                                          uint32_t *__restrict__ keys) {
+  for (int64_t v = blockIdx.x * 256LL + threadIdx.x; v < n; v += gridDim.x * 256LL)
+    keys[v] = top - static_cast<uint32_t>(xadj[v + 1] - xadj[v]);
 }
 
 // rk[order[t]] = t, with the high bit set when the degree exceeds the mean degree
 // (deg * n > nnz, exact in 64-bit integers).
 __global__ __launch_bounds__(256) void rank_kernel(const uint32_t *__restrict__ sorted_keys,
                                                    const int32_t *__restrict__ order, int64_t n,
-                                                   int64_t nnz, uint32_t *__restrict__ rk) {
+                                                   int64_t nnz, uint32_t top, uint32_t *__restrict__ rk) {
   for (int64_t t = blockIdx.x * 256LL + threadIdx.x; t < n; t += gridDim.x * 256LL) {
-    const int64_t deg = static_cast<int64_t>(kRankMask - sorted_keys[t]);
+    const int64_t deg = static_cast<int64_t>(top - sorted_keys[t]);
     rk[order[t]] = static_cast<uint32_t>(t) | (deg * n > nnz ? kHighBit : 0u);
   }
 }
@@ -71,7 +70,8 @@ __global__ __launch_bounds__(256) void rank_kernel(const uint32_t *__restrict__ 
 // Lanes per vertex of classify_kernel and join_kernel.  Both look at the entries of vertices of at most
 // mean degree, after a chain of dependent reads (rank, offsets, entry, rank or status), and are bound by
 // that chain: with a wavefront per vertex most lanes have no entry and few vertices are in flight.  Fewer
-// lanes pay until the vertices no longer fill the device.  us with 64 / 16 / 8 / 4 lanes, both kernels:
+// lanes pay until the vertices no longer fill the device.  us with 64 / 16 / 8 / 4 lanes, both kernels, before
+// the first stopped at a neighbour that decides and the second read ahead:
 //   4.2 M vertices, R-MAT, mean degree 30: 1,430 / 868 / 774 / 724    its next level, mean above 100: 421 / 152 / 109 / 84
 //   2.1 M, power law: 2,200 / 1,720 / 1,465 / 1,160                   1 M, uniform: 440 / 344 / 294 / 238
 //   the last one's next levels, each about a tenth: 288 / 192 / 177 / 196, 82 / 59 / 68 / 98, 24 / 50 / 80 / 140
@@ -81,7 +81,12 @@ inline int lanes_per_vertex(int64_t n, int64_t nnz) {
   return lanes;
 }
 
-// First classification, LANES lanes per vertex: needs no knowledge of other decisions.
+// First classification, LANES lanes per vertex: needs no knowledge of other decisions.  Most vertices have
+// a neighbour above the mean degree among their first few and need not look at the others.  What is left
+// undecided is gathered in LDS, a wavefront's by itself, and takes its places in the list a hundred
+// vertices at a time: one atomic per wavefront and turn, on one word, took 6 ns each and bound the kernel.
+// 67 M entries of 4.2 M vertices (power law) 1,186 us, now 242; 128 M (R-MAT) 440, now 170.
+constexpr int kHeldVertices = 128;
 template <typename OffT, int LANES>
 __global__ __launch_bounds__(256) void classify_kernel(const OffT *__restrict__ xadj,
                                                        const int32_t *__restrict__ adj,
@@ -90,34 +95,54 @@ __global__ __launch_bounds__(256) void classify_kernel(const OffT *__restrict__ 
                                                        int32_t *__restrict__ pending,
                                                        unsigned long long *__restrict__ pending_count) {
   constexpr int kPerWave = 64 / LANES;
+  __shared__ int32_t held[4][kHeldVertices];
   const int lane = threadIdx.x & 63, gl = lane & (LANES - 1), group = lane & ~(LANES - 1);
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const uint64_t of_group = ~uint64_t{0} >> (64 - LANES) << group;
+  int count = 0;  // vertices held, the same for the whole wavefront
+  auto list_held = [&] {
+    if (count == 0) return;
+    unsigned long long at = 0;
+    if (lane == 0) at = atomicAdd(pending_count, static_cast<unsigned long long>(count));
+    at = __shfl(at, 0, 64);
+    for (int i = lane; i < count; i += 64) pending[at + i] = held[wave][i];
+    count = 0;
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  };
   for (int64_t base = first_wave() * kPerWave; base < n; base += wave_count() * kPerWave) {
     const int64_t v = base + lane / LANES;
     const uint32_t r = v < n ? rk[v] : kHighBit;
-    bool high_neighbour = false, predecessor = false;
-    if (!(r & kHighBit)) {
-      const int64_t begin = static_cast<int64_t>(xadj[v]), end = static_cast<int64_t>(xadj[v + 1]);
-      for (int64_t e = begin + gl; e < end; e += LANES) {
+    bool open = !(r & kHighBit), taken = false, predecessor = false;  // the first two the same for a group
+    int64_t e = 0, end = 0;
+    if (open) {
+      e = static_cast<int64_t>(xadj[v]) + gl;
+      end = static_cast<int64_t>(xadj[v + 1]);
+    }
+    while (__ballot(open && e < end) != 0) {
+      bool high = false;
+      if (open && e < end) {
         const uint32_t ru = rk[adj[e]];
-        high_neighbour |= (ru & kHighBit) != 0;
+        high = (ru & kHighBit) != 0;
         predecessor |= (ru & kRankMask) < r;
       }
+      if ((__ballot(high) & of_group) != 0) {
+        taken = true;
+        open = false;
+      }
+      e += LANES;
     }
-    const uint64_t of_group = ~uint64_t{0} >> (64 - LANES) << group;
-    const bool taken = (__ballot(high_neighbour) & of_group) != 0;
     const bool undecided = !taken && (__ballot(predecessor) & of_group) != 0;
     if (gl == 0 && v < n) status[v] = taken ? kTaken : undecided ? kUndecided : kHub;
-    // one atomic per wavefront: thousands on one word follow one another
     const bool lists = gl == 0 && v < n && undecided;
     const uint64_t listed = __ballot(lists);
     if (listed != 0) {
-      const int leader = __builtin_ctzll(listed);
-      unsigned long long at = 0;
-      if (lane == leader) at = atomicAdd(pending_count, static_cast<unsigned long long>(__popcll(listed)));
-      at = __shfl(at, leader, 64) + __popcll(listed & ((uint64_t{1} << lane) - 1));
-      if (lists) pending[at] = static_cast<int32_t>(v);
+      if (lists) held[wave][count + __popcll(listed & ((uint64_t{1} << lane) - 1))] = static_cast<int32_t>(v);
+      count += __popcll(listed);
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      if (count > kHeldVertices - kPerWave) list_held();
     }
   }
+  list_held();
 }
 
 // One round over the undecided vertices, one wavefront per vertex.
@@ -163,12 +188,17 @@ __global__ __launch_bounds__(256) void hub_flags_kernel(const int32_t *__restric
 __global__ __launch_bounds__(256) void number_hubs_kernel(const int32_t *__restrict__ flags,
                                                           const int32_t *__restrict__ index,
                                                           const int32_t *__restrict__ order, int64_t n,
-                                                          int32_t *__restrict__ map) {
-  for (int64_t t = blockIdx.x * 256LL + threadIdx.x; t < n; t += gridDim.x * 256LL)
+                                                          int32_t *__restrict__ map,
+                                                          unsigned long long *__restrict__ hubs) {
+  for (int64_t t = blockIdx.x * 256LL + threadIdx.x; t < n; t += gridDim.x * 256LL) {
     if (flags[t]) map[order[t]] = index[t];
+    if (t == n - 1) *hubs = static_cast<unsigned long long>(index[t] + flags[t]);
+  }
 }
 
-// Every taken vertex joins its first hub in the order, LANES lanes per vertex.  The
+// Every taken vertex joins its first hub in the order, LANES lanes per vertex, four entries of a lane
+// requested together.  A neighbour above the mean degree is a hub without asking.  (Graphs as above 519 us,
+// now 336; 276, now 169.)  The
 // hubs' own entries of map (read here) were written by the launch before this one; this
 // launch writes only entries of taken vertices.
 template <typename OffT, int LANES>
@@ -178,7 +208,7 @@ __global__ __launch_bounds__(256) void join_kernel(const OffT *__restrict__ xadj
                                                    const int32_t *__restrict__ status,
                                                    const int32_t *__restrict__ order, int64_t n,
                                                    int32_t *map) {
-  constexpr int kPerWave = 64 / LANES;
+  constexpr int kPerWave = 64 / LANES, kAhead = 4;
   const int lane = threadIdx.x & 63, gl = lane & (LANES - 1);
   for (int64_t base = first_wave() * kPerWave; base < n; base += wave_count() * kPerWave) {
     const int64_t v = base + lane / LANES;
@@ -186,10 +216,18 @@ __global__ __launch_bounds__(256) void join_kernel(const OffT *__restrict__ xadj
     if (v < n && status[v] == kTaken) {
       const uint32_t r = rk[v];
       const int64_t begin = static_cast<int64_t>(xadj[v]), end = static_cast<int64_t>(xadj[v + 1]);
-      for (int64_t e = begin + gl; e < end; e += LANES) {
-        const int32_t u = adj[e];
-        const uint32_t ru = rk[u] & kRankMask;
-        if (ru < r && ru < best && status[u] == kHub) best = ru;
+      for (int64_t e = begin + gl; e < end; e += kAhead * LANES) {
+        int32_t u[kAhead];
+        uint32_t ru[kAhead];
+#pragma unroll
+        for (int q = 0; q < kAhead; ++q) u[q] = adj[std::min(e + q * LANES, end - 1)];
+#pragma unroll
+        for (int q = 0; q < kAhead; ++q) ru[q] = rk[u[q]];
+#pragma unroll
+        for (int q = 0; q < kAhead; ++q) {
+          const uint32_t t = ru[q] & kRankMask;
+          if (t < r && t < best && ((ru[q] & kHighBit) != 0 || status[u[q]] == kHub)) best = t;
+        }
       }
     }
     for (int offset = LANES / 2; offset > 0; offset >>= 1) best = min(best, __shfl_xor(best, offset, 64));
@@ -199,22 +237,42 @@ __global__ __launch_bounds__(256) void join_kernel(const OffT *__restrict__ xadj
   }
 }
 
-// Shape checks before any kernel follows the offsets or the neighbour ids: *bad becomes
-// nonzero if the offsets do not run from 0 to nnz without decreasing, or (second kernel)
-// if a neighbour id is outside [0, n).
+// Shape checks before any kernel follows the offsets or the neighbour ids: whether the offsets run
+// from 0 to nnz without decreasing, and (second kernel) whether every neighbour id is inside [0, n).
+// found->top becomes the largest degree met, for the order.
+struct Found {
+  uint32_t top;
+  int32_t bad_offsets, bad_neighbour;
+};
+
 template <typename OffT>
 __global__ __launch_bounds__(256) void check_offsets_kernel(const OffT *__restrict__ xadj, int64_t n,
-                                                            int64_t nnz, int32_t *__restrict__ bad) {
+                                                            int64_t nnz, Found *__restrict__ found) {
+  uint32_t top = 0;
   for (int64_t v = blockIdx.x * 256LL + threadIdx.x; v < n; v += gridDim.x * 256LL) {
     const int64_t lo = static_cast<int64_t>(xadj[v]), hi = static_cast<int64_t>(xadj[v + 1]);
-    if (lo > hi || lo < 0 || hi > nnz || (v == 0 && lo != 0) || (v == n - 1 && hi != nnz)) *bad = 1;
+    if (lo > hi || lo < 0 || hi > nnz || (v == 0 && lo != 0) || (v == n - 1 && hi != nnz)) found->bad_offsets = 1;
+    top = max(top, static_cast<uint32_t>(hi - lo));
   }
+  __shared__ unsigned int block_top;
+  if (threadIdx.x == 0) block_top = 0;
+  __syncthreads();
+  raise_by_block(&found->top, top, &block_top);
 }
 
+// Eight entries of a thread requested together: 128 M take 75 us, 152 one by one.
 __global__ __launch_bounds__(256) void check_neighbours_kernel(const int32_t *__restrict__ adj, int64_t nnz,
-                                                               int64_t n, int32_t *__restrict__ bad) {
-  for (int64_t e = blockIdx.x * 256LL + threadIdx.x; e < nnz; e += gridDim.x * 256LL)
-    if (adj[e] < 0 || adj[e] >= n) *bad = 1;
+                                                               int64_t n, Found *__restrict__ found) {
+  constexpr int kAhead = 8;
+  bool bad = false;
+  for (int64_t first = blockIdx.x * (256LL * kAhead) + threadIdx.x; first < nnz; first += gridDim.x * (256LL * kAhead)) {
+    int32_t u[kAhead];
+#pragma unroll
+    for (int q = 0; q < kAhead; ++q) u[q] = __builtin_nontemporal_load(adj + std::min(first + q * 256, nnz - 1));
+#pragma unroll
+    for (int q = 0; q < kAhead; ++q) bad |= u[q] < 0 || u[q] >= n;
+  }
+  if (bad) found->bad_neighbour = 1;
 }
 
 double ms_since(std::chrono::steady_clock::time_point t0) {
@@ -290,36 +348,30 @@ bool is_device_pointer(const void *p) {
 }
 
 // The kernels follow offsets and neighbour ids without further checks: verify them once.
-int device_level_check(const DeviceLevel &out) {
-  const gosh_csr host{out.n, out.nnz, out.xadj, out.adj, out.xadj_is64};
-  int32_t *bad_dev = nullptr;
-  if (int rc = persistent(&bad_dev, 1, "check flag")) return rc;
+int device_level_check(DeviceLevel &out) {
+  Found *found_dev = nullptr;
+  if (int rc = persistent(&found_dev, 1, "check flags")) return rc;
   struct FlagGuard {
-    int32_t *p;
-    ~FlagGuard() {
-      void *const block = p;
-      block_give(&block, 1);
-    }
-  } guard{bad_dev};
-  int32_t bad = 0;
-  GOSH_TRY_HIP(hipMemset(bad_dev, 0, 4), "clear check flag");
-  const int off_blocks = blocks_for(host.n, 256);
-  if (host.xadj_is64)
+    void *block;
+    ~FlagGuard() { block_give(&block, 1); }
+  } guard{found_dev};
+  GOSH_TRY_HIP(hipMemset(found_dev, 0, sizeof(Found)), "clear check flags");
+  const int off_blocks = std::min(blocks_for(out.n, 256), 4096);
+  if (out.xadj_is64)
     hipLaunchKernelGGL(check_offsets_kernel<int64_t>, dim3(off_blocks), dim3(256), 0, nullptr,
-                       static_cast<const int64_t *>(out.xadj), out.n, out.nnz, bad_dev);
+                       static_cast<const int64_t *>(out.xadj), out.n, out.nnz, found_dev);
   else
     hipLaunchKernelGGL(check_offsets_kernel<int32_t>, dim3(off_blocks), dim3(256), 0, nullptr,
-                       static_cast<const int32_t *>(out.xadj), out.n, out.nnz, bad_dev);
+                       static_cast<const int32_t *>(out.xadj), out.n, out.nnz, found_dev);
+  if (out.nnz > 0)
+    hipLaunchKernelGGL(check_neighbours_kernel, dim3(blocks_for(out.nnz, 2048)), dim3(256), 0, nullptr, out.adj, out.nnz,
+                       out.n, found_dev);
   if (int rc = gosh::check_launch("check_offsets_kernel")) return rc;
-  GOSH_TRY_HIP(hipMemcpy(&bad, bad_dev, 4, hipMemcpyDeviceToHost), "read check flag");
-  if (bad) return gosh::fail(GOSH_EINVAL, "xadj does not run from 0 to nnz without decreasing");
-  if (host.nnz > 0) {
-    hipLaunchKernelGGL(check_neighbours_kernel, dim3(blocks_for(host.nnz, 256)), dim3(256), 0, nullptr, out.adj,
-                       out.nnz, out.n, bad_dev);
-    if (int rc = gosh::check_launch("check_neighbours_kernel")) return rc;
-    GOSH_TRY_HIP(hipMemcpy(&bad, bad_dev, 4, hipMemcpyDeviceToHost), "read check flag");
-    if (bad) return gosh::fail(GOSH_EINVAL, "a neighbour id is outside [0, n)");
-  }
+  Found found{};
+  GOSH_TRY_HIP(hipMemcpy(&found, found_dev, sizeof(found), hipMemcpyDeviceToHost), "read check flags");
+  if (found.bad_offsets) return gosh::fail(GOSH_EINVAL, "xadj does not run from 0 to nnz without decreasing");
+  if (found.bad_neighbour) return gosh::fail(GOSH_EINVAL, "a neighbour id is outside [0, n)");
+  out.top_degree = found.top;
   return GOSH_OK;
 }
 
@@ -483,34 +535,36 @@ int mark_impl(DeviceCoarsener *dc, DeviceLevel &fine, int64_t *n_coarse, bool *d
 
   // degree order
   uint32_t *keys = nullptr, *keys_sorted = nullptr, *rk = nullptr;
-  int32_t *ids = nullptr, *order = nullptr;
+  int32_t *order = nullptr;
   if (int rc = buf.alloc(&keys, static_cast<size_t>(n), "degree keys")) return rc;
   if (int rc = buf.alloc(&keys_sorted, static_cast<size_t>(n), "sorted degree keys")) return rc;
-  if (int rc = buf.alloc(&ids, static_cast<size_t>(n), "vertex ids")) return rc;
   if (int rc = buf.alloc(&order, static_cast<size_t>(n), "order")) return rc;
   if (int rc = buf.alloc(&rk, static_cast<size_t>(n), "ranks")) return rc;
   const int flat_blocks = blocks_for(n, 256);
-  hipLaunchKernelGGL(degree_keys_kernel<OffT>, dim3(flat_blocks), dim3(256), 0, nullptr, xadj, n, keys, ids);
+  hipLaunchKernelGGL(degree_keys_kernel<OffT>, dim3(flat_blocks), dim3(256), 0, nullptr, xadj, n, fine.top_degree, keys);
   if (int rc = gosh::check_launch("degree_keys_kernel")) return rc;
   {
+    // a pass per eight bits: no more of them than the largest degree has
+    unsigned bits = 1;
+    while (bits < 32 && (fine.top_degree >> bits) != 0) ++bits;
+    const rocprim::counting_iterator<int32_t> ids(0);
     size_t temp_bytes = 0;
     GOSH_TRY_HIP(rocprim::radix_sort_pairs(nullptr, temp_bytes, keys, keys_sorted, ids, order,
-                                         static_cast<size_t>(n), 0u, 31u, nullptr),
+                                         static_cast<size_t>(n), 0u, bits, nullptr),
                "degree sort (size query)");
     char *temp = nullptr;
     if (int rc = buf.alloc(&temp, temp_bytes, "sort workspace")) return rc;
     GOSH_TRY_HIP(rocprim::radix_sort_pairs(temp, temp_bytes, keys, keys_sorted, ids, order,
-                                         static_cast<size_t>(n), 0u, 31u, nullptr),
+                                         static_cast<size_t>(n), 0u, bits, nullptr),
                "degree sort");
-    GOSH_TRY_HIP(hipDeviceSynchronize(), "degree sort");
-    buf.release(temp);
+    buf.release(temp);  // what takes it up again is on the same stream
   }
-  hipLaunchKernelGGL(rank_kernel, dim3(flat_blocks), dim3(256), 0, nullptr, keys_sorted, order, n, nnz, rk);
+  hipLaunchKernelGGL(rank_kernel, dim3(flat_blocks), dim3(256), 0, nullptr, keys_sorted, order, n, nnz, fine.top_degree,
+                     rk);
   if (int rc = gosh::check_launch("rank_kernel")) return rc;
   GOSH_TRY_HIP(hipDeviceSynchronize(), "ranks");
   buf.release(keys);
   buf.release(keys_sorted);
-  buf.release(ids);
   *order_ms = ms_since(t_order);
 
   // first classification
@@ -533,7 +587,8 @@ int mark_impl(DeviceCoarsener *dc, DeviceLevel &fine, int64_t *n_coarse, bool *d
                     : lanes == 32 ? join_kernel<OffT, 32>
                                   : join_kernel<OffT, 64>;
   const int group_blocks = blocks_for(n, 256 / lanes);
-  hipLaunchKernelGGL(classify, dim3(group_blocks), dim3(256), 0, nullptr, xadj, adj, rk, n, status, pending, counters);
+  // a wavefront walks enough vertices for its turns at the list to be few, where there are that many
+  hipLaunchKernelGGL(classify, dim3(std::min(group_blocks, 2048)), dim3(256), 0, nullptr, xadj, adj, rk, n, status, pending, counters);
   if (int rc = gosh::check_launch("classify_kernel")) return rc;
   unsigned long long count = 0;
   GOSH_TRY_HIP(hipMemcpy(&count, counters, 8, hipMemcpyDeviceToHost), "read pending count");
@@ -574,20 +629,17 @@ int mark_impl(DeviceCoarsener *dc, DeviceLevel &fine, int64_t *n_coarse, bool *d
     GOSH_TRY_HIP(rocprim::exclusive_scan(temp, temp_bytes, flags, index, int32_t(0), static_cast<size_t>(n),
                                        rocprim::plus<int32_t>(), nullptr),
                "hub scan");
-    GOSH_TRY_HIP(hipDeviceSynchronize(), "hub scan");
     buf.release(temp);
   }
-  int32_t last_flag = 0, last_index = 0;
-  GOSH_TRY_HIP(hipMemcpy(&last_flag, flags + (n - 1), 4, hipMemcpyDeviceToHost), "read hub count");
-  GOSH_TRY_HIP(hipMemcpy(&last_index, index + (n - 1), 4, hipMemcpyDeviceToHost), "read hub count");
   if (fine.map == nullptr)
     if (int rc = persistent(&fine.map, static_cast<size_t>(n), "map")) return rc;
-  hipLaunchKernelGGL(number_hubs_kernel, dim3(flat_blocks), dim3(256), 0, nullptr, flags, index, order, n, fine.map);
+  hipLaunchKernelGGL(number_hubs_kernel, dim3(flat_blocks), dim3(256), 0, nullptr, flags, index, order, n, fine.map,
+                     counters);
   if (int rc = gosh::check_launch("number_hubs_kernel")) return rc;
   hipLaunchKernelGGL(join, dim3(group_blocks), dim3(256), 0, nullptr, xadj, adj, rk, status, order, n, fine.map);
   if (int rc = gosh::check_launch("join_kernel")) return rc;
-  GOSH_TRY_HIP(hipDeviceSynchronize(), "marking");
-  *n_coarse = static_cast<int64_t>(last_flag) + last_index;
+  GOSH_TRY_HIP(hipMemcpy(&count, counters, 8, hipMemcpyDeviceToHost), "read hub count");  // and waits for the marking
+  *n_coarse = static_cast<int64_t>(count);
   *done = true;
   return GOSH_OK;
 }

@@ -65,6 +65,7 @@ struct DeviceLevel {
   int device = -1;
   int64_t n = 0, nnz = 0;
   int64_t weight = 0;  // entries of G_0, which no sum of multiplicities exceeds
+  uint32_t top_degree = 0;  // of any vertex
   int32_t xadj_is64 = 1;
   void *xadj = nullptr;     // n + 1 offsets
   int32_t *adj = nullptr;   // nnz neighbours
@@ -91,7 +92,8 @@ int device_level_upload(DeviceCoarsener *dc, const gosh_csr &host, DeviceLevel &
 // range-checks it.
 int device_level_borrow(const gosh_csr &on_device, DeviceLevel &out);
 // Offsets run from 0 to nnz without decreasing, neighbour ids lie in [0, n): GOSH_EINVAL if not.
-int device_level_check(const DeviceLevel &level);
+// Sets the largest degree.
+int device_level_check(DeviceLevel &level);
 // True for memory allocated on a device (hipMalloc); false for host memory of any kind.
 bool is_device_pointer(const void *p);
 // Replaces level.map with a copy of the host array (n entries).

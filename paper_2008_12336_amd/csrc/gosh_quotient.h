@@ -48,6 +48,15 @@ __device__ inline int32_t row_of_entry(const PosT *pos, int32_t lo, int32_t hi, 
   return lo;
 }
 
+// Raises *word to the largest `mine` of the workgroup: one atomic, and only if that is above
+// what is read there (the word only grows, so a stale value costs an atomic at most).
+__device__ inline void raise_by_block(unsigned int *word, unsigned int mine, unsigned int *block_top) {
+  if (mine) atomicMax(block_top, mine);
+  __syncthreads();
+  if (threadIdx.x == 0 && *block_top > __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+    atomicMax(word, *block_top);
+}
+
 // Merges the segments list[0 .. count) in place by sorting their entries as (segment, column) keys (not
 // WEIGHTED: they are held as columns alone);
 // length[a] becomes the length of a merged segment.  Queued on the null stream.  GOSH_ENOMEM, with

@@ -47,6 +47,7 @@ using gosh::persistent;
 using gosh::kGatherTile;
 using gosh::kInside;
 using gosh::Packing;
+using gosh::raise_by_block;
 using gosh::row_of_entry;
 
 constexpr int kGatherRows = 1024;          // rows of a tile that are looked up in LDS,
@@ -71,19 +72,12 @@ constexpr int64_t kSlice = 1 << 16;  // entries of a counted segment that one wo
 constexpr int64_t kRankColumns = int64_t{10} << kPieceBits, kCountColumns = int64_t{4} << kPieceBits;
 constexpr int kSumBytes = 30 << 10;  // LDS for the columns and sums of a piece, as many at a time as fit
 
-// Number of segments per way of merging, 1 + the largest column met, slices of the counted ones.
+// Number of segments per way of merging, 1 + the largest column met, slices of the counted ones; of the
+// coarse graph: its longest row and its entries.
 struct Classes {
-  unsigned int count[kWays], columns, slices;
+  unsigned int count[kWays], columns, slices, longest;
+  int64_t entries;
 };
-
-// Raises *word to the largest `mine` of the workgroup: one atomic, and only if that is above
-// what is read there (the word only grows, so a stale value costs an atomic at most).
-__device__ inline void raise_by_block(unsigned int *word, unsigned int mine, unsigned int *block_top) {
-  if (mine) atomicMax(block_top, mine);
-  __syncthreads();
-  if (threadIdx.x == 0 && *block_top > __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
-    atomicMax(word, *block_top);
-}
 
 __host__ __device__ inline int64_t pieces_of(int64_t columns) {
   return std::max<int64_t>((columns + (int64_t{1} << kPieceBits) - 1) >> kPieceBits, 1);
@@ -886,6 +880,20 @@ __global__ __launch_bounds__(256) void copy_merged_kernel(const int64_t *__restr
   }
 }
 
+// What is to be known of the coarse rows before there is room for them.
+__global__ __launch_bounds__(256) void coarse_shape_kernel(const int64_t *__restrict__ length,
+                                                           const int64_t *__restrict__ xadj_out, int64_t n_coarse,
+                                                           Classes *__restrict__ classes) {
+  __shared__ unsigned int block_top;
+  if (threadIdx.x == 0) block_top = 0;
+  __syncthreads();
+  unsigned int top = 0;
+  for (int64_t a = blockIdx.x * 256LL + threadIdx.x; a < n_coarse; a += gridDim.x * 256LL)
+    top = max(top, static_cast<unsigned int>(length[a]));
+  raise_by_block(&classes->longest, top, &block_top);
+  if (blockIdx.x == 0 && threadIdx.x == 0) classes->entries = xadj_out[n_coarse];
+}
+
 __global__ void clear_classes_kernel(Classes *classes) { *classes = Classes{}; }
 
 template <typename OffT, typename WT, bool WEIGHTED>
@@ -1039,7 +1047,13 @@ int quotient(gosh::DeviceCoarsener *dc, const gosh::DeviceLevel &fine, int64_t n
                                          rocprim::plus<int64_t>(), nullptr),
                  "offset scan");
   }
-  GOSH_TRY_HIP(hipMemcpy(&coarse.nnz, xadj_out + n_coarse, 8, hipMemcpyDeviceToHost), "read coarse size");
+  hipLaunchKernelGGL(coarse_shape_kernel, dim3(std::min(blocks_for(n_coarse, 256), 1024)), dim3(256), 0, nullptr, length,
+                     xadj_out, n_coarse, classes);
+  if (int rc = gosh::check_launch("coarse_shape_kernel")) return rc;
+  Classes shape{};
+  GOSH_TRY_HIP(hipMemcpy(&shape, classes, sizeof(shape), hipMemcpyDeviceToHost), "read coarse size");
+  coarse.nnz = shape.entries;
+  coarse.top_degree = shape.longest;
   if (int rc = persistent(&coarse.adj, static_cast<size_t>(coarse.nnz), "coarse adjacency")) return rc;
   WT *mult_out = nullptr;
   if (int rc = persistent(&mult_out, static_cast<size_t>(coarse.nnz), "coarse multiplicities")) return rc;

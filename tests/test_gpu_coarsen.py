@@ -432,3 +432,16 @@ def test_weights_beside_and_apart_from_their_columns(lengths, weight_bits, wide_
 def test_rows_of_a_tile(n, linked, m):
     """The tables by which the gather and the copy of the merged rows find the row of an entry."""
     assert_equals_host(graphgen.to_csr(n, graphgen.er_gnm(linked, m, 3)), threshold=10, min_shrink=1.0)
+
+
+def test_more_undecided_vertices_than_a_wavefront_holds():
+    """Two random permutations, and a vertex of a hundred neighbours that lifts the mean degree above the four of
+    all others: nearly every vertex is undecided at first."""
+    n = 1_200_007
+    g = torch.Generator().manual_seed(3)
+    ids = torch.arange(n)
+    ends = [torch.cat((ids, ids, torch.zeros(100, dtype=torch.int64))),
+            torch.cat([torch.randperm(n, generator=g) for _ in range(2)] + [torch.arange(1000, 1100)])]
+    lo, hi = torch.minimum(*ends), torch.maximum(*ends)
+    key = torch.unique((lo * n + hi)[lo < hi])
+    assert_equals_host(graphgen.to_csr(n, torch.stack((key // n, key % n), 1)), threshold=n // 2, min_shrink=1.0, max_levels=2)
