@@ -380,7 +380,8 @@ typedef struct {
                         GOSH_FLAG_EDGE_EPOCHS */
   double upload_ms;  /* host -> device copy of G_i (wall clock) */
   double train_ms;   /* the e_i epoch launches (HIP events on the stream) */
-  double project_ms; /* map upload + projection to level i-1 (wall clock; 0 at level 0) */
+  double project_ms; /* map upload + projection to level i-1 (wall clock, or HIP events where the call
+                        does not wait for it; 0 at level 0) */
   int32_t parts_K;   /* 0: trained with the epoch kernel; K > 0: trained with the part-pair
                         rotation on K parts (train_ms is then the wall time of that call) */
   float max_abs;     /* largest finite |entry| of M_i after training (levels trained by the
@@ -399,7 +400,8 @@ typedef struct {
  * matrix of level 0 exceed it, the call is refused with GOSH_EBUDGET (use gosh_embed_host,
  * which keeps such levels on the host).  stats: NULL or host array of D entries, filled per level.
  * Blocking: returns after the last level finished; intermediate device buffers are
- * allocated and freed inside the call.  Every level is checked after its training
+ * allocated and freed inside the call (those of up to 64 MB are blocks that the library keeps for the next
+ * call, as it does those of freed hierarchies; gosh_hierarchy_trim_scratch returns them).  Every level is checked after its training
  * (gosh_matrix_check: one more read of the matrix): if any level ends with non-finite
  * entries the run is still completed, stats are filled, and GOSH_EDIVERGED is returned. */
 int gosh_embed(const gosh_hierarchy *h, int32_t d, int32_t k_neg, int64_t epochs, double p,

@@ -97,7 +97,7 @@ struct CheckResult {
 // pinned.
 void *pinned_on_device(void *p, size_t bytes);
 
-int matrix_check_clear(CheckResult *result_dev, hipStream_t st);
+int matrix_check_clear(CheckResult *results_dev, hipStream_t st, int count = 1);
 int matrix_check_add(const float *rows_dev, int64_t floats, CheckResult *result_dev, hipStream_t st);
 int matrix_check_read(const CheckResult *result_dev, float *max_abs, int64_t *nonfinite, hipStream_t st);
 // A per-device CheckResult owned by the library (allocated on first use, kept).

@@ -377,10 +377,8 @@ __global__ __launch_bounds__(256) void matrix_check_kernel(const Float4 *__restr
   }
 }
 
-__global__ void clear_check_kernel(gosh::CheckResult *out) {
-  out->max_bits = 0;
-  out->pad = 0;
-  out->nonfinite = 0;
+__global__ void clear_checks_kernel(gosh::CheckResult *out, int count) {
+  for (int i = threadIdx.x; i < count; i += blockDim.x) out[i] = gosh::CheckResult{0, 0, 0};
 }
 
 int grid_for(int64_t items, int per_block, int max_blocks) {
@@ -545,9 +543,9 @@ int check_epoch_args(const gosh_csr *g_dev, float *M_dev, int32_t d, int32_t k_n
 
 namespace gosh {
 
-int matrix_check_clear(CheckResult *result_dev, hipStream_t st) {
-  hipLaunchKernelGGL(clear_check_kernel, dim3(1), dim3(1), 0, st, result_dev);
-  return check_launch("clear_check_kernel");
+int matrix_check_clear(CheckResult *results_dev, hipStream_t st, int count) {
+  hipLaunchKernelGGL(clear_checks_kernel, dim3(1), dim3(64), 0, st, results_dev, count);
+  return check_launch("clear_checks_kernel");
 }
 
 int matrix_check_add(const float *rows_dev, int64_t floats, CheckResult *result_dev, hipStream_t st) {

@@ -212,3 +212,21 @@ def test_pair_levels_vcycle_matches_the_oracle(host_matrix, small_pair_levels):
     # without the flag the same call trains every level with Alg. 3
     plain, *_ = O.embed(xadj, adj, d, k, epochs, 0.3, 0.05, 5, threshold=100, min_shrink=0.8)
     assert rel_err(got, plain) > 1e-3
+
+
+def test_levels_queued_and_waited_for_are_the_same():
+    """Without a budget the levels of a run follow one another on the stream and small matrices stay until its
+    end; under a budget each is waited for.  Two runs in a row take up each other's buffers."""
+    n, d, k, epochs = 20_003, 36, 3, 14
+    c = graphgen.to_csr(n, graphgen.chung_lu(n, 90_000, 3))
+    h = G.gosh_coarsen_device(n, c.xadj, c.adj, threshold=100, min_shrink=0.9)
+    assert h.levels >= 4
+    runs = []
+    for budget in (0, 1 << 30, 0):
+        M0 = torch.zeros(n, d, dtype=torch.float32, device=DEV)
+        stats = G.gosh_embed(h, M0, k, epochs, 0.3, 0.05, 3, flags=G.GOSH_FLAG_SEQUENTIAL, device_budget_bytes=budget)
+        runs.append(M0.cpu().numpy())
+        assert all(s["train_ms"] > 0 for s in stats) and all(s["project_ms"] > 0 for s in stats[1:])
+        assert all(s["max_abs"] > 0 and s["nonfinite"] == 0 for s in stats)
+        assert abs(stats[0]["max_abs"] - np.abs(runs[-1]).max()) == 0
+    assert np.array_equal(runs[0], runs[1]) and np.array_equal(runs[0], runs[2])
