@@ -244,9 +244,13 @@ __global__ __launch_bounds__(256) void init_embedding_kernel(float4 *__restrict_
 
 // A map entry that names no coarse vertex gives a row of zeros.  Four units of a thread are
 // requested together (map entries, then rows).  Bound by the row gather beside the write stream:
-// 0.6 M rows onto 4.2 M at d = 128 take 665 us, 6.4 TB/s of rows.  The stores are non-temporal: the
-// check of the matrix that follows a projection runs into fewer write-backs (1,060 -> 1,025 us for
-// the two calls; 290 -> 265 us at 3 M x 36).
+// 0.6 M rows onto 4.2 M at d = 128 take 665 us, 6.4 TB/s of rows.  The stores to a matrix that the memory-side
+// cache does not hold are non-temporal (STREAM): the check of the matrix that follows a projection runs into
+// fewer write-backs.  A smaller one stays there for the epochs that follow.  Projection and check / projection
+// and epoch at d = 128, us, streamed and plain: 64 MB 59, 57 / 205, 157;  96 MB 75, 72 / 297, 225;  128 MB 89, 91 /
+// 433, 435;  224 MB 134, 136 / 553, 550;  400 MB 207, 216 / 846, 865.
+constexpr int64_t kStreamBytes = int64_t{128} << 20;
+template <bool STREAM>
 __global__ __launch_bounds__(256) void project_kernel(const Float4 *__restrict__ coarse,
                                                       const int32_t *__restrict__ map,
                                                       Float4 *__restrict__ fine, int64_t n_fine,
@@ -273,8 +277,11 @@ __global__ __launch_bounds__(256) void project_kernel(const Float4 *__restrict__
       }
 #pragma unroll
       for (int q = 0; q < kUnits; ++q)
-        if (i0 + q * 256 < units)
-          __builtin_nontemporal_store(c[q] < n_coarse ? x[q] : Float4{0.f, 0.f, 0.f, 0.f}, out + i0 + q * 256);
+        if (i0 + q * 256 < units) {
+          const Float4 y = c[q] < n_coarse ? x[q] : Float4{0.f, 0.f, 0.f, 0.f};
+          if constexpr (STREAM) __builtin_nontemporal_store(y, out + i0 + q * 256);
+          else out[i0 + q * 256] = y;
+        }
     }
   }
 }
@@ -343,7 +350,8 @@ __global__ __launch_bounds__(256) void row_probe_kernel(float4 *__restrict__ M, 
 // first, and it adds its maximum only if that is above what it reads there.  The tiles are
 // taken from the end of the matrix: what was written last is still in the memory-side cache.
 // The loads are non-temporal (2.1 GB: 364 -> 325 us).  2.1 GB took 554 us with one atomic per
-// wavefront of 8,192 workgroups, a matrix of 67 MB 215 us of which 58 are left.
+// wavefront of 8,192 workgroups.  A workgroup takes four tiles where that leaves 256 of them: 67 MB in 2,048
+// workgroups, whose atomics all come at once, took 40 us, now 13.
 constexpr int kCheckTile = 2048;  // float4s per workgroup and turn
 constexpr int kCheckBlocks = 2048;
 __global__ __launch_bounds__(256) void matrix_check_kernel(const Float4 *__restrict__ M, int64_t total4,
@@ -551,7 +559,9 @@ int matrix_check_clear(CheckResult *results_dev, hipStream_t st, int count) {
 int matrix_check_add(const float *rows_dev, int64_t floats, CheckResult *result_dev, hipStream_t st) {
   const int64_t total4 = floats / 4;
   if (total4 <= 0) return GOSH_OK;
-  hipLaunchKernelGGL(matrix_check_kernel, dim3(grid_for(total4, kCheckTile, kCheckBlocks)), dim3(256), 0, st,
+  const int64_t tiles = (total4 + kCheckTile - 1) / kCheckTile;
+  const int64_t blocks = std::min<int64_t>(std::max(std::min<int64_t>(tiles, 256), tiles / 4), kCheckBlocks);
+  hipLaunchKernelGGL(matrix_check_kernel, dim3(static_cast<unsigned>(blocks)), dim3(256), 0, st,
                      reinterpret_cast<const Float4 *>(rows_dev), total4, result_dev);
   return check_launch("matrix_check_kernel");
 }
@@ -701,7 +711,8 @@ int gosh_project(const float *M_coarse_dev, int64_t n_coarse, const int32_t *map
   if (int rc = gosh::check_device_span(M_fine_dev, static_cast<size_t>(n_fine) * d * 4, "M_fine")) return rc;
   if (int rc = gosh::check_device_span(map_dev, static_cast<size_t>(n_fine) * 4, "map")) return rc;
   const RowTiles t = row_tiles(d / 4);
-  hipLaunchKernelGGL(project_kernel, dim3(grid_for(n_fine, t.rows, kTileBlocks)), dim3(256), 0,
+  const bool stream = n_fine * d * 4 > kStreamBytes;
+  hipLaunchKernelGGL(stream ? project_kernel<true> : project_kernel<false>, dim3(grid_for(n_fine, t.rows, kTileBlocks)), dim3(256), 0,
                      gosh::as_stream(hip_stream), reinterpret_cast<const Float4 *>(M_coarse_dev),
                      map_dev, reinterpret_cast<Float4 *>(M_fine_dev), n_fine, t,
                      static_cast<uint32_t>(std::min<int64_t>(n_coarse, 2147483647LL)));

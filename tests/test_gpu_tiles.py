@@ -55,3 +55,24 @@ def test_check_counts_every_entry_once(n):
     finite = flat[torch.isfinite(flat)]
     assert bad == len(marks)
     assert top == (finite.abs().max().item() if finite.numel() else 0.0)
+
+
+@pytest.mark.parametrize("d,mb", [(36, 127), (36, 129), (128, 200), (508, 140)])
+def test_projection_of_matrices_around_the_memory_side_cache(d, mb):
+    """From 128 MB on the rows are written past the caches."""
+    n, coarse_n = mb * (1 << 20) // (4 * d) + 1, 70_001
+    g = torch.Generator(device=DEV).manual_seed(d)
+    coarse = torch.randn(coarse_n, d, generator=g, device=DEV)
+    cmap = torch.randint(0, coarse_n, (n,), generator=g, device=DEV, dtype=torch.int32)
+    fine = torch.full((n + 1, d), 7.0, device=DEV)
+    G.gosh_project(coarse, cmap, fine[:n])
+    assert torch.equal(fine[:n], coarse[cmap.long()]) and (fine[n] == 7.0).all()
+
+
+def test_check_of_tiles_shared_unevenly():
+    """301 tiles for 256 workgroups."""
+    M = torch.zeros(300 * 2048 + 5, 4, device=DEV)
+    for at in (0, 255 * 2048, 256 * 2048 + 1, 300 * 2048 + 4):
+        M[at, 3] = float("inf")
+    M[256 * 2048, 0] = -5.0
+    assert G.gosh_matrix_check(M) == (5.0, 4)
