@@ -145,23 +145,24 @@ __global__ __launch_bounds__(256) void count_positives_kernel(SamplerArgs a, uin
 }
 
 // ---------------------------------------------------------------------------------
-// The two kernels below walk a row-major matrix in tiles of whole rows, at most kTileUnits
+// The projection below walks a row-major matrix in tiles of whole rows, at most kTileUnits
 // 128-bit units: inside a tile a unit's row comes from one 24-bit product instead of a 64-bit
 // division per unit, and consecutive lanes still write consecutive addresses whatever d is.
 constexpr int kTileUnits = 2048, kTileRows = 256, kTileBlocks = 1 << 16;
 
+// unit / d4 for unit < kTileUnits, magic = ceil(2^20 / d4), since unit * (magic * d4 - 2^20) < kTileUnits * d4 < 2^20.
+__device__ __forceinline__ uint32_t row_of(uint32_t unit, uint32_t magic) { return (unit * magic) >> 20; }
+uint32_t row_magic(int32_t d4) {
+  static_assert(static_cast<int64_t>(kTileUnits) * (GOSH_MAX_DIM / 4) < (1 << 20), "row_of");
+  return static_cast<uint32_t>(((1 << 20) + d4 - 1) / d4);
+}
+
 struct RowTiles {
   int32_t d4;     // units per row
   int32_t rows;   // rows per tile
-  uint32_t magic; // ceil(2^20 / d4): unit / d4 == (unit * magic) >> 20 for every unit of a tile, since
-                  // unit * (magic * d4 - 2^20) < kTileUnits * d4 < 2^20
-  __device__ __forceinline__ uint32_t row_of(uint32_t unit) const { return (unit * magic) >> 20; }
+  uint32_t magic;
 };
-
-RowTiles row_tiles(int32_t d4) {
-  static_assert(static_cast<int64_t>(kTileUnits) * (GOSH_MAX_DIM / 4) < (1 << 20), "RowTiles::magic");
-  return RowTiles{d4, std::min(kTileRows, kTileUnits / d4), static_cast<uint32_t>(((1 << 20) + d4 - 1) / d4)};
-}
+RowTiles row_tiles(int32_t d4) { return RowTiles{d4, std::min(kTileRows, kTileUnits / d4), row_magic(d4)}; }
 
 // A Philox round in four instructions instead of the eight the compiler makes of the same
 // expressions: both words of a product from one multiply-add, three-way xors.  For the kernel
@@ -183,42 +184,55 @@ __device__ __forceinline__ uint32_t xor3(uint32_t a, uint32_t b, uint32_t c) {
 // and are taken once per row of a tile and once per column (`by_row`, `by_col`).  The quotient
 // k / (d 2^24), k = bits - 2^23, is a product with the rounded reciprocal and one correction,
 // which is the rounded quotient (checked for every k and d) without a division.
-// Bound by the write stream: 4.2 M rows at d = 128 (2.1 GB) take 378 us, 5.7 TB/s; bound by its
-// arithmetic (64-bit division for the index, fp64 quotient, all rounds per unit) it took 655 us.
-__global__ __launch_bounds__(256) void init_embedding_kernel(float4 *__restrict__ M, int64_t rows_total,
-                                                             int64_t first_row, RowTiles t, float d_scaled,
-                                                             float rcp_scaled, uint32_t key0, uint32_t key1,
-                                                             uint32_t level) {
+//
+// Bound by the write stream, whose rate depends on how much is being written at a time: a workgroup writes
+// TILE units that begin at a multiple of as many, wherever in a row that is, and ends.  A matrix of more than
+// kStreamInit bytes, which no cache holds, is written 4 KB to a wavefront, others 16 KB to a workgroup.  us, with tiles
+// of whole rows up to 32 KB / 16 KB / 4 KB (both of any rows):
+//   d = 128: 1 MB 3.4 / 2.8 / 2.8   64 MB 12.4 / 12.5 / 14.5   256 MB 38.4 / 37.9 / 41.0   2 GB 377 / 358 / 312
+//   d = 100: 1 MB 3.5 / 2.9 / 2.8   64 MB 13.2 / 12.5 / 13.7   256 MB 39.1 / 37.8 / 42.2   2 GB 394 / 352 / 321
+// (2 GB: 6.9 TB/s now; d = 8 350, 300 of 4 KB, 512 371, 314.)  Its arithmetic alone takes 248 us for 2 GB.  The tables
+// of a wavefront take less than 5 KB of LDS, for 32 to fit a CU: 335 us with 5.2 KB.
+constexpr int64_t kStreamInit = int64_t{256} << 20;
+template <int THREADS, int TILE, int SHORTEST>  // rows of SHORTEST units at least
+__global__ __launch_bounds__(THREADS) void init_embedding_kernel(float4 *__restrict__ M, int64_t units_total,
+                                                                 int64_t first_row, uint32_t d4, uint32_t magic,
+                                                                 uint64_t magic64, float d_scaled, float rcp_scaled,
+                                                                 uint32_t key0, uint32_t key1, uint32_t level) {
   using namespace gosh;
-  __shared__ uint4 by_row[kTileRows];
+  static_assert(TILE + GOSH_MAX_DIM / 4 <= kTileUnits, "row_of");
+  __shared__ uint4 by_row[TILE / SHORTEST + 2];
   __shared__ uint2 by_col[GOSH_MAX_DIM / 4];
   // round 0 multiplies the constant third counter word, round 1 (lo_const) uses it
   constexpr uint32_t kWord = 0xFFFFFFFFu;
   const uint32_t hi_const = mul_hi32(kPhiloxMulB, kWord), lo_const = kPhiloxMulB * kWord;
-  for (uint32_t c = threadIdx.x; c < static_cast<uint32_t>(t.d4); c += 256) {
+  for (uint32_t c = threadIdx.x; c < d4; c += THREADS) {
     const uint32_t x = hi_const ^ c ^ key0;  // state word 0 after round 0
     by_col[c] = uint2{mul_hi32(kPhiloxMulA, x) ^ (key1 + kPhiloxWeylB), kPhiloxMulA * x};
   }
-  const int64_t tiles = (rows_total + t.rows - 1) / t.rows;
+  const int64_t tiles = (units_total + TILE - 1) / TILE;
   for (int64_t tile = blockIdx.x; tile < tiles; tile += gridDim.x) {
-    const int64_t lo = tile * t.rows;
-    const uint32_t rows = static_cast<uint32_t>(std::min<int64_t>(t.rows, rows_total - lo));
+    const uint64_t u0 = static_cast<uint64_t>(tile) * TILE;
+    // u0 / d4: magic64 = ceil(2^64 / d4) is exact for u0 * d4 < 2^64
+    const uint64_t row0 = d4 == 1 ? u0 : __umul64hi(u0, magic64);
+    const uint32_t c0 = static_cast<uint32_t>(u0 - row0 * d4);
+    const uint32_t units = static_cast<uint32_t>(std::min<int64_t>(TILE, units_total - static_cast<int64_t>(u0)));
+    const uint32_t rows = row_of(c0 + units - 1, magic) + 1;
     __syncthreads();  // by_col is there; the previous tile's by_row has been used
-    if (threadIdx.x < rows) {
-      const uint32_t v = static_cast<uint32_t>(first_row + lo + threadIdx.x);
+    for (uint32_t q = threadIdx.x; q < rows; q += THREADS) {
+      const uint32_t v = static_cast<uint32_t>(first_row + static_cast<int64_t>(row0) + q);
       const uint32_t lo0 = kPhiloxMulA * v;                                   // state word 3 after round 0
       const uint32_t x2 = mul_hi32(kPhiloxMulA, v) ^ level ^ key1;            // word 2 after round 0
       const uint32_t x0 = mul_hi32(kPhiloxMulB, x2) ^ lo_const ^ (key0 + kPhiloxWeylA);  // word 0 after round 1
-      by_row[threadIdx.x] = uint4{lo0, (kPhiloxMulB * x2) ^ (key0 + 2 * kPhiloxWeylA),
-                                  mul_hi32(kPhiloxMulA, x0) ^ (key1 + 2 * kPhiloxWeylB), kPhiloxMulA * x0};
+      by_row[q] = uint4{lo0, (kPhiloxMulB * x2) ^ (key0 + 2 * kPhiloxWeylA),
+                        mul_hi32(kPhiloxMulA, x0) ^ (key1 + 2 * kPhiloxWeylB), kPhiloxMulA * x0};
     }
     __syncthreads();
-    float4 *const out = M + lo * t.d4;
-    const uint32_t units = rows * t.d4;
-    for (uint32_t i = threadIdx.x; i < units; i += 256) {
-      const uint32_t row = t.row_of(i);
+    float4 *const out = M + u0;
+    for (uint32_t i = threadIdx.x; i < units; i += THREADS) {
+      const uint32_t j = c0 + i, row = row_of(j, magic);
       const uint4 r = by_row[row];
-      const uint2 c = by_col[i - row * t.d4];
+      const uint2 c = by_col[j - row * d4];
       const uint32_t x2 = c.x ^ r.x;  // word 2 after round 1
       const uint2 b2 = mul_wide(kPhiloxMulB, x2);
       uint32_t w[4] = {b2.y ^ r.y, b2.x, r.z ^ c.y, r.w};  // after round 2
@@ -267,7 +281,7 @@ __global__ __launch_bounds__(256) void project_kernel(const Float4 *__restrict__
       Float4 x[kUnits];
 #pragma unroll
       for (int q = 0; q < kUnits; ++q) {
-        row[q] = t.row_of(std::min(i0 + q * 256, units - 1));
+        row[q] = row_of(std::min(i0 + q * 256, units - 1), t.magic);
         c[q] = static_cast<uint32_t>(map_rows[row[q]]);
       }
 #pragma unroll
@@ -611,11 +625,16 @@ int row_probe(float *M_dev, int64_t n, int32_t d, int64_t accesses, uint64_t see
 
 int init_rows(float *rows_dev, int64_t first_row, int64_t count, int32_t d, uint64_t seed,
               uint32_t level, hipStream_t st) {
-  const RowTiles t = row_tiles(d / 4);
+  const uint32_t d4 = static_cast<uint32_t>(d / 4);
   const float d_scaled = static_cast<float>(d) * 16777216.0f;  // exact; its reciprocal is rounded once
-  hipLaunchKernelGGL(init_embedding_kernel, dim3(grid_for(count, t.rows, kTileBlocks)), dim3(256), 0, st,
-                     reinterpret_cast<float4 *>(rows_dev), count, first_row, t, d_scaled, 1.0f / d_scaled,
-                     static_cast<uint32_t>(seed), static_cast<uint32_t>(seed >> 32), level);
+  const uint64_t magic64 = d4 == 1 ? 0 : ~uint64_t{0} / d4 + 1;
+  auto run = [&](auto kernel, int threads, int tile) {
+    hipLaunchKernelGGL(kernel, dim3(grid_for(count * d4, tile, 1 << 30)), dim3(threads), 0, st,
+                       reinterpret_cast<float4 *>(rows_dev), count * d4, first_row, d4, row_magic(d / 4), magic64, d_scaled,
+                       1.0f / d_scaled, static_cast<uint32_t>(seed), static_cast<uint32_t>(seed >> 32), level);
+  };
+  if (count * d * 4 > kStreamInit && d4 >= 2) run(init_embedding_kernel<64, 256, 2>, 64, 256);
+  else run(init_embedding_kernel<256, 1024, 1>, 256, 1024);
   return check_launch("init_embedding_kernel");
 }
 

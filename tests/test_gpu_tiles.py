@@ -1,5 +1,6 @@
 """The tile-walking kernels (initial matrix, projection, divergence check) at the edges of their
-tiles: 2,048 units of 128 bits or 256 rows per tile, 2,048 units per turn of the check."""
+tiles: units of 128 bits, 1,024 or 256 to a tile of the initial matrix, 2,048 (or 256 rows) to one of the
+projection, 2,048 per turn of the check."""
 import numpy as np
 import pytest
 import torch
@@ -76,3 +77,13 @@ def test_check_of_tiles_shared_unevenly():
         M[at, 3] = float("inf")
     M[256 * 2048, 0] = -5.0
     assert G.gosh_matrix_check(M) == (5.0, 4)
+
+
+@pytest.mark.parametrize("d,mb", [(4, 257), (8, 257), (100, 255), (100, 257), (260, 300), (512, 300)])
+def test_initial_rows_of_matrices_around_a_cache(d, mb):
+    """More than 256 MB are written by other tiles (rows of one unit excepted)."""
+    n = mb * (1 << 20) // (4 * d) + 1
+    M = torch.full((n + 1, d), 7.0, device=DEV)
+    G.gosh_init_embedding(M[:n], 0x1234567890ABCDEF, 3)
+    assert (M[n] == 7.0).all()
+    assert np.array_equal(M[:n].cpu().numpy(), O.init_embedding(n, d, 0x1234567890ABCDEF, 3))
