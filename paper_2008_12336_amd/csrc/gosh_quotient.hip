@@ -6,7 +6,7 @@
 // one pass over the entries writes the cluster of each neighbour there.  What is left is to
 // sort each coarse row ("segment") by itself and to merge equal entries.  Three ways, by the
 // length S of the segment:
-//   S <= 1,024          one wavefront, bitonic in registers
+//   S <= 1,024          one wavefront or, up to 32, a part of one, bitonic in registers
 //   S <= bitmap_from()  one workgroup, the same
 //   longer              no comparisons: a bitmap in LDS with a bit per possible neighbour, 2^18
 //                       ("piece") at a time, whose set bits are the merged row in order
@@ -53,10 +53,10 @@ using gosh::row_of_entry;
 constexpr int kGatherRows = 1024;          // rows of a tile that are looked up in LDS,
 constexpr int kTileRows = 4096;            // among at most so many
 constexpr int64_t kNarrowFrom = 1 << 19;   // vertices whose map no L2 holds beside the streams
-// Longest segments that are sorted in the registers of a wavefront, 1, 2, 4, 8 or 16 per lane, and
-// in those of a workgroup, 8 or 16 per lane.
-constexpr int kSortClasses = 7;
-constexpr int kSortMax[kSortClasses] = {64, 128, 256, 512, 1024, 2048, 4096};
+// Longest segments that are sorted in the registers of a quarter, a half or a whole wavefront, one per lane, of a
+// wavefront, 2, 4, 8 or 16 per lane, and in those of a workgroup, 8 or 16 per lane.
+constexpr int kSortClasses = 9;
+constexpr int kSortMax[kSortClasses] = {16, 32, 64, 128, 256, 512, 1024, 2048, 4096};
 enum : int { kBitmap = kSortClasses, kDense, kRadix, kWays };
 constexpr int kPieceBits = 18, kPieceWords = 1 << (kPieceBits - 5);
 constexpr int kStripBits = 14, kStripsPerPiece = 1 << (kPieceBits - kStripBits);
@@ -430,6 +430,83 @@ __device__ __forceinline__ unsigned long long sum_upto_lane(unsigned long long x
 __device__ __forceinline__ int32_t lanes_below(unsigned long long mask) {
   return static_cast<int32_t>(__builtin_amdgcn_mbcnt_hi(static_cast<uint32_t>(mask >> 32),
                                                         __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(mask), 0)));
+}
+
+// Inclusive sum over the lanes of the group of LANES below and this one.
+template <int LANES, typename WT>
+__device__ __forceinline__ WT sum_upto_in_group(WT x, int gl) {
+  if constexpr (LANES == 64) {
+    return sum_upto_lane(x, gl);
+  } else if constexpr (sizeof(WT) == 4) {
+    auto step = [&](auto move) { x += static_cast<uint32_t>(move(static_cast<int>(x))); };
+    step([](int v) { return __builtin_amdgcn_update_dpp(0, v, 0x111, 0xF, 0xF, false); });  // row_shr 1
+    step([](int v) { return __builtin_amdgcn_update_dpp(0, v, 0x112, 0xF, 0xF, false); });
+    step([](int v) { return __builtin_amdgcn_update_dpp(0, v, 0x114, 0xF, 0xF, false); });
+    step([](int v) { return __builtin_amdgcn_update_dpp(0, v, 0x118, 0xF, 0xF, false); });
+    if constexpr (LANES == 32) step([](int v) { return __builtin_amdgcn_update_dpp(0, v, 0x142, 0xA, 0xF, false); });
+    return x;
+  } else {
+#pragma unroll
+    for (int step = 1; step < LANES; step <<= 1) {
+      const WT y = __shfl_up(x, step, LANES);
+      if (gl >= step) x += y;
+    }
+    return x;
+  }
+}
+
+// Segments of at most LANES entries, one per lane, 64 / LANES segments side by side in a wavefront; otherwise as
+// merge_sorted_kernel below.  Bound by the chain of reads before the entries, so several share it: 1.5 M segments
+// of up to 64 entries, 12 on average, one to a wavefront, took 438 us, now 190.
+template <int LANES, typename WT, bool WEIGHTED>
+__global__ __launch_bounds__(256) void merge_small_kernel(const int64_t *__restrict__ segment,
+                                                          const int32_t *__restrict__ list, int64_t count, Packing pack,
+                                                          uint32_t *__restrict__ entries, WT *__restrict__ weight,
+                                                          int64_t *__restrict__ length) {
+  constexpr int kPerWave = 64 / LANES;
+  __shared__ WT extra[256];
+  const int lane = threadIdx.x & 63, gl = lane & (LANES - 1), group = lane & ~(LANES - 1);
+  const uint64_t of_group = ~uint64_t{0} >> (64 - LANES) << group, below = (uint64_t{1} << lane) - 1;
+  const int64_t wave = (blockIdx.x * 256LL + threadIdx.x) >> 6, waves = (gridDim.x * 256LL) >> 6;
+  for (int64_t base = wave * kPerWave; base < count; base += waves * kPerWave) {
+    const int64_t i = base + lane / LANES;
+    const bool live = i < count;
+    const int32_t a = list[live ? i : base];
+    const int64_t lo = segment[a];
+    const int size = live ? static_cast<int>(segment[a + 1] - lo) : 0;
+    const uint32_t word = gl < size ? entries[lo + gl] : kInside;
+    uint32_t key[1] = {word};
+    key_blocks<2, LANES, LANES>(key, static_cast<uint32_t>(gl));
+    const uint32_t column = WEIGHTED ? pack.column(key[0]) : key[0];
+    const uint32_t before = __shfl_up(column, 1, LANES);
+    const bool starts = gl == 0 || column != before, head = starts && column != kInside;
+    const uint64_t changes = __ballot(starts) & of_group & ~below & ~(uint64_t{1} << lane);
+    const uint64_t heads = __ballot(head) & of_group;
+    const int end = changes != 0 ? __builtin_ctzll(changes) : group + LANES;  // lane behind the run
+    WT sum = static_cast<WT>(end - lane);
+    if constexpr (WEIGHTED) {
+      const WT mine = key[0] != kInside ? static_cast<WT>(key[0] & pack.top) : WT(0);
+      const WT upto = sum_upto_in_group<LANES, WT>(mine, gl);
+      sum = __shfl(upto, end - 1, 64) - upto + mine;
+      const bool apart = word != kInside && (word & pack.top) == pack.top;
+      if (__ballot(apart) != 0) {  // what the words left out, to the first lane of its run
+        extra[threadIdx.x] = 0;
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        int to = -1;
+        for (int q = LANES - 1; q >= 0; --q)
+          if (__shfl(column, q, LANES) == pack.column(word)) to = q;
+        if (apart) atomicAdd(&extra[threadIdx.x - gl + to], static_cast<WT>(weight[lo + gl] - pack.top));
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        sum += extra[threadIdx.x];
+      }
+    }
+    if (head) {
+      const int rank = __popcll(heads & below);
+      entries[lo + rank] = pack.entry(column, sum);
+      if (sum >= pack.top) weight[lo + rank] = sum;
+    }
+    if (live && gl == 0) length[a] = __popcll(heads);
+  }
 }
 
 // Segments of at most WAVES * 64 * R entries, WAVES wavefronts each: a bitonic network over the
@@ -1026,13 +1103,15 @@ int quotient(gosh::DeviceCoarsener *dc, const gosh::DeviceLevel &fine, int64_t n
       hipLaunchKernelGGL(kernel, dim3(blocks_for(c.count[cls], teams)), dim3(256), 0, nullptr, segment,
                          list + cls * n_coarse, static_cast<int64_t>(c.count[cls]), pack, entry, weight, length);
   };
-  merge_sorted(merge_sorted_kernel<16, 4, WT, WEIGHTED>, 6, 1);
-  merge_sorted(merge_sorted_kernel<8, 4, WT, WEIGHTED>, 5, 1);
-  merge_sorted(merge_sorted_kernel<16, 1, WT, WEIGHTED>, 4, 4);
-  merge_sorted(merge_sorted_kernel<8, 1, WT, WEIGHTED>, 3, 4);
-  merge_sorted(merge_sorted_kernel<4, 1, WT, WEIGHTED>, 2, 4);
-  merge_sorted(merge_sorted_kernel<2, 1, WT, WEIGHTED>, 1, 4);
-  merge_sorted(merge_sorted_kernel<1, 1, WT, WEIGHTED>, 0, 4);
+  merge_sorted(merge_sorted_kernel<16, 4, WT, WEIGHTED>, 8, 1);
+  merge_sorted(merge_sorted_kernel<8, 4, WT, WEIGHTED>, 7, 1);
+  merge_sorted(merge_sorted_kernel<16, 1, WT, WEIGHTED>, 6, 4);
+  merge_sorted(merge_sorted_kernel<8, 1, WT, WEIGHTED>, 5, 4);
+  merge_sorted(merge_sorted_kernel<4, 1, WT, WEIGHTED>, 4, 4);
+  merge_sorted(merge_sorted_kernel<2, 1, WT, WEIGHTED>, 3, 4);
+  merge_sorted(merge_small_kernel<64, WT, WEIGHTED>, 2, 4);
+  merge_sorted(merge_small_kernel<32, WT, WEIGHTED>, 1, 8);
+  merge_sorted(merge_small_kernel<16, WT, WEIGHTED>, 0, 16);
   if (int rc = gosh::check_launch("merge of the coarse rows")) return rc;
 
   // offsets; the last length is never read
