@@ -356,7 +356,7 @@ int device_level_check(DeviceLevel &out) {
     ~FlagGuard() { block_give(&block, 1); }
   } guard{found_dev};
   GOSH_TRY_HIP(hipMemset(found_dev, 0, sizeof(Found)), "clear check flags");
-  const int off_blocks = std::min(blocks_for(out.n, 256), 4096);
+  const int off_blocks = std::min(blocks_for(out.n, 1024), 512);  // whose maxima are atomics on one word
   if (out.xadj_is64)
     hipLaunchKernelGGL(check_offsets_kernel<int64_t>, dim3(off_blocks), dim3(256), 0, nullptr,
                        static_cast<const int64_t *>(out.xadj), out.n, out.nnz, found_dev);
@@ -549,12 +549,12 @@ int mark_impl(DeviceCoarsener *dc, DeviceLevel &fine, int64_t *n_coarse, bool *d
     while (bits < 32 && (fine.top_degree >> bits) != 0) ++bits;
     const rocprim::counting_iterator<int32_t> ids(0);
     size_t temp_bytes = 0;
-    GOSH_TRY_HIP(rocprim::radix_sort_pairs(nullptr, temp_bytes, keys, keys_sorted, ids, order,
+    GOSH_TRY_HIP(rocprim::radix_sort_pairs<SortConfig>(nullptr, temp_bytes, keys, keys_sorted, ids, order,
                                          static_cast<size_t>(n), 0u, bits, nullptr),
                "degree sort (size query)");
     char *temp = nullptr;
     if (int rc = buf.alloc(&temp, temp_bytes, "sort workspace")) return rc;
-    GOSH_TRY_HIP(rocprim::radix_sort_pairs(temp, temp_bytes, keys, keys_sorted, ids, order,
+    GOSH_TRY_HIP(rocprim::radix_sort_pairs<SortConfig>(temp, temp_bytes, keys, keys_sorted, ids, order,
                                          static_cast<size_t>(n), 0u, bits, nullptr),
                "degree sort");
     buf.release(temp);  // what takes it up again is on the same stream

@@ -131,7 +131,8 @@ __global__ __launch_bounds__(256) void row_lengths_kernel(const OffT *__restrict
 }
 
 // segment[a] = place of the first entry of cluster a (segment[n_coarse] = nnz); tile_row[k] =
-// row that holds entry k * kGatherTile.  pos is the scan of the row lengths.
+// row that holds entry k * kGatherTile, and behind the last tile's the last row with entries (vertices without
+// are clusters of their own, the last ones).  pos is the scan of the row lengths.
 __global__ __launch_bounds__(256) void segments_kernel(const int32_t *__restrict__ cluster,
                                                        const int64_t *__restrict__ pos, int64_t n, int64_t nnz,
                                                        int64_t n_coarse, int64_t *__restrict__ segment,
@@ -143,6 +144,7 @@ __global__ __launch_bounds__(256) void segments_kernel(const int32_t *__restrict
     if (t == n - 1)
       for (int64_t c = a + 1; c <= n_coarse; ++c) segment[c] = nnz;
     for (int64_t k = (lo + kGatherTile - 1) / kGatherTile; k * kGatherTile < hi; ++k) tile_row[k] = static_cast<int32_t>(t);
+    if (lo < hi && hi == nnz) tile_row[(nnz + kGatherTile - 1) / kGatherTile] = static_cast<int32_t>(t);
   }
 }
 
@@ -239,8 +241,8 @@ __global__ __launch_bounds__(256) void gather_kernel(const int32_t *__restrict__
                                                      const OffT *__restrict__ begin,
                                                      const int32_t *__restrict__ cluster,
                                                      const int64_t *__restrict__ pos,
-                                                     const int32_t *__restrict__ tile_row, int64_t n, int64_t nnz,
-                                                     Packing pack, uint32_t *__restrict__ entry,
+                                                     const int32_t *__restrict__ tile_row, int64_t nnz, Packing pack,
+                                                     uint32_t *__restrict__ entry,
                                                      WT *__restrict__ weight, Classes *__restrict__ classes) {
   constexpr int kUnits = 4;
   __shared__ unsigned int block_top;
@@ -253,8 +255,7 @@ __global__ __launch_bounds__(256) void gather_kernel(const int32_t *__restrict__
   const int64_t tiles = (nnz + kGatherTile - 1) / kGatherTile;
   for (int64_t tile = blockIdx.x; tile < tiles; tile += gridDim.x) {
     const int64_t e0 = tile * kGatherTile, e1 = std::min(e0 + kGatherTile, nnz);
-    const int32_t row0 = tile_row[tile];
-    const int32_t row1 = tile + 1 < tiles ? tile_row[tile + 1] : static_cast<int32_t>(n - 1);
+    const int32_t row0 = tile_row[tile], row1 = tile_row[tile + 1];
     const bool in_lds = lay_out_rows(rows, pos, row0, row1, e0, e1, [&](int32_t k, int32_t r, int64_t p) {
       from[k] = static_cast<int64_t>(begin[r]) - p;
       owner[k] = cluster[r];
@@ -890,12 +891,14 @@ __global__ __launch_bounds__(1024) void dense_strips_kernel(const int32_t *__res
   }
 }
 
-// tile_row[k] = coarse row that holds entry k * kGatherTile of the coarse graph.
+// tile_row[k] = coarse row that holds entry k * kGatherTile of the coarse graph, and behind the last tile's the last
+// row with entries.
 __global__ __launch_bounds__(256) void coarse_tiles_kernel(const int64_t *__restrict__ xadj_out, int64_t n_coarse,
-                                                           int32_t *__restrict__ tile_row) {
+                                                           int64_t nnz_coarse, int32_t *__restrict__ tile_row) {
   for (int64_t a = blockIdx.x * 256LL + threadIdx.x; a < n_coarse; a += gridDim.x * 256LL) {
     const int64_t lo = xadj_out[a], hi = xadj_out[a + 1];
     for (int64_t k = (lo + kGatherTile - 1) / kGatherTile; k * kGatherTile < hi; ++k) tile_row[k] = static_cast<int32_t>(a);
+    if (lo < hi && hi == nnz_coarse) tile_row[(nnz_coarse + kGatherTile - 1) / kGatherTile] = static_cast<int32_t>(a);
   }
 }
 
@@ -905,7 +908,7 @@ __global__ __launch_bounds__(256) void coarse_tiles_kernel(const int64_t *__rest
 template <typename WT>
 __global__ __launch_bounds__(256) void copy_merged_kernel(const int64_t *__restrict__ segment, int64_t sorted_to,
                                                           int64_t radix_from, const int32_t *__restrict__ tile_row,
-                                                          int64_t n_coarse, int64_t nnz_coarse,
+                                                          int64_t nnz_coarse,
                                                           const uint32_t *__restrict__ entry, Packing pack,
                                                           const WT *__restrict__ weight,
                                                           const int64_t *__restrict__ xadj_out,
@@ -923,8 +926,7 @@ __global__ __launch_bounds__(256) void copy_merged_kernel(const int64_t *__restr
   const int64_t tiles = (nnz_coarse + kGatherTile - 1) / kGatherTile;
   for (int64_t tile = blockIdx.x; tile < tiles; tile += gridDim.x) {
     const int64_t e0 = tile * kGatherTile, e1 = std::min(e0 + kGatherTile, nnz_coarse);
-    const int32_t row0 = tile_row[tile];
-    const int32_t row1 = tile + 1 < tiles ? tile_row[tile + 1] : static_cast<int32_t>(n_coarse - 1);
+    const int32_t row0 = tile_row[tile], row1 = tile_row[tile + 1];
     const bool in_lds = lay_out_rows(rows, xadj_out, row0, row1, e0, e1,
                                      [&](int32_t k, int32_t a, int64_t p) { from[k] = start_of(a, p); });
     for (int step = 0; step < kGatherTile / 256; step += kUnits) {
@@ -1007,11 +1009,11 @@ int quotient(gosh::DeviceCoarsener *dc, const gosh::DeviceLevel &fine, int64_t n
     if (int rc = buf.alloc(&lengths, static_cast<size_t>(n) + 1, "row lengths")) return rc;
     if (int rc = buf.alloc(&pos, static_cast<size_t>(n) + 1, "row places")) return rc;
     if (int rc = buf.alloc(&begin, static_cast<size_t>(n), "row starts")) return rc;
-    if (int rc = buf.alloc(&tile_row, static_cast<size_t>(tiles), "tile rows")) return rc;
+    if (int rc = buf.alloc(&tile_row, static_cast<size_t>(tiles) + 1, "tile rows")) return rc;
     unsigned bits = 1;
     while (bits < 31 && (n_coarse >> bits) != 0) ++bits;
     size_t sort_bytes = 0, scan_bytes = 0;
-    GOSH_TRY_HIP(rocprim::radix_sort_pairs(nullptr, sort_bytes, fine.map, cluster, ids, order, static_cast<size_t>(n),
+    GOSH_TRY_HIP(rocprim::radix_sort_pairs<gosh::SortConfig>(nullptr, sort_bytes, fine.map, cluster, ids, order, static_cast<size_t>(n),
                                            0u, bits, nullptr),
                  "cluster sort (size query)");
     GOSH_TRY_HIP(rocprim::exclusive_scan(nullptr, scan_bytes, lengths, pos, int64_t(0), static_cast<size_t>(n) + 1,
@@ -1019,7 +1021,7 @@ int quotient(gosh::DeviceCoarsener *dc, const gosh::DeviceLevel &fine, int64_t n
                  "row scan (size query)");
     char *temp = nullptr;
     if (int rc = buf.alloc(&temp, std::max(sort_bytes, scan_bytes), "sort workspace")) return rc;
-    GOSH_TRY_HIP(rocprim::radix_sort_pairs(temp, sort_bytes, fine.map, cluster, ids, order, static_cast<size_t>(n), 0u,
+    GOSH_TRY_HIP(rocprim::radix_sort_pairs<gosh::SortConfig>(temp, sort_bytes, fine.map, cluster, ids, order, static_cast<size_t>(n), 0u,
                                            bits, nullptr),
                  "cluster sort");
     hipLaunchKernelGGL(row_lengths_kernel<OffT>, dim3(flat_blocks), dim3(256), 0, nullptr, xadj, order, n, lengths, begin);
@@ -1036,8 +1038,7 @@ int quotient(gosh::DeviceCoarsener *dc, const gosh::DeviceLevel &fine, int64_t n
       table = ClusterTable{reinterpret_cast<const char *>(narrow), 3, 0xFFFFFFu};
     }
     hipLaunchKernelGGL((gather_kernel<OffT, WT, WEIGHTED>), dim3(blocks_for(nnz, kGatherTile)), dim3(256), 0, nullptr,
-                       fine.adj, static_cast<const WT *>(fine.mult), table, begin, cluster, pos, tile_row, n, nnz, pack, entry, weight,
-                       classes);
+                       fine.adj, static_cast<const WT *>(fine.mult), table, begin, cluster, pos, tile_row, nnz, pack, entry, weight, classes);
     if (int rc = gosh::check_launch("gather_kernel")) return rc;
     for (void *p : {static_cast<void *>(order), static_cast<void *>(cluster),
                     static_cast<void *>(lengths), static_cast<void *>(begin), static_cast<void *>(pos), static_cast<void *>(tile_row),
@@ -1126,7 +1127,7 @@ int quotient(gosh::DeviceCoarsener *dc, const gosh::DeviceLevel &fine, int64_t n
                                          rocprim::plus<int64_t>(), nullptr),
                  "offset scan");
   }
-  hipLaunchKernelGGL(coarse_shape_kernel, dim3(std::min(blocks_for(n_coarse, 256), 1024)), dim3(256), 0, nullptr, length,
+  hipLaunchKernelGGL(coarse_shape_kernel, dim3(std::min(blocks_for(n_coarse, 2048), 256)), dim3(256), 0, nullptr, length,
                      xadj_out, n_coarse, classes);
   if (int rc = gosh::check_launch("coarse_shape_kernel")) return rc;
   Classes shape{};
@@ -1149,11 +1150,11 @@ int quotient(gosh::DeviceCoarsener *dc, const gosh::DeviceLevel &fine, int64_t n
   if (coarse.nnz > 0) {
     const int64_t tiles = (coarse.nnz + kGatherTile - 1) / kGatherTile;
     int32_t *tile_row = nullptr;
-    if (int rc = buf.alloc(&tile_row, static_cast<size_t>(tiles), "tile rows")) return rc;
+    if (int rc = buf.alloc(&tile_row, static_cast<size_t>(tiles) + 1, "tile rows")) return rc;
     hipLaunchKernelGGL(coarse_tiles_kernel, dim3(blocks_for(n_coarse, 256)), dim3(256), 0, nullptr, xadj_out, n_coarse,
-                       tile_row);
+                       coarse.nnz, tile_row);
     hipLaunchKernelGGL(copy_merged_kernel<WT>, dim3(blocks_for(coarse.nnz, kGatherTile)), dim3(256), 0, nullptr, segment,
-                       bitmap_from(c.columns), radix_merged ? radix_above(c.columns, ways) : INT64_MAX, tile_row, n_coarse,
+                       bitmap_from(c.columns), radix_merged ? radix_above(c.columns, ways) : INT64_MAX, tile_row,
                        coarse.nnz, entry, pack, weight, xadj_out, coarse.adj, mult_out);
   }
   if (int rc = gosh::check_launch("coarse rows")) return rc;
