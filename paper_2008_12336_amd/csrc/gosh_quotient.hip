@@ -344,24 +344,17 @@ __global__ __launch_bounds__(1024) void classify_segments_kernel(const int64_t *
 template <int MASK>
 __device__ __forceinline__ uint32_t lane_xor(uint32_t x) {
   const int v = static_cast<int>(x);
-  if constexpr (MASK == 1) return __builtin_amdgcn_update_dpp(0, v, 0xB1, 0xF, 0xF, false);       // quad_perm [1,0,3,2]
-  else if constexpr (MASK == 2) return __builtin_amdgcn_update_dpp(0, v, 0x4E, 0xF, 0xF, false);  // quad_perm [2,3,0,1]
+  if constexpr (MASK == 1) return __builtin_amdgcn_mov_dpp(v, 0xB1, 0xF, 0xF, true);       // quad_perm [1,0,3,2]
+  else if constexpr (MASK == 2) return __builtin_amdgcn_mov_dpp(v, 0x4E, 0xF, 0xF, true);  // quad_perm [2,3,0,1]
   else if constexpr (MASK == 4) return __builtin_amdgcn_ds_swizzle(v, 0x101F);
-  else if constexpr (MASK == 8) return __builtin_amdgcn_update_dpp(0, v, 0x128, 0xF, 0xF, false);  // row_ror 8
+  else if constexpr (MASK == 8) return __builtin_amdgcn_mov_dpp(v, 0x128, 0xF, 0xF, true);  // row_ror 8
   else if constexpr (MASK == 16) return __builtin_amdgcn_ds_swizzle(v, 0x401F);
   else return __shfl_xor(v, 32, 64);
-}
-template <int MASK>
-__device__ __forceinline__ unsigned long long lane_xor(unsigned long long x) {
-  return static_cast<unsigned long long>(lane_xor<MASK>(static_cast<uint32_t>(x >> 32))) << 32 |
-         lane_xor<MASK>(static_cast<uint32_t>(x));
 }
 
 // Median of three: the smaller of a and b beside 0, the larger beside ~0.
 __device__ __forceinline__ uint32_t med3(uint32_t a, uint32_t b, uint32_t c) {
-  uint32_t m;
-  asm("v_med3_u32 %0, %1, %2, %3" : "=v"(m) : "v"(a), "v"(b), "v"(c));
-  return m;
+  return max(min(a, b), min(max(a, b), c));  // one instruction, which the compiler may place (as asm 10 to 20 % slower)
 }
 
 // ~0 where the bit is set in `index`, else 0.
@@ -379,8 +372,11 @@ __device__ __forceinline__ void key_stage(uint32_t (&key)[R], uint32_t index) {
   if constexpr (J >= R) {
     uint32_t larger = spread<J / R>(index);
     if constexpr (K < TOP) larger ^= spread<K / R>(index);
+    uint32_t other[R];
 #pragma unroll
-    for (int r = 0; r < R; ++r) key[r] = med3(key[r], lane_xor<J / R>(key[r]), larger);
+    for (int r = 0; r < R; ++r) other[r] = lane_xor<J / R>(key[r]);
+#pragma unroll
+    for (int r = 0; r < R; ++r) key[r] = med3(key[r], other[r], larger);
   } else {
 #pragma unroll
     for (int r = 0; r < R; ++r)
@@ -515,7 +511,7 @@ __global__ __launch_bounds__(256) void merge_small_kernel(const int64_t *__restr
 // then equal columns are merged in place.  The sum of a run is the difference of the running
 // sums at its end and at the end of the run before.  An entry is sorted as the word it is held in, weight
 // included; what a word does not hold of a weight is added to the sum of its column afterwards.  Bound by the network's
-// instructions: 74 M entries in segments of up to 2,048 take 0.38 ms, 65 M weighted ones 0.37 (0.66 and 1.00 with
+// instructions: 74 M entries in segments of up to 2,048 take 0.36 ms, 65 M weighted ones 0.30 (0.66 and 1.00 with
 // columns and weights sorted as pairs by compare and select).
 template <int R, int WAVES, typename WT, bool WEIGHTED>
 __global__ __launch_bounds__(256) void merge_sorted_kernel(const int64_t *__restrict__ segment,
