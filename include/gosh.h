@@ -190,8 +190,8 @@ int gosh_coarsen(const gosh_csr *g0_host, int64_t threshold, double min_shrink,
  * equal degrees) is marked on the host instead.  Device memory per entry of G_0 while running:
  * scratch of about 8 bytes (12 from 2^32 entries on), 16 more per entry of coarse rows that
  * are counted or 24 (32) of those that are radix-sorted -- both only rows of thousands of
- * entries, and only if there is room -- and up to 12 for G_1; afterwards 12 bytes per entry of
- * all levels but the first, and the scratch blocks, which stay
+ * entries, and only if there is room -- and up to 8 (12) for G_1, besides some 70 per vertex; afterwards
+ * 8 (12) bytes per entry of all levels but the first, and the scratch blocks, which stay
  * with the hierarchy until gosh_hierarchy_trim_scratch, gosh_hierarchy_release_device or
  * gosh_hierarchy_free, because freeing them at once would slow the host link down for whatever
  * follows (the driver clears freed memory in the background).  For the same reason

@@ -22,7 +22,7 @@
 //
 // Sorted distinct entries with summed multiplicities are unique, so the arrays are those of
 // the sequential algorithm.  128 M entries of a 4 M-vertex R-MAT graph and the 117 M weighted ones of its
-// second level take 5.2 ms together (7.5 with weights in arrays of their own, pairs sorted by compare and select, and
+// second level take 5.0 ms together (7.5 with weights in arrays of their own, pairs sorted by compare and select, and
 // a wavefront per segment to copy; 19.4 as a radix sort of 64-bit (row, column) keys of all entries).
 // 8 (wide sums: 12) bytes of scratch per entry, 16 more per entry of a row that is counted and 24 (wide sums: 32)
 // of one that is sorted by radix.  A third of it is the gather.
@@ -64,7 +64,7 @@ constexpr int64_t kSlice = 1 << 16;  // entries of a counted segment that one wo
 // Columns up to which long segments are worth ranking (each reads its entries once per piece and
 // pays for a bitmap per piece, twice) and counting (once per strip).  Beyond, all are sorted, which does
 // not grow with the columns.  Rebuilds, ms, with ranks / counters, by sort, with all entries sorted as
-// keys (the radix sort this file replaced):
+// keys (the radix sort this file replaced), all of them before entries were one word:
 //   2.0 M columns, 288 M entries 19.0, 16.7, 21.7     2.4 M, 535 M 27.9, 29.9, 38.8
 //   3.4 M, 308 M 27.8, 22.3, 22.7                     21.8 M, 536 M 67.7, 35.0, 42.7
 //   8.4 M, 3.6 G 336, 202, 264

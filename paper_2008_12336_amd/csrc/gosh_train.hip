@@ -400,7 +400,7 @@ __global__ __launch_bounds__(256) void matrix_check_kernel(const Float4 *__restr
 }
 
 __global__ void clear_checks_kernel(gosh::CheckResult *out, int count) {
-  for (int i = threadIdx.x; i < count; i += blockDim.x) out[i] = gosh::CheckResult{0, 0, 0};
+  for (int i = threadIdx.x; i < count; i += 64) out[i] = gosh::CheckResult{0, 0, 0};
 }
 
 int grid_for(int64_t items, int per_block, int max_blocks) {
