@@ -629,7 +629,8 @@ int init_rows(float *rows_dev, int64_t first_row, int64_t count, int32_t d, uint
   const float d_scaled = static_cast<float>(d) * 16777216.0f;  // exact; its reciprocal is rounded once
   const uint64_t magic64 = d4 == 1 ? 0 : ~uint64_t{0} / d4 + 1;
   auto run = [&](auto kernel, int threads, int tile) {
-    hipLaunchKernelGGL(kernel, dim3(grid_for(count * d4, tile, 1 << 30)), dim3(threads), 0, st,
+    const int most = (1 << 30) / threads;  // a grid counts its threads in 32 bits
+    hipLaunchKernelGGL(kernel, dim3(grid_for(count * d4, tile, most)), dim3(threads), 0, st,
                        reinterpret_cast<float4 *>(rows_dev), count * d4, first_row, d4, row_magic(d / 4), magic64, d_scaled,
                        1.0f / d_scaled, static_cast<uint32_t>(seed), static_cast<uint32_t>(seed >> 32), level);
   };
