@@ -160,6 +160,19 @@ def test_device_rejects_malformed_graphs():
     h.free()
 
 
+def test_entries_are_not_read_where_the_offsets_are_wrong():
+    """A device-resident graph whose nnz is more than its offsets end at, by far more than the memory there is:
+    refused for its offsets, before anybody looks at so many entries."""
+    xadj, adj = csr_from_pairs(300, [(i, i + 1) for i in range(299)])
+    xd, ad = torch.from_numpy(xadj).to("cuda:0"), torch.from_numpy(adj).to("cuda:0")
+    for nnz in (adj.size + 1, 1 << 36):
+        g, out = G.csr_view(300, xd, ad), C.c_void_p()
+        g.nnz = nnz
+        assert G.lib().gosh_coarsen_device(C.byref(g), 10, 1.0, 64, 0, C.byref(out)) == -1
+        assert "xadj" in G.gosh_last_error() and not out.value
+    G.gosh_coarsen_device(300, xd, ad, threshold=10).free()
+
+
 @pytest.mark.parametrize("offsets64", [False, True])
 def test_device_resident_input_graph(offsets64):
     """G_0 given as device tensors is used in place (no upload), gives the same hierarchy,
