@@ -380,8 +380,8 @@ typedef struct {
                         GOSH_FLAG_EDGE_EPOCHS */
   double upload_ms;  /* host -> device copy of G_i (wall clock) */
   double train_ms;   /* the e_i epoch launches (HIP events on the stream) */
-  double project_ms; /* map upload + projection to level i-1 (wall clock, or HIP events where the call
-                        does not wait for it; 0 at level 0) */
+  double project_ms; /* projection to level i-1 (0 at level 0): HIP events around it where both matrices and
+                        the map are on the device, else wall clock with the copies of map and rows */
   int32_t parts_K;   /* 0: trained with the epoch kernel; K > 0: trained with the part-pair
                         rotation on K parts (train_ms is then the wall time of that call) */
   float max_abs;     /* largest finite |entry| of M_i after training (levels trained by the

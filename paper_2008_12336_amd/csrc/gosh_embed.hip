@@ -405,10 +405,14 @@ class MultilevelRun {
   int project(int i, gosh_level_stats &ls) {
     const gosh_csr &g = G[static_cast<size_t>(i)];
     const size_t mat_bytes = static_cast<size_t>(g.n) * d * 4;
-    auto t0 = std::chrono::steady_clock::now();
     const int64_t n_fine = G[static_cast<size_t>(i - 1)].n;
     const gosh::DeviceLevel *fine_dev = resident(i - 1);
     const int32_t *map_dev_resident = fine_dev ? fine_dev->map : nullptr;
+    // Where everything is on the device two events time the projection.  The other ways wait for their copies:
+    // their clock starts when what was queued before has ended.
+    const bool by_events = cur_dev != nullptr && map_dev_resident != nullptr && fits(i - 1);
+    if (timed && !by_events) GOSH_TRY_HIP(hipStreamSynchronize(st), "train level");
+    const auto t0 = std::chrono::steady_clock::now();
     const int32_t *map_host = nullptr;
     if (map_dev_resident == nullptr) {
       int64_t len = 0;
@@ -455,11 +459,12 @@ class MultilevelRun {
       // without a budget that the matrices of two levels must keep to, small ones may stay until the end
       queued = pl.budget == 0 && map_dev_resident != nullptr && dev_own.pooled() &&
                retired_bytes + dev_own.bytes <= kPooledBytes;
-      if (queued)
+      if (by_events)
         if (int rc = mark(i, kProject)) return rc;
       if (int rc = gosh_project(src_dev, g.n, map_on_device, n_fine, d, next_dev, st)) return rc;
-      if (queued) {
+      if (by_events)
         if (int rc = mark(i, kProjected)) return rc;
+      if (queued) {
         retired_bytes += dev_own.bytes;
         retired.push_back(dev_own.release());
       } else {
@@ -510,7 +515,7 @@ class MultilevelRun {
         GOSH_TRY_HIP(hipStreamSynchronize(st), "upload projected level");
       }
     }
-    if (!queued) ls.project_ms = ms_since(t0);
+    if (!by_events) ls.project_ms = ms_since(t0);
     dev_own.swap(dev_next);
     dev_next.reset();
     host_own.swap(host_next);

@@ -1,5 +1,6 @@
 """The multilevel driver (Alg. 2) on the GPU against the oracle's V-cycle."""
 import sys
+import time
 
 import numpy as np
 import pytest
@@ -230,3 +231,40 @@ def test_levels_queued_and_waited_for_are_the_same():
         assert all(s["max_abs"] > 0 and s["nonfinite"] == 0 for s in stats)
         assert abs(stats[0]["max_abs"] - np.abs(runs[-1]).max()) == 0
     assert np.array_equal(runs[0], runs[1]) and np.array_equal(runs[0], runs[2])
+
+
+def three_levels(n=120_000, m=240_000):
+    c = graphgen.to_csr(n, graphgen.er_gnm(n, m, 3))
+    h = G.gosh_coarsen_device(n, c.xadj, c.adj, threshold=1000, min_shrink=0.9, max_levels=3)
+    assert h.levels == 3
+    return n, h
+
+
+@pytest.mark.parametrize("matrix,d,budget", [
+    ("device", 512, 0),         # level 1 (100 MB) is waited for, the small level above it is not
+    ("device", 512, 1 << 30),   # every level is waited for
+    ("device", 64, 0),          # no level is waited for
+    ("host", 512, 1 << 30),     # levels on the device, delivered to the host
+    ("host", 512, 200 << 20),   # level 0 on the host: projected slice by slice
+    ("host", 512, 60 << 20),    # levels 1 and 0 on the host: the latter's rows are gathered there
+    ("released", 512, 0)])      # graphs and maps are uploaded level by level
+def test_times_of_a_run_do_not_overlap(matrix, d, budget):
+    """What a level's projection takes is not what its training takes: all times of all levels fit the call."""
+    n, h = three_levels()
+    assert h.shape(1)[0] * 512 * 4 > 64 << 20 > h.shape(2)[0] * 512 * 4
+    if matrix == "released":
+        h.release_device()
+    M0 = torch.zeros(n, d, dtype=torch.float32, device="cpu" if matrix == "host" else DEV, pin_memory=matrix == "host")
+    embed = G.gosh_embed_host if matrix == "host" else G.gosh_embed
+    for _ in range(2):  # the first call also gets its memory
+        torch.cuda.synchronize()
+        t0 = time.perf_counter()
+        stats = embed(h, M0, 3, 600, 0.9, 0.01, 3, device_budget_bytes=budget)
+        wall = (time.perf_counter() - t0) * 1e3
+    say(f"[times] {matrix} d={d} budget={budget}: " + ", ".join(
+        f"L{s['level']} {s['upload_ms']:.2f}+{s['train_ms']:.2f}+{s['project_ms']:.2f}" for s in stats) + f" of {wall:.2f}")
+    assert all(s["train_ms"] > 0 for s in stats) and all(s["project_ms"] > 0 for s in stats[1:])
+    assert stats[0]["project_ms"] == 0
+    assert sum(s["upload_ms"] + s["train_ms"] + s["project_ms"] for s in stats) <= wall
+    assert matrix == "host" or all(s["project_ms"] < 0.1 * s["train_ms"] for s in stats[1:])
+    h.free()
