@@ -400,8 +400,8 @@ typedef struct {
  * matrix of level 0 exceed it, the call is refused with GOSH_EBUDGET (use gosh_embed_host,
  * which keeps such levels on the host).  stats: NULL or host array of D entries, filled per level.
  * Blocking: returns after the last level finished; intermediate device buffers are
- * allocated and freed inside the call (those of up to 64 MB are blocks that the library keeps for the next
- * call, as it does those of freed hierarchies; gosh_hierarchy_trim_scratch returns them).  Every level is checked after its training
+ * allocated and freed inside the call (without a budget those of up to 64 MB are blocks that the library keeps
+ * for the next call, as it does those of freed hierarchies; gosh_hierarchy_trim_scratch returns them).  Every level is checked after its training
  * (gosh_matrix_check: one more read of the matrix): if any level ends with non-finite
  * entries the run is still completed, stats are filled, and GOSH_EDIVERGED is returned. */
 int gosh_embed(const gosh_hierarchy *h, int32_t d, int32_t k_neg, int64_t epochs, double p,

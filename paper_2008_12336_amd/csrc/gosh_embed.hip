@@ -23,20 +23,24 @@
 namespace {
 
 // Small buffers are blocks of gosh_device_pool.cpp: a level of a few thousand vertices trains for less time
-// than hipMalloc and hipFree of its matrix take.
+// than hipMalloc and hipFree of its matrix take.  Not where the caller gave a budget: a block may be larger than
+// what is asked for, and what is kept after use is memory beside the budget of whatever follows.
 constexpr size_t kPooledBytes = size_t(64) << 20;
 
 struct DeviceBuffer {
+  const bool may_keep;
+  bool kept = false;  // a block of the store
   void *ptr = nullptr;
   size_t bytes = 0;
-  DeviceBuffer() = default;
+  explicit DeviceBuffer(bool may_keep) : may_keep(may_keep) {}
   DeviceBuffer(const DeviceBuffer &) = delete;
   DeviceBuffer &operator=(const DeviceBuffer &) = delete;
   ~DeviceBuffer() { reset(); }
   int alloc(size_t want, const char *what) {
     reset();
     if (want == 0) want = 16;
-    if (want <= kPooledBytes) {
+    kept = may_keep && want <= kPooledBytes;
+    if (kept) {
       ptr = gosh::block_take(want);
     } else if (gosh::device_malloc(&ptr, want) != hipSuccess) {
       (void)hipGetLastError();
@@ -46,7 +50,7 @@ struct DeviceBuffer {
     bytes = want;
     return GOSH_OK;
   }
-  bool pooled() const { return ptr != nullptr && bytes <= kPooledBytes; }
+  bool pooled() const { return ptr != nullptr && kept; }
   void *release() { return std::exchange(ptr, nullptr); }
   void reset() {
     if (pooled()) gosh::block_give(&ptr, 1);  // which waits for the device
@@ -56,6 +60,7 @@ struct DeviceBuffer {
   void swap(DeviceBuffer &o) {
     std::swap(ptr, o.ptr);
     std::swap(bytes, o.bytes);
+    std::swap(kept, o.kept);
   }
 };
 
@@ -212,6 +217,7 @@ class MultilevelRun {
   const int32_t d;
   float *const M0_dev, *const M0_host;
   const hipStream_t st;
+  const bool keeps = pl.budget == 0;  // small buffers are kept blocks
   std::vector<gosh_csr> G;
   int current_device = -1;
   std::vector<gosh_level_stats> levels;
@@ -221,7 +227,8 @@ class MultilevelRun {
   std::vector<hipEvent_t> marks;
   std::vector<int> marked;
   bool timed = false;
-  DeviceBuffer dev_own, dev_next, checks;
+  DeviceBuffer dev_own{keeps}, dev_next{keeps};
+  DeviceBuffer checks{true};  // a few bytes beside any budget
   std::vector<void *> retired;  // small matrices of earlier levels
   size_t retired_bytes = 0;
   PinnedBuffer host_own, host_next;
@@ -299,7 +306,7 @@ class MultilevelRun {
     }
     int64_t rows = 0;
     if (int rc = chunk_rows(pl.budget, 0, d, g.n, &rows)) return rc;
-    DeviceBuffer slice;
+    DeviceBuffer slice{keeps};
     if (int rc = slice.alloc(static_cast<size_t>(rows) * d * 4, "initialisation slice")) return rc;
     for (int64_t lo = 0; lo < g.n; lo += rows) {
       const int64_t cnt = std::min(rows, g.n - lo);
@@ -342,7 +349,7 @@ class MultilevelRun {
   // TrainInGPU
   int train_on_device(int i, gosh_level_stats &ls) {
     auto t0 = std::chrono::steady_clock::now();
-    DeviceBuffer xadj_dev, adj_dev;
+    DeviceBuffer xadj_dev{keeps}, adj_dev{keeps};
     gosh_csr dev{};
     if (int rc = graph_on_device(i, xadj_dev, adj_dev, &dev)) return rc;
     ls.upload_ms = ms_since(t0);
@@ -365,7 +372,7 @@ class MultilevelRun {
   // parts trained at half the rate of Alg. 3, in 2 parts a fifth slower).
   int train_in_place(int i, gosh_level_stats &ls, int32_t K) {
     auto t0 = std::chrono::steady_clock::now();
-    DeviceBuffer xadj_dev, adj_dev;
+    DeviceBuffer xadj_dev{keeps}, adj_dev{keeps};
     gosh_csr dev{};
     if (int rc = graph_on_device(i, xadj_dev, adj_dev, &dev)) return rc;
     ls.upload_ms = ms_since(t0);
@@ -437,7 +444,7 @@ class MultilevelRun {
     // still visit the device for the projection, which needs no graph.
     const float *src_dev = cur_dev;
     bool queued = false;
-    DeviceBuffer src_visit;
+    DeviceBuffer src_visit{keeps};
     if (src_dev == nullptr && next_host != nullptr) {
       const size_t smallest_slice = 64 * (static_cast<size_t>(d) * 4 + 4);
       if (pl.budget == 0 || mat_bytes + smallest_slice <= pl.budget) {
@@ -448,7 +455,7 @@ class MultilevelRun {
       }
     }
     if (src_dev && next_dev) {
-      DeviceBuffer map_dev;
+      DeviceBuffer map_dev{keeps};
       const int32_t *map_on_device = map_dev_resident;
       if (map_on_device == nullptr) {
         if (int rc = map_dev.alloc(static_cast<size_t>(n_fine) * 4, "map")) return rc;
@@ -456,9 +463,8 @@ class MultilevelRun {
                  "copy map");
         map_on_device = static_cast<const int32_t *>(map_dev.ptr);
       }
-      // without a budget that the matrices of two levels must keep to, small ones may stay until the end
-      queued = pl.budget == 0 && map_dev_resident != nullptr && dev_own.pooled() &&
-               retired_bytes + dev_own.bytes <= kPooledBytes;
+      // kept blocks may stay until the end
+      queued = map_dev_resident != nullptr && dev_own.pooled() && retired_bytes + dev_own.bytes <= kPooledBytes;
       if (by_events)
         if (int rc = mark(i, kProject)) return rc;
       if (int rc = gosh_project(src_dev, g.n, map_on_device, n_fine, d, next_dev, st)) return rc;
@@ -474,7 +480,7 @@ class MultilevelRun {
       // project slice by slice through a device staging buffer
       int64_t rows = 0;
       if (int rc = chunk_rows(pl.budget, mat_bytes, d, n_fine, &rows)) return rc;
-      DeviceBuffer slice, map_dev;
+      DeviceBuffer slice{keeps}, map_dev{keeps};
       if (int rc = slice.alloc(static_cast<size_t>(rows) * d * 4, "projection slice")) return rc;
       if (map_dev_resident == nullptr)
         if (int rc = map_dev.alloc(static_cast<size_t>(rows) * 4, "map slice")) return rc;

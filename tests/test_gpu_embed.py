@@ -268,3 +268,18 @@ def test_times_of_a_run_do_not_overlap(matrix, d, budget):
     assert sum(s["upload_ms"] + s["train_ms"] + s["project_ms"] for s in stats) <= wall
     assert matrix == "host" or all(s["project_ms"] < 0.1 * s["train_ms"] for s in stats[1:])
     h.free()
+
+
+@pytest.mark.parametrize("matrix", ["device", "host"])
+def test_a_run_under_a_budget_keeps_no_device_memory(matrix):
+    n, h = three_levels()
+    M0 = torch.zeros(n, 128, dtype=torch.float32, device=DEV if matrix == "device" else "cpu", pin_memory=matrix == "host")
+    embed, budget = (G.gosh_embed, 1 << 30) if matrix == "device" else (G.gosh_embed_host, 50 << 20)
+    run = lambda: embed(h, M0, 3, 30, 0.9, 0.01, 3, device_budget_bytes=budget)
+    run()
+    h.trim_scratch()
+    free_bytes = torch.cuda.mem_get_info()[0]
+    stats = run()
+    assert (matrix == "host") == (stats[0]["parts_K"] > 0)
+    assert free_bytes - torch.cuda.mem_get_info()[0] <= 4 << 20
+    h.free()
