@@ -398,7 +398,8 @@ typedef struct {
  * h: hierarchy (host).  M0_dev: device matrix n_0 x d, receives the embedding of G_0.
  * flags: as for gosh_train_epoch, plus GOSH_FLAG_EDGE_EPOCHS and GOSH_FLAG_PAIR_LEVELS.  device_budget_bytes: if non-zero and the graph plus
  * matrix of level 0 exceed it, the call is refused with GOSH_EBUDGET (use gosh_embed_host,
- * which keeps such levels on the host).  stats: NULL or host array of D entries, filled per level.
+ * which keeps such levels on the host).  stats: NULL or host array of D entries; a call that
+ * fails at some level has filled those of the levels that it finished before.
  * Blocking: returns after the last level finished; intermediate device buffers are
  * allocated and freed inside the call (without a budget those of up to 64 MB are blocks that the library keeps
  * for the next call, as it does those of freed hierarchies; gosh_hierarchy_trim_scratch returns them).  Every level is checked after its training

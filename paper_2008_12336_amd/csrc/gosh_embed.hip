@@ -161,6 +161,7 @@ class MultilevelRun {
                         "level 0 needs %zu bytes on the device, budget is %llu: use gosh_embed_host",
                         level_bytes(G[0], d), (unsigned long long)pl.budget);
     levels.assign(static_cast<size_t>(D), gosh_level_stats{});
+    found.assign(static_cast<size_t>(D), gosh::CheckResult{});
     marks.assign(static_cast<size_t>(D) * kMarks, nullptr);
     marked.assign(static_cast<size_t>(D), 0);
     retired.reserve(static_cast<size_t>(D));
@@ -169,32 +170,14 @@ class MultilevelRun {
     if (int rc = gosh::matrix_check_clear(check_of(0), st, D)) return rc;
 
     for (int i = D - 1; i >= 0; --i) {
-      const gosh_csr &g = G[static_cast<size_t>(i)];
-      gosh_level_stats &ls = levels[static_cast<size_t>(i)];
-      ls.level = i;
-      ls.n = g.n;
-      ls.nnz = g.nnz;
-      ls.epochs = e_i[static_cast<size_t>(i)];
-      if (pl.edge_epochs) {
-        // an epoch of the experiments samples |E_i| sources; one pass of Alg. 3 samples |V_i|
-        const int64_t edges = g.nnz / 2;
-        ls.epochs *= std::max<int64_t>(1, (edges + g.n - 1) / g.n);
-      }
-      if (i == D - 1)
-        if (int rc = init_coarsest(i)) return rc;
-      const int32_t in_place_parts = (cur_dev && pl.pair_levels)
-                                         ? gosh_pair_level_parts(ls.epochs, g.n, gosh::tuning().pair_level_min_n, kPairLevelB)
-                                         : 0;
-      if (int rc = !cur_dev         ? train_by_rotation(i, ls)
-                   : in_place_parts ? train_in_place(i, ls, in_place_parts)
-                                    : train_on_device(i, ls))
-        return rc;
-      if (cur_dev)
-        if (int rc = gosh::matrix_check_add(cur_dev, g.n * d, check_of(i), st)) return rc;
-      if (i > 0)
-        if (int rc = project(i, ls)) return rc;
+      const int rc = run_level(i, e_i[static_cast<size_t>(i)]);
+      if (rc == GOSH_OK) continue;
+      // what is known of the levels before stays known; the failure is the one to report
+      if (stats && i + 1 < D && read_checks_and_times(i + 1) == hipSuccess)
+        std::copy(levels.begin() + i + 1, levels.end(), stats + i + 1);
+      return rc;
     }
-    if (int rc = read_checks_and_times()) return rc;
+    GOSH_TRY_HIP(read_checks_and_times(0), "train levels");
     if (stats) std::copy(levels.begin(), levels.end(), stats);
     for (int i = D - 1; i >= 0 && diverged_level < 0; --i)
       if (levels[static_cast<size_t>(i)].nonfinite > 0) diverged_level = i;
@@ -221,6 +204,7 @@ class MultilevelRun {
   std::vector<gosh_csr> G;
   int current_device = -1;
   std::vector<gosh_level_stats> levels;
+  std::vector<gosh::CheckResult> found;  // read from `checks`
   // Of every level: training begins, has ended, projection begins, has ended; `marked` tells which pairs are
   // recorded.  Only where somebody wants the times.
   enum { kBegin, kTrained, kProject, kProjected, kMarks };
@@ -246,33 +230,57 @@ class MultilevelRun {
     return GOSH_OK;
   }
 
-  // Waits for the run.
-  int read_checks_and_times() {
-    std::vector<gosh::CheckResult> found(levels.size());
-    GOSH_TRY_HIP(hipMemcpyAsync(found.data(), checks.ptr, found.size() * sizeof(gosh::CheckResult),
-                                hipMemcpyDeviceToHost, st),
-                 "read matrix checks");
-    GOSH_TRY_HIP(hipStreamSynchronize(st), "train levels");
-    for (size_t i = 0; i < levels.size(); ++i) {
+  // Level i: trained, checked, projected.
+  int run_level(int i, int64_t epochs) {
+    const gosh_csr &g = G[static_cast<size_t>(i)];
+    gosh_level_stats &ls = levels[static_cast<size_t>(i)];
+    ls.level = i;
+    ls.n = g.n;
+    ls.nnz = g.nnz;
+    ls.epochs = epochs;
+    if (pl.edge_epochs) {
+      // an epoch of the experiments samples |E_i| sources; one pass of Alg. 3 samples |V_i|
+      const int64_t edges = g.nnz / 2;
+      ls.epochs *= std::max<int64_t>(1, (edges + g.n - 1) / g.n);
+    }
+    if (static_cast<size_t>(i) + 1 == levels.size())
+      if (int rc = init_coarsest(i)) return rc;
+    const int32_t in_place_parts = (cur_dev && pl.pair_levels)
+                                       ? gosh_pair_level_parts(ls.epochs, g.n, gosh::tuning().pair_level_min_n, kPairLevelB)
+                                       : 0;
+    if (int rc = !cur_dev         ? train_by_rotation(i, ls)
+                 : in_place_parts ? train_in_place(i, ls, in_place_parts)
+                                  : train_on_device(i, ls))
+      return rc;
+    if (cur_dev)
+      if (int rc = gosh::matrix_check_add(cur_dev, g.n * d, check_of(i), st)) return rc;
+    return i > 0 ? project(i, ls) : GOSH_OK;
+  }
+
+  // Waits for the run; the levels from `finest` on have been trained.
+  hipError_t read_checks_and_times(int finest) {
+    hipError_t e = hipMemcpyAsync(found.data(), checks.ptr, found.size() * sizeof(gosh::CheckResult),
+                                  hipMemcpyDeviceToHost, st);
+    if (e == hipSuccess) e = hipStreamSynchronize(st);
+    for (size_t i = static_cast<size_t>(finest); i < levels.size() && e == hipSuccess; ++i) {
       gosh_level_stats &ls = levels[i];
       float top = 0.f;
       std::memcpy(&top, &found[i].max_bits, sizeof(top));
       ls.max_abs = std::max(ls.max_abs, top);  // a level trained by the rotation has its own, and nothing here
       ls.nonfinite += static_cast<int64_t>(found[i].nonfinite);
-      auto between = [&](int from, int to, double &ms) -> int {
+      auto between = [&](int from, int to, double &ms) {
         const int both = 1 << from | 1 << to;
-        if ((marked[i] & both) != both) return GOSH_OK;
+        if (e != hipSuccess || (marked[i] & both) != both) return;
         float x = 0.f;
-        GOSH_TRY_HIP(hipEventElapsedTime(&x, marks[i * kMarks + static_cast<size_t>(from)],
-                                         marks[i * kMarks + static_cast<size_t>(to)]),
-                     "hipEventElapsedTime");
+        e = hipEventElapsedTime(&x, marks[i * kMarks + static_cast<size_t>(from)],
+                                marks[i * kMarks + static_cast<size_t>(to)]);
         ms = x;
-        return GOSH_OK;
       };
-      if (int rc = between(kBegin, kTrained, ls.train_ms)) return rc;
-      if (int rc = between(kProject, kProjected, ls.project_ms)) return rc;
+      between(kBegin, kTrained, ls.train_ms);
+      between(kProject, kProjected, ls.project_ms);
     }
-    return GOSH_OK;
+    if (e != hipSuccess) (void)hipGetLastError();
+    return e;
   }
 
   // The device-resident arrays of level i, if the hierarchy holds them on this device.

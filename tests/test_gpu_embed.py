@@ -283,3 +283,24 @@ def test_a_run_under_a_budget_keeps_no_device_memory(matrix):
     assert (matrix == "host") == (stats[0]["parts_K"] > 0)
     assert free_bytes - torch.cuda.mem_get_info()[0] <= 4 << 20
     h.free()
+
+
+def test_statistics_of_a_run_that_fails_at_its_last_level():
+    """Forty stars: level 1 is trained on the device, level 0 needs a rotation whose pools the budget does not
+    hold.  What is known of level 1 is there, level 0's entry is as it was."""
+    hubs, per_hub, d = 40, 20, 16
+    ids = torch.arange(hubs)
+    edges = torch.stack((torch.cat((ids, ids.repeat_interleave(per_hub))),
+                         torch.cat(((ids + 1) % hubs, hubs + torch.arange(hubs * per_hub)))), 1)
+    n = hubs * (per_hub + 1)
+    c = graphgen.to_csr(n, torch.unique(edges.sort(1).values, dim=0))
+    h = G.gosh_coarsen_device(n, c.xadj, c.adj, threshold=hubs, min_shrink=0.9)
+    assert h.levels == 2 and h.shape(1)[0] == hubs
+    M0 = torch.zeros(n, d, dtype=torch.float32).pin_memory()
+    stats = (G.binding.gosh_level_stats * 2)()
+    stats[0].n = -7
+    rc = G.lib().gosh_embed_host(h.handle, d, 3, 8, 0.5, 0.05, 9, 0, 20_000, 3, 64, 64, M0.data_ptr(), stats, None)
+    assert rc == -4 and "budget" in G.gosh_last_error()
+    assert stats[1].level == 1 and stats[1].n == hubs and stats[1].epochs > 0
+    assert stats[1].train_ms > 0 and stats[1].project_ms > 0 and stats[1].max_abs > 0 and stats[1].nonfinite == 0
+    assert stats[0].n == -7
