@@ -8,8 +8,9 @@
 // Kept blocks are bounded per device (kept_limit), handed out to any thread, given back when an
 // allocation of this library fails, when more would be kept than the bound (oldest first), and
 // on request (block_trim, behind gosh_hierarchy_trim_scratch and _release_device, which also gives
-// back the kept staging).  A block is kept only after the device has finished what was queued on it, so whoever gets it next may
-// use it on any stream.
+// back the kept staging).  A block is kept only after everything that uses it has finished -- the device is waited for,
+// unless the caller has waited for its own streams -- so whoever gets it next may use it on any stream.  Nobody
+// waits for a device with the mutex held, except where an allocation fails or on request.
 #include <hip/hip_runtime.h>
 
 #include <deque>
@@ -137,49 +138,67 @@ void *block_take(size_t bytes) {
 
 namespace {
 
-// One block of block_give; `idle` is the device known to have finished its queues.
-void give_one(Store &s, void *p, int *idle) {
+// One block of block_give, on a device whose queues have finished if `idle`.  What is freed waits for its device:
+// without the mutex.
+void give_one(Store &s, void *p, bool known_idle, uint64_t idle_devices) {
+  std::unique_lock<std::mutex> lock(s.mutex);
   const auto known = s.handed_out.find(p);
   if (known == s.handed_out.end()) {
+    lock.unlock();
     (void)hipFree(p);
     return;
   }
   const Block b = known->second;
   s.handed_out.erase(known);
-  if (*idle != b.device && hipSetDevice(b.device) == hipSuccess && hipDeviceSynchronize() == hipSuccess) *idle = b.device;
-  const size_t limit = *idle == b.device ? kept_limit(s, b.device) : 0;
+  const bool idle = known_idle || (b.device >= 0 && b.device < kMaxDevices && (idle_devices >> b.device & 1) != 0);
+  (void)hipSetDevice(b.device);  // whose memory the limit is a part of; block_give restores the current one
+  const size_t limit = idle ? kept_limit(s, b.device) : 0;
+  while (b.bytes <= limit && kept_bytes(s, b.device) + b.bytes > limit) {
+    auto oldest = s.kept.begin();
+    while (oldest->device != b.device) ++oldest;  // there is one: the block alone is within the limit
+    void *const old = oldest->p;
+    s.kept.erase(oldest);
+    lock.unlock();
+    (void)hipFree(old);
+    lock.lock();
+  }
   if (b.bytes <= limit) {
-    size_t have = kept_bytes(s, b.device);
-    for (size_t k = 0; k < s.kept.size() && have + b.bytes > limit;) {
-      if (s.kept[k].device != b.device) {
-        ++k;
-        continue;
-      }
-      have -= s.kept[k].bytes;
-      (void)hipFree(s.kept[k].p);
-      s.kept.erase(s.kept.begin() + static_cast<std::ptrdiff_t>(k));
-    }
     try {
       s.kept.push_back(b);
       return;
     } catch (const std::bad_alloc &) {
     }
   }
+  lock.unlock();
   (void)hipFree(p);
 }
 
 }  // namespace
 
-void block_give(void *const *blocks, size_t count) {
+void block_give(void *const *blocks, size_t count, bool idle) {
   bool any = false;
   for (size_t i = 0; i < count; ++i) any |= blocks[i] != nullptr;
   if (!any) return;
   Store &s = store();
-  std::lock_guard<std::mutex> lock(s.mutex);
-  int current = -1, idle = -1;
+  int current = -1;
   if (hipGetDevice(&current) != hipSuccess) current = -1;
+  uint64_t devices = 0, finished = 0;  // of the blocks; those whose queues have finished
+  static_assert(kMaxDevices == 64, "a bit per device");
+  if (!idle) {
+    {
+      std::lock_guard<std::mutex> lock(s.mutex);
+      for (size_t i = 0; i < count; ++i) {
+        const auto known = blocks[i] != nullptr ? s.handed_out.find(blocks[i]) : s.handed_out.end();
+        if (known != s.handed_out.end() && known->second.device >= 0 && known->second.device < kMaxDevices)
+          devices |= uint64_t{1} << known->second.device;
+      }
+    }
+    for (int device = 0; device < kMaxDevices; ++device)
+      if ((devices >> device & 1) != 0 && hipSetDevice(device) == hipSuccess && hipDeviceSynchronize() == hipSuccess)
+        finished |= uint64_t{1} << device;
+  }
   for (size_t i = 0; i < count; ++i)
-    if (blocks[i] != nullptr) give_one(s, blocks[i], &idle);
+    if (blocks[i] != nullptr) give_one(s, blocks[i], idle, finished);
   if (current >= 0) (void)hipSetDevice(current);
 }
 

@@ -12,10 +12,11 @@
 namespace gosh {
 
 // Device blocks that outlive a hierarchy (gosh_device_pool.cpp): at least `bytes` on the
-// current device, or null; given back on any thread, whatever device is current (never throws);
+// current device, or null; given back on any thread, whatever device is current (never throws),
+// after a wait for their devices unless they are `idle`: nothing that is queued uses them any more;
 // what is kept of them on the current device, freed, and the staging below.
 void *block_take(size_t bytes);
-void block_give(void *const *blocks, size_t count);
+void block_give(void *const *blocks, size_t count, bool idle = false);
 void block_trim();
 
 // Pinned staging for copies between pageable memory and the device: two slots of

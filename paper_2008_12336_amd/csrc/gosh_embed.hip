@@ -141,8 +141,8 @@ class MultilevelRun {
     DeviceBuffer *const own[3] = {&dev_own, &dev_next, &checks};
     for (int i = 0; i < 3; ++i)
       if (own[i]->pooled()) held[i] = own[i]->release();
-    gosh::block_give(held, 3);
-    gosh::block_give(retired.data(), retired.size());
+    gosh::block_give(held, 3, finished);
+    gosh::block_give(retired.data(), retired.size(), finished);
   }
 
   int run(int64_t epochs, double p, gosh_level_stats *stats) {
@@ -187,6 +187,7 @@ class MultilevelRun {
                "download M_0");
       GOSH_TRY_HIP(hipStreamSynchronize(st), "download M_0");
     }
+    finished = true;
     if (diverged_level >= 0)
       return gosh::fail(GOSH_EDIVERGED, "training diverged: the matrix of level %d holds non-finite values",
                         diverged_level);
@@ -217,6 +218,7 @@ class MultilevelRun {
   size_t retired_bytes = 0;
   PinnedBuffer host_own, host_next;
   float *cur_dev = nullptr, *cur_host = nullptr;
+  bool finished = false;    // the stream has been waited for, and nothing else uses the buffers
   int diverged_level = -1;  // first (coarsest) level whose training left non-finite entries
 
   gosh::CheckResult *check_of(int i) const { return static_cast<gosh::CheckResult *>(checks.ptr) + i; }

@@ -1,10 +1,13 @@
 // The store of device blocks (gosh_device_pool) against a runtime that only keeps books: what is
 // handed out, kept and given back, with every host allocation failing in turn.  No GPU.
+#include <atomic>
+#include <chrono>
 #include <cstdio>
 #include <cstdlib>
 #include <map>
 #include <new>
 #include <set>
+#include <thread>
 
 #include "gosh_device_pool.h"
 
@@ -13,6 +16,8 @@ std::map<void *, size_t> device_blocks;
 std::set<void *> pinned;
 size_t device_total = size_t(64) << 20;
 int64_t allocations_left = -1;  // -1: no limit
+int waits = 0;         // for the device
+bool probing = false;  // waits and frees, which wait too, must leave the store to other threads
 
 [[noreturn]] void broken(const char *what) {
   std::printf("broken: %s\n", what);
@@ -37,6 +42,7 @@ struct Unlimited {
   Unlimited() { allocations_left = -1; }
   ~Unlimited() { allocations_left = left; }
 };
+void leave_the_store_to_others();
 }  // namespace
 
 void *operator new(size_t bytes) {
@@ -57,6 +63,7 @@ hipError_t hipMalloc(void **p, size_t bytes) {
 }
 hipError_t hipFree(void *p) {
   Unlimited u;
+  leave_the_store_to_others();
   if (p != nullptr && device_blocks.erase(p) != 1) broken("freed what is no block");
   std::free(p);
   return hipSuccess;
@@ -80,7 +87,11 @@ hipError_t hipMemGetInfo(size_t *free_bytes, size_t *total) {
 }
 hipError_t hipGetDevice(int *d) { return *d = 0, hipSuccess; }
 hipError_t hipSetDevice(int) { return hipSuccess; }
-hipError_t hipDeviceSynchronize() { return hipSuccess; }
+hipError_t hipDeviceSynchronize() {
+  ++waits;
+  leave_the_store_to_others();
+  return hipSuccess;
+}
 hipError_t hipGetLastError() { return hipSuccess; }
 }
 
@@ -93,6 +104,23 @@ int64_t &seam(Seam) {
 }  // namespace gosh
 
 namespace {
+void leave_the_store_to_others() {
+  if (!probing) return;
+  Unlimited u;
+  std::atomic<bool> done{false};
+  std::thread other([&] {
+    (void)gosh::block_kept();
+    done = true;
+  });
+  for (int i = 0; i < 2000 && !done; ++i) std::this_thread::sleep_for(std::chrono::milliseconds(1));
+  if (!done) {
+    std::printf("broken: the store is held while the device is waited for\n");
+    std::fflush(stdout);
+    std::_Exit(1);
+  }
+  other.join();
+}
+
 // A run like that of a hierarchy: scratch of several levels, arrays that outlive it, all given back.
 void run() {
   gosh::Pool pool;
@@ -140,6 +168,18 @@ int main() {
     gosh::block_trim();
     expect(device_blocks.empty(), "blocks are lost after a failed host allocation");
   }
+  // three blocks, two of which are kept: nobody waits with the store held, and not at all for idle blocks
+  void *blocks[3];
+  for (void *&b : blocks) b = gosh::block_take(400 << 10);
+  probing = true;
+  waits = 0;
+  gosh::block_give(blocks, 3);
+  expect(waits == 1 && device_blocks.size() == 2, "one wait for the blocks of a device, the oldest goes");
+  probing = false;
+  for (int i = 0; i < 2; ++i) blocks[i] = gosh::block_take(400 << 10);
+  gosh::block_give(blocks, 2, true);
+  expect(waits == 1 && device_blocks.size() == 2 && gosh::block_kept() == device_used(), "idle blocks are kept without a wait");
+  gosh::block_trim();
   std::printf("pool ok\n");
   return 0;
 }

@@ -304,3 +304,46 @@ def test_statistics_of_a_run_that_fails_at_its_last_level():
     assert stats[1].level == 1 and stats[1].n == hubs and stats[1].epochs > 0
     assert stats[1].train_ms > 0 and stats[1].project_ms > 0 and stats[1].max_abs > 0 and stats[1].nonfinite == 0
     assert stats[0].n == -7
+
+
+def streams_side_by_side():
+    """A stream that is kept busy for some tenths of a second by `busy`, and one whose work does not wait for it."""
+    block = torch.zeros(1 << 30, device=DEV)
+
+    def busy(stream):
+        with torch.cuda.stream(stream):
+            for _ in range(150):
+                block.mul_(1.0)
+            return stream.record_event()
+
+    first = torch.cuda.Stream()
+    small = torch.zeros(64, device=DEV)
+    torch.cuda.synchronize()
+    for _ in range(8):  # streams share a few hardware queues
+        second = torch.cuda.Stream()
+        ends = busy(first)
+        with torch.cuda.stream(second):
+            small.add_(1.0)
+        second.synchronize()
+        apart = not ends.query()
+        torch.cuda.synchronize()
+        if apart:
+            return first, second, busy
+    pytest.skip("no two streams run side by side here")
+
+
+@pytest.mark.parametrize("levels", [1, 2])
+def test_a_run_does_not_wait_for_other_streams(levels):
+    n, d = 20_000, 32
+    c = graphgen.to_csr(n, graphgen.er_gnm(n, 60_000, 3)).to(DEV)
+    h = G.gosh_coarsen_device(n, c.xadj, c.adj, threshold=100, min_shrink=0.9, max_levels=levels)
+    assert h.levels == levels
+    M0 = torch.zeros(n, d, dtype=torch.float32, device=DEV)
+    first, second, busy = streams_side_by_side()
+    G.gosh_embed(h, M0, 3, 8, 0.5, 0.05, 9, stream=second)
+    torch.cuda.synchronize()
+    ends = busy(first)
+    G.gosh_embed(h, M0, 3, 8, 0.5, 0.05, 9, stream=second)
+    assert not ends.query()
+    torch.cuda.synchronize()
+    h.free()
