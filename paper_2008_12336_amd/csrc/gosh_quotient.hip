@@ -1029,9 +1029,9 @@ int quotient(gosh::DeviceCoarsener *dc, const gosh::DeviceLevel &fine, int64_t n
     hipLaunchKernelGGL(segments_kernel, dim3(flat_blocks), dim3(256), 0, nullptr, cluster, pos, n, nnz, n_coarse,
                        segment, tile_row);
     ClusterTable table{reinterpret_cast<const char *>(fine.map), 4, ~0u};
-    if (n >= kNarrowFrom && n_coarse <= (int64_t{1} << 24)) {
-      uint32_t *narrow = nullptr;  // and a word for what is read past the last vertex
-      if (int rc = buf.alloc(&narrow, static_cast<size_t>((n + 3) / 4) * 3 + 1, "narrow map")) return rc;
+    uint32_t *narrow = nullptr;  // and a word for what is read past the last vertex; without room the map itself does
+    if (n >= kNarrowFrom && n_coarse <= (int64_t{1} << 24) && !gosh::denied(gosh::kDenyNarrow) &&
+        buf.alloc(&narrow, static_cast<size_t>((n + 3) / 4) * 3 + 1, "narrow map") == GOSH_OK) {
       hipLaunchKernelGGL(narrow_map_kernel, dim3(blocks_for((n + 3) / 4, 256)), dim3(256), 0, nullptr, fine.map, n, narrow);
       table = ClusterTable{reinterpret_cast<const char *>(narrow), 3, 0xFFFFFFu};
     }
@@ -1040,7 +1040,7 @@ int quotient(gosh::DeviceCoarsener *dc, const gosh::DeviceLevel &fine, int64_t n
     if (int rc = gosh::check_launch("gather_kernel")) return rc;
     for (void *p : {static_cast<void *>(order), static_cast<void *>(cluster),
                     static_cast<void *>(lengths), static_cast<void *>(begin), static_cast<void *>(pos), static_cast<void *>(tile_row),
-                    static_cast<void *>(temp)})
+                    static_cast<void *>(temp), static_cast<void *>(narrow)})
       buf.release(p);  // what takes them up again is on the same stream
   }
   const int64_t radix_from = gosh::seam(gosh::kSeamRadixFrom);

@@ -11,7 +11,8 @@ import graphgen
 import paper_2008_12336_amd as G
 from oracle import gosh_oracle as O
 from tests.test_coarsen import _ring_lattice, assert_same_hierarchy
-from tests.util import SEAM_WEIGHT_BITS, DENY_RADIX, DENY_STAGING, DENY_TABLE, SEAM_DENY, SEAM_RADIX_FROM, SEAM_WIDE_SUMS, csr_from_pairs, seam
+from tests.util import (DENY_NARROW, DENY_RADIX, DENY_STAGING, DENY_TABLE, SEAM_DENY, SEAM_RADIX_FROM, SEAM_WEIGHT_BITS,
+                        SEAM_WIDE_SUMS, csr_from_pairs, seam)
 
 pytestmark = pytest.mark.gpu
 
@@ -445,6 +446,12 @@ def test_weights_beside_and_apart_from_their_columns(lengths, weight_bits, wide_
 def test_rows_of_a_tile(n, linked, m):
     """The tables by which the gather and the copy of the merged rows find the row of an entry."""
     assert_equals_host(graphgen.to_csr(n, graphgen.er_gnm(linked, m, 3)), threshold=10, min_shrink=1.0)
+
+
+def test_clusters_are_looked_up_in_the_map_where_there_is_no_room_for_a_narrower_one():
+    n = (1 << 19) + 5
+    with seam(SEAM_DENY, DENY_NARROW):
+        assert_equals_host(graphgen.to_csr(n, graphgen.er_gnm(n, 900_000, 3)), threshold=10, min_shrink=1.0, max_levels=3)
 
 
 def test_more_undecided_vertices_than_a_wavefront_holds():
