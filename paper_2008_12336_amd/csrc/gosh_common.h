@@ -46,7 +46,8 @@ enum Seam : int32_t {
   kSeamWeightBits, // if not 0: at most so many bits of a weight lie beside its column while rows are merged
   kSeams
 };
-enum Deny : int64_t { kDenyLocks = 1, kDenyStaging = 2, kDenyRadix = 4, kDenyTable = 8, kDenyNarrow = 16 };
+enum Deny : int64_t { kDenyLocks = 1, kDenyStaging = 2, kDenyRadix = 4, kDenyTable = 8, kDenyNarrow = 16,
+                      kDenyRetired = 32 };
 int64_t &seam(Seam which);
 inline bool denied(Deny what) { return (seam(kSeamDeny) & what) != 0; }
 

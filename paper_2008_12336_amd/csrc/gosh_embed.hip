@@ -232,6 +232,24 @@ class MultilevelRun {
     return GOSH_OK;
   }
 
+  // The stream has been waited for.
+  void give_retired() {
+    gosh::block_give(retired.data(), retired.size(), true);
+    retired.clear();
+    retired_bytes = 0;
+  }
+
+  // Memory for the next matrix.  Where there is none, those that are kept until the end go first.
+  int next_matrix(size_t bytes) {
+    const char *const what = "finer embedding";
+    if (retired.empty()) return dev_next.alloc(bytes, what);
+    const int rc = gosh::denied(gosh::kDenyRetired) ? GOSH_ENOMEM : dev_next.alloc(bytes, what);
+    if (rc != GOSH_ENOMEM) return rc;
+    GOSH_TRY_HIP(hipStreamSynchronize(st), "train levels");
+    give_retired();
+    return dev_next.alloc(bytes, what);
+  }
+
   // Level i: trained, checked, projected.
   int run_level(int i, int64_t epochs) {
     const gosh_csr &g = G[static_cast<size_t>(i)];
@@ -387,6 +405,7 @@ class MultilevelRun {
     if (int rc = graph_on_device(i, xadj_dev, adj_dev, &dev)) return rc;
     ls.upload_ms = ms_since(t0);
     GOSH_TRY_HIP(hipStreamSynchronize(st), "before the rotation");
+    give_retired();  // its pools may need the memory
     gosh_parts_stats ps{};
     const int rc = gosh_train_parts(&dev, cur_dev, d, pl.k_neg, ls.epochs, pl.lr0, pl.seed, static_cast<uint32_t>(i),
                                     0, pl.P_gpu, 1, kPairLevelB, K, pl.parts_flags, &ps);
@@ -440,7 +459,7 @@ class MultilevelRun {
     if (fits(i - 1)) {
       if (i - 1 == 0 && M0_dev) next_dev = M0_dev;
       else {
-        if (int rc = dev_next.alloc(fine_bytes, "finer embedding")) return rc;
+        if (int rc = next_matrix(fine_bytes)) return rc;
         next_dev = static_cast<float *>(dev_next.ptr);
       }
     } else {

@@ -10,7 +10,7 @@ import graphgen
 import paper_2008_12336_amd as G
 from oracle import gosh_oracle as O
 from tests.linkpred import aucroc, make_eval_sets
-from tests.util import rel_err
+from tests.util import DENY_RETIRED, SEAM_DENY, rel_err, seam
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
@@ -217,20 +217,22 @@ def test_pair_levels_vcycle_matches_the_oracle(host_matrix, small_pair_levels):
 
 def test_levels_queued_and_waited_for_are_the_same():
     """Without a budget the levels of a run follow one another on the stream and small matrices stay until its
-    end; under a budget each is waited for.  Two runs in a row take up each other's buffers."""
+    end, unless there is no room for the next one beside them; under a budget each is waited for.  Two runs in a row
+    take up each other's buffers."""
     n, d, k, epochs = 20_003, 36, 3, 14
     c = graphgen.to_csr(n, graphgen.chung_lu(n, 90_000, 3))
     h = G.gosh_coarsen_device(n, c.xadj, c.adj, threshold=100, min_shrink=0.9)
     assert h.levels >= 4
     runs = []
-    for budget in (0, 1 << 30, 0):
+    for budget, deny in ((0, 0), (1 << 30, 0), (0, 0), (0, DENY_RETIRED)):
         M0 = torch.zeros(n, d, dtype=torch.float32, device=DEV)
-        stats = G.gosh_embed(h, M0, k, epochs, 0.3, 0.05, 3, flags=G.GOSH_FLAG_SEQUENTIAL, device_budget_bytes=budget)
+        with seam(SEAM_DENY, deny):
+            stats = G.gosh_embed(h, M0, k, epochs, 0.3, 0.05, 3, flags=G.GOSH_FLAG_SEQUENTIAL, device_budget_bytes=budget)
         runs.append(M0.cpu().numpy())
         assert all(s["train_ms"] > 0 for s in stats) and all(s["project_ms"] > 0 for s in stats[1:])
         assert all(s["max_abs"] > 0 and s["nonfinite"] == 0 for s in stats)
         assert abs(stats[0]["max_abs"] - np.abs(runs[-1]).max()) == 0
-    assert np.array_equal(runs[0], runs[1]) and np.array_equal(runs[0], runs[2])
+    assert all(np.array_equal(runs[0], run) for run in runs[1:])
 
 
 def three_levels(n=120_000, m=240_000):

@@ -107,7 +107,7 @@ def conditioned_bar(sensitivity):
 # Seams of the library for its own tests (gosh_common.h), of the calling thread.
 (SEAM_HOT_MODE, SEAM_DENY, SEAM_RADIX_FROM, SEAM_WIDE_SUMS, SEAM_LOCK_TRIES, SEAM_LOCKS_HELD,
  SEAM_SWAPS, SEAM_WEIGHT_BITS) = range(8)
-DENY_LOCKS, DENY_STAGING, DENY_RADIX, DENY_TABLE, DENY_NARROW = 1, 2, 4, 8, 16
+DENY_LOCKS, DENY_STAGING, DENY_RADIX, DENY_TABLE, DENY_NARROW, DENY_RETIRED = (1 << i for i in range(6))
 HOT_NONE, HOT_BITMAP, HOT_ALL, HOT_LOCKED = range(4)
 
 
