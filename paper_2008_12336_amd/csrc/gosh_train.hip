@@ -364,10 +364,13 @@ __global__ __launch_bounds__(256) void row_probe_kernel(float4 *__restrict__ M, 
 // first, and it adds its maximum only if that is above what it reads there.  The tiles are
 // taken from the end of the matrix: what was written last is still in the memory-side cache.
 // The loads are non-temporal (2.1 GB: 364 -> 325 us).  2.1 GB took 554 us with one atomic per
-// wavefront of 8,192 workgroups.  A workgroup takes four tiles where that leaves 256 of them: 67 MB in 2,048
-// workgroups, whose atomics all come at once, took 40 us, now 13.
+// wavefront of 8,192 workgroups.  A workgroup takes four tiles where that leaves 256 of them, and more in large
+// matrices: beyond two on a CU the atomics of all, which come at once, cost more than the further loads in flight
+// bring.  us of a whole gosh_matrix_check of matrices read before, with 2,048 workgroups / a quarter of the tiles, up to
+// 2,048 / the same up to 512: 64 MB 60 / 40 / 40, 128 MB 65 / 54 / 48, 200 MB 64 / 68 / 57, 256 MB 75 / 75 / 65,
+// 400 MB 90 / 91 / 86, 2 GB 325 / 325 / 321.
 constexpr int kCheckTile = 2048;  // float4s per workgroup and turn
-constexpr int kCheckBlocks = 2048;
+constexpr int kCheckBlocks = 512;
 __global__ __launch_bounds__(256) void matrix_check_kernel(const Float4 *__restrict__ M, int64_t total4,
                                                            gosh::CheckResult *__restrict__ out) {
   constexpr int kUnits = kCheckTile / 256;

@@ -79,6 +79,20 @@ def test_check_of_tiles_shared_unevenly():
     assert G.gosh_matrix_check(M) == (5.0, 4)
 
 
+@pytest.mark.parametrize("tiles", [2047, 2048, 2053, 4000])
+def test_check_of_tiles_beyond_its_workgroups(tiles):
+    """512 workgroups from 2,048 tiles on."""
+    M = torch.zeros((tiles - 1) * 2048 + 7, 4, device=DEV)
+    M.view(-1)[:: 2048 * 4] = 2.0  # the first float of every tile
+    at = [(tiles - 1) * 2048 + 6, 1536 * 2048, 512 * 2048 - 1, 0]
+    for row in at:
+        M[row, 3] = float("nan")
+    M[1024 * 2048 + 5, 2] = -9.0
+    assert G.gosh_matrix_check(M) == (9.0, len(at))
+    M.fill_(float("inf"))
+    assert G.gosh_matrix_check(M) == (0.0, M.numel())
+
+
 @pytest.mark.parametrize("d,mb", [(4, 257), (8, 257), (100, 255), (100, 257), (260, 300), (512, 300)])
 def test_initial_rows_of_matrices_around_a_cache(d, mb):
     """More than 256 MB are written by other tiles (rows of one unit excepted)."""
