@@ -187,13 +187,14 @@ __device__ __forceinline__ uint32_t xor3(uint32_t a, uint32_t b, uint32_t c) {
 //
 // Bound by the write stream, whose rate depends on how much is being written at a time: a workgroup writes
 // TILE units that begin at a multiple of as many, wherever in a row that is, and ends.  A matrix of more than
-// kStreamInit bytes, which no cache holds, is written 4 KB to a wavefront, others 16 KB to a workgroup.  us, with tiles
-// of whole rows up to 32 KB / 16 KB / 4 KB (both of any rows):
-//   d = 128: 1 MB 3.4 / 2.8 / 2.8   64 MB 12.4 / 12.5 / 14.5   256 MB 38.4 / 37.9 / 41.0   2 GB 377 / 358 / 312
-//   d = 100: 1 MB 3.5 / 2.9 / 2.8   64 MB 13.2 / 12.5 / 13.7   256 MB 39.1 / 37.8 / 42.2   2 GB 394 / 352 / 321
-// (2 GB: 6.9 TB/s now; d = 8 350, 300 of 4 KB, 512 371, 314.)  Its arithmetic alone takes 248 us for 2 GB.  The tables
-// of a wavefront take less than 5 KB of LDS, for 32 to fit a CU: 335 us with 5.2 KB.
-constexpr int64_t kStreamInit = int64_t{256} << 20;
+// kStreamInit bytes, which no cache holds, is written 4 KB to a wavefront, others 16 KB to a workgroup.  Calls one after
+// another on one matrix, us, with tiles of whole rows up to 32 KB / 16 KB / 4 KB (both of any rows):
+//   d = 128: 260 MB 41.2 / 41.5 / 42.5   300 MB 48 / 50 / 50   400 MB 80 / 75 / 66   1 GB 194 / 183 / 162   2.1 GB 382 / 353 / 323
+//   d = 8:   260 MB 59 / 44 / 45         300 MB 61 / 53 / 53   400 MB 76 / 70 / 70   1 GB 170 / 170 / 168   2.1 GB 334 / 337 / 336
+// (2.1 GB: 6.5 TB/s at d = 128, 6.4 where other matrices were written in between.)  Below, 4 KB lose: 64 MB 12.5 / 14.5 in
+// the kernel, 1 MB the same.  Its arithmetic alone takes 248 us for 2.1 GB.  The tables of a wavefront take less than 5 KB
+// of LDS, for 32 to fit a CU: 335 us with 5.2 KB.
+constexpr int64_t kStreamInit = int64_t{320} << 20;
 template <int THREADS, int TILE, int SHORTEST>  // rows of SHORTEST units at least
 __global__ __launch_bounds__(THREADS) void init_embedding_kernel(float4 *__restrict__ M, int64_t units_total,
                                                                  int64_t first_row, uint32_t d4, uint32_t magic,

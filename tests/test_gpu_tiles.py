@@ -93,9 +93,10 @@ def test_check_of_tiles_beyond_its_workgroups(tiles):
     assert G.gosh_matrix_check(M) == (0.0, M.numel())
 
 
-@pytest.mark.parametrize("d,mb", [(4, 257), (8, 257), (100, 255), (100, 257), (260, 300), (512, 300)])
+@pytest.mark.parametrize("d,mb", [(4, 257), (8, 257), (100, 255), (100, 257), (260, 300), (512, 300),
+                                  (4, 321), (8, 321), (100, 319), (100, 321), (260, 340), (512, 340)])
 def test_initial_rows_of_matrices_around_a_cache(d, mb):
-    """More than 256 MB are written by other tiles (rows of one unit excepted)."""
+    """More than 320 MB are written by other tiles (rows of one unit excepted)."""
     n = mb * (1 << 20) // (4 * d) + 1
     M = torch.full((n + 1, d), 7.0, device=DEV)
     G.gosh_init_embedding(M[:n], 0x1234567890ABCDEF, 3)
