@@ -263,9 +263,9 @@ def assert_equals_host(csr, levels=None, **kw):
 @pytest.mark.parametrize("wide_sums", [0, 1])
 @pytest.mark.parametrize("lengths", [range(20, 44), [*range(140, 250, 2), 1024], [2000, 2040, 2100, 9000, 17000, 40000]])
 def test_coarse_rows_of_every_way_of_merging(lengths, wide_sums):
-    """Rows around the lengths at which the rebuild changes its way (64, 128, 256, 512 entries: one
-    to eight per lane of a wavefront; 2,048: a workgroup; then a bitmap; from 32,768 counters),
-    level by level with growing multiplicities, against gosh_coarsen."""
+    """Rows that a wavefront sorts (among few columns those of up to 512 entries, of up to 2,400 among
+    120,000), then bitmaps, from 32,768 on counters, level by level with growing multiplicities, against
+    gosh_coarsen."""
     lengths = list(lengths)
     hubs = max(64, 3 * max(lengths))
     edges = [lengths[a] if a < len(lengths) else 3 for a in range(hubs)]
@@ -431,12 +431,59 @@ def test_marking_with_few_lanes_per_vertex(n, per_vertex):
 @pytest.mark.parametrize("lengths", [[*range(120, 140), *range(1000, 1040, 3)], [2040, 2050, 4090, 4100, 9000, 40000]])
 def test_weights_beside_and_apart_from_their_columns(lengths, weight_bits, wide_sums, radix_from):
     """Multiplicities that fit the bits a column leaves, and such as do not, up to none: the seam takes the
-    bits away that graphs of 2^28 clusters lack.  Rows of the sorting networks around 1,024 and 4,096 entries,
+    bits away that graphs of 2^28 clusters lack.  Rows of the sorting networks (up to 512 entries, and 2,048),
     of the bitmap, the counters and the radix sort."""
     hubs = max(64, 3 * max(lengths))
     edges = [lengths[a] if a < len(lengths) else 3 for a in range(hubs)]
     with seam(SEAM_WIDE_SUMS, wide_sums), seam(SEAM_WEIGHT_BITS, weight_bits), seam(SEAM_RADIX_FROM, radix_from):
         assert_equals_host(hub_graph(hubs, edges, 5), 3, threshold=4, min_shrink=1.0)
+
+
+NETWORKS = [16, 32, 64, 128, 256, 512, 1024, 2048, 4096]  # the longest row of each sorting network
+
+
+@pytest.fixture(scope="module")
+def bordered():
+    """Rows of the lengths around every network's longest, at both levels of a rebuild, without weights and
+    with: 240,000 hubs in a ring, each with a leaf, and vertices tied to some of them, all of which are centres
+    of stars of three in the finest graph.  So many columns leave even rows of 4,096 entries to the networks."""
+    hubs, rng = 240_000, np.random.default_rng(5)
+    wanted = [(level, b + o) for b in NETWORKS for o in (-1, 0, 1) for level in (0, 1)]
+    apart = iter(np.split(rng.permutation(hubs), np.cumsum([w for _, w in wanted])))
+    hub = len(wanted) + np.arange(hubs)
+    n1 = len(wanted) + 2 * hubs
+    ends, twice_ends = [(hub, hub + hubs), (hub, np.roll(hub, 1)), (hub, np.roll(hub, 2))], []
+    for s, (level, w) in enumerate(wanted):
+        twice = max(1, w // 16)  # entries that name a column once more
+        x = w - 3 * twice if level else w - 6 - 3 * twice
+        to, me = hub[next(apart)[:x]], np.full(x, s)
+        ends.append((me, to))
+        if level:  # through a leaf of the coarse level; some entries have a weight of their own
+            leaves = n1 + np.arange(twice)
+            n1 += twice
+            ends += [(me[:twice], leaves), (leaves, to[:twice])]
+        twice_ends.append((me[:twice], to[-twice:]))
+    stars, leaves = np.repeat(np.arange(n1), 3), np.arange(n1, 4 * n1)
+    u2, v2 = (np.concatenate(e) for e in zip(*twice_ends))
+    more = 4 * n1 + np.arange(u2.size)  # leaves of a star that are tied to another, too
+    u, v = (np.concatenate((*e, *rest)) for e, rest in zip(zip(*ends), ((stars, u2, v2), (leaves, more, more))))
+    n = 4 * n1 + u2.size
+    key = np.unique(np.minimum(u, v) * n + np.maximum(u, v))
+    return graphgen.to_csr(n, torch.from_numpy(np.stack((key // n, key % n), 1)))
+
+
+@pytest.mark.parametrize("wide_sums", [0, 1])
+@pytest.mark.parametrize("weight_bits", [0, 1])
+def test_rows_around_the_longest_of_every_network(bordered, weight_bits, wide_sums):
+    """Weights that all lie beside their columns (0: the 14 bits that are left) and such as do not."""
+    n = bordered.xadj.numel() - 1
+    ref = G.gosh_coarsen(n, bordered.xadj, bordered.adj, threshold=4, min_shrink=1.0, max_levels=3)
+    for i in range(2):
+        lengths = np.bincount(ref.map(i), weights=np.diff(ref.graph(i)[1])).astype(int)
+        assert {b + o for b in NETWORKS for o in (-1, 0, 1)} <= set(lengths), i
+        assert ref.shape(i + 1)[0] > 14 << 14 and ref.mult(i + 1).max() > 1
+    with seam(SEAM_WEIGHT_BITS, weight_bits), seam(SEAM_WIDE_SUMS, wide_sums):
+        assert_equals_host(bordered, 3, threshold=4, min_shrink=1.0, max_levels=3)
 
 
 @pytest.mark.parametrize("n,linked,m", [
