@@ -198,9 +198,8 @@ __global__ __launch_bounds__(256) void number_hubs_kernel(const int32_t *__restr
 
 // Every taken vertex joins its first hub in the order, LANES lanes per vertex, four entries of a lane
 // requested together.  A neighbour above the mean degree is a hub without asking.  (Graphs as above 519 us,
-// now 336; 276, now 169.)  The
-// hubs' own entries of map (read here) were written by the launch before this one; this
-// launch writes only entries of taken vertices.
+// now 336; 276, now 169.)  The hubs' own entries of map (read here) were written by the launch before this
+// one; this launch writes only entries of taken vertices.
 template <typename OffT, int LANES>
 __global__ __launch_bounds__(256) void join_kernel(const OffT *__restrict__ xadj,
                                                    const int32_t *__restrict__ adj,
@@ -590,7 +589,8 @@ int mark_impl(DeviceCoarsener *dc, DeviceLevel &fine, int64_t *n_coarse, bool *d
                                   : join_kernel<OffT, 64>;
   const int group_blocks = blocks_for(n, 256 / lanes);
   // a wavefront walks enough vertices for its turns at the list to be few, where there are that many
-  hipLaunchKernelGGL(classify, dim3(std::min(group_blocks, 2048)), dim3(256), 0, nullptr, xadj, adj, rk, n, status, pending, counters);
+  hipLaunchKernelGGL(classify, dim3(std::min(group_blocks, 2048)), dim3(256), 0, nullptr, xadj, adj, rk, n, status,
+                     pending, counters);
   if (int rc = gosh::check_launch("classify_kernel")) return rc;
   unsigned long long count = 0;
   GOSH_TRY_HIP(hipMemcpy(&count, counters, 8, hipMemcpyDeviceToHost), "read pending count");

@@ -347,11 +347,14 @@ inline int32_t lock_tries() { return seam(kSeamLockTries) ? static_cast<int32_t>
 // line of the row; here the rows to be added (one per lane group that asks, `mine`) are laid out
 // side by side in LDS, 4 * LPG floats each, and lane l of the wavefront adds float l of every 64:
 // 16 / LPG rows per instruction, each line touched once, and at most four instructions however many
-// groups a wavefront has.  (One row per instruction, its floats fetched from the lanes that hold them,
-// made a wavefront's rows a serial chain: epochs of 1,024 sources, k = 3, d = 8 / 16 / 32 / 64 took 24.8 /
-// 12.1 / 9.4 / 7.0 us, now 6.4 / 6.0 / 5.9 / 6.0; 65,536 sources 29.4 / 26.1 / 42.1, now 20.0 / 24.1 / 39.8 at
-// d = 8 / 16 / 32, where the adds themselves bound it; a store and add mix of 4.2 M x 32 1,124, now 1,100.)  Needs d <= 64 and every lane of the wavefront present (no divergent branch around
-// the call); `mine` and `row` are uniform inside a lane group.
+// groups a wavefront has.  Needs d <= 64 and every lane of the wavefront present (no divergent branch
+// around the call); `mine` and `row` are uniform inside a lane group.
+//
+// One row per instruction, its floats fetched from the lanes that hold them, made a wavefront's rows a
+// serial chain.  us of epochs with k = 3, before / now (65,536 sources: the adds themselves bound it):
+//   1,024 sources:  d = 8 24.8 / 6.4   d = 16 12.1 / 6.0   d = 32 9.4 / 5.9   d = 64 7.0 / 6.0
+//   65,536 sources: d = 8 29.4 / 20.0  d = 16 26.1 / 24.1  d = 32 42.1 / 39.8
+//   4.2 M sources, a mix of stores and adds: d = 32 1,124 / 1,100
 template <int LPG>
 struct RowsOfWave {
   Float4 step[64];

@@ -22,9 +22,16 @@
 
 namespace {
 
-// Small buffers are blocks of gosh_device_pool.cpp: a level of a few thousand vertices trains for less time
-// than hipMalloc and hipFree of its matrix take.  Not where the caller gave a budget: a block may be larger than
-// what is asked for, and what is kept after use is memory beside the budget of whatever follows.
+// Small buffers are blocks of gosh_device_pool.cpp, kept for the next call: a level of a few thousand vertices
+// trains for less time than hipMalloc and hipFree of its matrix take, 0.1 ms of waiting for a small one to 0.4 for a
+// large one.  The bound is on what stays allocated for that: a buffer, and a run's matrices that wait for its end.
+// ms of runs of 2 epochs per level on 3,000 x 16 / 120,000 x 128 / 500,000 x 64 / 1 M x 128 / 4 M x 128 (the second
+// levels' matrices take 0.1 / 32 / 67 / 269 / 1,077 MB) with a bound of
+//   0: 0.27 / 1.55 / 3.27 / 10.2 / 28.7      16 MB: 0.19 / 1.36 / 3.11 / 10.0 / 28.5
+//   64 MB: 0.19 / 1.21 / 3.07 / 10.0 / 28.4  1 GB: 0.19 / 1.21 / 2.62 / 9.2 / 27.8
+// so more would still gain, by a smaller part the longer a level trains.
+// Not where the caller gave a budget: a block may be larger than what is asked for, and what is kept after use
+// is memory beside the budget of whatever follows.
 constexpr size_t kPooledBytes = size_t(64) << 20;
 
 struct DeviceBuffer {

@@ -143,7 +143,8 @@ __global__ __launch_bounds__(256) void segments_kernel(const int32_t *__restrict
     for (int64_t c = t == 0 ? 0 : cluster[t - 1] + 1LL; c <= a; ++c) segment[c] = lo;
     if (t == n - 1)
       for (int64_t c = a + 1; c <= n_coarse; ++c) segment[c] = nnz;
-    for (int64_t k = (lo + kGatherTile - 1) / kGatherTile; k * kGatherTile < hi; ++k) tile_row[k] = static_cast<int32_t>(t);
+    for (int64_t k = (lo + kGatherTile - 1) / kGatherTile; k * kGatherTile < hi; ++k)
+      tile_row[k] = static_cast<int32_t>(t);
     if (lo < hi && hi == nnz) tile_row[(nnz + kGatherTile - 1) / kGatherTile] = static_cast<int32_t>(t);
   }
 }
@@ -234,8 +235,8 @@ __device__ __forceinline__ bool lay_out_rows(RowStarts &t, const int64_t *__rest
 // tail and the writes are coalesced.  Bound by the lookups: where the table is larger than an L2, most read a
 // line from the memory side (7 TB/s of lines).  Hence the narrow table, and streams that pass the L2 by: 128 M
 // entries of 4.2 M vertices 1.35 ms without both, now 1.21 (1.43 with a binary search per entry besides).  Eight
-// entries of a thread are requested together, as many as leave eight wavefronts to a SIMD: 117 M weighted entries of 2.3 M
-// vertices 0.66 ms by fours, now 0.53.
+// entries of a thread are requested together, as many as leave eight wavefronts to a SIMD: 117 M weighted
+// entries of 2.3 M vertices 0.66 ms by fours, now 0.53.
 template <typename OffT, typename WT, bool WEIGHTED>
 __global__ __launch_bounds__(256) void gather_kernel(const int32_t *__restrict__ adj,
                                                      const WT *__restrict__ mult,
@@ -540,7 +541,8 @@ __global__ __launch_bounds__(256) void merge_sorted_kernel(const int64_t *__rest
       __builtin_amdgcn_wave_barrier();
     }
   };
-  for (int64_t i = static_cast<int64_t>(blockIdx.x) * kTeams + team; i < count; i += static_cast<int64_t>(gridDim.x) * kTeams) {
+  for (int64_t i = static_cast<int64_t>(blockIdx.x) * kTeams + team; i < count;
+       i += static_cast<int64_t>(gridDim.x) * kTeams) {
     const int32_t a = list[i];
     const int64_t lo = segment[a];
     const uint32_t size = static_cast<uint32_t>(segment[a + 1] - lo);
@@ -895,7 +897,8 @@ __global__ __launch_bounds__(256) void coarse_tiles_kernel(const int64_t *__rest
                                                            int64_t nnz_coarse, int32_t *__restrict__ tile_row) {
   for (int64_t a = blockIdx.x * 256LL + threadIdx.x; a < n_coarse; a += gridDim.x * 256LL) {
     const int64_t lo = xadj_out[a], hi = xadj_out[a + 1];
-    for (int64_t k = (lo + kGatherTile - 1) / kGatherTile; k * kGatherTile < hi; ++k) tile_row[k] = static_cast<int32_t>(a);
+    for (int64_t k = (lo + kGatherTile - 1) / kGatherTile; k * kGatherTile < hi; ++k)
+      tile_row[k] = static_cast<int32_t>(a);
     if (lo < hi && hi == nnz_coarse) tile_row[(nnz_coarse + kGatherTile - 1) / kGatherTile] = static_cast<int32_t>(a);
   }
 }
@@ -1011,18 +1014,19 @@ int quotient(gosh::DeviceCoarsener *dc, const gosh::DeviceLevel &fine, int64_t n
     unsigned bits = 1;
     while (bits < 31 && (n_coarse >> bits) != 0) ++bits;
     size_t sort_bytes = 0, scan_bytes = 0;
-    GOSH_TRY_HIP(rocprim::radix_sort_pairs<gosh::SortConfig>(nullptr, sort_bytes, fine.map, cluster, ids, order, static_cast<size_t>(n),
-                                           0u, bits, nullptr),
+    GOSH_TRY_HIP(rocprim::radix_sort_pairs<gosh::SortConfig>(nullptr, sort_bytes, fine.map, cluster, ids, order,
+                                                             static_cast<size_t>(n), 0u, bits, nullptr),
                  "cluster sort (size query)");
     GOSH_TRY_HIP(rocprim::exclusive_scan(nullptr, scan_bytes, lengths, pos, int64_t(0), static_cast<size_t>(n) + 1,
                                          rocprim::plus<int64_t>(), nullptr),
                  "row scan (size query)");
     char *temp = nullptr;
     if (int rc = buf.alloc(&temp, std::max(sort_bytes, scan_bytes), "sort workspace")) return rc;
-    GOSH_TRY_HIP(rocprim::radix_sort_pairs<gosh::SortConfig>(temp, sort_bytes, fine.map, cluster, ids, order, static_cast<size_t>(n), 0u,
-                                           bits, nullptr),
+    GOSH_TRY_HIP(rocprim::radix_sort_pairs<gosh::SortConfig>(temp, sort_bytes, fine.map, cluster, ids, order,
+                                                             static_cast<size_t>(n), 0u, bits, nullptr),
                  "cluster sort");
-    hipLaunchKernelGGL(row_lengths_kernel<OffT>, dim3(flat_blocks), dim3(256), 0, nullptr, xadj, order, n, lengths, begin);
+    hipLaunchKernelGGL(row_lengths_kernel<OffT>, dim3(flat_blocks), dim3(256), 0, nullptr, xadj, order, n, lengths,
+                       begin);
     GOSH_TRY_HIP(rocprim::exclusive_scan(temp, scan_bytes, lengths, pos, int64_t(0), static_cast<size_t>(n) + 1,
                                          rocprim::plus<int64_t>(), nullptr),
                  "row scan");
@@ -1032,19 +1036,22 @@ int quotient(gosh::DeviceCoarsener *dc, const gosh::DeviceLevel &fine, int64_t n
     uint32_t *narrow = nullptr;  // and a word for what is read past the last vertex; without room the map itself does
     if (n >= kNarrowFrom && n_coarse <= (int64_t{1} << 24) && !gosh::denied(gosh::kDenyNarrow) &&
         buf.alloc(&narrow, static_cast<size_t>((n + 3) / 4) * 3 + 1, "narrow map") == GOSH_OK) {
-      hipLaunchKernelGGL(narrow_map_kernel, dim3(blocks_for((n + 3) / 4, 256)), dim3(256), 0, nullptr, fine.map, n, narrow);
+      hipLaunchKernelGGL(narrow_map_kernel, dim3(blocks_for((n + 3) / 4, 256)), dim3(256), 0, nullptr, fine.map, n,
+                         narrow);
       table = ClusterTable{reinterpret_cast<const char *>(narrow), 3, 0xFFFFFFu};
     }
     hipLaunchKernelGGL((gather_kernel<OffT, WT, WEIGHTED>), dim3(blocks_for(nnz, kGatherTile)), dim3(256), 0, nullptr,
-                       fine.adj, static_cast<const WT *>(fine.mult), table, begin, cluster, pos, tile_row, nnz, pack, entry, weight, classes);
+                       fine.adj, static_cast<const WT *>(fine.mult), table, begin, cluster, pos, tile_row, nnz, pack,
+                       entry, weight, classes);
     if (int rc = gosh::check_launch("gather_kernel")) return rc;
-    for (void *p : {static_cast<void *>(order), static_cast<void *>(cluster),
-                    static_cast<void *>(lengths), static_cast<void *>(begin), static_cast<void *>(pos), static_cast<void *>(tile_row),
+    for (void *p : {static_cast<void *>(order), static_cast<void *>(cluster), static_cast<void *>(lengths),
+                    static_cast<void *>(begin), static_cast<void *>(pos), static_cast<void *>(tile_row),
                     static_cast<void *>(temp), static_cast<void *>(narrow)})
       buf.release(p);  // what takes them up again is on the same stream
   }
   const int64_t radix_from = gosh::seam(gosh::kSeamRadixFrom);
-  const Ways ways{radix_from ? radix_from : kRankColumns, radix_from ? radix_from : kCountColumns, static_cast<int>(sizeof(WT))};
+  const Ways ways{radix_from ? radix_from : kRankColumns, radix_from ? radix_from : kCountColumns,
+                  static_cast<int>(sizeof(WT))};
   hipLaunchKernelGGL(classify_segments_kernel, dim3(blocks_for(n_coarse, 1024)), dim3(1024), 0, nullptr, segment,
                      n_coarse, list, length, slices, ways, classes);
   if (int rc = gosh::check_launch("classify_segments_kernel")) return rc;

@@ -189,11 +189,12 @@ __device__ __forceinline__ uint32_t xor3(uint32_t a, uint32_t b, uint32_t c) {
 // TILE units that begin at a multiple of as many, wherever in a row that is, and ends.  A matrix of more than
 // kStreamInit bytes, which no cache holds, is written 4 KB to a wavefront, others 16 KB to a workgroup.  Calls one after
 // another on one matrix, us, with tiles of whole rows up to 32 KB / 16 KB / 4 KB (both of any rows):
-//   d = 128: 260 MB 41.2 / 41.5 / 42.5   300 MB 48 / 50 / 50   400 MB 80 / 75 / 66   1 GB 194 / 183 / 162   2.1 GB 382 / 353 / 323
-//   d = 8:   260 MB 59 / 44 / 45         300 MB 61 / 53 / 53   400 MB 76 / 70 / 70   1 GB 170 / 170 / 168   2.1 GB 334 / 337 / 336
-// (2.1 GB: 6.5 TB/s at d = 128, 6.4 where other matrices were written in between.)  Below, 4 KB lose: 64 MB 12.5 / 14.5 in
-// the kernel, 1 MB the same.  Its arithmetic alone takes 248 us for 2.1 GB.  The tables of a wavefront take less than 5 KB
-// of LDS, for 32 to fit a CU: 335 us with 5.2 KB.
+//   d = 128: 260 MB 41.2 / 41.5 / 42.5   300 MB 48 / 50 / 50   400 MB 80 / 75 / 66   1 GB 194 / 183 / 162
+//            2.1 GB 382 / 353 / 323 (6.5 TB/s; 6.4 where other matrices were written in between)
+//   d = 8:   260 MB 59 / 44 / 45         300 MB 61 / 53 / 53   400 MB 76 / 70 / 70   1 GB 170 / 170 / 168
+//            2.1 GB 334 / 337 / 336
+// Below, 4 KB lose: 64 MB 12.5 / 14.5 in the kernel, 1 MB the same.  Its arithmetic alone takes 248 us for 2.1 GB.
+// The tables of a wavefront take less than 5 KB of LDS, for 32 to fit a CU: 335 us with 5.2 KB.
 constexpr int64_t kStreamInit = int64_t{320} << 20;
 template <int THREADS, int TILE, int SHORTEST>  // rows of SHORTEST units at least
 __global__ __launch_bounds__(THREADS) void init_embedding_kernel(float4 *__restrict__ M, int64_t units_total,
@@ -263,7 +264,8 @@ __global__ __launch_bounds__(THREADS) void init_embedding_kernel(float4 *__restr
 // cache does not hold are non-temporal (STREAM): the check of the matrix that follows a projection runs into
 // fewer write-backs.  A smaller one stays there for the epochs that follow.  Projection and check / projection
 // and epoch at d = 128, us, streamed and plain: 64 MB 59, 57 / 205, 157;  96 MB 75, 72 / 297, 225;  128 MB 89, 91 /
-// 433, 435;  224 MB 134, 136 / 553, 550;  400 MB 207, 216 / 846, 865.
+// 433, 435;  224 MB 134, 136 / 553, 550;  400 MB 207, 216 / 846, 865.  (The projection by itself gains nothing:
+// 64 MB 22.3 streamed, 23.1 plain; 120 MB 39.3, 40.3.)
 constexpr int64_t kStreamBytes = int64_t{128} << 20;
 template <bool STREAM>
 __global__ __launch_bounds__(256) void project_kernel(const Float4 *__restrict__ coarse,
@@ -736,7 +738,8 @@ int gosh_project(const float *M_coarse_dev, int64_t n_coarse, const int32_t *map
   if (int rc = gosh::check_device_span(map_dev, static_cast<size_t>(n_fine) * 4, "map")) return rc;
   const RowTiles t = row_tiles(d / 4);
   const bool stream = n_fine * d * 4 > kStreamBytes;
-  hipLaunchKernelGGL(stream ? project_kernel<true> : project_kernel<false>, dim3(grid_for(n_fine, t.rows, kTileBlocks)), dim3(256), 0,
+  hipLaunchKernelGGL(stream ? project_kernel<true> : project_kernel<false>,
+                     dim3(grid_for(n_fine, t.rows, kTileBlocks)), dim3(256), 0,
                      gosh::as_stream(hip_stream), reinterpret_cast<const Float4 *>(M_coarse_dev),
                      map_dev, reinterpret_cast<Float4 *>(M_fine_dev), n_fine, t,
                      static_cast<uint32_t>(std::min<int64_t>(n_coarse, 2147483647LL)));
