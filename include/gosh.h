@@ -396,13 +396,16 @@ typedef struct {
  * counter, then (i > 0) project to level i-1 with map_{i-1}.  The paper prints the loop
  * as "D-1 to 1"; the text trains until M_0 is obtained, which is what is done here.
  * h: hierarchy (host).  M0_dev: device matrix n_0 x d, receives the embedding of G_0.
- * flags: as for gosh_train_epoch, plus GOSH_FLAG_EDGE_EPOCHS and GOSH_FLAG_PAIR_LEVELS.  device_budget_bytes: if non-zero and the graph plus
- * matrix of level 0 exceed it, the call is refused with GOSH_EBUDGET (use gosh_embed_host,
- * which keeps such levels on the host).  stats: NULL or host array of D entries; a call that
- * fails at some level has filled those of the levels that it finished before.
+ * flags: as for gosh_train_epoch, plus GOSH_FLAG_EDGE_EPOCHS and GOSH_FLAG_PAIR_LEVELS.
+ * device_budget_bytes: if non-zero and the graph plus matrix of level 0 exceed it, the call is
+ * refused with GOSH_EBUDGET (use gosh_embed_host, which keeps such levels on the host).
+ * stats: NULL or host array of D entries; a call that fails at some level has filled those of the
+ * levels that it finished before.
  * Blocking: returns after the last level finished; intermediate device buffers are
- * allocated and freed inside the call (without a budget those of up to 64 MB are blocks that the library keeps
- * for the next call, as it does those of freed hierarchies; gosh_hierarchy_trim_scratch returns them).  Every level is checked after its training
+ * allocated and freed inside the call (without a budget those of up to 64 MB are blocks that the
+ * library keeps for the next call, as it does those of freed hierarchies; gosh_hierarchy_trim_scratch
+ * returns them).  The call waits for its own stream; it waits for the whole device only where it frees
+ * buffers on the way or fails.  Every level is checked after its training
  * (gosh_matrix_check: one more read of the matrix): if any level ends with non-finite
  * entries the run is still completed, stats are filled, and GOSH_EDIVERGED is returned. */
 int gosh_embed(const gosh_hierarchy *h, int32_t d, int32_t k_neg, int64_t epochs, double p,
